@@ -11,20 +11,38 @@ namespace triaccel {
 // ---------------------------------------------------------------------------------------------
 // wavefront (64 lanes) helpers
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// Reductions and the inclusive scan over the 64 lanes move data inside the vector ALU (data-parallel
+// primitives) instead of through LDS: shifts by 1, 2, 4, 8 inside the rows of 16 lanes, then the last
+// lane of row 0 / 2 to row 1 / 3 (row_bcast15) and of the first half to the second (row_bcast31).
+// Lanes without a source get `0`, the identity of +, | and of max over unsigned values.
+#define TA_DPP(v, ctrl, rows) ((uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), (ctrl), (rows), 0xF, false))
+#define TA_DPP_TREE(v, OP)                        \
+  do {                                            \
+    v = OP(v, TA_DPP(v, 0x111, 0xF));             \
+    v = OP(v, TA_DPP(v, 0x112, 0xF));             \
+    v = OP(v, TA_DPP(v, 0x114, 0xF));             \
+    v = OP(v, TA_DPP(v, 0x118, 0xF));             \
+    v = OP(v, TA_DPP(v, 0x142, 0xA));             \
+    v = OP(v, TA_DPP(v, 0x143, 0xC));             \
+  } while (0)
+#define TA_OP_ADD(a, b) ((a) + (b))
+#define TA_OP_OR(a, b) ((a) | (b))
+#define TA_OP_MAX(a, b) (max((uint32_t)(a), (uint32_t)(b)))
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1); }
+__device__ __forceinline__ uint32_t first_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 0); }
+// Sum over this lane and the lanes below it; all lanes of the wavefront must be active.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+  TA_DPP_TREE(v, TA_OP_ADD);
   return v;
 }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return last_lane(wave_scan(v)); }
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor(v, o));
-  return v;
+  TA_DPP_TREE(v, TA_OP_MAX);
+  return last_lane(v);
 }
 __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v |= (uint32_t)__shfl_xor(v, o);
-  return v;
+  TA_DPP_TREE(v, TA_OP_OR);
+  return last_lane(v);
 }
 
 __device__ __forceinline__ bool step_skipped(const GlobalDev* glob, uint64_t step_id) {
@@ -48,17 +66,20 @@ __device__ __forceinline__ uint32_t gather_mask_word(uint32_t nib, int lane) {
   return v;
 }
 
-// Store the kRows mask words of a chunk: lane (8j + r) of a wavefront writes row r's word j.
+// Mask words of a chunk from the 16 flags of every lane (bit 4 r + i = element i of row r): lane
+// (8 j + r) of a wavefront writes row r's word j.
 template <bool FULL>
-__device__ __forceinline__ void store_mask_words(const TensorDesc& td, int64_t base, const uint32_t word[kRows]) {
+__device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t base, uint32_t flags) {
+  static_assert(kRows == 4, "one word per row, chosen by two bits of the lane");
   const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
   const int sub = tid & 7;
+  const uint32_t w0 = gather_mask_word(flags & 15u, lane), w1 = gather_mask_word((flags >> 4) & 15u, lane);
+  const uint32_t w2 = gather_mask_word((flags >> 8) & 15u, lane), w3 = gather_mask_word((flags >> 12) & 15u, lane);
+  const uint32_t lo = (sub & 1) ? w1 : w0, hi = (sub & 1) ? w3 : w2;
   if (sub < kRows) {
-    uint32_t v = word[0];
-#pragma unroll
-    for (int r = 1; r < kRows; ++r) v = (sub == r) ? word[r] : v;
     const int64_t widx = ((base + (int64_t)sub * kRowElems) >> 5) + (tid >> 3);
-    if (FULL || widx < ((td.numel + 31) >> 5)) as_global<uint32_t>(td.mask)[widx] = v;
+    if (FULL || widx < ((td.numel + 31) >> 5)) as_global<uint32_t>(td.mask)[widx] = (sub & 2) ? hi : lo;
   }
 }
 
@@ -84,13 +105,8 @@ __device__ __forceinline__ void append_candidates(uint32_t flags, const float (&
   if (!__any(flags != 0u)) return;  // uniform over the wavefront
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const uint32_t mine = __popc(flags);
-  uint32_t incl = mine;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o);
-    if (lane >= o) incl += t;
-  }
-  const uint32_t total = __shfl(incl, kWave - 1);
+  const uint32_t incl = wave_scan(mine);
+  const uint32_t total = last_lane(incl);
   const uint32_t list = (chunk_index * (kThreads / kWave) + wave) % kCandLists;
   uint32_t start = 0, fit = 0, ostart = 0;
   if (lane == 0) {
@@ -98,9 +114,9 @@ __device__ __forceinline__ void append_candidates(uint32_t flags, const float (&
     fit = start < td.sub_cap ? min(total, td.sub_cap - start) : 0u;
     if (fit < total) ostart = atomicAdd(cand_counter(counters, tensor, kCandLists), total - fit);
   }
-  start = __shfl(start, 0);
-  fit = __shfl(fit, 0);
-  ostart = __shfl(ostart, 0);
+  start = first_lane(start);
+  fit = first_lane(fit);
+  ostart = first_lane(ostart);
   uint32_t rank = incl - mine;
   Candidate* lists = cands + td.cand_offset;
 #pragma unroll
@@ -144,7 +160,6 @@ __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, u
                                            uint32_t rng_lo, uint32_t rng_hi, uint32_t chunk_index,
                                            uint32_t tensor, Candidate* cands, uint32_t* counters) {
   const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
   float h[kRows][4];
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
@@ -152,25 +167,23 @@ __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, u
     if (FULL) load4<kFP32>(td.curv, idx, h[r]);
     else load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, h[r]);
   }
-  uint32_t word[kRows];
-  uint32_t cflags = 0;
+  // one rule for both modes: keys >= keep_lo are kept, keys in [list_lo, keep_lo) are listed; the
+  // guarded fill 0 is below both bounds, so it is never kept and never listed
+  const bool exact = mode == kSelExact;
+  const uint32_t keep_lo = max(exact ? theta : rng_hi, 1u);
+  const uint32_t list_lo = exact ? keep_lo : min(max(rng_lo, 1u), keep_lo);
+  uint32_t kflags = 0, cflags = 0;
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
-    uint32_t nib = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t key = f2u(h[r][i]) & 0x7fffffffu;  // guarded fill 0: never kept, never listed
-      if (mode == kSelExact) {
-        if (key >= theta && key != 0u) nib |= 1u << i;
-      } else if (key >= rng_hi) {
-        nib |= 1u << i;
-      } else if (key != 0u && key >= rng_lo) {
-        cflags |= 1u << (r * 4 + i);
-      }
+      const uint32_t key = f2u(h[r][i]) & 0x7fffffffu;
+      kflags |= (key >= keep_lo ? 1u : 0u) << (r * 4 + i);
+      cflags |= (key >= list_lo ? 1u : 0u) << (r * 4 + i);
     }
-    word[r] = gather_mask_word(nib, lane);
   }
-  store_mask_words<FULL>(td, base, word);
+  cflags ^= kflags;  // the kept keys are above list_lo too
+  store_mask_flags<FULL>(td, base, kflags);
   append_candidates(cflags, h, base, chunk_index, tensor, td, cands, counters);
 }
 
