@@ -45,9 +45,14 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   return last_lane(v);
 }
 
-__device__ __forceinline__ bool step_skipped(const GlobalDev* glob, uint64_t step_id) {
-  return *reinterpret_cast<const volatile uint64_t*>(&glob->skip_epoch) == step_id;
-}
+// Set by the gradient-statistics kernel and read by the kernels after it (an ordinary load: the writer
+// is an earlier kernel).
+__device__ __forceinline__ bool step_skipped(const GlobalDev* glob, uint64_t step_id) { return glob->skip_epoch == step_id; }
+
+// TA_LOADED(operands): the loads of these wave-uniform values ("s"(x), ...) are issued together and ahead of
+// whatever follows.  Without it the compiler moves a load that is only used behind a branch to behind that
+// branch, where its latency comes on top of that of the load that the branch waits for.
+#define TA_LOADED(...) asm volatile("" ::__VA_ARGS__)
 
 __device__ __forceinline__ StepScalars step_scalars(const StepArg& sa) { return sa.dev ? *sa.dev : sa.value; }
 

@@ -252,17 +252,22 @@ __global__ __launch_bounds__(kThreads) void k_curv_ema(const TensorDesc* __restr
                                                        Candidate* cands, uint32_t* counters, StepArg sa,
                                                        float beta_h, float omb_h) {
   const StepScalars sc = step_scalars(sa);
-  if (step_skipped(glob, sc.step_id)) return;
+  // the skip word travels together with the tables: its latency is not one more before the data's
+  const uint64_t skip_epoch = glob->skip_epoch;
   const ChunkRef cr = chunks[blockIdx.x];
   const TensorDesc td = tds[cr.tensor];
-  if (!td.has_probe) return;
   const LayerDev& ls = layers[cr.tensor];
-  const bool first = ls.probes_seen == 0;
+  const uint32_t probes_seen = ls.probes_seen, use_band = ls.use_band, band_lo = ls.band_lo, band_hi = ls.band_hi;
+  TA_LOADED("s"(td.grad), "s"(td.z), "s"(td.hz), "s"(td.curv), "s"(td.mask), "s"(td.numel), "s"(td.grad_dtype),
+            "s"(td.has_probe), "s"(td.list_all), "s"(td.cand_offset), "s"(probes_seen), "s"(use_band), "s"(band_lo),
+            "s"(band_hi));
+  if (skip_epoch == sc.step_id || !td.has_probe) return;
+  const bool first = probes_seen == 0;
   const bool list_all = td.list_all != 0;
-  const bool listing = list_all || ls.use_band != 0;
+  const bool listing = list_all || use_band != 0;
   // band_lo >= 1 and band_hi <= 0x7f800000, so key 0 is never in a range; no key reaches 2^31
-  const uint32_t list_lo = list_all ? 1u : listing ? ls.band_lo : 0x80000000u;
-  const uint32_t list_hi = list_all || !listing ? 0x80000000u : ls.band_hi;
+  const uint32_t list_lo = list_all ? 1u : listing ? band_lo : 0x80000000u;
+  const uint32_t list_hi = list_all || !listing ? 0x80000000u : band_hi;
   const int64_t base = (int64_t)cr.index * kChunk;
   uint32_t above_zeros = 0, maxkey = 0, nonfin = 0;
 #define TA_EMA(FULL_, SRC_)                                                                                   \

@@ -19,7 +19,7 @@ namespace triaccel {
 // wg + n_wg, ...  The list and its length are written on the device by the per-layer kernel, so the
 // work is offered on every step and nothing happens when the list is empty.  Uniform over the
 // workgroup (it contains barriers).
-template <bool ELEM>
+template <bool ELEM, bool MOM>
 __device__ __forceinline__ void resize_items(const TensorDesc* __restrict__ tds, const LayerDev* layers,
                                              const GlobalDev* glob, const uint32_t* trans_list, uint32_t n_tensors,
                                              const ResizePlan& plan, uint32_t launch, uint32_t slots, uint32_t wg,
@@ -41,15 +41,15 @@ __device__ __forceinline__ void resize_items(const TensorDesc* __restrict__ tds,
     if (stage == 0) {
       resize_walk_top(plan, td.n_chunks, narrowing, [&](uint32_t c) {
         ChunkRegs regs;
-        update_load_any<ELEM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
+        update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
         __syncthreads();  // chunk 0 overwrites itself; a later chunk overwrites what an earlier one loaded
-        update_store_any(td, nd, (int64_t)c * kChunk, tid, regs);
+        update_store_any<MOM>(td, nd, (int64_t)c * kChunk, tid, regs);
       });
     } else {
       if (plan.root[stage] + r >= td.n_chunks) continue;
       resize_walk_subtree(
           plan, stage, r, td.n_chunks, narrowing,
-          [&](uint32_t c) { update_any<ELEM>(td, pd, nd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid); },
+          [&](uint32_t c) { update_any<ELEM, MOM>(td, pd, nd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid); },
           [&]() { __syncthreads(); });
     }
   }

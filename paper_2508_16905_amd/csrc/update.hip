@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kThreads) void k_mask_pass(const TensorDesc* __rest
 //
 // In the element-wise form (ELEM) the threshold must be final before the update, so the mask and
 // the listed keys are completed by the kernels before this one and no mask pass runs here.
-template <bool ELEM>
+template <bool ELEM, bool MOM>
 __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restrict__ tds,
                                                      const ChunkRef* __restrict__ chunks, LayerDev* layers,
                                                      const GlobalDev* glob, Candidate* cands, uint32_t* counters,
@@ -51,27 +51,34 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
                                                      uint32_t resize_slots, uint32_t resize_wgs, StepArg sa, float wd,
                                                      float mu, float alpha) {
   const StepScalars sc = step_scalars(sa);
-  if (step_skipped(glob, sc.step_id)) return;
   if (blockIdx.x < resize_wgs) {
-    resize_items<ELEM>(tds, layers, glob, trans_list, n_tensors, plan, 0u, resize_slots, blockIdx.x, resize_wgs, sc, wd, mu,
-                       alpha);
+    if (step_skipped(glob, sc.step_id)) return;
+    resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, 0u, resize_slots, blockIdx.x, resize_wgs, sc,
+                            wd, mu, alpha);
     return;
   }
+  // the skip word travels together with the tables: its latency is not one more before the data's
+  const uint64_t skip_epoch = glob->skip_epoch;
   const ChunkRef cr = chunks[blockIdx.x - resize_wgs];
   LayerDev& ls = layers[cr.tensor];
   const int pd = ls.prev_code, nd = ls.code;
   const TensorDesc td = tds[cr.tensor];
+  const float eta = ls.eta;
+  const uint32_t mode = ls.mode, mask_done = ls.mask_done;
+  const uint32_t theta_key = ls.theta_key;
+  TA_LOADED("s"(td.param), "s"(td.grad), "s"(td.mom), "s"(td.curv), "s"(td.numel), "s"(td.grad_dtype),
+            "s"(td.has_probe), "s"(pd), "s"(nd), "s"(eta), "s"(mode), "s"(mask_done), "s"(theta_key));
+  if (skip_epoch == sc.step_id) return;
   const int64_t base = (int64_t)cr.index * kChunk;
-  const StepSize ss{-ls.eta, sc.lr, alpha, ls.theta_key};
-  if (elem_size(pd) == elem_size(nd)) update_any<ELEM>(td, pd, nd, base, sc.inv_scale, wd, mu, ss, (int)threadIdx.x);
+  const StepSize ss{-eta, sc.lr, alpha, theta_key};
+  if (elem_size(pd) == elem_size(nd)) update_any<ELEM, MOM>(td, pd, nd, base, sc.inv_scale, wd, mu, ss, (int)threadIdx.x);
   if constexpr (ELEM) return;
   // kSelHist cannot remain after the last scan; never write a mask from a stale range
-  const uint32_t mode = ls.mode;
-  if (td.has_probe && !ls.mask_done && mode != kSelHist) {
+  if (td.has_probe && !mask_done && mode != kSelHist) {
     if (base + kChunk <= td.numel)
-      mask_chunk<true>(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
+      mask_chunk<true>(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
     else
-      mask_chunk<false>(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
+      mask_chunk<false>(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
   }
 }
 
@@ -80,12 +87,10 @@ hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, flo
   const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
   const ResizeGrid rg = resize_grid(plan, 0u, t.n_tensors);
   const dim3 grid(t.total_chunks + rg.grid);
-  if (elem)
-    hipLaunchKernelGGL(k_update<true>, grid, dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers, t.glob, t.cands,
-                       t.cand_counters, t.trans_list, t.n_tensors, plan, rg.slots, rg.grid, sa, wd, mu, alpha);
-  else
-    hipLaunchKernelGGL(k_update<false>, grid, dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers, t.glob, t.cands,
-                       t.cand_counters, t.trans_list, t.n_tensors, plan, rg.slots, rg.grid, sa, wd, mu, alpha);
+  const auto kernel = elem ? (mu != 0.0f ? k_update<true, true> : k_update<true, false>)
+                           : (mu != 0.0f ? k_update<false, true> : k_update<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers, t.glob, t.cands,
+                     t.cand_counters, t.trans_list, t.n_tensors, plan, rg.slots, rg.grid, sa, wd, mu, alpha);
   TA_LAUNCH_CHECK();
   return hipSuccess;
 }
