@@ -170,7 +170,10 @@ typedef struct {
                                   2 per-layer kernel (band check, assign), 3 fallback radix select
                                   (histogram passes), 4 update + cast of tensors whose storage size is
                                   unchanged (+ fallback mask pass), 5 in-place update of tensors whose
-                                  size changes, 6 threshold resolution among listed keys + mask patch   */
+                                  size changes, 6 threshold resolution among listed keys + mask patch.
+                                  Sets of fewer than 16,384 pieces of 4096 elements, none of whose tensors
+                                  has more than 1024: stages 2 and 3 are part of stage 4 and read 0, the
+                                  fallback mask pass is part of stage 6                               */
 } triaccel_stage_times;
 
 /*
@@ -178,7 +181,9 @@ typedef struct {
  * curv / mom / mask contents are taken as the initial state (normally zero).  `hip_stream` is a
  * hipStream_t (NULL = the default stream).  Allocates the workspace (chunk table, partials,
  * histograms, candidate lists, per-layer state, eight device copies of the tensor table; a few MB plus
- * 40 bytes per 4096 parameters, plus up to 4 MB of candidate lists per tensor of 262,144 elements or more).
+ * 40 bytes per 4096 parameters, plus up to 4 MB of candidate lists per tensor of 262,144 elements or more,
+ * plus up to 1 MB per tensor of scratch for storage sizes that change, in sets with a tensor of more than
+ * 524,288 elements).
  */
 int triaccel_init(triaccel_handle *out, const triaccel_config *config, const triaccel_tensor *tensors,
                   int32_t n, void *hip_stream);

@@ -14,6 +14,7 @@
 #include "../../include/triaccel.h"
 #include "kernels.h"
 #include "power.h"
+#include "resize_schedule.h"
 
 using namespace triaccel;
 
@@ -183,11 +184,25 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   const DeviceTables& T = h->t;
   hipStream_t s = h->stream;
   const bool fisher = h->cfg.curvature_source == 1;
+  const bool elem = h->cfg.elementwise_scale == 1;
+  const bool local = !elem && T.total_chunks < kLaunchBoundChunks && T.max_chunks_per_tensor <= kLocalMaxChunks;
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
-  TA_HIP(launch_grad_stats(T, sa, s));
+  TA_HIP(launch_grad_stats(T, sa, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
   if (any_probe) TA_HIP(launch_curv_ema(T, sa, beta_h, omb_h, fisher ? 1 : 0, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[2], s));
+  if (local) {
+    // a set bound by its launches: the update takes the layers' decisions and settles the thresholds
+    if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
+    if (ev) TA_HIP(hipEventRecord(ev[4], s));
+    TA_HIP(launch_update_local(T, sa, h->hp, any_probe, s));
+    if (ev) TA_HIP(hipEventRecord(ev[5], s));
+    TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
+    if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
+    if (any_probe) TA_HIP(launch_select_tail(T, sa, beta_h, s));
+    if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
+    return TRIACCEL_OK;
+  }
   TA_HIP(launch_layer(T, sa, h->hp, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
   if (any_probe) {
@@ -199,7 +214,6 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
     if (T.total_chunks >= kLaunchBoundChunks) TA_HIP(launch_hist_pass(T, sa, 0, s));
     TA_HIP(launch_hist_pass(T, sa, 8, s));
   }
-  const bool elem = h->cfg.elementwise_scale == 1;
   if (elem && any_probe) {
     // element-wise step sizes need the final threshold: finish the mask and the selection first
     TA_HIP(launch_mask_pass(T, sa, s));
@@ -365,6 +379,14 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     ls.win_hi = 0x80000000u;
     ls.var_ext = 3.0e38f;  // no extrapolation error measured yet
   }
+  // scratch of the in-place resize: the first `top` chunks of every tensor, if the set needs subtree stages
+  const ResizePlan resize = make_resize_plan(max_chunks, (uint32_t)chunks.size());
+  uint64_t scratch_chunks = 0;
+  if (resize.n_stages > 1)
+    for (TensorDesc& d : c->desc) {
+      d.resize_slot = (uint32_t)scratch_chunks;
+      scratch_chunks += d.n_chunks < resize.top ? d.n_chunks : resize.top;
+    }
   DeviceTables& T = c->t;
   T.n_tensors = (uint32_t)n;
   T.total_chunks = (uint32_t)chunks.size();
@@ -382,6 +404,9 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   if ((rc = dev_alloc(c, &T.cands, (size_t)cand_total))) return fail(rc);
   if ((rc = dev_alloc(c, &T.cand_counters, (size_t)n * (kCandLists + 1) * kCandCounterStride))) return fail(rc);
   if ((rc = dev_alloc(c, &T.trans_list, (size_t)n * 2))) return fail(rc);
+  if ((rc = dev_alloc(c, &T.resize_scratch, (size_t)scratch_chunks * kChunk * 4))) return fail(rc);
+  if ((rc = dev_alloc(c, &T.inputs, (size_t)n))) return fail(rc);
+  if ((rc = dev_alloc(c, &T.arrived, (size_t)n * kCandCounterStride))) return fail(rc);
   if ((rc = dev_alloc(c, &T.scalars, 1))) return fail(rc);
   e = hipMemcpy(T.chunks, chunks.data(), chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
   if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(chunks)"));

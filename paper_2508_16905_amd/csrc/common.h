@@ -17,6 +17,12 @@ constexpr int kFinishThreads = 1024;          // workgroup of the per-tensor thr
 // Sets below this many chunks (67 M parameters) are bound by the number of dependent launches, not
 // by memory bandwidth: for them the step makes fewer, longer launches.
 constexpr uint32_t kLaunchBoundChunks = 16384;
+// Among them, sets whose tensors have at most this many chunks (4.2 M elements) need no per-layer kernel:
+// every workgroup of the update adds up its tensor's chunk records itself (k_update_local).  The limit bounds
+// what it reads for that, 32 bytes per chunk of the tensor, to half of what it streams: at 1024 chunks per
+// tensor (50 M parameters) the launch's decisions cost 20 us of 110, as much as the kernel they replace and its
+// gap together; at 576 (ResNet-18 set) the step is 4.6 us shorter.
+constexpr uint32_t kLocalMaxChunks = 1024;
 
 // Radix-select parameters: magnitudes are 31-bit keys (sign bit cleared).
 constexpr int kHistBins = 2048;
@@ -84,7 +90,7 @@ struct TensorDesc {
   uint32_t cand_cap;     // min(numel, kCandCap): capacity of the overflow list
   uint32_t sub_cap;      // capacity of each of the kCandLists sub-lists: ceil(cand_cap / kCandLists)
   uint32_t list_all;     // numel <= kListAllMax: every non-zero key is listed, no prediction
-  uint32_t pad_;
+  uint32_t resize_slot;  // the tensor's first chunk in the scratch area of the in-place resize
 };
 
 // Per-layer device state.  The leading part mirrors triaccel_layer_info.
@@ -129,7 +135,8 @@ struct LayerDev {
   uint32_t count_above;    // the next histogram pass must count the keys above its window
   uint32_t hist_arrived;   // chunks whose keys are in the histogram of the pass under way (cleared by the scan)
   // accumulators filled by atomics during a step and cleared by the kernel that consumes them
-  uint32_t acc_above, acc_maxkey, acc_nonfinite;
+  uint32_t acc_above, acc_maxkey;
+  uint32_t reserved_;      // keeps the size of saved states
 };
 
 // Small global record (device), copied to pinned host memory at the end of a step.
@@ -151,16 +158,29 @@ struct ChunkRef {
   uint32_t index;  // chunk number inside the tensor
 };
 
-struct Candidate {
+struct alignas(8) Candidate {
   uint32_t idx;
   uint32_t key;
 };
 
 struct EmaPartial {
-  uint32_t above;      // keys at or above the band
-  uint32_t zeros;      // zero keys
-  uint32_t maxkey;     // largest key
-  uint32_t nonfinite;  // a probe sample of the chunk was non-finite
+  uint32_t above_zeros;  // keys at or above the band in the low half, zero keys in the high half
+  uint32_t maxkey;       // largest key
+  uint32_t listed;       // keys listed
+  uint32_t nonfinite;    // a probe sample of the chunk was non-finite
+};
+
+// The layer's fields that the decisions of an applied step read.
+struct LayerIn {
+  float v, lambda, lambda_ctrl, lambda_power;
+  int32_t code;
+  uint32_t applied_steps;
+};
+
+// The plan of a step's threshold selection, laid at the last probed step (a copy of LayerDev's fields).
+struct SelNow {
+  uint32_t use_band, band_lo, band_hi, predicted;
+  uint32_t win_lo, win_hi, win_shift, win_bins;
 };
 
 struct StatPartial {

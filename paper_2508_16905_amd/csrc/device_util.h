@@ -71,12 +71,23 @@ __device__ __forceinline__ uint32_t gather_mask_word(uint32_t nib, int lane) {
   return v;
 }
 
+// Stores that another workgroup of the same launch will read: at device scope they go through the L2 to the
+// memory side, so that waiting for their acknowledgement (published_before_here) is all the release that is
+// needed -- a release fence would write back all that the L2 holds of the launch's other stores.
+template <bool SHARED, typename T>
+__device__ __forceinline__ void store_word(T* p, T v) {
+  if constexpr (SHARED) __hip_atomic_store((TA_GLOBAL T*)(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *as_global<T>(p) = v;
+}
+// Every thread: its device-scope stores and atomics so far have been performed.
+__device__ __forceinline__ void published_before_here() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Mask words of a chunk from the 16 flags of every lane (bit 4 r + i = element i of row r): lane
 // (8 j + r) of a wavefront writes row r's word j.
-template <bool FULL>
+template <bool FULL, bool SHARED = false>
 __device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t base, uint32_t flags) {
   static_assert(kRows == 4, "one word per row, chosen by two bits of the lane");
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & (kThreads - 1);
   const int lane = tid & (kWave - 1);
   const int sub = tid & 7;
   const uint32_t w0 = gather_mask_word(flags & 15u, lane), w1 = gather_mask_word((flags >> 4) & 15u, lane);
@@ -84,7 +95,7 @@ __device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t b
   const uint32_t lo = (sub & 1) ? w1 : w0, hi = (sub & 1) ? w3 : w2;
   if (sub < kRows) {
     const int64_t widx = ((base + (int64_t)sub * kRowElems) >> 5) + (tid >> 3);
-    if (FULL || widx < ((td.numel + 31) >> 5)) as_global<uint32_t>(td.mask)[widx] = (sub & 2) ? hi : lo;
+    if (FULL || widx < ((td.numel + 31) >> 5)) store_word<SHARED>(td.mask + widx, (sub & 2) ? hi : lo);
   }
 }
 
@@ -104,11 +115,13 @@ __device__ __forceinline__ void reset_cand_counters(uint32_t* counters, uint32_t
 // Append a wavefront's candidates of one chunk (flag bit e of `flags` = element e of the lane's
 // 16) with one atomic per wavefront: lanes take consecutive slots by a prefix sum.  The sub-list
 // is chosen by (chunk, wavefront), so wavefronts running at the same time use different counters.
+template <bool SHARED = false>
 __device__ __forceinline__ void append_candidates(uint32_t flags, const float (&h)[kRows][4], int64_t base,
                                                   uint32_t chunk_index, uint32_t tensor, const TensorDesc& td,
                                                   Candidate* cands, uint32_t* counters) {
   if (!__any(flags != 0u)) return;  // uniform over the wavefront
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int tid = threadIdx.x & (kThreads - 1);
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
   const uint32_t mine = __popc(flags);
   const uint32_t incl = wave_scan(mine);
   const uint32_t total = last_lane(incl);
@@ -129,13 +142,14 @@ __device__ __forceinline__ void append_candidates(uint32_t flags, const float (&
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       if (flags & (1u << (r * 4 + i))) {
-        const int64_t idx = base + r * kRowElems + threadIdx.x * kVec + i;
-        const Candidate c{(uint32_t)idx, f2u(h[r][i]) & 0x7fffffffu};
+        const int64_t idx = base + r * kRowElems + tid * kVec + i;
+        // one 8-byte store of a Candidate: idx in the low word, key in the high one
+        const uint64_t c = (uint64_t)(f2u(h[r][i]) & 0x7fffffffu) << 32 | (uint32_t)idx;
         if (rank < fit) {
-          lists[(size_t)list * td.sub_cap + start + rank] = c;
+          store_word<SHARED>(reinterpret_cast<uint64_t*>(lists + (size_t)list * td.sub_cap + start + rank), c);
         } else {
           const uint32_t o = ostart + (rank - fit);
-          if (o < td.cand_cap) lists[(size_t)kCandLists * td.sub_cap + o] = c;
+          if (o < td.cand_cap) store_word<SHARED>(reinterpret_cast<uint64_t*>(lists + (size_t)kCandLists * td.sub_cap + o), c);
         }
         ++rank;
       }
@@ -160,11 +174,11 @@ __device__ __forceinline__ void for_each_candidate(const TensorDesc& td, const C
 // writes the bit mask.  Keys above the range are kept, keys below dropped; keys inside it are
 // listed and their bits are set afterwards by k_select_finish.  Called from k_update.
 // ---------------------------------------------------------------------------------------------
-template <bool FULL>
+template <bool FULL, bool SHARED = false>
 __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, uint32_t mode, uint32_t theta,
                                            uint32_t rng_lo, uint32_t rng_hi, uint32_t chunk_index,
                                            uint32_t tensor, Candidate* cands, uint32_t* counters) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & (kThreads - 1);
   float h[kRows][4];
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
@@ -188,8 +202,8 @@ __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, u
     }
   }
   cflags ^= kflags;  // the kept keys are above list_lo too
-  store_mask_flags<FULL>(td, base, kflags);
-  append_candidates(cflags, h, base, chunk_index, tensor, td, cands, counters);
+  store_mask_flags<FULL, SHARED>(td, base, kflags);
+  append_candidates<SHARED>(cflags, h, base, chunk_index, tensor, td, cands, counters);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -19,6 +19,9 @@ struct DeviceTables {
   Candidate* cands;      // pool: per tensor kCandLists * sub_cap + cand_cap entries
   uint32_t* cand_counters;  // n_tensors x (kCandLists + 1) counters, kCandCounterStride words apart
   uint32_t* trans_list;  // 2 x n_tensors
+  char* resize_scratch;  // new values of the first chunks of tensors that change size (resize_schedule.h)
+  LayerIn* inputs;       // n_tensors: what the running step's decisions read of the layers' records (k_update_local)
+  uint32_t* arrived;     // n_tensors counters, kCandCounterStride words apart: chunks done in a fallback pass; 0 between steps
   StepScalars* scalars;  // device copy of the per-step scalars, read by the kernels of a replayed graph
   uint32_t n_tensors;
   uint32_t total_chunks;
@@ -26,7 +29,7 @@ struct DeviceTables {
   uint32_t persistent_grid;  // workgroups of the persistent streaming kernels
 };
 
-hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, hipStream_t s);
+hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, bool local, hipStream_t s);
 hipError_t launch_curv_ema(const DeviceTables& t, const StepArg& sa, float beta_h, float omb_h, int fisher,
                            hipStream_t s);
 hipError_t launch_hist_pass(const DeviceTables& t, const StepArg& sa, int serial_rounds, hipStream_t s);
@@ -34,6 +37,8 @@ hipError_t launch_select_finish(const DeviceTables& t, const StepArg& sa, float 
 hipError_t launch_layer(const DeviceTables& t, const StepArg& sa, const Hyper& hp, hipStream_t s);
 hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem,
                          hipStream_t s);
+hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool any_probe, hipStream_t s);
+hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, float beta_h, hipStream_t s);
 hipError_t launch_mask_pass(const DeviceTables& t, const StepArg& sa, hipStream_t s);
 hipError_t launch_update_resize(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha,
                                 bool elem, hipStream_t s);

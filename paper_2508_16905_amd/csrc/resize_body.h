@@ -7,51 +7,95 @@
 
 namespace triaccel {
 
-// The tensors are rewritten in place in the order resize_schedule.h lays down: stage 0 (the first
-// chunks of a tensor, one workgroup, a barrier between the loads and the stores of every chunk), then
-// subtree stages in which every workgroup walks the levels of its own subtree of chunks with a
-// barrier between levels.  No workgroup waits for another; what a stage depends on was done by an
+// The tensors are rewritten in place in the order resize_schedule.h lays down: stage 0 (the first chunks of
+// a tensor), then subtree stages in which every workgroup walks the levels of its own subtree of chunks with
+// a barrier between levels.  No workgroup waits for another; what a stage depends on was done by an
 // earlier launch.  Launch q performs stage q for the narrowing tensors of the step's list and stage
-// n_stages - 1 - q for the widening ones.
+// n_stages - 1 - q for the widening ones; the slots [0, top) of a tensor belong to stage 0, the others to the
+// subtrees.
 //
-// Work items of a launch are (list entry, workgroup of that tensor) pairs, `slots` per entry (the
-// larger of the two stages' workgroup counts); workgroup `wg` of `n_wg` takes the items wg,
-// wg + n_wg, ...  The list and its length are written on the device by the per-layer kernel, so the
-// work is offered on every step and nothing happens when the list is empty.  Uniform over the
-// workgroup (it contains barriers).
+// With one workgroup taking the 16 first chunks one after the other, as the form without subtree stages still
+// does, that stage is a chain of 2-6 us per chunk; side by side the 64 first chunks of 12 tensors take 26 us with
+// the rest of that launch.
+// Scratch of the tensor for chunk c < top: kChunk elements of 4 bytes.
+__device__ __forceinline__ char* resize_scratch(const TensorDesc& td, char* scratch, uint32_t c) {
+  return scratch + ((size_t)td.resize_slot + c) * (kChunk * 4);
+}
+
+// Copies the new values of chunk c from the scratch area into place.
+__device__ __forceinline__ void resize_copy(const TensorDesc& td, const char* src, uint32_t esz, uint32_t c) {
+  const int64_t base = (int64_t)c * kChunk, left = td.numel - base;
+  const uint32_t bytes = (uint32_t)(left < kChunk ? left : kChunk) * esz;
+  char* const dst = static_cast<char*>(td.param) + base * esz;
+  for (uint32_t off = threadIdx.x * 16; off < bytes; off += kThreads * 16) {
+    if (off + 16 <= bytes) {
+      *as_global<v4f>(dst + off) = *as_global<v4f>(src + off);
+    } else {
+      for (uint32_t b = off; b < bytes; b += 2) *as_global<uint16_t>(dst + b) = *as_global<uint16_t>(src + b);
+    }
+  }
+}
+
+// One tensor's work of slot `r` in launch `launch`.  Uniform over the workgroup (it contains barriers).
+template <bool ELEM, bool MOM>
+__device__ __forceinline__ void resize_item(const TensorDesc& td, int pd, int nd, const StepSize& ss, const ResizePlan& plan,
+                                            char* scratch, uint32_t launch, uint32_t r, const StepScalars& sc, float wd,
+                                            float mu) {
+  const int tid = (int)threadIdx.x;
+  const bool narrowing = elem_size(nd) < elem_size(pd);
+  if (plan.n_stages == 1) {
+    if (r != 0) return;
+    resize_walk_top(plan, td.n_chunks, narrowing, [&](uint32_t c) {
+      ChunkRegs regs;
+      update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
+      __syncthreads();  // chunk 0 overwrites itself; a later chunk overwrites what an earlier one loaded
+      update_store_any<MOM>(td, nd, (int64_t)c * kChunk, tid, regs);
+    });
+    return;
+  }
+  const uint32_t stage = resize_stage_of_launch(plan, launch, narrowing);
+  // in place for the subtrees, into the scratch area for a chunk of stage 0
+  TensorDesc to = td;
+  uint32_t sub = r - plan.top;
+  if (r < plan.top) {
+    if (r >= td.n_chunks) return;
+    if (launch != 0) {
+      if (launch == resize_copy_launch(plan, narrowing)) resize_copy(td, resize_scratch(td, scratch, r), elem_size(nd), r);
+      return;
+    }
+    to.param = resize_scratch(td, scratch, r) - (int64_t)r * kChunk * elem_size(nd);
+  } else {
+    if (stage == 0 || sub >= resize_stage_roots(plan, stage) || plan.root[stage] + sub >= td.n_chunks) return;
+  }
+  const auto chunk = [&](uint32_t c) {
+    ChunkRegs regs;
+    update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
+    update_store_any<MOM>(to, nd, (int64_t)c * kChunk, tid, regs);
+  };
+  // a chunk of stage 0 is a walk of one level and one chunk
+  if (r < plan.top) chunk(r);
+  else resize_walk_subtree(plan, stage, sub, td.n_chunks, narrowing, chunk, [&]() { __syncthreads(); });
+}
+
+// Work items of a launch are (list entry, slot) pairs, `slots` per entry (enough for either direction);
+// workgroup `wg` of `n_wg` takes the items wg,
+// wg + n_wg, ...  The list and its length are written on the device by the kernel that takes the layers'
+// decisions, so the work is offered on every step and nothing happens when the list is empty.
 template <bool ELEM, bool MOM>
 __device__ __forceinline__ void resize_items(const TensorDesc* __restrict__ tds, const LayerDev* layers,
                                              const GlobalDev* glob, const uint32_t* trans_list, uint32_t n_tensors,
-                                             const ResizePlan& plan, uint32_t launch, uint32_t slots, uint32_t wg,
+                                             const ResizePlan& plan, char* scratch, uint32_t launch, uint32_t slots, uint32_t wg,
                                              uint32_t n_wg, const StepScalars& sc, float wd, float mu, float alpha) {
   const uint32_t count = glob->trans_count[sc.step_id & 1u];
   const uint32_t* list = trans_list + (sc.step_id & 1u) * n_tensors;
-  const int tid = (int)threadIdx.x;
   const uint64_t items = (uint64_t)count * slots;
   for (uint64_t item = wg; item < items; item += n_wg) {
     const uint32_t l = list[item / slots];
     const uint32_t r = (uint32_t)(item % slots);
     const LayerDev& ls = layers[l];
-    const int pd = ls.prev_code, nd = ls.code;
-    const bool narrowing = elem_size(nd) < elem_size(pd);
-    const uint32_t stage = resize_stage_of_launch(plan, launch, narrowing);
-    if (r >= resize_stage_roots(plan, stage)) continue;
-    const TensorDesc td = tds[l];
     const StepSize ss{-ls.eta, sc.lr, alpha, ls.theta_key};
-    if (stage == 0) {
-      resize_walk_top(plan, td.n_chunks, narrowing, [&](uint32_t c) {
-        ChunkRegs regs;
-        update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
-        __syncthreads();  // chunk 0 overwrites itself; a later chunk overwrites what an earlier one loaded
-        update_store_any<MOM>(td, nd, (int64_t)c * kChunk, tid, regs);
-      });
-    } else {
-      if (plan.root[stage] + r >= td.n_chunks) continue;
-      resize_walk_subtree(
-          plan, stage, r, td.n_chunks, narrowing,
-          [&](uint32_t c) { update_any<ELEM, MOM>(td, pd, nd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid); },
-          [&]() { __syncthreads(); });
-    }
+    const TensorDesc td = tds[l];
+    resize_item<ELEM, MOM>(td, ls.prev_code, ls.code, ss, plan, scratch, launch, r, sc, wd, mu);
   }
 }
 
@@ -60,12 +104,18 @@ struct ResizeGrid {
   uint32_t slots;
   uint32_t grid;
 };
-inline ResizeGrid resize_grid(const ResizePlan& plan, uint32_t launch, uint32_t n_tensors) {
-  // a narrowing tensor is at stage `launch`, a widening one at the mirrored stage
-  const uint32_t a = resize_stage_roots(plan, launch), b = resize_stage_roots(plan, plan.n_stages - 1u - launch);
-  const uint32_t slots = a > b ? a : b;
+inline ResizeGrid resize_grid(const ResizePlan& plan, uint32_t launch, uint32_t n_tensors, bool small) {
+  uint32_t slots = 1;
+  if (plan.n_stages > 1) {
+    // a narrowing tensor is at stage `launch`, a widening one at the mirrored stage
+    const uint32_t sa = launch, sb = plan.n_stages - 1u - launch;
+    const uint32_t a = sa ? resize_stage_roots(plan, sa) : 0u, b = sb ? resize_stage_roots(plan, sb) : 0u;
+    slots = plan.top + (a > b ? a : b);
+  }
   uint64_t grid = (uint64_t)n_tensors * slots;
-  if (grid > 65536u) grid = 65536u;
+  // the workgroups are offered on every step: small sets loop over their items rather than pay for more
+  const uint64_t cap = small ? 1024u : 65536u;
+  if (grid > cap) grid = cap;
   return ResizeGrid{slots, (uint32_t)grid};
 }
 

@@ -15,10 +15,17 @@
 // level with a workgroup barrier between levels (root to leaves when narrowing, leaves to root when
 // widening) and without waiting for any other workgroup.  What a root itself depends on lies in
 // [A / 2, A) (narrowing) -- chunks done by an earlier launch.  A step therefore needs
-//   stage 0      chunks [0, top): one workgroup per tensor, chunk by chunk, barrier in every chunk
+//   stage 0      chunks [0, top)
 //   stage j >= 1 chunks [root_j, root_j 2^depth_j): root_j workgroups per tensor, depth_j levels each
 // with root_1 = top and root_{j+1} = root_j 2^depth_j, in this order for a narrowing tensor and in
 // the reverse order for a widening one.
+//
+// Stage 0 has two forms.  In a set without a subtree stage it is one workgroup per tensor that takes the
+// chunks one after the other, with a barrier in every chunk: no launch of its own is needed.  With subtree
+// stages, `top` workgroups compute one chunk each in launch 0 and put the new values into a scratch area of
+// the tensor's own; they are copied into place by resize_copy_launch, after all chunks that hold old data
+// there (those below 2 top) have been loaded by earlier launches: no chain, at the price of moving 2 or 4
+// bytes per element of `top` chunks twice.
 #pragma once
 #include <stdint.h>
 
@@ -31,7 +38,9 @@
 namespace triaccel {
 
 constexpr uint32_t kResizeMaxStages = 8;     // stage 0 plus up to 7 subtree stages
-constexpr uint32_t kResizeTop = 16;          // chunks of stage 0 when subtree stages follow
+constexpr uint32_t kResizeTop = 16;          // chunks of stage 0 when subtree stages follow, large sets
+constexpr uint32_t kResizeTopSmall = 64;     // the same, sets below kResizeBigSet: fewer levels in all, so fewer
+                                             // stages and shallower subtrees
 constexpr uint32_t kResizeTopOnly = 128;     // tensors up to this many chunks: stage 0 alone
 constexpr uint32_t kResizeBigSet = 16384;    // chunks in the whole set from which a launch more costs nothing
                                              // (= kLaunchBoundChunks of the step's other kernels)
@@ -53,7 +62,7 @@ TA_HD ResizePlan make_resize_plan(uint32_t max_chunks, uint32_t total_chunks) {
     p.top = max_chunks ? max_chunks : 1u;
     return p;
   }
-  p.top = kResizeTop;
+  p.top = total_chunks >= kResizeBigSet ? kResizeTop : kResizeTopSmall;
   uint32_t levels = 0;  // smallest count with top << levels >= max_chunks
   while (((uint64_t)p.top << levels) < max_chunks) ++levels;
   const uint32_t dmax = total_chunks >= kResizeBigSet ? 4u : 6u;
@@ -74,10 +83,15 @@ TA_HD uint32_t resize_stage_of_launch(const ResizePlan& p, uint32_t launch, bool
   return narrowing ? launch : p.n_stages - 1u - launch;
 }
 
-// Workgroups one tensor needs in a stage (stage 0: one).
+// Launch in which a scratch copy of chunks [0, top) is put into place (plans with subtree stages): a
+// narrowing chunk overwrites old data of [0, top) only, a widening one of [0, 2 top), whose last part is
+// loaded by stage 1.
+TA_HD uint32_t resize_copy_launch(const ResizePlan& p, bool narrowing) { return narrowing ? 1u : p.n_stages - 1u; }
+
+// Workgroups one tensor needs in a stage (stage 0 in one workgroup: one).
 TA_HD uint32_t resize_stage_roots(const ResizePlan& p, uint32_t stage) { return stage == 0 ? 1u : p.root[stage]; }
 
-// Stage 0: chunks [0, min(top, n_chunks)), ascending when narrowing, descending when widening.
+// Stage 0 in one workgroup: chunks [0, min(top, n_chunks)), ascending when narrowing, descending when widening.
 // `chunk_op(c)` must load the chunk, pass a workgroup barrier, then store it.
 template <class ChunkOp>
 TA_HD void resize_walk_top(const ResizePlan& p, uint32_t n_chunks, bool narrowing, ChunkOp&& chunk_op) {

@@ -48,12 +48,12 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
                                                      const ChunkRef* __restrict__ chunks, LayerDev* layers,
                                                      const GlobalDev* glob, Candidate* cands, uint32_t* counters,
                                                      const uint32_t* trans_list, uint32_t n_tensors, ResizePlan plan,
-                                                     uint32_t resize_slots, uint32_t resize_wgs, StepArg sa, float wd,
+                                                     char* scratch, uint32_t resize_slots, uint32_t resize_wgs, StepArg sa, float wd,
                                                      float mu, float alpha) {
   const StepScalars sc = step_scalars(sa);
   if (blockIdx.x < resize_wgs) {
     if (step_skipped(glob, sc.step_id)) return;
-    resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, 0u, resize_slots, blockIdx.x, resize_wgs, sc,
+    resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, scratch, 0u, resize_slots, blockIdx.x, resize_wgs, sc,
                             wd, mu, alpha);
     return;
   }
@@ -85,12 +85,12 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
 hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem,
                          hipStream_t s) {
   const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
-  const ResizeGrid rg = resize_grid(plan, 0u, t.n_tensors);
+  const ResizeGrid rg = resize_grid(plan, 0u, t.n_tensors, t.total_chunks < kResizeBigSet);
   const dim3 grid(t.total_chunks + rg.grid);
   const auto kernel = elem ? (mu != 0.0f ? k_update<true, true> : k_update<true, false>)
                            : (mu != 0.0f ? k_update<false, true> : k_update<false, false>);
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers, t.glob, t.cands,
-                     t.cand_counters, t.trans_list, t.n_tensors, plan, rg.slots, rg.grid, sa, wd, mu, alpha);
+                     t.cand_counters, t.trans_list, t.n_tensors, plan, t.resize_scratch, rg.slots, rg.grid, sa, wd, mu, alpha);
   TA_LAUNCH_CHECK();
   return hipSuccess;
 }

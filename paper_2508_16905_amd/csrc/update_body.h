@@ -23,16 +23,18 @@ struct StepSize {
   uint32_t theta_key;  // element-wise form: bit pattern of the mask threshold
 };
 
-// New parameter values and momentum of a lane's 16 elements of one chunk.
+// A lane's 16 elements of one chunk: parameters, momentum and gradient as loaded, then the new values.
 struct ChunkRegs {
   float th[kRows][4];
   float m[kRows][4];
+  float g[kRows][4];
+};
+struct CurvRegs {
+  float h[kRows][4];
 };
 
 template <int GD, int PD, bool FULL, bool MOM, bool ELEM>
-__device__ __forceinline__ void update_load(const TensorDesc& td, int64_t base, float inv_scale, float wd, float mu,
-                                            const StepSize& ss, int tid, ChunkRegs& r) {
-  float g[kRows][4], h[ELEM ? kRows : 1][4];
+__device__ __forceinline__ void update_fetch(const TensorDesc& td, int64_t base, int tid, ChunkRegs& r, CurvRegs& c) {
   // Row by row, the arrays interleaved.  (Measured over 48 placements of the arrays in memory each,
   // with the accesses in the global address space: issuing the loads array by array instead is 2 %
   // slower on average, rotating the row order between the arrays changes nothing.)
@@ -40,28 +42,33 @@ __device__ __forceinline__ void update_load(const TensorDesc& td, int64_t base, 
   for (int q = 0; q < kRows; ++q) {
     const int64_t idx = base + q * kRowElems + tid * kVec;
     if constexpr (FULL) {
-      load4<GD>(td.grad, idx, g[q]);
+      load4<GD>(td.grad, idx, r.g[q]);
       load4<PD>(td.param, idx, r.th[q]);
       if constexpr (MOM) load4<kFP32>(td.mom, idx, r.m[q]);
-      if constexpr (ELEM) load4<kFP32>(td.curv, idx, h[q]);
+      if constexpr (ELEM) load4<kFP32>(td.curv, idx, c.h[q]);
     } else {
-      load4_guard<GD>(td.grad, idx, td.numel, 0.0f, g[q]);
+      load4_guard<GD>(td.grad, idx, td.numel, 0.0f, r.g[q]);
       load4_guard<PD>(td.param, idx, td.numel, 0.0f, r.th[q]);
       if constexpr (MOM) load4_guard<kFP32>(td.mom, idx, td.numel, 0.0f, r.m[q]);
-      if constexpr (ELEM) load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, h[q]);
+      if constexpr (ELEM) load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, c.h[q]);
     }
   }
+}
+
+template <bool MOM, bool ELEM>
+__device__ __forceinline__ void update_math(float inv_scale, float wd, float mu, const StepSize& ss, ChunkRegs& r,
+                                            const CurvRegs& c) {
 #pragma unroll
   for (int q = 0; q < kRows; ++q) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float gt = g[q][i] * inv_scale;
+      const float gt = r.g[q][i] * inv_scale;
       const float d = fmaf(wd, r.th[q][i], gt);
       const float mm = MOM ? fmaf(mu, r.m[q][i], d) : d;
       r.m[q][i] = mm;
       float neg_eta = ss.neg_eta;
       if constexpr (ELEM) {
-        const uint32_t key = f2u(h[q][i]) & 0x7fffffffu;
+        const uint32_t key = f2u(c.h[q][i]) & 0x7fffffffu;
         const float a = (key >= ss.theta_key && key != 0u) ? u2f(key) : 0.0f;
         const float den = fmaf(ss.alpha, a, 1.0f);
         neg_eta = -(ss.lr / den);
@@ -92,30 +99,36 @@ __device__ __forceinline__ void update_store(const TensorDesc& td, int64_t base,
 // row of a chunk ahead of the branch and wait for it there, two memory latencies per chunk instead of
 // one (50 M parameters that all change size: 252 -> 236 us a step; 11.2 M ordinary: 55.2 -> 54.6 us).
 template <bool ELEM, bool MOM, int GD, int PD>
-__device__ __forceinline__ void update_load2(const TensorDesc& td, int64_t base, float inv_scale, float wd, float mu,
-                                             const StepSize& ss, int tid, ChunkRegs& r) {
-  if (base + kChunk <= td.numel) update_load<GD, PD, true, MOM, ELEM>(td, base, inv_scale, wd, mu, ss, tid, r);
-  else update_load<GD, PD, false, MOM, ELEM>(td, base, inv_scale, wd, mu, ss, tid, r);
+__device__ __forceinline__ void update_fetch2(const TensorDesc& td, int64_t base, int tid, ChunkRegs& r, CurvRegs& c) {
+  if (base + kChunk <= td.numel) update_fetch<GD, PD, true, MOM, ELEM>(td, base, tid, r, c);
+  else update_fetch<GD, PD, false, MOM, ELEM>(td, base, tid, r, c);
 }
 
 template <bool ELEM, bool MOM, int GD>
-__device__ __forceinline__ void update_load1(int pd, const TensorDesc& td, int64_t base, float inv_scale, float wd,
-                                             float mu, const StepSize& ss, int tid, ChunkRegs& r) {
+__device__ __forceinline__ void update_fetch1(int pd, const TensorDesc& td, int64_t base, int tid, ChunkRegs& r, CurvRegs& c) {
   switch (pd) {
-    case kFP32: update_load2<ELEM, MOM, GD, kFP32>(td, base, inv_scale, wd, mu, ss, tid, r); break;
-    case kBF16: update_load2<ELEM, MOM, GD, kBF16>(td, base, inv_scale, wd, mu, ss, tid, r); break;
-    default: update_load2<ELEM, MOM, GD, kFP16>(td, base, inv_scale, wd, mu, ss, tid, r); break;
+    case kFP32: update_fetch2<ELEM, MOM, GD, kFP32>(td, base, tid, r, c); break;
+    case kBF16: update_fetch2<ELEM, MOM, GD, kBF16>(td, base, tid, r, c); break;
+    default: update_fetch2<ELEM, MOM, GD, kFP16>(td, base, tid, r, c); break;
+  }
+}
+
+template <bool ELEM, bool MOM>
+__device__ __forceinline__ void update_fetch_any(const TensorDesc& td, int pd, int64_t base, int tid, ChunkRegs& r,
+                                                 CurvRegs& c) {
+  switch (td.grad_dtype) {
+    case kFP32: update_fetch1<ELEM, MOM, kFP32>(pd, td, base, tid, r, c); break;
+    case kBF16: update_fetch1<ELEM, MOM, kBF16>(pd, td, base, tid, r, c); break;
+    default: update_fetch1<ELEM, MOM, kFP16>(pd, td, base, tid, r, c); break;
   }
 }
 
 template <bool ELEM, bool MOM>
 __device__ __forceinline__ void update_load_any(const TensorDesc& td, int pd, int64_t base, float inv_scale, float wd,
                                                 float mu, const StepSize& ss, int tid, ChunkRegs& r) {
-  switch (td.grad_dtype) {
-    case kFP32: update_load1<ELEM, MOM, kFP32>(pd, td, base, inv_scale, wd, mu, ss, tid, r); break;
-    case kBF16: update_load1<ELEM, MOM, kBF16>(pd, td, base, inv_scale, wd, mu, ss, tid, r); break;
-    default: update_load1<ELEM, MOM, kFP16>(pd, td, base, inv_scale, wd, mu, ss, tid, r); break;
-  }
+  CurvRegs c;
+  update_fetch_any<ELEM, MOM>(td, pd, base, tid, r, c);
+  update_math<MOM, ELEM>(inv_scale, wd, mu, ss, r, c);
 }
 
 template <bool MOM, int ND>

@@ -1,0 +1,213 @@
+// gfx950 kernels for sets bound by their launches: k_update_local does what the per-layer kernel, the fallback
+// histogram pass, the fused update + cast and the first launch of the in-place resize do one after the other on
+// larger sets, k_select_tail what the mask pass and the threshold resolution do.
+#include "layer_body.h"
+#include "resize_body.h"
+
+namespace triaccel {
+
+// Arrival counter of a tensor, in a cache line of its own.
+__device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { return arrived + (size_t)l * kCandCounterStride; }
+
+// Every workgroup of a chunk adds up its tensor's chunk records (at most kLocalMaxChunks x 32 bytes, from
+// the caches) and takes the layer's decisions itself, each the same ones, while the chunk's own data is on
+// the way.  No workgroup waits for another: the fields of the layer's record that the decisions read were
+// copied aside by the statistics kernel and the selection's plan by the curvature kernel, so that the
+// workgroup of chunk 0 and the selection may write the record while the others run.  (An arrival counter per
+// tensor instead, with the last workgroup writing, cost one atomic per chunk: with the counters side by side
+// in a cache line 20 ns each, 205 us instead of 35 on the ResNet-18 set.)
+//
+// For a tensor whose listed keys do not settle the threshold the chunk workgroups also count |h| into its
+// histogram, and the last of the tensor scans it; k_select_tail does what is left of the selection.  (Settling
+// the listed keys in this launch, by workgroups beside the streaming ones, took 100-200 us: each of their
+// dependent accesses queues behind the streams of its compute unit.)
+//
+// Measured, per step, against the separate launches: two-layer perceptron (4 tensors, 0.1 M) 13.4 -> 8.8 us,
+// EfficientNet-B0 set 23.4 -> 19.5 (16-bit gradients, no probe) and 65.7 -> 57.1 (probed), ResNet-18 set
+// 54.6 -> 50.0 and 102.4 -> 94.5.
+template <bool MOM, bool PROBED>
+__global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __restrict__ tds,
+                                                           const ChunkRef* __restrict__ chunks,
+                                                           const StatPartial* __restrict__ partials,
+                                                           const EmaPartial* __restrict__ ema_partials,
+                                                           const LayerIn* __restrict__ inputs, LayerDev* layers,
+                                                           GlobalDev* glob, GlobalDev* host_result, uint32_t* counters,
+                                                           uint32_t* hist, uint32_t* arrived, uint32_t* trans_list,
+                                                           uint32_t n_tensors, ResizePlan plan, char* scratch, StepArg sa,
+                                                           Hyper hp) {
+  __shared__ LayerShared sh_layer;
+  __shared__ HistShared sh;
+  __shared__ LayerOut s_decision;
+  __shared__ uint32_t s_last;
+  const StepScalars sc = step_scalars(sa);
+  const uint64_t skip_epoch = glob->skip_epoch;
+  const bool skip = skip_epoch == sc.step_id;
+  const ChunkRef cr = chunks[blockIdx.x];
+  const TensorDesc td = tds[cr.tensor];
+  LayerDev& ls = layers[cr.tensor];
+  const LayerIn in = inputs[cr.tensor];
+  TA_LOADED("s"(td.param), "s"(td.grad), "s"(td.mom), "s"(td.curv), "s"(td.numel), "s"(td.first_chunk), "s"(td.grad_dtype),
+            "s"(td.has_probe), "s"(in.v), "s"(in.lambda), "s"(in.lambda_ctrl), "s"(in.code), "s"(in.applied_steps),
+            "s"(in.lambda_power), "s"(td.n_chunks));
+  if (skip) {
+    if (threadIdx.x == 0 && cr.index == 0) {
+      ls.found_inf = (ls.found_epoch == sc.step_id) ? 1u : 0u;
+      if (cr.tensor == 0) step_record(glob, host_result, sc, hp, true);
+    }
+    return;
+  }
+  const int64_t base = (int64_t)cr.index * kChunk;
+  const bool probed = PROBED && td.has_probe != 0;
+  const LayerAcc acc = layer_accumulate<PROBED>(td, partials, ema_partials, probed);
+  const LayerSums sums = layer_reduce<PROBED>(acc, td.numel, sh_layer);
+  const LayerOut o = layer_decide(in, sums, probed, sc.lr, hp);
+  if (threadIdx.x == 0) s_decision = o;  // for this thread alone, below
+  const int pd = in.code, nd = (int)uniform((uint32_t)o.code);
+  const StepSize ss{-u2f(uniform(f2u(o.eta))), sc.lr, hp.alpha, 0u};
+  if (elem_size(pd) == elem_size(nd)) {
+    update_any<false, MOM>(td, pd, nd, base, sc.inv_scale, hp.weight_decay, hp.momentum, ss, (int)threadIdx.x);
+  } else {
+    // launch 0 of the in-place resize: slot r of the tensor is the workgroup of its chunk r
+    resize_item<false, MOM>(td, pd, nd, ss, plan, scratch, 0u, cr.index, sc, hp.weight_decay, hp.momentum);
+  }
+  const EmaTotals ema = sums.ema;
+  uint32_t k = 0;
+  int outcome = kOutListed;
+  if constexpr (PROBED) {
+    if (probed) {
+      const SelNow now = select_plan(ls);
+      k = topk_count(td.numel, hp.sparsity_ppm, hp.topk_abs);
+      outcome = select_outcome(td, now, ema, k);
+      if (outcome == kOutHist) {
+        const Window w = first_window(now, ema.maxkey);
+        for (int b = threadIdx.x; b < kHistBins; b += kThreads) sh.hist[b] = 0;
+        __syncthreads();
+        uint32_t above = 0;
+        if (base + kChunk <= td.numel) hist_chunk<true>(td, base, w, sh.hist, now.predicted != 0, above);
+        else hist_chunk<false>(td, base, w, sh.hist, now.predicted != 0, above);
+        flush_hist(sh.hist, w.bins, hist + (size_t)cr.tensor * kHistBins);
+        above = wave_sum(above);
+        if ((threadIdx.x & (kWave - 1)) == 0 && above) atomicAdd(&ls.acc_above, above);
+        // This workgroup's counts (device-scope atomics) are complete before its arrival is counted.  With a
+        // release fence instead the first probed step of the ResNet-18 set took 833 us, 163 without.
+        published_before_here();
+        __syncthreads();
+      }
+    }
+  }
+  if (threadIdx.x == 0 && cr.index == 0) {
+    if (probed && outcome != kOutHist) select_setup(td, ls, glob, select_plan(ls), ema, k, outcome, sc.step_id);
+    layer_publish(cr.tensor, ls, s_decision, glob, trans_list, n_tensors, sc.step_id);
+    if (cr.tensor == 0) step_record(glob, host_result, sc, hp, false);
+  }
+  if constexpr (PROBED) {
+    if (cr.index == 0 && outcome != kOutListed) reset_cand_counters(counters, cr.tensor);  // drop what was listed
+    if (outcome != kOutHist) return;
+    if (threadIdx.x == 0) {
+      const bool last = atomicAdd(arrival(arrived, cr.tensor), 1u) + 1u == td.n_chunks;
+      if (last) {
+        *arrival(arrived, cr.tensor) = 0;
+        select_setup(td, ls, glob, select_plan(ls), ema, k, outcome, sc.step_id);
+      }
+      s_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // the scan reads what the other workgroups added with device-scope loads
+    select_scan(cr.tensor, td, ls, glob, hist, sc.step_id, sh.hist, sh.part, sh.out, true);
+    select_serial(cr.tensor, td, ls, glob, hist, sc.step_id, sh.hist, sh.part, sh.out, 8);
+  }
+}
+
+hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool any_probe, hipStream_t s) {
+  const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
+  const bool mom = hp.momentum != 0.0f;
+  const auto kernel = any_probe ? (mom ? k_update_local<true, true> : k_update_local<false, true>)
+                                : (mom ? k_update_local<true, false> : k_update_local<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.partials, t.ema_partials,
+                     t.inputs, t.layers, t.glob, t.host_result, t.cand_counters, t.hist, t.arrived, t.trans_list, t.n_tensors,
+                     plan, t.resize_scratch, sa, hp);
+  TA_LAUNCH_CHECK();
+  return hipSuccess;
+}
+
+// What is left of the selection after k_update_local.  Workgroup l < n_tensors settles tensor l if its listed
+// keys suffice.  The workgroups after those make the mask pass of the other tensors, four chunks at a time, and
+// the last workgroup to finish a part of such a tensor settles it among the keys the pass listed; they leave at
+// once when there is no such tensor (the steady state).
+__global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc* __restrict__ tds,
+                                                                const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
+                                                                uint32_t n_tensors, LayerDev* layers, const GlobalDev* glob,
+                                                                Candidate* cands, uint32_t* counters, uint32_t* arrived,
+                                                                StepArg sa, float beta_h) {
+  __shared__ SelectShared<kFinishThreads> sh;
+  __shared__ uint32_t s_last;
+  const StepScalars sc = step_scalars(sa);
+  const uint64_t skip_epoch = glob->skip_epoch;
+  if (blockIdx.x < n_tensors) {
+    const uint32_t l = blockIdx.x;
+    const TensorDesc td = tds[l];
+    LayerDev& ls = layers[l];
+    // sel_outcome is not written here: it tells the two kinds apart while the records are rewritten
+    const uint32_t sel_outcome = ls.sel_outcome;
+    TA_LOADED("s"(td.mask), "s"(td.has_probe), "s"(sel_outcome));
+    if (skip_epoch == sc.step_id || !td.has_probe || sel_outcome > 1u) return;
+    select_finish<kFinishThreads, kFinishRegs>(l, td, ls, cands, counters, beta_h, sh);
+    return;
+  }
+  const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
+  if (pending == 0 || skip_epoch == sc.step_id) return;
+  const uint32_t part = blockIdx.x - n_tensors, parts = gridDim.x - n_tensors;
+  const uint32_t per = (total_chunks + parts - 1) / parts;
+  const uint32_t c1 = min((part + 1) * per, total_chunks);
+  const uint32_t group = threadIdx.x / kThreads;
+  uint32_t c = min(part * per, total_chunks);
+  while (c < c1) {
+    const uint32_t l = chunks[c].tensor;
+    const TensorDesc td = tds[l];
+    const uint32_t end = min(td.first_chunk + td.n_chunks, c1);
+    const uint32_t mine = end - c;
+    LayerDev& ls = layers[l];
+    const uint32_t mode = ls.mode;
+    if (!td.has_probe || ls.sel_outcome <= 1u || mode == kSelHist) {
+      c = end;
+      continue;
+    }
+    const uint32_t theta = ls.theta_key, rng_lo = ls.rng_lo, rng_hi = ls.rng_hi;
+    for (uint32_t q = c + group; q < end; q += kFinishThreads / kThreads) {
+      const uint32_t index = q - td.first_chunk;
+      const int64_t base = (int64_t)index * kChunk;
+      if (base + kChunk <= td.numel) mask_chunk<true, true>(td, base, mode, theta, rng_lo, rng_hi, index, l, cands, counters);
+      else mask_chunk<false, true>(td, base, mode, theta, rng_lo, rng_hi, index, l, cands, counters);
+    }
+    c = end;
+    published_before_here();  // mask words and listed keys are complete before the arrival is counted
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const bool last = atomicAdd(arrival(arrived, l), mine) + mine == td.n_chunks;
+      if (last) *arrival(arrived, l) = 0;
+      s_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    const bool last = s_last != 0;
+    __syncthreads();
+    if (last) {
+      // the resolution reads what the other workgroups listed: nothing older of it in this unit's caches
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      select_finish<kFinishThreads, kFinishRegs>(l, td, ls, cands, counters, beta_h, sh);
+      __syncthreads();
+    }
+  }
+}
+
+hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, float beta_h, hipStream_t s) {
+  constexpr uint32_t kGroups = kFinishThreads / kThreads;
+  const uint32_t all = (t.total_chunks + kGroups - 1) / kGroups, cap = t.persistent_grid / kGroups;
+  hipLaunchKernelGGL(k_select_tail, dim3(t.n_tensors + (all < cap ? all : cap)), dim3(kFinishThreads), 0, s, t.tensors,
+                     t.chunks, t.total_chunks, t.n_tensors, t.layers, t.glob, t.cands, t.cand_counters, t.arrived, sa,
+                     beta_h);
+  TA_LAUNCH_CHECK();
+  return hipSuccess;
+}
+
+}  // namespace triaccel

@@ -8,11 +8,11 @@ namespace triaccel {
 template <bool ELEM, bool MOM>
 __global__ __launch_bounds__(kThreads) void k_update_resize(const TensorDesc* __restrict__ tds, const LayerDev* layers,
                                                             const GlobalDev* glob, const uint32_t* trans_list,
-                                                            uint32_t n_tensors, ResizePlan plan, uint32_t launch,
+                                                            uint32_t n_tensors, ResizePlan plan, char* scratch, uint32_t launch,
                                                             uint32_t slots, StepArg sa, float wd, float mu, float alpha) {
   const StepScalars sc = step_scalars(sa);
   if (step_skipped(glob, sc.step_id)) return;
-  resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, launch, slots, blockIdx.x, gridDim.x, sc, wd, mu,
+  resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, scratch, launch, slots, blockIdx.x, gridDim.x, sc, wd, mu,
                      alpha);
 }
 
@@ -45,11 +45,11 @@ hipError_t launch_update_resize(const DeviceTables& t, const StepArg& sa, float 
                                 bool elem, hipStream_t s) {
   const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
   for (uint32_t launch = 1; launch < plan.n_stages; ++launch) {
-    const ResizeGrid rg = resize_grid(plan, launch, t.n_tensors);
+    const ResizeGrid rg = resize_grid(plan, launch, t.n_tensors, t.total_chunks < kResizeBigSet);
     const auto kernel = elem ? (mu != 0.0f ? k_update_resize<true, true> : k_update_resize<true, false>)
                              : (mu != 0.0f ? k_update_resize<false, true> : k_update_resize<false, false>);
     hipLaunchKernelGGL(kernel, dim3(rg.grid), dim3(kThreads), 0, s, t.tensors, t.layers, t.glob, t.trans_list,
-                       t.n_tensors, plan, launch, rg.slots, sa, wd, mu, alpha);
+                       t.n_tensors, plan, t.resize_scratch, launch, rg.slots, sa, wd, mu, alpha);
     TA_LAUNCH_CHECK();
   }
   return hipSuccess;
