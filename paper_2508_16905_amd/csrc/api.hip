@@ -89,10 +89,7 @@ struct triaccel_ctx {
   StepGraph graphs[2][kTableSlots];
   // power iteration (only with cfg.power_k > 0)
   PowerTables pt{};
-  PowerDesc* power_staging[kRing] = {};
-  hipEvent_t power_ev[kRing] = {};
-  bool power_used[kRing] = {};
-  int power_pos = 0;
+  std::vector<PowerDesc> power_descs;
   bool power_called = false;
   hipEvent_t power_prof[4] = {};
   bool power_timed = false;  // the last call recorded its kernel boundaries
@@ -158,10 +155,9 @@ void free_ctx(triaccel_ctx* c) {
   for (int i = 0; i < kRing; ++i) {
     if (c->staging[i]) (void)hipHostFree(c->staging[i]);
     if (c->staging_ev[i]) (void)hipEventDestroy(c->staging_ev[i]);
-    if (c->power_staging[i]) (void)hipHostFree(c->power_staging[i]);
-    if (c->power_ev[i]) (void)hipEventDestroy(c->power_ev[i]);
-    if (c->power_prof[i]) (void)hipEventDestroy(c->power_prof[i]);
   }
+  for (auto& e : c->power_prof)
+    if (e) (void)hipEventDestroy(e);
   for (auto& variant : c->graphs)
     for (auto& g : variant) {
       if (g.exec) (void)hipGraphExecDestroy(g.exec);
@@ -427,9 +423,10 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     // workspace of the power iteration: segment table, per-segment sums, per-layer records
     std::vector<SegRef> segs;
     std::vector<uint32_t> seg_first((size_t)n);
+    const uint32_t seg = power_seg(T.total_chunks);
     for (int32_t i = 0; i < n; ++i) {
       seg_first[i] = (uint32_t)segs.size();
-      const uint32_t ns = (c->desc[i].n_chunks + kPowerSeg - 1) / kPowerSeg;
+      const uint32_t ns = (c->desc[i].n_chunks + seg - 1) / seg;
       for (uint32_t k = 0; k < ns; ++k) segs.push_back(SegRef{(uint32_t)i, k});
     }
     PowerTables& P = c->pt;
@@ -439,6 +436,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     P.n_tensors = (uint32_t)n;
     P.total_chunks = T.total_chunks;
     P.total_segs = (uint32_t)segs.size();
+    P.seg = seg;
     if ((rc = dev_alloc(c, &P.descs, (size_t)n))) return fail(rc);
     if ((rc = dev_alloc(c, &P.segs, segs.size()))) return fail(rc);
     if ((rc = dev_alloc(c, &P.seg_first, (size_t)n))) return fail(rc);
@@ -448,12 +446,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segments)"));
     e = hipMemcpy(P.seg_first, seg_first.data(), (size_t)n * sizeof(uint32_t), hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segment index)"));
-    for (int i = 0; i < kRing; ++i) {
-      e = hipHostMalloc(reinterpret_cast<void**>(&c->power_staging[i]), (size_t)n * sizeof(PowerDesc), hipHostMallocDefault);
-      if (e != hipSuccess) return fail(hip_fail(e, "hipHostMalloc(power staging)"));
-      e = hipEventCreateWithFlags(&c->power_ev[i], hipEventDisableTiming);
-      if (e != hipSuccess) return fail(hip_fail(e, "hipEventCreate"));
-    }
+    c->power_descs.resize((size_t)n);
     c->power_host.resize((size_t)n);
   }
   e = hipHostMalloc(reinterpret_cast<void**>(&c->pinned_res), sizeof(GlobalDev), hipHostMallocDefault);
@@ -703,18 +696,11 @@ int triaccel_power_iter(triaccel_handle h, const triaccel_power_tensor* vectors,
     if (v.stride < h->numel[i] || (v.stride & 3) != 0) return TRIACCEL_E_INVALID_ARG;
     if (!aligned16(v.u) || !aligned16(v.hu)) return TRIACCEL_E_ALIGNMENT;
   }
-  const int slot = h->power_pos;
-  h->power_pos = (h->power_pos + 1) % kRing;
-  if (h->power_used[slot]) TA_HIP(hipEventSynchronize(h->power_ev[slot]));
-  for (int32_t i = 0; i < n; ++i) h->power_staging[slot][i] = PowerDesc{vectors[i].u, vectors[i].hu, vectors[i].stride};
-  TA_HIP(hipMemcpyAsync(h->pt.descs, h->power_staging[slot], (size_t)n * sizeof(PowerDesc), hipMemcpyHostToDevice,
-                        h->stream));
-  TA_HIP(hipEventRecord(h->power_ev[slot], h->stream));
-  h->power_used[slot] = true;
+  for (int32_t i = 0; i < n; ++i) h->power_descs[i] = PowerDesc{vectors[i].u, vectors[i].hu, vectors[i].stride};
   if (h->profiling)
     for (auto& e : h->power_prof)
       if (!e) TA_HIP(hipEventCreate(&e));
-  TA_HIP(launch_power_iter(h->pt, k, latch ? 1 : 0, h->stream, h->profiling ? h->power_prof : nullptr));
+  TA_HIP(launch_power_iter(h->pt, h->power_descs.data(), k, latch ? 1 : 0, h->stream, h->profiling ? h->power_prof : nullptr));
   h->power_timed = h->profiling;
   h->power_called = true;
   return TRIACCEL_OK;

@@ -45,6 +45,19 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   return last_lane(v);
 }
 
+// Sum over the 64 lanes, in a fixed order, valid in every lane.
+#define TA_DPP_F64(v, ctrl, rows)                                                                          \
+  __hiloint2double((int)TA_DPP((uint32_t)__double2hiint(v), ctrl, rows), (int)TA_DPP((uint32_t)__double2loint(v), ctrl, rows))
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  v += TA_DPP_F64(v, 0x111, 0xF);
+  v += TA_DPP_F64(v, 0x112, 0xF);
+  v += TA_DPP_F64(v, 0x114, 0xF);
+  v += TA_DPP_F64(v, 0x118, 0xF);
+  v += TA_DPP_F64(v, 0x142, 0xA);
+  v += TA_DPP_F64(v, 0x143, 0xC);
+  return __hiloint2double((int)last_lane((uint32_t)__double2hiint(v)), (int)last_lane((uint32_t)__double2loint(v)));
+}
+
 // Set by the gradient-statistics kernel and read by the kernels after it (an ordinary load: the writer
 // is an earlier kernel).
 __device__ __forceinline__ bool step_skipped(const GlobalDev* glob, uint64_t step_id) { return glob->skip_epoch == step_id; }

@@ -6,19 +6,6 @@
 
 namespace triaccel {
 
-// Sum over the 64 lanes, in a fixed order, valid in every lane.
-#define TA_DPP_F64(v, ctrl, rows)                                                                          \
-  __hiloint2double((int)TA_DPP((uint32_t)__double2hiint(v), ctrl, rows), (int)TA_DPP((uint32_t)__double2loint(v), ctrl, rows))
-__device__ __forceinline__ double wave_sum_f64(double v) {
-  v += TA_DPP_F64(v, 0x111, 0xF);
-  v += TA_DPP_F64(v, 0x112, 0xF);
-  v += TA_DPP_F64(v, 0x114, 0xF);
-  v += TA_DPP_F64(v, 0x118, 0xF);
-  v += TA_DPP_F64(v, 0x142, 0xA);
-  v += TA_DPP_F64(v, 0x143, 0xC);
-  return __hiloint2double((int)last_lane((uint32_t)__double2hiint(v)), (int)last_lane((uint32_t)__double2loint(v)));
-}
-
 // Shared memory of layer_sums.
 struct LayerShared {
   double s1[kThreads / kWave], s2[kThreads / kWave];

@@ -8,7 +8,10 @@
 namespace triaccel {
 
 constexpr int kMaxPowerK = 8;  // vectors per layer the workspace can be sized for
-constexpr int kPowerSeg = 8;   // chunks of one tensor that one workgroup of the Gram pass sums
+// Chunks of one tensor that one workgroup of the Gram pass sums: 8, and 4 on sets below 16,384 chunks, where
+// segments of 8 leave the chip (768 workgroups at k = 5) short of work: 2768 chunks at k = 5, the three kernels of
+// an iteration together, 172 us with 8, 162 with 4, 165 with 2, 167 with 1 (more partial sums to add per tensor).
+constexpr uint32_t power_seg(uint32_t total_chunks) { return total_chunks < 16384 ? 4u : 8u; }
 
 // Doubles one workgroup of the Gram pass leaves for k vectors: the upper triangle of W^T W
 // (W = [H u_0 .. H u_{k-1}]), then u_j . (H u_j), then u_j . u_j.
@@ -23,8 +26,16 @@ struct PowerDesc {
 
 struct SegRef {
   uint32_t tensor;
-  uint32_t index;  // segment number inside the tensor: chunks [index * kPowerSeg, (index + 1) * kPowerSeg)
+  uint32_t index;  // segment number inside the tensor: chunks [index * seg, (index + 1) * seg)
 };
+
+// Pointers of a call with few enough tensors, passed by value to its first kernel.
+constexpr int kPowerArgTensors = 128;
+struct PowerDescArg {
+  uint32_t count;  // 0: read the table
+  PowerDesc e[kPowerArgTensors];
+};
+static_assert(sizeof(PowerDescArg) <= 3200, "passed by value as a kernel argument");
 
 // Per-tensor result of the last call.
 struct PowerLayer {
@@ -49,11 +60,13 @@ struct PowerTables {
   uint32_t n_tensors;
   uint32_t total_chunks;
   uint32_t total_segs;
+  uint32_t seg;  // power_seg(total_chunks)
 };
 
 // One iteration on k vectors per tensor: Gram pass, per-layer factorisation, apply pass.  With
-// `ev` (four events) the boundaries of the three kernels are recorded on the stream.
-hipError_t launch_power_iter(const PowerTables& t, int k, int latch, hipStream_t s, hipEvent_t* ev);
+// `ev` (four events) the boundaries of the three kernels are recorded on the stream.  `descs` (host, n_tensors
+// entries; null: the table t.descs is filled already) travels as kernel arguments.
+hipError_t launch_power_iter(const PowerTables& t, const PowerDesc* descs, int k, int latch, hipStream_t s, hipEvent_t* ev);
 
 // The same iteration without a handle and without any allocation: tables and partial sums live in a
 // fixed device array of this library (one per GPU), rebuilt by a small kernel on every call.

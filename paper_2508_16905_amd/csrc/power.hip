@@ -16,17 +16,11 @@
 
 #include <mutex>
 
-#include "numerics.h"
+#include "device_util.h"
 
 namespace triaccel {
 
 namespace {
-
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 
 __device__ __forceinline__ constexpr int tri(int i, int j) { return j * (j + 1) / 2 + i; }  // i <= j
 
@@ -59,32 +53,40 @@ __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, i
 #pragma unroll
         for (int i = 0; i <= j; ++i) g[tri(i, j)] = fma((double)w[i][e], wj, g[tri(i, j)]);
       }
+      // one element's conversions to double at a time: those of all four took 80 registers more
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-// Gram pass: one workgroup per segment (kPowerSeg consecutive chunks of one tensor).
+// Gram pass: one workgroup per segment (`seg` consecutive chunks of one tensor).  The pointers come with the
+// kernel's arguments when the call has few enough tensors, and the first segment of a tensor leaves them in the
+// table for the apply pass: a copy from host memory ahead of the pass cost the stream 10 us a call.
+// Bound by HBM: 447 MB (11.2 M parameters, k = 5) in 70 us, 6.3 TB/s; with 2 wavefronts per SIMD (206 registers),
+// segments of 8 chunks and reductions through LDS it took 79.
 template <int K>
-__global__ __launch_bounds__(kThreads) void k_power_gram(const TensorDesc* __restrict__ tds,
-                                                         const PowerDesc* __restrict__ pds,
-                                                         const SegRef* __restrict__ segs, double* __restrict__ partials) {
+__global__ __launch_bounds__(kThreads, K <= 5 ? 3 : 1) void k_power_gram(const TensorDesc* __restrict__ tds,
+                                                                         PowerDescArg arg, PowerDesc* __restrict__ pds,
+                                                                         const SegRef* __restrict__ segs, uint32_t seg,
+                                                                         double* __restrict__ partials) {
   constexpr int NG = K * (K + 1) / 2, PP = NG + 2 * K;
   const SegRef sr = segs[blockIdx.x];
   const int64_t numel = tds[sr.tensor].numel;
   const uint32_t n_chunks = tds[sr.tensor].n_chunks;
-  const PowerDesc pd = pds[sr.tensor];
+  const PowerDesc pd = arg.count ? arg.e[sr.tensor] : pds[sr.tensor];
+  if (arg.count && sr.index == 0 && threadIdx.x == 0) pds[sr.tensor] = pd;
   double g[NG], c[K], d[K];
 #pragma unroll
   for (int i = 0; i < NG; ++i) g[i] = 0.0;
 #pragma unroll
   for (int j = 0; j < K; ++j) c[j] = d[j] = 0.0;
-  const uint32_t c0 = sr.index * kPowerSeg;
-  const uint32_t c1 = min(c0 + (uint32_t)kPowerSeg, n_chunks);
-  for (uint32_t ch = c0; ch < c1; ++ch) {
-    const int64_t base = (int64_t)ch * kChunk;
-    if (base + kChunk <= numel) gram_chunk<K, true>(pd, numel, base, g, c, d);
-    else gram_chunk<K, false>(pd, numel, base, g, c, d);
-  }
+  const uint32_t c0 = sr.index * seg;
+  const uint32_t c1 = min(c0 + seg, n_chunks);
+  // the ragged chunk, if it is this segment's, comes after the loop over the full ones: with both bodies in one
+  // loop the sums were held twice (206 registers at k = 5, 2 wavefronts per SIMD)
+  const uint32_t full = min(c1, (uint32_t)(numel / kChunk));
+  for (uint32_t ch = c0; ch < full; ++ch) gram_chunk<K, true>(pd, numel, (int64_t)ch * kChunk, g, c, d);
+  if (full < c1) gram_chunk<K, false>(pd, numel, (int64_t)full * kChunk, g, c, d);
   // lanes, then wavefronts, in a fixed order
   __shared__ double s_part[kThreads / kWave][PP];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -114,16 +116,17 @@ __global__ __launch_bounds__(kThreads) void k_power_gram(const TensorDesc* __res
 template <int K>
 __global__ __launch_bounds__(kThreads) void k_power_layer(const TensorDesc* __restrict__ tds,
                                                           const uint32_t* __restrict__ seg_first,
-                                                          const double* __restrict__ partials, PowerLayer* state,
-                                                          LayerDev* layers, int latch) {
+                                                          uint32_t seg, const double* __restrict__ partials,
+                                                          PowerLayer* state, LayerDev* layers, int latch) {
   constexpr int NG = K * (K + 1) / 2, PP = NG + 2 * K;
   static_assert(PP <= kWave, "one lane per partial entry");
   const uint32_t l = blockIdx.x;
-  const uint32_t n_segs = (tds[l].n_chunks + kPowerSeg - 1) / kPowerSeg;
+  const uint32_t n_segs = (tds[l].n_chunks + seg - 1) / seg;
   const double* p = partials + (size_t)seg_first[l] * PP;
   const int e = threadIdx.x & (kWave - 1), part = threadIdx.x / kWave;
   double acc = 0.0;
   if (e < PP)
+#pragma unroll 8
     for (uint32_t s = part; s < n_segs; s += kThreads / kWave) acc += p[(size_t)s * PP + e];
   __shared__ double s_acc[kThreads / kWave][kWave];
   s_acc[part][e] = acc;
@@ -237,15 +240,32 @@ __global__ __launch_bounds__(kThreads) void k_power_apply(const TensorDesc* __re
   else apply_chunk<K, false>(pd, numel, base, t);
 }
 
+// Part of the pointer table of a call with many tensors.
+__global__ __launch_bounds__(kPowerArgTensors) void k_power_descs(PowerDescArg a, PowerDesc* __restrict__ pds) {
+  if (threadIdx.x < a.count) pds[threadIdx.x] = a.e[threadIdx.x];
+}
+
 template <int K>
-hipError_t launch_k(const PowerTables& t, int latch, hipStream_t s, hipEvent_t* ev) {
+hipError_t launch_k(const PowerTables& t, const PowerDesc* descs, int latch, hipStream_t s, hipEvent_t* ev) {
   hipError_t e;
+  PowerDescArg arg{};
+  if (descs) {
+    for (uint32_t first = 0; first < t.n_tensors; first += kPowerArgTensors) {
+      arg.count = t.n_tensors - first < (uint32_t)kPowerArgTensors ? t.n_tensors - first : (uint32_t)kPowerArgTensors;
+      for (uint32_t i = 0; i < arg.count; ++i) arg.e[i] = descs[first + i];
+      if (t.n_tensors <= (uint32_t)kPowerArgTensors) break;
+      hipLaunchKernelGGL(k_power_descs, dim3(1), dim3(kPowerArgTensors), 0, s, arg, t.descs + first);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (t.n_tensors > (uint32_t)kPowerArgTensors) arg.count = 0;
+  }
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_power_gram<K>, dim3(t.total_segs), dim3(kThreads), 0, s, t.tensors, t.descs, t.segs, t.partials);
+  hipLaunchKernelGGL(k_power_gram<K>, dim3(t.total_segs), dim3(kThreads), 0, s, t.tensors, arg, t.descs, t.segs,
+                     t.seg, t.partials);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_power_layer<K>, dim3(t.n_tensors), dim3(kThreads), 0, s, t.tensors, t.seg_first, t.partials,
-                     t.state, t.layers, latch);
+  hipLaunchKernelGGL(k_power_layer<K>, dim3(t.n_tensors), dim3(kThreads), 0, s, t.tensors, t.seg_first, t.seg,
+                     t.partials, t.state, t.layers, latch);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_power_apply<K>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.descs, t.chunks,
@@ -261,7 +281,9 @@ hipError_t launch_k(const PowerTables& t, int latch, hipStream_t s, hipEvent_t* 
 // device address is looked up once per GPU (each GPU holds its own copy) and passed to the kernels.
 // ---------------------------------------------------------------------------------------------
 constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
-constexpr size_t kStaticMaxSegs = kStaticMaxChunks / kPowerSeg + kStaticMaxTensors;
+constexpr size_t kStaticMaxSegs = kStaticMaxChunks / 8 + kStaticMaxTensors;
+static_assert(power_seg(16383) == 4 && power_seg(kStaticMaxChunks) == 8 && kStaticMaxChunks / 8 >= 16384 / 4,
+              "segments of any set fit the array");
 constexpr size_t kOffTensors = 0;
 constexpr size_t kOffDescs = kOffTensors + align256(sizeof(TensorDesc) * kStaticMaxTensors);
 constexpr size_t kOffSegFirst = kOffDescs + align256(sizeof(PowerDesc) * kStaticMaxTensors);
@@ -294,11 +316,11 @@ struct StaticBatchArg {
 static_assert(sizeof(StaticBatchArg) <= 3072, "passed by value as a kernel argument");
 
 // Table kernel: workgroup b writes the tables of tensor first + b (descriptor, chunk and segment lists).
-__global__ __launch_bounds__(kThreads) void k_static_tables(StaticBatchArg a, unsigned char* base) {
+__global__ __launch_bounds__(kThreads) void k_static_tables(StaticBatchArg a, uint32_t seg, unsigned char* base) {
   const StaticEntry en = a.e[blockIdx.x];
   const uint32_t l = a.first + blockIdx.x;
   const uint32_t nc = (uint32_t)((en.numel + kChunk - 1) / kChunk);
-  const uint32_t ns = (nc + kPowerSeg - 1) / kPowerSeg;
+  const uint32_t ns = (nc + seg - 1) / seg;
   if (threadIdx.x == 0) {
     TensorDesc td{};
     td.numel = en.numel;
@@ -354,7 +376,9 @@ hipError_t launch_power_iter_static(const StaticTensor* tensors, int n, int k, P
   unsigned char* base = g_scratch_ptr[dev];
   if (n == 0) return hipSuccess;
   // tables: the prefix sums are formed here, the lists are written on the device
-  uint32_t chunk_pos = 0, seg_pos = 0;
+  uint32_t chunk_pos = 0, seg_pos = 0, total = 0;
+  for (int i = 0; i < n; ++i) total += (uint32_t)((tensors[i].numel + kChunk - 1) / kChunk);
+  const uint32_t seg = power_seg(total);
   for (int first = 0; first < n; first += kStaticBatch) {
     StaticBatchArg a{};
     a.first = (uint32_t)first;
@@ -364,9 +388,9 @@ hipError_t launch_power_iter_static(const StaticTensor* tensors, int n, int k, P
       const uint32_t nc = (uint32_t)((t.numel + kChunk - 1) / kChunk);
       a.e[i] = StaticEntry{t.u, t.hu, t.stride, t.numel, chunk_pos, seg_pos};
       chunk_pos += nc;
-      seg_pos += (nc + kPowerSeg - 1) / kPowerSeg;
+      seg_pos += (nc + seg - 1) / seg;
     }
-    hipLaunchKernelGGL(k_static_tables, dim3(a.count), dim3(kThreads), 0, s, a, base);
+    hipLaunchKernelGGL(k_static_tables, dim3(a.count), dim3(kThreads), 0, s, a, seg, base);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   PowerTables t{};
@@ -381,23 +405,24 @@ hipError_t launch_power_iter_static(const StaticTensor* tensors, int n, int k, P
   t.n_tensors = (uint32_t)n;
   t.total_chunks = chunk_pos;
   t.total_segs = seg_pos;
+  t.seg = seg;
   // every partial sum and every record the kernels read is written earlier in this same call, so
   // nothing in the array has to start at zero
-  if ((e = launch_power_iter(t, k, 0, s, nullptr)) != hipSuccess) return e;
+  if ((e = launch_power_iter(t, nullptr, k, 0, s, nullptr)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_static_export, dim3((n + kWave - 1) / kWave), dim3(kWave), 0, s, t.state, info, n);
   return hipGetLastError();
 }
 
-hipError_t launch_power_iter(const PowerTables& t, int k, int latch, hipStream_t s, hipEvent_t* ev) {
+hipError_t launch_power_iter(const PowerTables& t, const PowerDesc* descs, int k, int latch, hipStream_t s, hipEvent_t* ev) {
   switch (k) {
-    case 1: return launch_k<1>(t, latch, s, ev);
-    case 2: return launch_k<2>(t, latch, s, ev);
-    case 3: return launch_k<3>(t, latch, s, ev);
-    case 4: return launch_k<4>(t, latch, s, ev);
-    case 5: return launch_k<5>(t, latch, s, ev);
-    case 6: return launch_k<6>(t, latch, s, ev);
-    case 7: return launch_k<7>(t, latch, s, ev);
-    case 8: return launch_k<8>(t, latch, s, ev);
+    case 1: return launch_k<1>(t, descs, latch, s, ev);
+    case 2: return launch_k<2>(t, descs, latch, s, ev);
+    case 3: return launch_k<3>(t, descs, latch, s, ev);
+    case 4: return launch_k<4>(t, descs, latch, s, ev);
+    case 5: return launch_k<5>(t, descs, latch, s, ev);
+    case 6: return launch_k<6>(t, descs, latch, s, ev);
+    case 7: return launch_k<7>(t, descs, latch, s, ev);
+    case 8: return launch_k<8>(t, descs, latch, s, ev);
     default: return hipErrorInvalidValue;
   }
 }
