@@ -34,6 +34,7 @@ constexpr uint32_t kMinPredShift = 6;        // finest predicted window: 2048 bi
 constexpr uint32_t kUnknownPredErr = 1u << 16;  // assumed prediction error (keys) before any is measured
 constexpr uint32_t kCandCap = 262144;        // keys a tensor may list in total (entries)
 constexpr uint32_t kListAllMax = 8192;       // tensors up to this size list every non-zero key (no prediction)
+static_assert(kListAllMax / (kChunk / 4) <= 64, "a list for each wavefront of such a tensor");
 constexpr int kFinishRegs = 8;               // listed keys per thread the finish kernel can hold in registers
 constexpr uint32_t kCandLists = 64;          // sub-lists per tensor (plus one overflow list)
 constexpr uint32_t kCandCounterStride = 32;  // words between list counters: one 128-byte line each
@@ -87,8 +88,9 @@ struct TensorDesc {
   int32_t grad_dtype;
   int32_t has_probe;
   uint64_t cand_offset;  // first entry of the tensor's candidate lists in the pool
-  uint32_t cand_cap;     // min(numel, kCandCap): capacity of the overflow list
-  uint32_t sub_cap;      // capacity of each of the kCandLists sub-lists: ceil(cand_cap / kCandLists)
+  uint32_t cand_cap;     // min(numel, kCandCap): capacity of the overflow list (none if list_all)
+  uint32_t sub_cap;      // capacity of each of the kCandLists sub-lists: ceil(cand_cap / kCandLists); if list_all, of
+                         // the one list per wavefront: the keys it can have
   uint32_t list_all;     // numel <= kListAllMax: every non-zero key is listed, no prediction
   uint32_t resize_slot;  // the tensor's first chunk in the scratch area of the in-place resize
 };

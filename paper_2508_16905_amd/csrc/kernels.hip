@@ -146,6 +146,7 @@ __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, fl
     if (FULL) load4<kFP32>(td.curv, idx, h[r]);
     else load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, h[r]);
   }
+  __builtin_amdgcn_sched_barrier(0);  // all loads first
   uint32_t hflags = 0, lflags = 0, zeros = 0;  // keys >= list_hi / >= list_lo (bit 4 r + i), zero keys
   const uint32_t first_mask = first ? ~0u : 0u;
 #pragma unroll
@@ -188,8 +189,9 @@ __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, fl
   }
 }
 
+// At most 6 wavefronts per SIMD: room for the loads of all rows to be under way at once.
 template <bool FISHER>
-__global__ __launch_bounds__(kThreads) void k_curv_ema(const TensorDesc* __restrict__ tds,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void k_curv_ema(const TensorDesc* __restrict__ tds,
                                                        const ChunkRef* __restrict__ chunks, const LayerDev* layers,
                                                        const GlobalDev* glob, EmaPartial* __restrict__ ema_partials,
                                                        Candidate* cands, uint32_t* counters, StepArg sa,
