@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kThreads) void k_hist_pass(const TensorDesc* __rest
   if (step_skipped(glob, sc.step_id)) return;
   if (__hip_atomic_load(&glob->hist_pending[sc.step_id & 1u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
   __shared__ uint32_t s_hist[kHistBins];
-  __shared__ uint32_t s_part[kThreads];
+  __shared__ uint32_t s_part[kThreads / kWave];
   __shared__ uint32_t s_out[8];
   __shared__ uint32_t s_last;
   for (int b = threadIdx.x; b < kHistBins; b += kThreads) s_hist[b] = 0;
@@ -360,13 +360,16 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_finish(const TensorDe
                                                                   LayerDev* layers, const GlobalDev* glob,
                                                                   const Candidate* cands, uint32_t* counters,
                                                                   StepArg sa, float beta_h) {
-  const StepScalars sc = step_scalars(sa);
-  if (step_skipped(glob, sc.step_id)) return;
-  const uint32_t l = blockIdx.x;
-  const TensorDesc td = tds[l];
-  if (!td.has_probe) return;
   __shared__ SelectShared<kFinishThreads> sh;
-  select_finish<kFinishThreads, kFinishRegs>(l, td, layers[l], cands, counters, beta_h, sh);
+  const StepScalars sc = step_scalars(sa);
+  const uint64_t skip_epoch = glob->skip_epoch;
+  const uint32_t l = blockIdx.x;
+  const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
+  const TensorDesc td = tds[l];
+  const FinishIn in = finish_in(layers[l]);
+  TA_LOADED("s"(td.mask), "s"(td.has_probe), "s"(td.cand_cap), "s"(in.mode), "s"(in.probes_seen), "s"(in.var_hold));
+  if (skip_epoch == sc.step_id || !td.has_probe) return;
+  select_finish<kFinishThreads, kFinishRegs>(l, td, layers[l], in, listed, cands, counters, beta_h, sh);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -71,63 +71,52 @@ struct BinHit {
 };
 template <int NT>
 __device__ __forceinline__ BinHit find_rank_from_top(const uint32_t* s_hist, uint32_t bins, uint32_t r, uint32_t* s_part,
-                                     uint32_t* s_out) {
-  // level 0: every thread sums its run of bins; level 1: every lane of wavefront 0 sums a run of
-  // thread sums; a suffix scan over the 64 lanes locates the lane, then the thread, then the bin.
-  constexpr int G = NT / kWave;  // thread sums per lane of wavefront 0
-  const uint32_t per = (bins + NT - 1) / NT;
-  const uint32_t b0 = threadIdx.x * per;
-  uint32_t sum = 0;
-  for (uint32_t b = b0; b < min(b0 + per, bins); ++b) sum += s_hist[b];
-  s_part[threadIdx.x] = sum;
+                                                     uint32_t* s_out) {
+  // Every thread sums its run of bins and every wavefront its threads; each wavefront walks the wavefront sums
+  // from the top, and the one that holds the rank finds the lane in a scan and the bin in the lane's run.  Two
+  // barriers and no serial walk longer than a run (2 bins of 2048 with 1024 threads).
+  constexpr int PER = kHistBins / NT, NW = NT / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint32_t b0 = threadIdx.x * PER;
+  uint32_t v[PER], sum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    v[i] = b0 + i < bins ? s_hist[b0 + i] : 0u;
+    sum += v[i];
+  }
+  const uint32_t incl = wave_scan(sum), total = last_lane(incl);
+  if (lane == 0) s_part[wave] = total;
   __syncthreads();
-  if (threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
-    uint32_t mine = 0;
-#pragma unroll
-    for (int i = 0; i < G; ++i) mine += s_part[lane * G + i];
-    uint32_t suffix = mine;  // sum over lanes >= this one
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const uint32_t t = __shfl_down(suffix, o);
-      if (lane + o < kWave) suffix += t;
-    }
-    const unsigned long long reach = __ballot(suffix >= r);  // lanes from which the top reaches rank r
-    const int pick = reach ? 63 - __clzll(reach) : 0;         // the highest such lane holds the rank
+  uint32_t higher = 0;  // keys in wavefronts above the one that holds the rank
+  int hit = NW - 1;
+  for (; hit > 0; --hit) {
+    const uint32_t p = s_part[hit];
+    if (higher + p >= r) break;
+    higher += p;
+  }
+  if (wave == hit) {
+    const uint32_t from_here = total - incl + sum;  // sum over lanes >= this one
+    const unsigned long long reach = __ballot(higher + from_here >= r);
+    const int pick = reach ? 63 - __clzll(reach) : 0;  // the highest lane from which the top reaches rank r
     if (lane == pick) {
-      uint32_t acc = suffix - mine;  // keys in lanes above
-      int t = pick * G + G - 1;
-      for (; t > pick * G; --t) {
-        if (acc + s_part[t] >= r) break;
-        acc += s_part[t];
+      uint32_t acc = higher + from_here - sum;
+      uint32_t bin = b0, cnt = v[0];
+#pragma unroll
+      for (int i = PER - 1; i > 0; --i) {
+        if (acc + v[i] >= r) {
+          bin = b0 + i;
+          cnt = v[i];
+          break;
+        }
+        acc += v[i];
       }
-      s_out[0] = (uint32_t)t;
+      s_out[0] = bin;
       s_out[1] = acc;
+      s_out[2] = cnt;
     }
   }
   __syncthreads();
-  if (threadIdx.x == s_out[0]) {
-    uint32_t acc = s_out[1];
-    uint32_t b = min(b0 + per, bins);
-    uint32_t found = b0, cnt = 0;
-    while (b > b0) {
-      --b;
-      const uint32_t v = s_hist[b];
-      if (acc + v >= r) {
-        found = b;
-        cnt = v;
-        break;
-      }
-      acc += v;
-    }
-    s_out[2] = found;
-    s_out[3] = acc;
-    s_out[4] = cnt;
-  }
-  __syncthreads();
-  BinHit hit{s_out[2], s_out[3], s_out[4]};
-  __syncthreads();
-  return hit;
+  return BinHit{s_out[0], s_out[1], s_out[2]};
 }
 
 __device__ __forceinline__ uint32_t topk_count(int64_t n, uint32_t s_ppm, uint32_t k_abs) {
@@ -345,23 +334,23 @@ __device__ __forceinline__ void select_serial(uint32_t l, const TensorDesc& td, 
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t abs_diff(uint32_t a, uint32_t b) { return a > b ? a - b : b - a; }
 
-// Sum of a per-thread count over the workgroup (NT threads); s_red holds one word per wavefront.
-template <int NT>
-__device__ __forceinline__ uint32_t finish_block_sum(uint32_t v, uint32_t* s_red) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0) s_red[threadIdx.x / kWave] = v;
-  __syncthreads();
-  uint32_t t = 0;
-#pragma unroll
-  for (int w = 0; w < NT / kWave; ++w) t += s_red[w];
-  return t;
+// The fields of a layer's record that the finish reads: loaded together and ahead of the listed keys, instead of
+// one after the other where they are used.
+struct FinishIn {
+  uint32_t mode, above, rng_lo, rng_hi, theta_key, sel_count, nonzero, k_rem, passes, mask_done, probes_seen;
+  uint32_t theta_key_last, theta_key_last2, n_theta, pred_ext_key, window_missed, dens_count, dens_width;
+  float var_hold, var_ext;
+};
+__device__ __forceinline__ FinishIn finish_in(const LayerDev& ls) {
+  return FinishIn{ls.mode, ls.above, ls.rng_lo, ls.rng_hi, ls.theta_key, ls.sel_count, ls.nonzero, ls.k_rem, ls.passes,
+                  ls.mask_done, ls.probes_seen, ls.theta_key_last, ls.theta_key_last2, ls.n_theta, ls.pred_ext_key,
+                  ls.window_missed, ls.dens_count, ls.dens_width, ls.var_hold, ls.var_ext};
 }
 
 // Shared memory of the histogram functions, for a workgroup of kThreads threads.
 struct HistShared {
   uint32_t hist[kHistBins];
-  uint32_t part[kThreads];
+  uint32_t part[kThreads / kWave];
   uint32_t out[8];
 };
 
@@ -369,51 +358,50 @@ struct HistShared {
 template <int NT>
 struct SelectShared {
   uint32_t hist[kHistBins];
-  uint32_t part[NT];
-  uint32_t red[NT / kWave];
+  uint32_t part[NT / kWave];
   uint32_t out[8];
+  uint32_t kept;
   uint32_t counts[kCandLists + 1];
   uint32_t prefix[kCandLists + 2];
 };
 
 // The whole workgroup (NT threads) calls it for tensor l, whose threshold is exact or confined to a range
 // whose keys are all listed (ls.mode).  Up to REGS listed keys per thread are held in registers.
+// `listed` is this thread's list length (threads 0 .. kCandLists), read ahead together with `in`.
 template <int NT, int REGS>
-__device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, LayerDev& ls, const Candidate* cands,
-                              uint32_t* counters, float beta_h, SelectShared<NT>& sh) {
+__device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, LayerDev& ls, const FinishIn& in,
+                                              uint32_t listed, const Candidate* cands, uint32_t* counters, float beta_h,
+                                              SelectShared<NT>& sh) {
   uint32_t* const s_hist = sh.hist;
-  uint32_t* const s_part = sh.part;
-  uint32_t* const s_red = sh.red;
-  uint32_t* const s_out = sh.out;
   uint32_t* const s_counts = sh.counts;
   uint32_t* const s_prefix = sh.prefix;
-  if (threadIdx.x <= kCandLists) {
-    const uint32_t c = *cand_counter(counters, l, threadIdx.x);
-    s_counts[threadIdx.x] = min(c, threadIdx.x < kCandLists ? td.sub_cap : td.cand_cap);
+  // lengths and exclusive prefix sums of the lists (flat numbering of the listed keys)
+  static_assert(kCandLists == kWave, "one lane per sub-list");
+  if (threadIdx.x <= kCandLists) s_counts[threadIdx.x] = min(listed, threadIdx.x < kCandLists ? td.sub_cap : td.cand_cap);
+  if (threadIdx.x < kWave) {
+    const uint32_t incl = wave_scan(min(listed, td.sub_cap));
+    if (threadIdx.x == 0) {
+      s_prefix[0] = 0;
+      sh.kept = 0;
+    }
+    s_prefix[threadIdx.x + 1] = incl;
   }
   __syncthreads();
-  const uint32_t mode = ls.mode;
-  const uint32_t above = ls.above;
-  const uint32_t rng_lo = ls.rng_lo, rng_hi = ls.rng_hi;
-  uint32_t theta = ls.theta_key;
-  uint32_t nnz = above + ls.sel_count;
-  if (mode == kSelExact && theta == 0u) nnz = ls.nonzero;
+  if (threadIdx.x == 0) s_prefix[kCandLists + 1] = s_prefix[kCandLists] + s_counts[kCandLists];
+  __syncthreads();
+  const uint32_t mode = in.mode;
+  const uint32_t above = in.above;
+  const uint32_t rng_lo = in.rng_lo, rng_hi = in.rng_hi;
+  uint32_t theta = in.theta_key;
+  uint32_t nnz = above + in.sel_count;
+  if (mode == kSelExact && theta == 0u) nnz = in.nonzero;
   if (mode == kSelCand) {
     // all listed keys lie in [rng_lo, rng_hi); select inside the enclosing power-of-two range
     uint32_t lo = rng_lo;
     const uint32_t width = rng_hi - rng_lo;
     uint32_t width_shift = 32u - (uint32_t)__clz(width - 1u);  // ceil(log2(width)), width >= 2
     if (width <= 1u) width_shift = 0;
-    uint32_t r = ls.k_rem - above;
-    // exclusive prefix sums of the list lengths (flat numbering of the listed keys)
-    static_assert(kCandLists == kWave, "one lane per sub-list");
-    if (threadIdx.x < kWave) {
-      const uint32_t incl = wave_scan(s_counts[threadIdx.x]);
-      if (threadIdx.x == 0) s_prefix[0] = 0;
-      s_prefix[threadIdx.x + 1] = incl;
-      if (threadIdx.x == kWave - 1) s_prefix[kCandLists + 1] = incl + s_counts[kCandLists];
-    }
-    __syncthreads();
+    uint32_t r = in.k_rem - above;
     const uint32_t inside = s_prefix[kCandLists + 1];
     // up to REGS keys per thread are held in registers for the passes below; longer lists
     // are re-read from memory in every pass
@@ -458,7 +446,7 @@ __device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, 
           if (c.key >= lo && ((uint64_t)(c.key - lo) >> width_shift) == 0u) atomicAdd(&s_hist[(c.key - lo) >> ns], 1u);
         });
         __syncthreads();
-        const BinHit hit = find_rank_from_top<NT>(s_hist, bins, r, s_part, s_out);
+        const BinHit hit = find_rank_from_top<NT>(s_hist, bins, r, sh.part, sh.out);
         r -= hit.higher;
         lo += hit.bin << ns;
         width_shift = ns;
@@ -473,20 +461,22 @@ __device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, 
         ++kept;
       }
     });
-    kept = finish_block_sum<NT>(kept, s_red);
-    nnz = above + kept;
+    kept = wave_sum(kept);
+    if ((threadIdx.x & (kWave - 1)) == 0 && kept) atomicAdd(&sh.kept, kept);
+    __syncthreads();
+    nnz = above + sh.kept;
   }
   __syncthreads();
   reset_cand_counters(counters, l);
   if (threadIdx.x != 0) return;
   // ---- publish ----
-  const uint32_t prev = ls.theta_key_last;
-  const uint32_t have = ls.n_theta;
+  const uint32_t prev = in.theta_key_last;
+  const uint32_t have = in.n_theta;
   ls.theta_key = theta;
   ls.theta = u2f(theta);
   ls.nnz = nnz;
-  ls.sel_passes = ls.passes - 1 + (ls.mask_done ? 0u : 1u);  // passes over h beyond the EMA pass
-  ls.probes_seen = ls.probes_seen + 1;
+  ls.sel_passes = in.passes - 1 + (in.mask_done ? 0u : 1u);  // passes over h beyond the EMA pass
+  ls.probes_seen = in.probes_seen + 1;
   // ---- plan the next probed step ----
   // Two predictors of the next threshold are tracked by the error each made for this step:
   // "hold" (the last threshold; best when the threshold only jitters) and a damped extrapolation
@@ -497,17 +487,17 @@ __device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, 
   // are known.  Each predictor keeps a running mean of its squared error in keys (an error three
   // times the running deviation replaces the mean at once); the one with the smaller mean is
   // used, and the band is a multiple of its deviation.
-  const uint32_t prev2 = ls.theta_key_last2;
+  const uint32_t prev2 = in.theta_key_last2;
   const float unknown2 = (float)kUnknownPredErr * (float)kUnknownPredErr;
   auto track = [](float var, float err, bool first) {
     const float e2 = err * err;
     if (first || e2 > 9.0f * var) return e2;
     return 0.75f * var + 0.25f * e2;
   };
-  float v_hold = unknown2, v_ext = ls.pred_ext_key ? ls.var_ext : 3.0e38f;
-  if (have >= 1) v_hold = track(ls.var_hold, (float)abs_diff(theta, prev), have < 2);
-  if (ls.pred_ext_key) v_ext = track(v_ext, (float)abs_diff(theta, ls.pred_ext_key), !(v_ext < 3.0e38f));
-  if (ls.window_missed) {
+  float v_hold = unknown2, v_ext = in.pred_ext_key ? in.var_ext : 3.0e38f;
+  if (have >= 1) v_hold = track(in.var_hold, (float)abs_diff(theta, prev), have < 2);
+  if (in.pred_ext_key) v_ext = track(v_ext, (float)abs_diff(theta, in.pred_ext_key), !(v_ext < 3.0e38f));
+  if (in.window_missed) {
     v_hold = fmaxf(v_hold, unknown2);
     if (v_ext < 3.0e38f) v_ext = fmaxf(v_ext, unknown2);
   }
@@ -549,7 +539,7 @@ __device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, 
   const uint32_t band_hi = hi64 < 0x7f800000ull ? (uint32_t)hi64 : 0x7f800000u;
   // expected number of keys inside the band, from the key density around this step's threshold;
   // listing them only pays when they fit the lists with room to spare
-  const uint64_t expect = ls.dens_width ? ((uint64_t)(band_hi - band_lo) * ls.dens_count) / ls.dens_width : 0u;
+  const uint64_t expect = in.dens_width ? ((uint64_t)(band_hi - band_lo) * in.dens_count) / in.dens_width : 0u;
   ls.mode = kSelHist;
   ls.win_lo = lo_bin << s;
   ls.win_hi = ls.win_lo + ((uint32_t)kHistBins << s);

@@ -146,13 +146,16 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
   const uint64_t skip_epoch = glob->skip_epoch;
   if (blockIdx.x < n_tensors) {
     const uint32_t l = blockIdx.x;
+    const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
     const TensorDesc td = tds[l];
     LayerDev& ls = layers[l];
     // sel_outcome is not written here: it tells the two kinds apart while the records are rewritten
     const uint32_t sel_outcome = ls.sel_outcome;
-    TA_LOADED("s"(td.mask), "s"(td.has_probe), "s"(sel_outcome));
+    const FinishIn in = finish_in(ls);
+    TA_LOADED("s"(td.mask), "s"(td.has_probe), "s"(td.cand_cap), "s"(sel_outcome), "s"(in.mode), "s"(in.probes_seen),
+              "s"(in.var_hold));
     if (skip_epoch == sc.step_id || !td.has_probe || sel_outcome > 1u) return;
-    select_finish<kFinishThreads, kFinishRegs>(l, td, ls, cands, counters, beta_h, sh);
+    select_finish<kFinishThreads, kFinishRegs>(l, td, ls, in, listed, cands, counters, beta_h, sh);
     return;
   }
   const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
@@ -194,7 +197,10 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
     if (last) {
       // the resolution reads what the other workgroups listed: nothing older of it in this unit's caches
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      select_finish<kFinishThreads, kFinishRegs>(l, td, ls, cands, counters, beta_h, sh);
+      uint32_t listed = 0;
+      if (threadIdx.x <= kCandLists)
+        listed = __hip_atomic_load(cand_counter(counters, l, threadIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      select_finish<kFinishThreads, kFinishRegs>(l, td, ls, finish_in(ls), listed, cands, counters, beta_h, sh);
       __syncthreads();
     }
   }
