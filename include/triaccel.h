@@ -172,8 +172,9 @@ typedef struct {
                                   unchanged (+ fallback mask pass), 5 in-place update of tensors whose
                                   size changes, 6 threshold resolution among listed keys + mask patch.
                                   Sets of fewer than 16,384 pieces of 4096 elements, none of whose tensors
-                                  has more than 1024: stages 2 and 3 are part of stage 4 and read 0, the
-                                  fallback mask pass is part of stage 6                               */
+                                  has more than 1024: stages 2 and 3 are part of stage 4 and read 0; the
+                                  fallback mask pass and, on steps that refresh the curvature, the later
+                                  part of stage 5 are part of stage 6                                 */
 } triaccel_stage_times;
 
 /*

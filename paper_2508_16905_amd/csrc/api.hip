@@ -193,9 +193,9 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
     if (ev) TA_HIP(hipEventRecord(ev[4], s));
     TA_HIP(launch_update_local(T, sa, h->hp, any_probe, s));
     if (ev) TA_HIP(hipEventRecord(ev[5], s));
-    TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
+    if (!any_probe) TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
-    if (any_probe) TA_HIP(launch_select_tail(T, sa, beta_h, s));
+    if (any_probe) TA_HIP(launch_select_tail(T, sa, h->hp, true, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
     return TRIACCEL_OK;
   }
@@ -212,8 +212,12 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   }
   if (elem && any_probe) {
     // element-wise step sizes need the final threshold: finish the mask and the selection first
-    TA_HIP(launch_mask_pass(T, sa, s));
-    TA_HIP(launch_select_finish(T, sa, h->hp.beta_curv, s));
+    if (T.total_chunks < kLaunchBoundChunks) {
+      TA_HIP(launch_select_tail(T, sa, h->hp, false, s));
+    } else {
+      TA_HIP(launch_mask_pass(T, sa, s));
+      TA_HIP(launch_select_finish(T, sa, beta_h, s));
+    }
   }
   if (ev) TA_HIP(hipEventRecord(ev[4], s));
   TA_HIP(launch_update(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, s));

@@ -175,7 +175,7 @@ struct EmaPartial {
 // The layer's fields that the decisions of an applied step read.
 struct LayerIn {
   float v, lambda, lambda_ctrl, lambda_power;
-  int32_t code;
+  int32_t code, prev_code;
   uint32_t applied_steps;
 };
 

@@ -287,8 +287,9 @@ __global__ __launch_bounds__(kThreads) void k_hist_pass(const TensorDesc* __rest
                                                         LayerDev* layers, GlobalDev* glob, uint32_t* hist,
                                                         StepArg sa, int serial_rounds) {
   const StepScalars sc = step_scalars(sa);
-  if (step_skipped(glob, sc.step_id)) return;
-  if (__hip_atomic_load(&glob->hist_pending[sc.step_id & 1u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+  const uint64_t skip_epoch = glob->skip_epoch;
+  const uint32_t pending = __hip_atomic_load(&glob->hist_pending[sc.step_id & 1u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (pending == 0 || skip_epoch == sc.step_id) return;
   __shared__ uint32_t s_hist[kHistBins];
   __shared__ uint32_t s_part[kThreads / kWave];
   __shared__ uint32_t s_out[8];

@@ -27,7 +27,7 @@ __device__ __forceinline__ void resize_copy(const TensorDesc& td, const char* sr
   const int64_t base = (int64_t)c * kChunk, left = td.numel - base;
   const uint32_t bytes = (uint32_t)(left < kChunk ? left : kChunk) * esz;
   char* const dst = static_cast<char*>(td.param) + base * esz;
-  for (uint32_t off = threadIdx.x * 16; off < bytes; off += kThreads * 16) {
+  for (uint32_t off = threadIdx.x * 16; off < bytes; off += blockDim.x * 16) {
     if (off + 16 <= bytes) {
       *as_global<v4f>(dst + off) = *as_global<v4f>(src + off);
     } else {
@@ -36,15 +36,17 @@ __device__ __forceinline__ void resize_copy(const TensorDesc& td, const char* sr
   }
 }
 
-// One tensor's work of slot `r` in launch `launch`.  Uniform over the workgroup (it contains barriers).
-template <bool ELEM, bool MOM>
+// One tensor's work of slot `r` in launch `launch`.  Uniform over the workgroup (it contains barriers), which
+// consists of GROUPS times kThreads threads that take the chunks of a level in turn (launch 0: GROUPS = 1).
+template <bool ELEM, bool MOM, int GROUPS = 1>
 __device__ __forceinline__ void resize_item(const TensorDesc& td, int pd, int nd, const StepSize& ss, const ResizePlan& plan,
                                             char* scratch, uint32_t launch, uint32_t r, const StepScalars& sc, float wd,
                                             float mu) {
-  const int tid = (int)threadIdx.x;
+  const int tid = (int)(threadIdx.x & (kThreads - 1));
+  const uint32_t group = threadIdx.x / kThreads;
   const bool narrowing = elem_size(nd) < elem_size(pd);
   if (plan.n_stages == 1) {
-    if (r != 0) return;
+    if (r != 0 || launch != 0) return;
     resize_walk_top(plan, td.n_chunks, narrowing, [&](uint32_t c) {
       ChunkRegs regs;
       update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
@@ -68,6 +70,7 @@ __device__ __forceinline__ void resize_item(const TensorDesc& td, int pd, int nd
     if (stage == 0 || sub >= resize_stage_roots(plan, stage) || plan.root[stage] + sub >= td.n_chunks) return;
   }
   const auto chunk = [&](uint32_t c) {
+    if (GROUPS > 1 && c % GROUPS != group) return;
     ChunkRegs regs;
     update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
     update_store_any<MOM>(to, nd, (int64_t)c * kChunk, tid, regs);
@@ -81,7 +84,7 @@ __device__ __forceinline__ void resize_item(const TensorDesc& td, int pd, int nd
 // workgroup `wg` of `n_wg` takes the items wg,
 // wg + n_wg, ...  The list and its length are written on the device by the kernel that takes the layers'
 // decisions, so the work is offered on every step and nothing happens when the list is empty.
-template <bool ELEM, bool MOM>
+template <bool ELEM, bool MOM, int GROUPS = 1>
 __device__ __forceinline__ void resize_items(const TensorDesc* __restrict__ tds, const LayerDev* layers,
                                              const GlobalDev* glob, const uint32_t* trans_list, uint32_t n_tensors,
                                              const ResizePlan& plan, char* scratch, uint32_t launch, uint32_t slots, uint32_t wg,
@@ -95,7 +98,7 @@ __device__ __forceinline__ void resize_items(const TensorDesc* __restrict__ tds,
     const LayerDev& ls = layers[l];
     const StepSize ss{-ls.eta, sc.lr, alpha, ls.theta_key};
     const TensorDesc td = tds[l];
-    resize_item<ELEM, MOM>(td, ls.prev_code, ls.code, ss, plan, scratch, launch, r, sc, wd, mu);
+    resize_item<ELEM, MOM, GROUPS>(td, ls.prev_code, ls.code, ss, plan, scratch, launch, r, sc, wd, mu);
   }
 }
 

@@ -14,8 +14,10 @@ __global__ __launch_bounds__(kThreads) void k_mask_pass(const TensorDesc* __rest
                                                         const LayerDev* layers, const GlobalDev* glob, Candidate* cands,
                                                         uint32_t* counters, StepArg sa) {
   const StepScalars sc = step_scalars(sa);
-  if (step_skipped(glob, sc.step_id)) return;
-  if (glob->mask_pending[sc.step_id & 1u] == 0) return;
+  const uint64_t skip_epoch = glob->skip_epoch;
+  const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
+  TA_LOADED("s"(skip_epoch), "s"(pending));
+  if (pending == 0 || skip_epoch == sc.step_id) return;
   for (uint32_t c = blockIdx.x; c < total_chunks; c += gridDim.x) {
     const ChunkRef cr = chunks[c];
     const TensorDesc td = tds[cr.tensor];
@@ -52,7 +54,10 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
                                                      float mu, float alpha) {
   const StepScalars sc = step_scalars(sa);
   if (blockIdx.x < resize_wgs) {
-    if (step_skipped(glob, sc.step_id)) return;
+    const uint64_t skip_epoch = glob->skip_epoch;
+    const uint32_t count = glob->trans_count[sc.step_id & 1u];
+    TA_LOADED("s"(skip_epoch), "s"(count));
+    if (count == 0 || skip_epoch == sc.step_id) return;
     resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, scratch, 0u, resize_slots, blockIdx.x, resize_wgs, sc,
                             wd, mu, alpha);
     return;

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   LayerDev& ls = layers[cr.tensor];
   const LayerIn in = inputs[cr.tensor];
   TA_LOADED("s"(td.param), "s"(td.grad), "s"(td.mom), "s"(td.curv), "s"(td.numel), "s"(td.first_chunk), "s"(td.grad_dtype),
-            "s"(td.has_probe), "s"(in.v), "s"(in.lambda), "s"(in.lambda_ctrl), "s"(in.code), "s"(in.applied_steps),
+            "s"(td.has_probe), "s"(in.v), "s"(in.lambda), "s"(in.lambda_ctrl), "s"(in.code), "s"(in.prev_code), "s"(in.applied_steps),
             "s"(in.lambda_power), "s"(td.n_chunks));
   if (skip) {
     if (threadIdx.x == 0 && cr.index == 0) {
@@ -59,13 +59,23 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   const int64_t base = (int64_t)cr.index * kChunk;
   const bool probed = PROBED && td.has_probe != 0;
   const LayerAcc acc = layer_accumulate<PROBED>(td, partials, ema_partials, probed);
+  // The chunk's own loads are under way while the sums are reduced and the decisions taken (2-3 % of a step from
+  // 11 M to 30 M parameters against loading after them, at 4 wavefronts per SIMD instead of 7).  They are of no use
+  // if the layer changes its storage size (50 M parameters all changing: 312 us a step with them, 238 without);
+  // a layer that did so at its last step, or has its first, is taken to be about to do it.
+  const bool early = in.applied_steps != 0 && elem_size(in.code) == elem_size(in.prev_code);
+  ChunkRegs regs;
+  CurvRegs unused;
+  if (early) update_fetch_any<false, MOM>(td, in.code, base, (int)threadIdx.x, regs, unused);
   const LayerSums sums = layer_reduce<PROBED>(acc, td.numel, sh_layer);
   const LayerOut o = layer_decide(in, sums, probed, sc.lr, hp);
   if (threadIdx.x == 0) s_decision = o;  // for this thread alone, below
   const int pd = in.code, nd = (int)uniform((uint32_t)o.code);
   const StepSize ss{-u2f(uniform(f2u(o.eta))), sc.lr, hp.alpha, 0u};
   if (elem_size(pd) == elem_size(nd)) {
-    update_any<false, MOM>(td, pd, nd, base, sc.inv_scale, hp.weight_decay, hp.momentum, ss, (int)threadIdx.x);
+    if (!early) update_fetch_any<false, MOM>(td, pd, base, (int)threadIdx.x, regs, unused);
+    update_math<MOM, false>(sc.inv_scale, hp.weight_decay, hp.momentum, ss, regs, unused);
+    update_store_any<MOM>(td, nd, base, (int)threadIdx.x, regs);
   } else {
     // launch 0 of the in-place resize: slot r of the tensor is the workgroup of its chunk r
     resize_item<false, MOM>(td, pd, nd, ss, plan, scratch, 0u, cr.index, sc, hp.weight_decay, hp.momentum);
@@ -131,15 +141,20 @@ hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const H
   return hipSuccess;
 }
 
-// What is left of the selection after k_update_local.  Workgroup l < n_tensors settles tensor l if its listed
-// keys suffice.  The workgroups after those make the mask pass of the other tensors, four chunks at a time, and
-// the last workgroup to finish a part of such a tensor settles it among the keys the pass listed; they leave at
-// once when there is no such tensor (the steady state).
+// What is left of the selection after k_update_local, and before the element-wise form of the update on sets
+// of that size (one launch for the mask pass and the threshold resolution).  Workgroup l < n_tensors settles tensor l if its listed
+// keys suffice.  The `mask_wgs` workgroups after those make the mask pass of the other tensors, four chunks at a
+// time, and the last workgroup to finish a part of such a tensor settles it among the keys the pass listed; the
+// rest take launch 1 of the in-place resize, four chunks of a level at a time.  The last two kinds leave at once
+// when no tensor needs them (the steady state); in a launch of its own the resize cost 4.5 us a step all the same.
+template <bool MOM>
 __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc* __restrict__ tds,
                                                                 const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
                                                                 uint32_t n_tensors, LayerDev* layers, const GlobalDev* glob,
                                                                 Candidate* cands, uint32_t* counters, uint32_t* arrived,
-                                                                StepArg sa, float beta_h) {
+                                                                uint32_t mask_wgs, const uint32_t* trans_list,
+                                                                ResizePlan plan, char* scratch, uint32_t resize_slots,
+                                                                StepArg sa, float beta_h, float wd, float mu) {
   __shared__ SelectShared<kFinishThreads> sh;
   __shared__ uint32_t s_last;
   const StepScalars sc = step_scalars(sa);
@@ -158,9 +173,19 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
     select_finish<kFinishThreads, kFinishRegs>(l, td, ls, in, listed, cands, counters, beta_h, sh);
     return;
   }
+  if (blockIdx.x >= n_tensors + mask_wgs) {
+    const uint32_t count = glob->trans_count[sc.step_id & 1u];
+    TA_LOADED("s"(skip_epoch), "s"(count));
+    if (count == 0 || skip_epoch == sc.step_id) return;
+    resize_items<false, MOM, kFinishThreads / kThreads>(tds, layers, glob, trans_list, n_tensors, plan, scratch, 1u,
+                                                        resize_slots, blockIdx.x - n_tensors - mask_wgs,
+                                                        gridDim.x - n_tensors - mask_wgs, sc, wd, mu, 0.0f);
+    return;
+  }
   const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
+  TA_LOADED("s"(skip_epoch), "s"(pending));
   if (pending == 0 || skip_epoch == sc.step_id) return;
-  const uint32_t part = blockIdx.x - n_tensors, parts = gridDim.x - n_tensors;
+  const uint32_t part = blockIdx.x - n_tensors, parts = mask_wgs;
   const uint32_t per = (total_chunks + parts - 1) / parts;
   const uint32_t c1 = min((part + 1) * per, total_chunks);
   const uint32_t group = threadIdx.x / kThreads;
@@ -206,12 +231,22 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
   }
 }
 
-hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, float beta_h, hipStream_t s) {
+static_assert((kResizeTopSmall << 6) >= kLocalMaxChunks && kLaunchBoundChunks <= kResizeBigSet,
+              "one subtree stage: the resize of a set of the local form has two launches at most");
+hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool resize, hipStream_t s) {
   constexpr uint32_t kGroups = kFinishThreads / kThreads;
-  const uint32_t all = (t.total_chunks + kGroups - 1) / kGroups, cap = t.persistent_grid / kGroups;
-  hipLaunchKernelGGL(k_select_tail, dim3(t.n_tensors + (all < cap ? all : cap)), dim3(kFinishThreads), 0, s, t.tensors,
-                     t.chunks, t.total_chunks, t.n_tensors, t.layers, t.glob, t.cands, t.cand_counters, t.arrived, sa,
-                     beta_h);
+  const uint32_t all = (t.total_chunks + kGroups - 1) / kGroups, cap = t.persistent_grid / 8;  // one per CU
+  const uint32_t mask_wgs = all < cap ? all : cap;
+  const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
+  ResizeGrid rg{1u, 0u};
+  if (resize && plan.n_stages > 1) {
+    rg = resize_grid(plan, 1u, t.n_tensors, true);
+    if (rg.grid > cap) rg.grid = cap;
+  }
+  const auto kernel = hp.momentum != 0.0f ? k_select_tail<true> : k_select_tail<false>;
+  hipLaunchKernelGGL(kernel, dim3(t.n_tensors + mask_wgs + rg.grid), dim3(kFinishThreads), 0, s, t.tensors, t.chunks,
+                     t.total_chunks, t.n_tensors, t.layers, t.glob, t.cands, t.cand_counters, t.arrived, mask_wgs,
+                     t.trans_list, plan, t.resize_scratch, rg.slots, sa, hp.beta_curv, hp.weight_decay, hp.momentum);
   TA_LAUNCH_CHECK();
   return hipSuccess;
 }
