@@ -20,13 +20,15 @@ __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, 
                                             double& s1, double& s2, uint32_t& bad) {
   const int tid = threadIdx.x;
   float g[kRows][4];
+  // The update reads the gradients again: they are left in the caches (55 M parameters, step without a probe:
+  // 228 -> 202 us; 11 M: 49 -> 45; 250 M: 1071 -> 1049).
   // the shift is read in the same batch of loads as the data: one memory latency per chunk, not two
   const float first = load1<GD>(td.grad, base);
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
     const int64_t idx = base + r * kRowElems + tid * kVec;
-    if (FULL) load4<GD>(td.grad, idx, g[r]);
-    else load4_guard<GD>(td.grad, idx, td.numel, 0.0f, g[r]);
+    if (FULL) load4<GD, true>(td.grad, idx, g[r]);
+    else load4_guard<GD, true>(td.grad, idx, td.numel, 0.0f, g[r]);
   }
   shift = (double)(first * inv_scale);
 #pragma unroll

@@ -42,7 +42,8 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return u2f(b << 
 // ---- 4 consecutive elements, index multiple of 4, base 16-byte aligned ------------------------
 // Every tensor is streamed exactly once per kernel, so the vector accesses carry the
 // non-temporal hint (measured on MI355X: read-only streaming 6.5 -> 7.3 TB/s, read-modify-write
-// 5.3 -> 5.7 TB/s).
+// 5.3 -> 5.7 TB/s), except where a later kernel of the same step reads the array again (KEEP): the hint
+// also keeps the data out of the caches.
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
@@ -62,13 +63,15 @@ __device__ __forceinline__ TA_GLOBAL T* as_global(void* p) {
   return (TA_GLOBAL T*)(p);
 }
 
-template <int DT>
+template <int DT, bool KEEP = false>
 __device__ __forceinline__ void load4(const void* base, int64_t idx, float out[4]) {
   if constexpr (DT == kFP32) {
-    const v4f v = __builtin_nontemporal_load(as_global<v4f>(static_cast<const float*>(base) + idx));
+    const auto p = as_global<v4f>(static_cast<const float*>(base) + idx);
+    const v4f v = KEEP ? *p : __builtin_nontemporal_load(p);
     out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
   } else {
-    const v2u v = __builtin_nontemporal_load(as_global<v2u>(static_cast<const uint16_t*>(base) + idx));
+    const auto p = as_global<v2u>(static_cast<const uint16_t*>(base) + idx);
+    const v2u v = KEEP ? *p : __builtin_nontemporal_load(p);
     const uint32_t h0 = v.x & 0xffffu, h1 = v.x >> 16, h2 = v.y & 0xffffu, h3 = v.y >> 16;
     if constexpr (DT == kBF16) {
       out[0] = bf16_bits_to_f32(h0); out[1] = bf16_bits_to_f32(h1);
@@ -88,12 +91,13 @@ __device__ __forceinline__ float load1(const void* base, int64_t idx) {
   return f16_bits_to_f32(h);
 }
 
-template <int DT>
+template <int DT, bool KEEP = false>
 __device__ __forceinline__ void store4(void* base, int64_t idx, const float v[4]) {
   if constexpr (DT == kFP32) {
     v4f o;
     o.x = v[0]; o.y = v[1]; o.z = v[2]; o.w = v[3];
-    __builtin_nontemporal_store(o, as_global<v4f>(static_cast<float*>(base) + idx));
+    if constexpr (KEEP) *as_global<v4f>(static_cast<float*>(base) + idx) = o;
+    else __builtin_nontemporal_store(o, as_global<v4f>(static_cast<float*>(base) + idx));
   } else {
     uint32_t h[4];
 #pragma unroll
@@ -101,7 +105,8 @@ __device__ __forceinline__ void store4(void* base, int64_t idx, const float v[4]
     v2u o;
     o.x = h[0] | (h[1] << 16);
     o.y = h[2] | (h[3] << 16);
-    __builtin_nontemporal_store(o, as_global<v2u>(static_cast<uint16_t*>(base) + idx));
+    if constexpr (KEEP) *as_global<v2u>(static_cast<uint16_t*>(base) + idx) = o;
+    else __builtin_nontemporal_store(o, as_global<v2u>(static_cast<uint16_t*>(base) + idx));
   }
 }
 
@@ -114,9 +119,9 @@ __device__ __forceinline__ void store1(void* base, int64_t idx, float v) {
 
 // Guarded variants for the ragged end of a tensor: elements at or beyond `n` read as `fill`
 // and are not written.
-template <int DT>
+template <int DT, bool KEEP = false>
 __device__ __forceinline__ void load4_guard(const void* base, int64_t idx, int64_t n, float fill, float out[4]) {
-  if (idx + 4 <= n) { load4<DT>(base, idx, out); return; }
+  if (idx + 4 <= n) { load4<DT, KEEP>(base, idx, out); return; }
 #pragma unroll
   for (int i = 0; i < 4; ++i) out[i] = (idx + i < n) ? load1<DT>(base, idx + i) : fill;
 }
