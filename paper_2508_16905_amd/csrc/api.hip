@@ -98,21 +98,37 @@ struct triaccel_ctx {
 
 namespace {
 
-template <typename T>
-int dev_alloc(triaccel_ctx* c, T** out, size_t count) {
-  void* p = nullptr;
-  const size_t bytes = (count ? count : 1) * sizeof(T);
-  hipError_t e = hipMalloc(&p, bytes);
-  if (e != hipSuccess) {
-    g_last_error = std::string("hipMalloc: ") + hipGetErrorString(e);
-    return TRIACCEL_E_NO_MEMORY;
+// Device workspace: the requests are gathered and served from one allocation, cleared once (an allocation and a
+// clear of its own for each of the twenty-odd tables were most of the time of triaccel_init on a small set).
+class Workspace {
+ public:
+  template <typename T>
+  void add(T** out, size_t count) {
+    requests_.push_back({reinterpret_cast<void**>(out), size_});
+    size_ += ((count ? count : 1) * sizeof(T) + 255) & ~size_t(255);
   }
-  c->device_allocs.push_back(p);
-  e = hipMemset(p, 0, bytes);
-  if (e != hipSuccess) return hip_fail(e, "hipMemset");
-  *out = static_cast<T*>(p);
-  return TRIACCEL_OK;
-}
+  int allocate(triaccel_ctx* c) {
+    void* p = nullptr;
+    hipError_t e = hipMalloc(&p, size_);
+    if (e != hipSuccess) {
+      g_last_error = std::string("hipMalloc: ") + hipGetErrorString(e);
+      return TRIACCEL_E_NO_MEMORY;
+    }
+    c->device_allocs.push_back(p);
+    e = hipMemset(p, 0, size_);
+    if (e != hipSuccess) return hip_fail(e, "hipMemset");
+    for (const auto& r : requests_) *r.out = static_cast<char*>(p) + r.offset;
+    return TRIACCEL_OK;
+  }
+
+ private:
+  struct Request {
+    void** out;
+    size_t offset;
+  };
+  std::vector<Request> requests_;
+  size_t size_ = 0;
+};
 
 int validate_config(const triaccel_config* cfg) {
   if (!cfg) return TRIACCEL_E_NULL_PTR;
@@ -398,22 +414,23 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   T.total_chunks = (uint32_t)chunks.size();
   T.max_chunks_per_tensor = max_chunks;
   T.persistent_grid = cus * 8;
-  for (auto& slot : c->tables)
-    if ((rc = dev_alloc(c, &slot.dev, (size_t)n))) return fail(rc);
+  Workspace ws;
+  for (auto& slot : c->tables) ws.add(&slot.dev, (size_t)n);
+  ws.add(&T.chunks, chunks.size());
+  ws.add(&T.partials, chunks.size());
+  ws.add(&T.ema_partials, chunks.size());
+  ws.add(&T.layers, (size_t)n);
+  ws.add(&T.glob, 1);
+  ws.add(&T.hist, (size_t)n * kHistBins);
+  ws.add(&T.cands, (size_t)cand_total);
+  ws.add(&T.cand_counters, (size_t)n * (kCandLists + 1) * kCandCounterStride);
+  ws.add(&T.trans_list, (size_t)n * 2);
+  ws.add(&T.resize_scratch, (size_t)scratch_chunks * kChunk * 4);
+  ws.add(&T.inputs, (size_t)n);
+  ws.add(&T.arrived, (size_t)n * kCandCounterStride);
+  ws.add(&T.scalars, 1);
+  if ((rc = ws.allocate(c))) return fail(rc);
   T.tensors = c->tables[0].dev;
-  if ((rc = dev_alloc(c, &T.chunks, chunks.size()))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.partials, chunks.size()))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.ema_partials, chunks.size()))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.layers, (size_t)n))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.glob, 1))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.hist, (size_t)n * kHistBins))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.cands, (size_t)cand_total))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.cand_counters, (size_t)n * (kCandLists + 1) * kCandCounterStride))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.trans_list, (size_t)n * 2))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.resize_scratch, (size_t)scratch_chunks * kChunk * 4))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.inputs, (size_t)n))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.arrived, (size_t)n * kCandCounterStride))) return fail(rc);
-  if ((rc = dev_alloc(c, &T.scalars, 1))) return fail(rc);
   e = hipMemcpy(T.chunks, chunks.data(), chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
   if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(chunks)"));
   // shapes and chunk ranges are valid from now on; the pointers arrive with every step
@@ -447,11 +464,13 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     P.total_chunks = T.total_chunks;
     P.total_segs = (uint32_t)segs.size();
     P.seg = seg;
-    if ((rc = dev_alloc(c, &P.descs, (size_t)n))) return fail(rc);
-    if ((rc = dev_alloc(c, &P.segs, segs.size()))) return fail(rc);
-    if ((rc = dev_alloc(c, &P.seg_first, (size_t)n))) return fail(rc);
-    if ((rc = dev_alloc(c, &P.partials, segs.size() * (size_t)power_partial_len(config->power_k)))) return fail(rc);
-    if ((rc = dev_alloc(c, &P.state, (size_t)n))) return fail(rc);
+    Workspace pws;
+    pws.add(&P.descs, (size_t)n);
+    pws.add(&P.segs, segs.size());
+    pws.add(&P.seg_first, (size_t)n);
+    pws.add(&P.partials, segs.size() * (size_t)power_partial_len(config->power_k));
+    pws.add(&P.state, (size_t)n);
+    if ((rc = pws.allocate(c))) return fail(rc);
     e = hipMemcpy(P.segs, segs.data(), segs.size() * sizeof(SegRef), hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segments)"));
     e = hipMemcpy(P.seg_first, seg_first.data(), (size_t)n * sizeof(uint32_t), hipMemcpyHostToDevice);
