@@ -413,6 +413,9 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   T.n_tensors = (uint32_t)n;
   T.total_chunks = (uint32_t)chunks.size();
   T.max_chunks_per_tensor = max_chunks;
+  uint64_t grad_bytes = 0;
+  for (int32_t i = 0; i < n; ++i) grad_bytes += (uint64_t)tensors[i].numel * (tensors[i].grad_dtype == TRIACCEL_FP32 ? 4u : 2u);
+  T.keep_grads = grad_bytes <= kKeepBytes;
   T.persistent_grid = cus * 8;
   Workspace ws;
   for (auto& slot : c->tables) ws.add(&slot.dev, (size_t)n);

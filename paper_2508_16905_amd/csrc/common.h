@@ -39,6 +39,13 @@ constexpr int kFinishRegs = 8;               // listed keys per thread the finis
 constexpr uint32_t kCandLists = 64;          // sub-lists per tensor (plus one overflow list)
 constexpr uint32_t kCandCounterStride = 32;  // words between list counters: one 128-byte line each
 
+// An array that two kernels of a step read one after the other is read first without the non-temporal hint, so
+// that the caches (256 MB on the memory side) keep what they can of it, if it has at most this many bytes: beyond
+// it the slower plain reads cost more than the cached part gains (step without a probe, fp32 gradients, without and with
+// the hint: 100 M parameters 357 and 391 us, 250 M 951 and 979, 500 M 2086 and 2094, 800 M 3409 and 3401, 1073 M 4594
+// and 4560; power iteration at k = 5: 40 M 531 and 552, 120 M 1616 and 1643, 240 M 3262 and 3252).
+constexpr uint64_t kKeepBytes = 2ull << 30;
+
 enum SelMode : uint32_t {
   kSelHist = 0,   // a histogram over the window is (being) accumulated; the scan decides what next
   kSelCand = 1,   // theta lies in [rng_lo, rng_hi): few enough keys there to list them
@@ -106,7 +113,7 @@ struct LayerDev {
   uint32_t found_inf, curv_nonfinite;
   uint32_t sel_passes;     // passes over h beyond the EMA pass that the last probed step needed
   uint32_t sel_listed;     // keys the EMA kernel listed at the last probed step
-  uint32_t sel_outcome;    // how the band check of the last probed step ended (see select_begin)
+  uint32_t sel_outcome;    // how the band check of the last probed step ended (see select_setup)
   float lambda_power;      // max_j |Rayleigh quotient| latched by the power iteration (Sec. 3.2)
   // bookkeeping
   uint32_t applied_steps;  // steps that were not skipped

@@ -190,7 +190,8 @@ __device__ __forceinline__ void for_each_candidate(const TensorDesc& td, const C
 // ---------------------------------------------------------------------------------------------
 // Fallback mask pass for tensors whose mask was not settled by the EMA kernel: re-reads |h| and
 // writes the bit mask.  Keys above the range are kept, keys below dropped; keys inside it are
-// listed and their bits are set afterwards by k_select_finish.  Called from k_update.
+// listed and their bits are set afterwards by k_select_finish.  Called from k_update and k_mask_pass; SHARED: from
+// k_select_tail, where a workgroup of the same launch resolves the threshold.
 // ---------------------------------------------------------------------------------------------
 template <bool FULL, bool SHARED = false>
 __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, uint32_t mode, uint32_t theta,

@@ -26,6 +26,7 @@ struct DeviceTables {
   uint32_t n_tensors;
   uint32_t total_chunks;
   uint32_t max_chunks_per_tensor;
+  bool keep_grads;           // the gradients of the set have at most kKeepBytes
   uint32_t persistent_grid;  // workgroups of the persistent streaming kernels
 };
 

@@ -15,20 +15,20 @@ namespace triaccel {
 // (a sample of the data, so the sums stay small against their cancellation).  Lanes and
 // wavefronts are added in a fixed order; one (mean, M2) partial per chunk.
 // ---------------------------------------------------------------------------------------------
-template <int GD, bool FULL>
+template <int GD, bool FULL, bool KEEP>
 __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, float inv_scale, double& shift,
                                             double& s1, double& s2, uint32_t& bad) {
   const int tid = threadIdx.x;
   float g[kRows][4];
-  // The update reads the gradients again: they are left in the caches (55 M parameters, step without a probe:
+  // The update reads the gradients again: KEEP leaves them in the caches (55 M parameters, step without a probe:
   // 228 -> 202 us; 11 M: 49 -> 45; 250 M: 1071 -> 1049).
   // the shift is read in the same batch of loads as the data: one memory latency per chunk, not two
   const float first = load1<GD>(td.grad, base);
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
     const int64_t idx = base + r * kRowElems + tid * kVec;
-    if (FULL) load4<GD, true>(td.grad, idx, g[r]);
-    else load4_guard<GD, true>(td.grad, idx, td.numel, 0.0f, g[r]);
+    if (FULL) load4<GD, KEEP>(td.grad, idx, g[r]);
+    else load4_guard<GD, KEEP>(td.grad, idx, td.numel, 0.0f, g[r]);
   }
   shift = (double)(first * inv_scale);
 #pragma unroll
@@ -47,6 +47,7 @@ __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, 
   }
 }
 
+template <bool KEEP>
 __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __restrict__ tds,
                                                          const ChunkRef* __restrict__ chunks,
                                                          StatPartial* __restrict__ partials, LayerDev* layers,
@@ -63,15 +64,15 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
   double shift = 0.0;
   if (full) {
     switch (td.grad_dtype) {
-      case kFP32: stats_chunk<kFP32, true>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      case kBF16: stats_chunk<kBF16, true>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      default: stats_chunk<kFP16, true>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+      case kFP32: stats_chunk<kFP32, true, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+      case kBF16: stats_chunk<kBF16, true, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+      default: stats_chunk<kFP16, true, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
     }
   } else {
     switch (td.grad_dtype) {
-      case kFP32: stats_chunk<kFP32, false>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      case kBF16: stats_chunk<kBF16, false>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      default: stats_chunk<kFP16, false>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+      case kFP32: stats_chunk<kFP32, false, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+      case kBF16: stats_chunk<kBF16, false, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+      default: stats_chunk<kFP16, false, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
     }
   }
   s1 = wave_sum_f64(s1);
@@ -376,10 +377,9 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_finish(const TensorDe
 }
 
 // ---------------------------------------------------------------------------------------------
-// Stage 4: per-layer kernel (one workgroup per tensor): band check of the threshold selection
-// (select_begin above), then the per-layer assignment: merge the chunk moments, variance
-// EMA (Sec. 3.1 first equation), precision rule (second equation) with curvature promotion
-// (Sec. 3.2), step size eta_l (Sec. 3.2), overflow decision and loss-scale schedule.
+// Stage 4: per-layer kernel (one workgroup per tensor; sets of the local form have none): band check of the
+// threshold selection (select_outcome, select_setup), then the per-layer assignment (layer_body.h), overflow
+// decision and loss-scale schedule.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void k_layer(const TensorDesc* __restrict__ tds,
                                                     const StatPartial* __restrict__ partials,
@@ -417,7 +417,8 @@ __global__ __launch_bounds__(kThreads) void k_layer(const TensorDesc* __restrict
 // Host-side launchers
 // ---------------------------------------------------------------------------------------------
 hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, bool local, hipStream_t s) {
-  hipLaunchKernelGGL(k_grad_stats, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.partials,
+  const auto kernel = t.keep_grads ? k_grad_stats<true> : k_grad_stats<false>;
+  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.partials,
                      t.layers, t.glob, local ? t.inputs : nullptr, sa);
   TA_LAUNCH_CHECK();
   return hipSuccess;

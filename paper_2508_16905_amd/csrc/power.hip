@@ -24,10 +24,10 @@ namespace {
 
 __device__ __forceinline__ constexpr int tri(int i, int j) { return j * (j + 1) / 2 + i; }  // i <= j
 
-template <int K, bool FULL>
+template <int K, bool FULL, bool KEEP>
 __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, int64_t base, double (&g)[K * (K + 1) / 2],
                                            double (&c)[K], double (&d)[K]) {
-  // the products are read again by the apply pass: they are left in the caches (iteration of the ResNet-18 set,
+  // the products are read again by the apply pass: KEEP leaves them in the caches (iteration of the ResNet-18 set,
   // k = 5: 160 -> 146 us)
   // one row at a time: the 2k loads of a row are in flight together, and the accumulators leave
   // room for several wavefronts per SIMD to overlap their loads with the fp64 arithmetic
@@ -39,10 +39,10 @@ __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, i
     for (int j = 0; j < K; ++j) {
       if constexpr (FULL) {
         load4<kFP32>(pd.u + (int64_t)j * pd.stride, idx, u[j]);
-        load4<kFP32, true>(pd.hu + (int64_t)j * pd.stride, idx, w[j]);
+        load4<kFP32, KEEP>(pd.hu + (int64_t)j * pd.stride, idx, w[j]);
       } else {
         load4_guard<kFP32>(pd.u + (int64_t)j * pd.stride, idx, numel, 0.0f, u[j]);
-        load4_guard<kFP32, true>(pd.hu + (int64_t)j * pd.stride, idx, numel, 0.0f, w[j]);
+        load4_guard<kFP32, KEEP>(pd.hu + (int64_t)j * pd.stride, idx, numel, 0.0f, w[j]);
       }
     }
 #pragma unroll
@@ -66,7 +66,7 @@ __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, i
 // table for the apply pass: a copy from host memory ahead of the pass cost the stream 10 us a call.
 // Bound by HBM: 447 MB (11.2 M parameters, k = 5) in 70 us, 6.3 TB/s; with 2 wavefronts per SIMD (206 registers),
 // segments of 8 chunks and reductions through LDS it took 79.
-template <int K>
+template <int K, bool KEEP>
 __global__ __launch_bounds__(kThreads, K <= 5 ? 3 : 1) void k_power_gram(const TensorDesc* __restrict__ tds,
                                                                          PowerDescArg arg, PowerDesc* __restrict__ pds,
                                                                          const SegRef* __restrict__ segs, uint32_t seg,
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(kThreads, K <= 5 ? 3 : 1) void k_power_gram(const T
   // the ragged chunk, if it is this segment's, comes after the loop over the full ones: with both bodies in one
   // loop the sums were held twice (206 registers at k = 5, 2 wavefronts per SIMD)
   const uint32_t full = min(c1, (uint32_t)(numel / kChunk));
-  for (uint32_t ch = c0; ch < full; ++ch) gram_chunk<K, true>(pd, numel, (int64_t)ch * kChunk, g, c, d);
-  if (full < c1) gram_chunk<K, false>(pd, numel, (int64_t)full * kChunk, g, c, d);
+  for (uint32_t ch = c0; ch < full; ++ch) gram_chunk<K, true, KEEP>(pd, numel, (int64_t)ch * kChunk, g, c, d);
+  if (full < c1) gram_chunk<K, false, KEEP>(pd, numel, (int64_t)full * kChunk, g, c, d);
   // lanes, then wavefronts, in a fixed order
   __shared__ double s_part[kThreads / kWave][PP];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -262,7 +262,10 @@ hipError_t launch_k(const PowerTables& t, const PowerDesc* descs, int latch, hip
     if (t.n_tensors > (uint32_t)kPowerArgTensors) arg.count = 0;
   }
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_power_gram<K>, dim3(t.total_segs), dim3(kThreads), 0, s, t.tensors, arg, t.descs, t.segs,
+  // total_chunks * kChunk: the vectors' length to within a chunk per tensor
+  const bool keep = (uint64_t)t.total_chunks * kChunk * K * 4 <= kKeepBytes;
+  const auto gram = keep ? k_power_gram<K, true> : k_power_gram<K, false>;
+  hipLaunchKernelGGL(gram, dim3(t.total_segs), dim3(kThreads), 0, s, t.tensors, arg, t.descs, t.segs,
                      t.seg, t.partials);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
