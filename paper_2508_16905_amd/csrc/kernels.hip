@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
     const double n = (double)(left < kChunk ? left : kChunk);
     const double m2 = t2 - t1 * t1 / n;
     partials[blockIdx.x].mean = shift + t1 / n;
-    partials[blockIdx.x].m2 = m2 > 0.0 ? m2 : 0.0;
+    partials[blockIdx.x].m2 = m2 < 0.0 ? 0.0 : m2;  // inf and NaN (x overflowed) stay
   }
 }
 

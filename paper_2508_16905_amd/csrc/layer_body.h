@@ -106,7 +106,9 @@ __device__ __forceinline__ LayerSums layer_reduce(const LayerAcc& a, int64_t num
   e = EmaTotals{uniform(e.above), uniform(e.zeros), uniform(e.maxkey), uniform(e.listed), uniform(e.nonfin)};
   const double n = (double)numel;
   const double m2 = s2 - s1 * s1 / n;
-  return LayerSums{a.shift + s1 / n, (m2 > 0.0 ? m2 : 0.0) / n, e};
+  // only a negative rounding error is cut off: an unscaled gradient that overflowed leaves NaN here, and the
+  // precision rule's comparisons then choose FP32
+  return LayerSums{a.shift + s1 / n, (m2 < 0.0 ? 0.0 : m2) / n, e};
 }
 
 __device__ __forceinline__ LayerIn layer_in(const LayerDev& ls) {
