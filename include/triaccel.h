@@ -180,11 +180,12 @@ typedef struct {
 /*
  * Create a handle for n tensors.  `tensors` gives shapes, dtypes and the initial pointers;
  * curv / mom / mask contents are taken as the initial state (normally zero).  `hip_stream` is a
- * hipStream_t (NULL = the default stream).  Allocates the workspace (chunk table, partials,
- * histograms, candidate lists, per-layer state, eight device copies of the tensor table; a few MB plus
- * 40 bytes per 4096 parameters, plus up to 4 MB of candidate lists per tensor of 262,144 elements or more,
- * plus up to 1 MB per tensor of scratch for storage sizes that change, in sets with a tensor of more than
- * 524,288 elements).
+ * hipStream_t (NULL = the default stream).  Allocates the workspace (chunk table, partials, histograms, key
+ * lists, per-layer state, eight device copies of the tensor table): a few MB, plus 20 KB per tensor, 40 bytes
+ * per 4096 parameters of a tensor and its key lists, 16 bytes per element up to 4 MB a tensor.  In sets with a
+ * tensor of more than 524,288 elements, further, scratch for storage sizes that change: 4 bytes for each of the
+ * first 262,144 elements of every tensor (65,536 in sets of 16,384 pieces of 4096 elements and more), rounded up
+ * to 4096 elements.
  */
 int triaccel_init(triaccel_handle *out, const triaccel_config *config, const triaccel_tensor *tensors,
                   int32_t n, void *hip_stream);

@@ -377,16 +377,11 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     d.n_chunks = nc;
     d.grad_dtype = t.grad_dtype;
     d.cand_offset = cand_total;
-    d.cand_cap = t.numel < (int64_t)kCandCap ? (uint32_t)t.numel : kCandCap;
-    d.sub_cap = (d.cand_cap + kCandLists - 1) / kCandLists;
-    d.list_all = t.numel <= (int64_t)kListAllMax ? 1u : 0u;
-    if (d.list_all) {
-      // a list for each wavefront of the tensor's chunks, large enough for all its keys; no overflow list
-      d.sub_cap = kChunk / (kThreads / kWave);
-      cand_total += (uint64_t)nc * (kThreads / kWave) * d.sub_cap;
-    } else {
-      cand_total += (uint64_t)kCandLists * d.sub_cap + d.cand_cap;
-    }
+    const KeyLists lists = key_lists(t.numel);
+    d.cand_cap = lists.over_cap;
+    d.sub_cap = lists.sub_cap;
+    d.list_all = lists.list_all;
+    cand_total += lists.entries;
     for (uint32_t k = 0; k < nc; ++k) chunks.push_back(ChunkRef{(uint32_t)i, k});
     if (nc > max_chunks) max_chunks = nc;
     c->numel[i] = t.numel;

@@ -34,10 +34,34 @@ constexpr uint32_t kMinPredShift = 6;        // finest predicted window: 2048 bi
 constexpr uint32_t kUnknownPredErr = 1u << 16;  // assumed prediction error (keys) before any is measured
 constexpr uint32_t kCandCap = 262144;        // keys a tensor may list in total (entries)
 constexpr uint32_t kListAllMax = 8192;       // tensors up to this size list every non-zero key (no prediction)
-static_assert(kListAllMax / (kChunk / 4) <= 64, "a list for each wavefront of such a tensor");
 constexpr int kFinishRegs = 8;               // listed keys per thread the finish kernel can hold in registers
 constexpr uint32_t kCandLists = 64;          // sub-lists per tensor (plus one overflow list)
 constexpr uint32_t kCandCounterStride = 32;  // words between list counters: one 128-byte line each
+static_assert(kListAllMax / (kChunk / 4) <= kCandLists, "a list for each wavefront of such a tensor");
+
+// Key lists of a tensor: kCandLists sub-lists of sub_cap entries and an overflow list of over_cap; or, if it lists
+// all its keys, one list per wavefront (list 4 * chunk + wavefront) that can hold all the wavefront's keys.  Such a
+// list is sized by the tensor, not by the chunk: 32 KB for a bias of 10 elements otherwise.  At most 2 entries
+// per element either way.
+struct KeyLists {
+  uint32_t list_all, sub_cap, over_cap, entries;
+};
+inline KeyLists key_lists(int64_t numel) {
+  KeyLists k{};
+  k.over_cap = numel < (int64_t)kCandCap ? (uint32_t)numel : kCandCap;
+  k.sub_cap = (k.over_cap + kCandLists - 1) / kCandLists;
+  k.entries = kCandLists * k.sub_cap + k.over_cap;
+  if (numel <= (int64_t)kListAllMax) {
+    constexpr uint32_t kWaves = kThreads / kWave, kWaveRow = kWave * kVec;  // a wavefront's elements of a row
+    const uint32_t n = (uint32_t)numel, head = n < (uint32_t)kChunk ? n : (uint32_t)kChunk;
+    const uint32_t wave0 = (head + kRowElems - 1) / kRowElems * kWaveRow;   // no wavefront has more than the first
+    const uint32_t tail_waves = (n % kChunk + kWaveRow - 1) / kWaveRow;     // of the ragged chunk, with elements
+    k.list_all = 1;
+    k.sub_cap = head < wave0 ? head : wave0;
+    k.entries = (n / kChunk * kWaves + (tail_waves < kWaves ? tail_waves : kWaves)) * k.sub_cap;
+  }
+  return k;
+}
 
 // An array that two kernels of a step read one after the other is read first without the non-temporal hint, so
 // that the caches (256 MB on the memory side) keep what they can of it, if it has at most this many bytes: beyond
@@ -96,8 +120,7 @@ struct TensorDesc {
   int32_t has_probe;
   uint64_t cand_offset;  // first entry of the tensor's candidate lists in the pool
   uint32_t cand_cap;     // min(numel, kCandCap): capacity of the overflow list (none if list_all)
-  uint32_t sub_cap;      // capacity of each of the kCandLists sub-lists: ceil(cand_cap / kCandLists); if list_all, of
-                         // the one list per wavefront: the keys it can have
+  uint32_t sub_cap;      // capacity of each of the other lists (key_lists)
   uint32_t list_all;     // numel <= kListAllMax: every non-zero key is listed, no prediction
   uint32_t resize_slot;  // the tensor's first chunk in the scratch area of the in-place resize
 };

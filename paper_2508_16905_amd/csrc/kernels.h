@@ -16,7 +16,7 @@ struct DeviceTables {
   GlobalDev* glob;
   GlobalDev* host_result;  // pinned host memory (device-visible address): the per-layer kernel leaves the step's result record there
   uint32_t* hist;        // n_tensors x kHistBins
-  Candidate* cands;      // pool: per tensor kCandLists * sub_cap + cand_cap entries (list_all: a list per wavefront)
+  Candidate* cands;      // pool of the tensors' key lists (key_lists)
   uint32_t* cand_counters;  // n_tensors x (kCandLists + 1) counters, kCandCounterStride words apart
   uint32_t* trans_list;  // 2 x n_tensors
   char* resize_scratch;  // new values of the first chunks of tensors that change size (resize_schedule.h)
