@@ -186,6 +186,11 @@ void free_ctx(triaccel_ctx* c) {
   delete c;
 }
 
+// Sets bound by their launches, whose update takes the layers' decisions itself (k_update_local).
+bool local_form(const triaccel_ctx& c) {
+  return c.cfg.elementwise_scale != 1 && c.t.total_chunks < kLaunchBoundChunks && c.t.max_chunks_per_tensor <= kLocalMaxChunks;
+}
+
 // The kernels of one optimizer step, in order, on the handle's stream.  `ev` (eight events) records
 // the stage boundaries.  Order of the stages: the per-layer assignment needs only the gradient
 // moments and lambda_l = max |h_i| (known after the EMA pass), so it runs before the threshold is
@@ -197,7 +202,7 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   hipStream_t s = h->stream;
   const bool fisher = h->cfg.curvature_source == 1;
   const bool elem = h->cfg.elementwise_scale == 1;
-  const bool local = !elem && T.total_chunks < kLaunchBoundChunks && T.max_chunks_per_tensor <= kLocalMaxChunks;
+  const bool local = local_form(*h);
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
   TA_HIP(launch_grad_stats(T, sa, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
@@ -412,9 +417,17 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   for (int32_t i = 0; i < n; ++i) grad_bytes += (uint64_t)tensors[i].numel * (tensors[i].grad_dtype == TRIACCEL_FP32 ? 4u : 2u);
   T.keep_grads = grad_bytes <= kKeepBytes;
   T.persistent_grid = cus * 8;
+  std::vector<ChunkRef> wg_chunks;  // empty: the order of `chunks`
+  if (local_form(*c) && resize.n_stages == 1) {
+    wg_chunks.reserve(chunks.size());
+    heads_first((uint32_t)n, [&](uint32_t t) { return c->desc[t].n_chunks; },
+                [&](uint32_t t, uint32_t k) { wg_chunks.push_back(ChunkRef{t, k}); });
+  }
+  ChunkRef* wg_chunks_dev = nullptr;
   Workspace ws;
   for (auto& slot : c->tables) ws.add(&slot.dev, (size_t)n);
   ws.add(&T.chunks, chunks.size());
+  ws.add(&wg_chunks_dev, wg_chunks.size());
   ws.add(&T.partials, chunks.size());
   ws.add(&T.ema_partials, chunks.size());
   ws.add(&T.layers, (size_t)n);
@@ -431,6 +444,11 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   T.tensors = c->tables[0].dev;
   e = hipMemcpy(T.chunks, chunks.data(), chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
   if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(chunks)"));
+  T.wg_chunks = wg_chunks.empty() ? T.chunks : wg_chunks_dev;
+  if (!wg_chunks.empty()) {
+    e = hipMemcpy(wg_chunks_dev, wg_chunks.data(), wg_chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(workgroup order)"));
+  }
   // shapes and chunk ranges are valid from now on; the pointers arrive with every step
   for (auto& slot : c->tables) {
     e = hipMemcpy(slot.dev, c->desc.data(), (size_t)n * sizeof(TensorDesc), hipMemcpyHostToDevice);

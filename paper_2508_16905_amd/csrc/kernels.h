@@ -9,9 +9,10 @@ namespace triaccel {
 // Device pointers and sizes of a handle's workspace.
 struct DeviceTables {
   TensorDesc* tensors;
-  ChunkRef* chunks;
-  StatPartial* partials;
-  EmaPartial* ema_partials;  // one record per chunk, written by the EMA kernel
+  ChunkRef* chunks;          // tensor by tensor, in order
+  const ChunkRef* wg_chunks; // chunk of each workgroup of the kernels that have one for every chunk: `chunks`, or heads_first
+  StatPartial* partials;     // one record per chunk, in the order of `chunks`
+  EmaPartial* ema_partials;  // the same, written by the EMA kernel
   LayerDev* layers;
   GlobalDev* glob;
   GlobalDev* host_result;  // pinned host memory (device-visible address): the per-layer kernel leaves the step's result record there

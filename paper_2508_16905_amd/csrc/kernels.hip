@@ -99,8 +99,9 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
     const int64_t left = td.numel - base;
     const double n = (double)(left < kChunk ? left : kChunk);
     const double m2 = t2 - t1 * t1 / n;
-    partials[blockIdx.x].mean = shift + t1 / n;
-    partials[blockIdx.x].m2 = m2 < 0.0 ? 0.0 : m2;  // inf and NaN (x overflowed) stay
+    StatPartial& p = partials[td.first_chunk + cr.index];
+    p.mean = shift + t1 / n;
+    p.m2 = m2 < 0.0 ? 0.0 : m2;  // inf and NaN (x overflowed) stay
   }
 }
 
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const LayerDev& ls = layers[cr.tensor];
   const uint32_t probes_seen = ls.probes_seen, use_band = ls.use_band, band_lo = ls.band_lo, band_hi = ls.band_hi;
   TA_LOADED("s"(td.grad), "s"(td.z), "s"(td.hz), "s"(td.curv), "s"(td.mask), "s"(td.numel), "s"(td.grad_dtype),
-            "s"(td.has_probe), "s"(td.list_all), "s"(td.cand_offset), "s"(probes_seen), "s"(use_band), "s"(band_lo),
+            "s"(td.has_probe), "s"(td.list_all), "s"(td.first_chunk), "s"(td.cand_offset), "s"(probes_seen), "s"(use_band), "s"(band_lo),
             "s"(band_hi));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
   const bool first = probes_seen == 0;
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
     // elements past the end of the tensor were counted as zero keys
     const int64_t left = td.numel - base;
     const uint32_t past = left < kChunk ? (uint32_t)(kChunk - left) : 0u;
-    ema_partials[blockIdx.x] = EmaPartial{az - (past << 16), mk, ln, nf};
+    ema_partials[td.first_chunk + cr.index] = EmaPartial{az - (past << 16), mk, ln, nf};
   }
 }
 
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(kThreads) void k_layer(const TensorDesc* __restrict
 // ---------------------------------------------------------------------------------------------
 hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, bool local, hipStream_t s) {
   const auto kernel = t.keep_grads ? k_grad_stats<true> : k_grad_stats<false>;
-  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.partials,
+  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.partials,
                      t.layers, t.glob, local ? t.inputs : nullptr, sa);
   TA_LAUNCH_CHECK();
   return hipSuccess;
@@ -427,10 +428,10 @@ hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, bool loca
 hipError_t launch_curv_ema(const DeviceTables& t, const StepArg& sa, float beta_h, float omb_h, int fisher,
                            hipStream_t s) {
   if (fisher)
-    hipLaunchKernelGGL(k_curv_ema<true>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers,
+    hipLaunchKernelGGL(k_curv_ema<true>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.layers,
                        t.glob, t.ema_partials, t.cands, t.cand_counters, sa, beta_h, omb_h);
   else
-    hipLaunchKernelGGL(k_curv_ema<false>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers,
+    hipLaunchKernelGGL(k_curv_ema<false>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.layers,
                        t.glob, t.ema_partials, t.cands, t.cand_counters, sa, beta_h, omb_h);
   TA_LAUNCH_CHECK();
   return hipSuccess;

@@ -134,7 +134,7 @@ hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const H
   const bool mom = hp.momentum != 0.0f;
   const auto kernel = any_probe ? (mom ? k_update_local<true, true> : k_update_local<false, true>)
                                 : (mom ? k_update_local<true, false> : k_update_local<false, false>);
-  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.chunks, t.partials, t.ema_partials,
+  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.partials, t.ema_partials,
                      t.inputs, t.layers, t.glob, t.host_result, t.cand_counters, t.hist, t.arrived, t.trans_list, t.n_tensors,
                      plan, t.resize_scratch, sa, hp);
   TA_LAUNCH_CHECK();
