@@ -90,6 +90,10 @@ struct triaccel_ctx {
   // power iteration (only with cfg.power_k > 0)
   PowerTables pt{};
   std::vector<PowerDesc> power_descs;
+  PowerDesc* power_staging[kRing] = {};  // pinned, for calls with more than kPowerArgMax tensors
+  hipEvent_t power_ev[kRing] = {};
+  bool power_used[kRing] = {};
+  int power_pos = 0;
   bool power_called = false;
   hipEvent_t power_prof[4] = {};
   bool power_timed = false;  // the last call recorded its kernel boundaries
@@ -171,6 +175,8 @@ void free_ctx(triaccel_ctx* c) {
   for (int i = 0; i < kRing; ++i) {
     if (c->staging[i]) (void)hipHostFree(c->staging[i]);
     if (c->staging_ev[i]) (void)hipEventDestroy(c->staging_ev[i]);
+    if (c->power_staging[i]) (void)hipHostFree(c->power_staging[i]);
+    if (c->power_ev[i]) (void)hipEventDestroy(c->power_ev[i]);
   }
   for (auto& e : c->power_prof)
     if (e) (void)hipEventDestroy(e);
@@ -491,6 +497,12 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segments)"));
     e = hipMemcpy(P.seg_first, seg_first.data(), (size_t)n * sizeof(uint32_t), hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segment index)"));
+    for (int i = 0; i < kRing && (uint32_t)n > kPowerArgMax; ++i) {
+      e = hipHostMalloc(reinterpret_cast<void**>(&c->power_staging[i]), (size_t)n * sizeof(PowerDesc), hipHostMallocDefault);
+      if (e != hipSuccess) return fail(hip_fail(e, "hipHostMalloc(power staging)"));
+      e = hipEventCreateWithFlags(&c->power_ev[i], hipEventDisableTiming);
+      if (e != hipSuccess) return fail(hip_fail(e, "hipEventCreate"));
+    }
     c->power_descs.resize((size_t)n);
     c->power_host.resize((size_t)n);
   }
@@ -742,10 +754,28 @@ int triaccel_power_iter(triaccel_handle h, const triaccel_power_tensor* vectors,
     if (!aligned16(v.u) || !aligned16(v.hu)) return TRIACCEL_E_ALIGNMENT;
   }
   for (int32_t i = 0; i < n; ++i) h->power_descs[i] = PowerDesc{vectors[i].u, vectors[i].hu, vectors[i].stride};
+  const PowerDesc* args = h->power_descs.data();
+  if ((uint32_t)n > kPowerArgMax) {
+    // many tensors: one copy from pinned memory, unless the caller is capturing the stream (a replay would read
+    // the staging buffer again)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (h->stream) TA_HIP(hipStreamIsCapturing(h->stream, &capture));
+    if (capture == hipStreamCaptureStatusNone) {
+      const int slot = h->power_pos;
+      if (h->power_used[slot]) TA_HIP(hipEventSynchronize(h->power_ev[slot]));
+      std::memcpy(h->power_staging[slot], args, (size_t)n * sizeof(PowerDesc));
+      TA_HIP(hipMemcpyAsync(h->pt.descs, h->power_staging[slot], (size_t)n * sizeof(PowerDesc), hipMemcpyHostToDevice,
+                            h->stream));
+      TA_HIP(hipEventRecord(h->power_ev[slot], h->stream));
+      h->power_used[slot] = true;
+      h->power_pos = (slot + 1) % kRing;
+      args = nullptr;
+    }
+  }
   if (h->profiling)
     for (auto& e : h->power_prof)
       if (!e) TA_HIP(hipEventCreate(&e));
-  TA_HIP(launch_power_iter(h->pt, h->power_descs.data(), k, latch ? 1 : 0, h->stream, h->profiling ? h->power_prof : nullptr));
+  TA_HIP(launch_power_iter(h->pt, args, k, latch ? 1 : 0, h->stream, h->profiling ? h->power_prof : nullptr));
   h->power_timed = h->profiling;
   h->power_called = true;
   return TRIACCEL_OK;

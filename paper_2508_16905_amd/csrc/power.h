@@ -36,6 +36,12 @@ struct PowerDescArg {
   PowerDesc e[kPowerArgTensors];
 };
 static_assert(sizeof(PowerDescArg) <= 3200, "passed by value as a kernel argument");
+// Up to this many tensors the pointers travel that way, kPowerArgTensors a launch; for more the launches cost as much
+// as a copy from pinned memory, which is what such calls make unless the stream is being captured.  An iteration of
+// tensors of 3000 elements, k = 2, arguments (its two speeds) and copy: 129 tensors 15.8 / 19.4 and 18.3 us, 256
+// 16.4 / 19.5 and 17.9, 384 20 / 24 and 19.6, 640 28 / 33 and 23.7, 1000 38 / 45 and 42, 2000 72 / 81 and 61, 4000
+// 133 / 148 and 94.
+constexpr uint32_t kPowerArgMax = 2 * kPowerArgTensors;
 
 // Per-tensor result of the last call.
 struct PowerLayer {
@@ -65,7 +71,7 @@ struct PowerTables {
 
 // One iteration on k vectors per tensor: Gram pass, per-layer factorisation, apply pass.  With
 // `ev` (four events) the boundaries of the three kernels are recorded on the stream.  `descs` (host, n_tensors
-// entries; null: the table t.descs is filled already) travels as kernel arguments.
+// entries) travels as kernel arguments; null: the table t.descs is filled already, or is by a copy enqueued before.
 hipError_t launch_power_iter(const PowerTables& t, const PowerDesc* descs, int k, int latch, hipStream_t s, hipEvent_t* ev);
 
 // The same iteration without a handle and without any allocation: tables and partial sums live in a
