@@ -19,9 +19,12 @@ constexpr int kFinishThreads = 1024;          // workgroup of the per-tensor thr
 constexpr uint32_t kLaunchBoundChunks = 16384;
 // Among them, sets whose tensors have at most this many chunks (4.2 M elements) need no per-layer kernel:
 // every workgroup of the update adds up its tensor's chunk records itself (k_update_local).  The limit bounds
-// what it reads for that, 32 bytes per chunk of the tensor, to half of what it streams: at 1024 chunks per
-// tensor (50 M parameters) the launch's decisions cost 20 us of 110, as much as the kernel they replace and its
-// gap together; at 576 (ResNet-18 set) the step is 4.6 us shorter.
+// what it reads for that, 16 bytes per chunk of the tensor and 16 more on a probed step: 32 KB at 1024 chunks,
+// beside the 80 KB it streams with fp32 storage and momentum, 56 KB with 16 bits and 24 KB without momentum.  At
+// 1024 chunks per tensor (50 M parameters) the launch's decisions cost 20 us of 110, as much as the kernel they
+// replace and its gap together; at 576 (ResNet-18 set) the step is 4.6 us shorter.  Steps of 12 tensors of 1024
+// chunks before this form existed and now (other kernels changed with it): fp32 199 and 178 us, probed 364 and 322;
+// 16 bits without momentum 75 and 68, probed 236 and 220, Fisher 189 and 165.
 constexpr uint32_t kLocalMaxChunks = 1024;
 
 // Radix-select parameters: magnitudes are 31-bit keys (sign bit cleared).
@@ -68,6 +71,17 @@ inline KeyLists key_lists(int64_t numel) {
 // it the slower plain reads cost more than the cached part gains (step without a probe, fp32 gradients, without and with
 // the hint: 100 M parameters 357 and 391 us, 250 M 951 and 979, 500 M 2086 and 2094, 800 M 3409 and 3401, 1073 M 4594
 // and 4560; power iteration at k = 5: 40 M 531 and 552, 120 M 1616 and 1643, 240 M 3262 and 3252).
+// Those are calls repeated on two input sets.  What the caches hold beforehand matters (us, without and with the hint):
+//                                   step 11 M     step 55 M     step 120 M    power 11 M k=5  power 40 M k=5
+//   repeated                        45.6  48.7    200  225      457  487      148  164        522  532
+//   after 1 GiB read by others      49.5  54.0    208  232      459  492      152  167        528  549
+//   inputs written one by one with others' traffic between, as a backward pass leaves them
+//     as many bytes, 64 MB (power)  48.1  51.3    214  232      498  503      169  181        586  605
+//     four times, 256 MB            48.4  51.6    224  233      518  503      184  186        588  610
+//   after 1 GiB written by others   57.8  55.0    244  234      508  496      209  169        617  552
+//   ... and 1 GiB read after it     352   354      518  528      772  786      494  475        875  835
+// The last two lines belong together: keeping the inputs drives the others' dirty lines out, whose writing back
+// the call then pays and the traffic after it saves, all of it after a step, half of it after a power iteration.
 constexpr uint64_t kKeepBytes = 2ull << 30;
 
 enum SelMode : uint32_t {
@@ -209,7 +223,10 @@ struct LayerIn {
   uint32_t applied_steps;
 };
 
-// The plan of a step's threshold selection, laid at the last probed step (a copy of LayerDev's fields).
+// The plan of a step's threshold selection, laid at the last probed step (a copy of LayerDev's fields).  The
+// workgroups of k_update_local read these fields of the live record while one of them writes others: of the
+// functions that run there only select_setup's kOutHist branch and what follows it may write them, in the workgroup
+// that arrives last, when all others have read them.
 struct SelNow {
   uint32_t use_band, band_lo, band_hi, predicted;
   uint32_t win_lo, win_hi, win_shift, win_bins;

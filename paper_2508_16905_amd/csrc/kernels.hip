@@ -20,10 +20,9 @@ __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, 
                                             double& s1, double& s2, uint32_t& bad) {
   const int tid = threadIdx.x;
   float g[kRows][4];
-  // The update reads the gradients again: KEEP leaves them in the caches (55 M parameters, step without a probe:
-  // 228 -> 202 us; 11 M: 49 -> 45; 250 M: 1071 -> 1049).
   // the shift is read in the same batch of loads as the data: one memory latency per chunk, not two
   const float first = load1<GD>(td.grad, base);
+  // the update reads the gradients again: KEEP leaves them in the caches (figures at kKeepBytes)
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
     const int64_t idx = base + r * kRowElems + tid * kVec;

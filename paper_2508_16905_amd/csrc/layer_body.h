@@ -23,7 +23,10 @@ struct LayerSums {
 //   S1 = sum n_i (mean_i - K),  S2 = sum M2_i + n_i (mean_i - K)^2,
 //   mean = K + S1 / n,  M2 = S2 - S1^2 / n     (fp64; fixed order over threads, lanes and wavefronts)
 // -- four operations per record and one division in all, where merging records pairwise takes a division
-// per pair; K is one of the means, so S2 stays within a small factor of M2 times the number of chunks.
+// per pair.  K is one of the means, so S2 is at most about M2 times the number of chunks (chunk 0 far off all the
+// others), and the cancellation can multiply the sums' rounding error, some 1e-15, by that factor: below 1e-9 for the
+// largest tensor (2^19 chunks), where the variance is kept to 6e-8 (fp32).  Replayed for 400 chunks: ordinary data
+// 1e-16 to 1e-15 (pairwise 1e-16), chunk 0 off by 1000 standard deviations 2e-14 to 7e-13.
 struct LayerAcc {  // one thread's part
   double shift, s1, s2;
   EmaTotals ema;

@@ -42,8 +42,8 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return u2f(b << 
 // ---- 4 consecutive elements, index multiple of 4, base 16-byte aligned ------------------------
 // Every tensor is streamed exactly once per kernel, so the vector accesses carry the
 // non-temporal hint (measured on MI355X: read-only streaming 6.5 -> 7.3 TB/s, read-modify-write
-// 5.3 -> 5.7 TB/s), except where a later kernel of the same step reads the array again (KEEP): the hint
-// also keeps the data out of the caches.
+// 5.3 -> 5.7 TB/s), except loads of an array that a later kernel of the same step reads again (KEEP): the
+// hint also keeps the data out of the caches.
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 
@@ -91,13 +91,12 @@ __device__ __forceinline__ float load1(const void* base, int64_t idx) {
   return f16_bits_to_f32(h);
 }
 
-template <int DT, bool KEEP = false>
+template <int DT>
 __device__ __forceinline__ void store4(void* base, int64_t idx, const float v[4]) {
   if constexpr (DT == kFP32) {
     v4f o;
     o.x = v[0]; o.y = v[1]; o.z = v[2]; o.w = v[3];
-    if constexpr (KEEP) *as_global<v4f>(static_cast<float*>(base) + idx) = o;
-    else __builtin_nontemporal_store(o, as_global<v4f>(static_cast<float*>(base) + idx));
+    __builtin_nontemporal_store(o, as_global<v4f>(static_cast<float*>(base) + idx));
   } else {
     uint32_t h[4];
 #pragma unroll
@@ -105,8 +104,7 @@ __device__ __forceinline__ void store4(void* base, int64_t idx, const float v[4]
     v2u o;
     o.x = h[0] | (h[1] << 16);
     o.y = h[2] | (h[3] << 16);
-    if constexpr (KEEP) *as_global<v2u>(static_cast<uint16_t*>(base) + idx) = o;
-    else __builtin_nontemporal_store(o, as_global<v2u>(static_cast<uint16_t*>(base) + idx));
+    __builtin_nontemporal_store(o, as_global<v2u>(static_cast<uint16_t*>(base) + idx));
   }
 }
 

@@ -27,8 +27,7 @@ __device__ __forceinline__ constexpr int tri(int i, int j) { return j * (j + 1) 
 template <int K, bool FULL, bool KEEP>
 __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, int64_t base, double (&g)[K * (K + 1) / 2],
                                            double (&c)[K], double (&d)[K]) {
-  // the products are read again by the apply pass: KEEP leaves them in the caches (iteration of the ResNet-18 set,
-  // k = 5: 160 -> 146 us)
+  // the products are read again by the apply pass: KEEP leaves them in the caches (figures at kKeepBytes)
   // one row at a time: the 2k loads of a row are in flight together, and the accumulators leave
   // room for several wavefronts per SIMD to overlap their loads with the fp64 arithmetic
 #pragma unroll 1

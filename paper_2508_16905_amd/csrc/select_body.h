@@ -161,7 +161,8 @@ __device__ __forceinline__ Window first_window(const SelNow& now, uint32_t maxke
   return Window{hi > span ? hi - span : 0u, kFirstShift, (uint32_t)kHistBins, hi};
 }
 
-// Lays down the selection state of tensor l for the outcome (one thread).
+// Lays down the selection state of tensor l for the outcome (one thread).  Only the kOutHist branch writes fields of
+// the plan (SelNow): in k_update_local the other two run while workgroups of the same tensor still read it.
 __device__ __forceinline__ void select_setup(const TensorDesc& td, LayerDev& ls, GlobalDev* glob, const SelNow& now,
                                              const EmaTotals& e, uint32_t k, int outcome, uint64_t step_id) {
   const uint32_t nonzero = (uint32_t)td.numel - e.zeros;

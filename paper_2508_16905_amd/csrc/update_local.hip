@@ -12,8 +12,9 @@ __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { re
 // Every workgroup of a chunk adds up its tensor's chunk records (at most kLocalMaxChunks x 32 bytes, from
 // the caches) and takes the layer's decisions itself, each the same ones, while the chunk's own data is on
 // the way.  No workgroup waits for another: the fields of the layer's record that the decisions read were
-// copied aside by the statistics kernel and the selection's plan by the curvature kernel, so that the
-// workgroup of chunk 0 and the selection may write the record while the others run.  (An arrival counter per
+// copied aside by the statistics kernel, so that the workgroup of chunk 0 may write the record while the others
+// run; the selection's plan (SelNow) is read from the record, and nothing writes those fields before the last
+// workgroup of a tensor in histogram mode has arrived.  (An arrival counter per
 // tensor instead, with the last workgroup writing, cost one atomic per chunk: with the counters side by side
 // in a cache line 20 ns each, 205 us instead of 35 on the ResNet-18 set.)
 //
@@ -24,7 +25,7 @@ __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { re
 //
 // Measured, per step, against the separate launches: two-layer perceptron (4 tensors, 0.1 M) 13.4 -> 8.8 us,
 // EfficientNet-B0 set 23.4 -> 19.5 (16-bit gradients, no probe) and 65.7 -> 57.1 (probed), ResNet-18 set
-// 54.6 -> 50.0 and 102.4 -> 94.5.
+// 54.6 -> 50.7 and 102.4 -> 94.5.
 template <bool MOM, bool PROBED>
 __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __restrict__ tds,
                                                            const ChunkRef* __restrict__ chunks,
