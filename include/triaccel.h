@@ -181,7 +181,7 @@ typedef struct {
  * Create a handle for n tensors.  `tensors` gives shapes, dtypes and the initial pointers;
  * curv / mom / mask contents are taken as the initial state (normally zero).  `hip_stream` is a
  * hipStream_t (NULL = the default stream).  Allocates the workspace (chunk table, partials, histograms, key
- * lists, per-layer state, eight device copies of the tensor table): a few MB, plus 20 KB per tensor, 40 bytes
+ * lists, per-layer state, eight device copies of the tensor table): a few MB, plus 20 KB per tensor, 48 bytes
  * per 4096 parameters of a tensor and its key lists, 16 bytes per element up to 4 MB a tensor.  In sets with a
  * tensor of more than 524,288 elements, further, scratch for storage sizes that change: 4 bytes for each of the
  * first 262,144 elements of every tensor (65,536 in sets of 16,384 pieces of 4096 elements and more), rounded up

@@ -423,19 +423,15 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   for (int32_t i = 0; i < n; ++i) grad_bytes += (uint64_t)tensors[i].numel * (tensors[i].grad_dtype == TRIACCEL_FP32 ? 4u : 2u);
   T.keep_grads = grad_bytes <= kKeepBytes;
   T.persistent_grid = cus * 8;
-  std::vector<ChunkRef> wg_chunks;  // empty: the order of `chunks`
-  if (local_form(*c) && resize.n_stages == 1) {
-    wg_chunks.reserve(chunks.size());
+  const uint32_t n_wg_chunks = local_form(*c) && resize.n_stages == 1 ? T.total_chunks : 0u;  // else the order of `chunks`
+  if (n_wg_chunks)
     heads_first((uint32_t)n, [&](uint32_t t) { return c->desc[t].n_chunks; },
-                [&](uint32_t t, uint32_t k) { wg_chunks.push_back(ChunkRef{t, k}); });
-  }
-  ChunkRef* wg_chunks_dev = nullptr;
+                [&](uint32_t t, uint32_t k) { chunks.push_back(ChunkRef{t, k}); });
   Workspace ws;
   for (auto& slot : c->tables) ws.add(&slot.dev, (size_t)n);
   ws.add(&T.chunks, chunks.size());
-  ws.add(&wg_chunks_dev, wg_chunks.size());
-  ws.add(&T.partials, chunks.size());
-  ws.add(&T.ema_partials, chunks.size());
+  ws.add(&T.partials, T.total_chunks);
+  ws.add(&T.ema_partials, T.total_chunks);
   ws.add(&T.layers, (size_t)n);
   ws.add(&T.glob, 1);
   ws.add(&T.hist, (size_t)n * kHistBins);
@@ -450,11 +446,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   T.tensors = c->tables[0].dev;
   e = hipMemcpy(T.chunks, chunks.data(), chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
   if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(chunks)"));
-  T.wg_chunks = wg_chunks.empty() ? T.chunks : wg_chunks_dev;
-  if (!wg_chunks.empty()) {
-    e = hipMemcpy(wg_chunks_dev, wg_chunks.data(), wg_chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(workgroup order)"));
-  }
+  T.wg_chunks = n_wg_chunks ? T.chunks + T.total_chunks : T.chunks;
   // shapes and chunk ranges are valid from now on; the pointers arrive with every step
   for (auto& slot : c->tables) {
     e = hipMemcpy(slot.dev, c->desc.data(), (size_t)n * sizeof(TensorDesc), hipMemcpyHostToDevice);

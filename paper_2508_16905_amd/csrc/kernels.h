@@ -9,7 +9,7 @@ namespace triaccel {
 // Device pointers and sizes of a handle's workspace.
 struct DeviceTables {
   TensorDesc* tensors;
-  ChunkRef* chunks;          // tensor by tensor, in order
+  ChunkRef* chunks;          // tensor by tensor, in order; then the order heads_first, in sets that use it
   const ChunkRef* wg_chunks; // chunk of each workgroup of the kernels that have one for every chunk: `chunks`, or heads_first
   StatPartial* partials;     // one record per chunk, in the order of `chunks`
   EmaPartial* ema_partials;  // the same, written by the EMA kernel
