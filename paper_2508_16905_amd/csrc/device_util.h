@@ -30,6 +30,8 @@ namespace triaccel {
 #define TA_OP_MAX(a, b) (max((uint32_t)(a), (uint32_t)(b)))
 __device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1); }
 __device__ __forceinline__ uint32_t first_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 0); }
+// The same value in every lane, in a scalar register from here on.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 // Sum over this lane and the lanes below it; all lanes of the wavefront must be active.
 __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
   TA_DPP_TREE(v, TA_OP_ADD);
@@ -84,6 +86,28 @@ __device__ __forceinline__ uint32_t gather_mask_word(uint32_t nib, int lane) {
   return v;
 }
 
+// A tensor's elements from `base`, W bytes each, and their number as far as a chunk goes.
+template <int W>
+__device__ __forceinline__ const void* chunk_of(const void* tensor, int64_t base) {
+  return static_cast<const char*>(tensor) + base * W;
+}
+template <int W>
+__device__ __forceinline__ void* chunk_of(void* tensor, int64_t base) {
+  return static_cast<char*>(tensor) + base * W;
+}
+static_assert(kRowLanes == kThreads && kRowElems == kRowLanes * kVec, "rows of the accessors");
+__device__ __forceinline__ int32_t chunk_left(int64_t base, int64_t n) { return (int32_t)(n - base < kChunk ? n - base : kChunk); }
+
+// The 16 elements of every lane of the chunk that starts at `chunk`, as they lie in memory, and the seventeenth of
+// the lanes that have one (0 in the others).
+template <int W, bool KEEP = false>
+__device__ __forceinline__ uint32_t load_chunk(const void* chunk, int32_t left, const Tail& t, uint32_t (&w)[kRows][4]) {
+  const Rows rows = rows_of<W>(chunk, left);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) load_words<W, KEEP>(rows, r, threadIdx.x & (kThreads - 1), w[r]);
+  return t.any ? load_tail<W>(chunk, t) : 0u;
+}
+
 // Stores that another workgroup of the same launch will read: at device scope they go through the L2 to the
 // memory side, so that waiting for their acknowledgement (published_before_here) is all the release that is
 // needed -- a release fence would write back all that the L2 holds of the launch's other stores.
@@ -95,20 +119,26 @@ __device__ __forceinline__ void store_word(T* p, T v) {
 // Every thread: its device-scope stores and atomics so far have been performed.
 __device__ __forceinline__ void published_before_here() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Mask words of a chunk from the 16 flags of every lane (bit 4 r + i = element i of row r): lane
-// (8 j + r) of a wavefront writes row r's word j.
-template <bool FULL, bool SHARED = false>
-__device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t base, uint32_t flags) {
+// Flags of a lane's elements: bit 4 r + i = element i of row r, kTailFlag = the seventeenth.
+constexpr uint32_t kTailFlag = 1u << 16;
+
+// Mask words of a chunk from every lane's flags: lane (8 j + r) of a wavefront writes row r's word j.
+template <bool SHARED = false>
+__device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t base, uint32_t flags, const Tail& tail) {
   static_assert(kRows == 4, "one word per row, chosen by two bits of the lane");
   const int tid = threadIdx.x & (kThreads - 1);
   const int lane = tid & (kWave - 1);
   const int sub = tid & 7;
+  if (tail.any) {
+    const uint32_t bits = (uint32_t)__ballot((flags & kTailFlag) != 0u) & 7u;
+    if ((uint32_t)tid == tail.owner) flags |= bits << (4 * tail.row);
+  }
   const uint32_t w0 = gather_mask_word(flags & 15u, lane), w1 = gather_mask_word((flags >> 4) & 15u, lane);
   const uint32_t w2 = gather_mask_word((flags >> 8) & 15u, lane), w3 = gather_mask_word((flags >> 12) & 15u, lane);
   const uint32_t lo = (sub & 1) ? w1 : w0, hi = (sub & 1) ? w3 : w2;
   if (sub < kRows) {
     const int64_t widx = ((base + (int64_t)sub * kRowElems) >> 5) + (tid >> 3);
-    if (FULL || widx < ((td.numel + 31) >> 5)) store_word<SHARED>(td.mask + widx, (sub & 2) ? hi : lo);
+    if (widx < ((td.numel + 31) >> 5)) store_word<SHARED>(td.mask + widx, (sub & 2) ? hi : lo);
   }
 }
 
@@ -132,7 +162,7 @@ __device__ __forceinline__ void reset_cand_counters(uint32_t* counters, uint32_t
 // its keys (at most 8 wavefronts' worth) has a list of full size for each of them and needs no atomic.
 // EfficientNet-B0 set, curvature kernel: 19.4 us with both the other way, 16.0 now.
 template <bool SHARED = false>
-__device__ __forceinline__ void append_candidates(uint32_t flags, const float (&h)[kRows][4], int64_t base,
+__device__ __forceinline__ void append_candidates(uint32_t flags, const uint32_t (&h)[kRows][4], uint32_t ht, const Tail& tail, int64_t base,
                                                   uint32_t chunk_index, uint32_t tensor, const TensorDesc& td,
                                                   Candidate* cands, uint32_t* counters) {
   if (!__any(flags != 0u)) return;  // uniform over the wavefront
@@ -156,23 +186,23 @@ __device__ __forceinline__ void append_candidates(uint32_t flags, const float (&
   Candidate* const own = cands + td.cand_offset + (size_t)list * td.sub_cap + start;
   Candidate* const over = cands + td.cand_offset + (size_t)kCandLists * td.sub_cap + ostart;
   uint32_t before = 0;  // candidates of earlier elements
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool mine = (flags & (1u << (r * 4 + i))) != 0u;
-      const unsigned long long lanes = __ballot(mine);
-      if (mine) {
-        const uint32_t rank = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
-        const int64_t idx = base + r * kRowElems + tid * kVec + i;
-        // one 8-byte store of a Candidate: idx in the low word, key in the high one
-        const uint64_t c = (uint64_t)(f2u(h[r][i]) & 0x7fffffffu) << 32 | (uint32_t)idx;
-        if (rank < fit) store_word<SHARED>(reinterpret_cast<uint64_t*>(own + rank), c);
-        else if (ostart + (rank - fit) < td.cand_cap) store_word<SHARED>(reinterpret_cast<uint64_t*>(over + (rank - fit)), c);
-      }
-      before += (uint32_t)__popcll(lanes);
+  const auto put = [&](bool mine, uint32_t value, uint32_t idx) {
+    const unsigned long long lanes = __ballot(mine);
+    if (mine) {
+      const uint32_t rank = before + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
+      // one 8-byte store of a Candidate: idx in the low word, key in the high one
+      const uint64_t c = (uint64_t)(value & 0x7fffffffu) << 32 | idx;
+      if (rank < fit) store_word<SHARED>(reinterpret_cast<uint64_t*>(own + rank), c);
+      else if (ostart + (rank - fit) < td.cand_cap) store_word<SHARED>(reinterpret_cast<uint64_t*>(over + (rank - fit)), c);
     }
-  }
+    before += (uint32_t)__popcll(lanes);
+  };
+#pragma unroll
+  for (int r = 0; r < kRows; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      put((flags & (1u << (r * 4 + i))) != 0u, h[r][i], (uint32_t)base + r * kRowElems + tid * kVec + i);
+  if (tail.any) put((flags & kTailFlag) != 0u, ht, (uint32_t)base + tail.at);
 }
 
 // Visit every listed candidate of a tensor.  s_counts holds the kCandLists + 1 clamped counts.
@@ -193,20 +223,16 @@ __device__ __forceinline__ void for_each_candidate(const TensorDesc& td, const C
 // listed and their bits are set afterwards by k_select_finish.  Called from k_update and k_mask_pass; SHARED: from
 // k_select_tail, where a workgroup of the same launch resolves the threshold.
 // ---------------------------------------------------------------------------------------------
-template <bool FULL, bool SHARED = false>
+template <bool SHARED = false>
 __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, uint32_t mode, uint32_t theta,
                                            uint32_t rng_lo, uint32_t rng_hi, uint32_t chunk_index,
                                            uint32_t tensor, Candidate* cands, uint32_t* counters) {
-  const int tid = threadIdx.x & (kThreads - 1);
-  float h[kRows][4];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + r * kRowElems + tid * kVec;
-    if (FULL) load4<kFP32>(td.curv, idx, h[r]);
-    else load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, h[r]);
-  }
-  // one rule for both modes: keys >= keep_lo are kept, keys in [list_lo, keep_lo) are listed; the
-  // guarded fill 0 is below both bounds, so it is never kept and never listed
+  uint32_t h[kRows][4];
+  const int32_t left = chunk_left(base, td.numel);
+  const Tail tail = tail_of(left, (uint32_t)threadIdx.x & (kThreads - 1));
+  const uint32_t ht = load_chunk<4>(chunk_of<4>(td.curv, base), left, tail, h);
+  // one rule for both modes: keys >= keep_lo are kept, keys in [list_lo, keep_lo) are listed; what lies past the
+  // end reads as 0, below both bounds, so it is never kept and never listed
   const bool exact = mode == kSelExact;
   const uint32_t keep_lo = max(exact ? theta : rng_hi, 1u);
   const uint32_t list_lo = exact ? keep_lo : min(max(rng_lo, 1u), keep_lo);
@@ -215,14 +241,17 @@ __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, u
   for (int r = 0; r < kRows; ++r) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t key = f2u(h[r][i]) & 0x7fffffffu;
+      const uint32_t key = h[r][i] & 0x7fffffffu;
       kflags |= (key >= keep_lo ? 1u : 0u) << (r * 4 + i);
       cflags |= (key >= list_lo ? 1u : 0u) << (r * 4 + i);
     }
   }
+  const uint32_t tkey = ht & 0x7fffffffu;
+  if (tkey >= keep_lo) kflags |= kTailFlag;
+  if (tkey >= list_lo) cflags |= kTailFlag;
   cflags ^= kflags;  // the kept keys are above list_lo too
-  store_mask_flags<FULL, SHARED>(td, base, kflags);
-  append_candidates<SHARED>(cflags, h, base, chunk_index, tensor, td, cands, counters);
+  store_mask_flags<SHARED>(td, base, kflags, tail);
+  append_candidates<SHARED>(cflags, h, ht, tail, base, chunk_index, tensor, td, cands, counters);
 }
 
 // ---------------------------------------------------------------------------------------------

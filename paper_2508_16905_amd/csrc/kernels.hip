@@ -15,34 +15,39 @@ namespace triaccel {
 // (a sample of the data, so the sums stay small against their cancellation).  Lanes and
 // wavefronts are added in a fixed order; one (mean, M2) partial per chunk.
 // ---------------------------------------------------------------------------------------------
-template <int GD, bool FULL, bool KEEP>
+template <int GD, bool KEEP>
 __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, float inv_scale, double& shift,
                                             double& s1, double& s2, uint32_t& bad) {
-  const int tid = threadIdx.x;
-  float g[kRows][4];
+  uint32_t g[kRows][4];
   // the shift is read in the same batch of loads as the data: one memory latency per chunk, not two
   const float first = load1<GD>(td.grad, base);
   // the update reads the gradients again: KEEP leaves them in the caches (figures at kKeepBytes)
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + r * kRowElems + tid * kVec;
-    if (FULL) load4<GD, KEEP>(td.grad, idx, g[r]);
-    else load4_guard<GD, KEEP>(td.grad, idx, td.numel, 0.0f, g[r]);
-  }
+  const int32_t left = chunk_left(base, td.numel);
+  const Tail tail = tail_of(left, threadIdx.x);
+  const uint32_t gt = load_chunk<kWords<GD>, KEEP>(chunk_of<kWords<GD>>(td.grad, base), left, tail, g);
   shift = (double)(first * inv_scale);
+  const auto add = [&](uint32_t bits, bool inside) {
+    bad |= ((bits & 0x7f800000u) == 0x7f800000u) ? 1u : 0u;
+    double d = (double)(u2f(bits) * inv_scale) - shift;
+    if (!inside) d = 0.0;
+    s1 += d;
+    s2 = fma(d, d, s2);
+  };
+  if (left == kChunk) {
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) {
+    for (int r = 0; r < kRows; ++r) {
+      widen4<GD>(g[r]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t idx = base + r * kRowElems + tid * kVec + i;
-      if (FULL || idx < td.numel) {
-        const float raw = g[r][i];
-        bad |= ((f2u(raw) & 0x7f800000u) == 0x7f800000u) ? 1u : 0u;
-        const double d = (double)(raw * inv_scale) - shift;
-        s1 += d;
-        s2 = fma(d, d, s2);
-      }
+      for (int i = 0; i < 4; ++i) add(g[r][i], true);
     }
+  } else {
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      widen4<GD>(g[r]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) add(g[r][i], r * kRowElems + (int)threadIdx.x * kVec + 4 <= left);
+    }
+    if (tail.any) add(widen1<GD>(gt), tail.mine);
   }
 }
 
@@ -57,22 +62,13 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
   // k_update_local takes the step's decisions from this copy: it writes the layers' records while it runs
   if (inputs && cr.index == 0 && threadIdx.x == 0) inputs[cr.tensor] = layer_in(layers[cr.tensor]);
   const int64_t base = (int64_t)cr.index * kChunk;
-  const bool full = base + kChunk <= td.numel;
   double s1 = 0.0, s2 = 0.0;
   uint32_t bad = 0;
   double shift = 0.0;
-  if (full) {
-    switch (td.grad_dtype) {
-      case kFP32: stats_chunk<kFP32, true, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      case kBF16: stats_chunk<kBF16, true, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      default: stats_chunk<kFP16, true, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-    }
-  } else {
-    switch (td.grad_dtype) {
-      case kFP32: stats_chunk<kFP32, false, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      case kBF16: stats_chunk<kBF16, false, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-      default: stats_chunk<kFP16, false, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-    }
+  switch (td.grad_dtype) {
+    case kFP32: stats_chunk<kFP32, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+    case kBF16: stats_chunk<kBF16, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+    default: stats_chunk<kFP16, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
   }
   s1 = wave_sum_f64(s1);
   s2 = wave_sum_f64(s2);
@@ -122,73 +118,79 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
 // instructions on sets that fit the chip at once (4.0 M parameters: 29.6 us with, 21.2 us
 // without; 11.2 M: 45.2, 35.6 us).  Elements past the tensor's end read as 0, whose sample is 0 and
 // whose key is 0: they only have to be taken off the count of zero keys.
-template <bool FULL, int SRC>
+template <int SRC>
 __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, float inv_scale, float beta_h,
                                           float omb_h, bool first, bool listing, uint32_t list_lo, uint32_t list_hi,
                                           uint32_t chunk_index, uint32_t tensor, Candidate* cands,
                                           uint32_t* counters, uint32_t& above_zeros, uint32_t& maxkey,
                                           uint32_t& listed, uint32_t& nonfin) {
-  const int tid = threadIdx.x;
-  float z[kRows][4], hz[SRC < 0 ? kRows : 1][4], h[kRows][4];
+  const uint32_t tid = threadIdx.x;
+  constexpr int ZW = SRC < 0 ? 4 : kWords<SRC>;
+  const void* const zp = chunk_of<ZW>(SRC < 0 ? static_cast<const void*>(td.z) : td.grad, base);
+  const void* const hzp = chunk_of<4>(static_cast<const void*>(td.hz), base);
+  void* const hp = chunk_of<4>(static_cast<void*>(td.curv), base);
+  const int32_t left = chunk_left(base, td.numel);
+  const Rows zrows = rows_of<ZW>(zp, left), hzrows = rows_of<4>(hzp, left), hrows = rows_of<4>(hp, left);
+  uint32_t z[kRows][4], hz[SRC < 0 ? kRows : 1][4], h[kRows][4];
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + r * kRowElems + tid * kVec;
-    if constexpr (SRC < 0) {
-      if (FULL) {
-        load4<kFP32>(td.z, idx, z[r]);
-        load4<kFP32>(td.hz, idx, hz[r]);
-      } else {
-        load4_guard<kFP32>(td.z, idx, td.numel, 0.0f, z[r]);
-        load4_guard<kFP32>(td.hz, idx, td.numel, 0.0f, hz[r]);
-      }
-    } else {
-      // x = g / S in both factors: u = x * x
-      if (FULL) load4<SRC>(td.grad, idx, z[r]);
-      else load4_guard<SRC>(td.grad, idx, td.numel, 0.0f, z[r]);
-    }
-    if (FULL) load4<kFP32>(td.curv, idx, h[r]);
-    else load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, h[r]);
+    load_words<ZW>(zrows, r, tid, z[r]);
+    if constexpr (SRC < 0) load_words<4>(hzrows, r, tid, hz[r]);
+    load_words<4>(hrows, r, tid, h[r]);
+  }
+  const Tail tail = tail_of(left, tid);
+  uint32_t zt = 0, hzt = 0, ht = 0;
+  if (tail.any) {
+    zt = load_tail<ZW>(zp, tail);
+    if constexpr (SRC < 0) hzt = load_tail<4>(hzp, tail);
+    ht = load_tail<4>(hp, tail);
   }
   __builtin_amdgcn_sched_barrier(0);  // all loads first
   uint32_t hflags = 0, lflags = 0, zeros = 0;  // keys >= list_hi / >= list_lo (bit 4 r + i), zero keys
   const uint32_t first_mask = first ? ~0u : 0u;
+  const auto element = [&](uint32_t zbits, uint32_t hzbits, uint32_t& hbits, uint32_t flag) {
+    float u;
+    if constexpr (SRC < 0) {
+      u = u2f(zbits) * u2f(hzbits);
+      u = u * inv_scale;
+    } else {
+      // x = g / S in both factors: u = x * x
+      const float x = u2f(zbits) * inv_scale;
+      u = x * x;
+    }
+    const uint32_t bad = (f2u(u) & 0x7f800000u) == 0x7f800000u ? ~0u : 0u;
+    nonfin |= bad;
+    const float p = omb_h * u;
+    const uint32_t next = f2u(fmaf(beta_h, u2f(hbits), p));
+    // bits: u on the first probe, the average after it, the old value where the sample is not finite
+    uint32_t bits = (f2u(u) & first_mask) | (next & ~first_mask);
+    bits = (hbits & bad) | (bits & ~bad);
+    hbits = bits;
+    const uint32_t key = bits & 0x7fffffffu;
+    maxkey = max(maxkey, key);
+    zeros += key == 0u ? 1u : 0u;
+    hflags |= key >= list_hi ? flag : 0u;
+    lflags |= key >= list_lo ? flag : 0u;
+  };
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + r * kRowElems + tid * kVec;
+    if constexpr (SRC >= 0) widen4<SRC>(z[r]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float u;
-      if constexpr (SRC < 0) {
-        u = z[r][i] * hz[r][i];
-        u = u * inv_scale;
-      } else {
-        const float x = z[r][i] * inv_scale;
-        u = x * x;
-      }
-      const uint32_t bad = (f2u(u) & 0x7f800000u) == 0x7f800000u ? ~0u : 0u;
-      nonfin |= bad;
-      const float p = omb_h * u;
-      const uint32_t next = f2u(fmaf(beta_h, h[r][i], p));
-      // bits: u on the first probe, the average after it, the old value where the sample is not finite
-      uint32_t bits = (f2u(u) & first_mask) | (next & ~first_mask);
-      bits = (f2u(h[r][i]) & bad) | (bits & ~bad);
-      h[r][i] = u2f(bits);
-      const uint32_t key = bits & 0x7fffffffu;
-      maxkey = max(maxkey, key);
-      zeros += key == 0u ? 1u : 0u;
-      hflags |= (key >= list_hi ? 1u : 0u) << (r * 4 + i);
-      lflags |= (key >= list_lo ? 1u : 0u) << (r * 4 + i);
-    }
-    if (FULL) store4<kFP32>(td.curv, idx, h[r]);
-    else store4_guard<kFP32>(td.curv, idx, td.numel, h[r]);
+    for (int i = 0; i < 4; ++i) element(z[r][i], SRC < 0 ? hz[r][i] : 0u, h[r][i], 1u << (r * 4 + i));
+    store_words<4>(hrows, r, tid, h[r]);
+  }
+  if (tail.any) {
+    // lanes without a seventeenth element read 0 for it, like what lies past the end
+    element(SRC < 0 ? zt : widen1<SRC < 0 ? kFP32 : SRC>(zt), hzt, ht, kTailFlag);
+    store_tail<kFP32>(hp, tail, ht);
   }
   // zero keys in the high half, keys above the band in the low half
   above_zeros = (zeros << 16) | (uint32_t)__popc(hflags);
   const uint32_t cflags = lflags ^ hflags;  // a key at or above list_hi is above list_lo too
   listed = (uint32_t)__popc(cflags);
   if (listing) {
-    store_mask_flags<FULL>(td, base, hflags);
-    append_candidates(cflags, h, base, chunk_index, tensor, td, cands, counters);
+    store_mask_flags(td, base, hflags, tail);
+    append_candidates(cflags, h, ht, tail, base, chunk_index, tensor, td, cands, counters);
   }
 }
 
@@ -218,27 +220,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const uint32_t list_hi = list_all || !listing ? 0x80000000u : band_hi;
   const int64_t base = (int64_t)cr.index * kChunk;
   uint32_t above_zeros = 0, maxkey = 0, listed = 0, nonfin = 0;
-#define TA_EMA(FULL_, SRC_)                                                                                   \
-  ema_chunk<FULL_, SRC_>(td, base, sc.inv_scale, beta_h, omb_h, first, listing, list_lo, list_hi, cr.index,   \
+#define TA_EMA(SRC_)                                                                                   \
+  ema_chunk<SRC_>(td, base, sc.inv_scale, beta_h, omb_h, first, listing, list_lo, list_hi, cr.index,   \
                          cr.tensor, cands, counters, above_zeros, maxkey, listed, nonfin)
-  const bool full = base + kChunk <= td.numel;
   if constexpr (!FISHER) {
-    if (full) TA_EMA(true, -1);
-    else TA_EMA(false, -1);
+    TA_EMA(-1);
   } else {
     switch (td.grad_dtype) {
-      case kFP32:
-        if (full) TA_EMA(true, kFP32);
-        else TA_EMA(false, kFP32);
-        break;
-      case kBF16:
-        if (full) TA_EMA(true, kBF16);
-        else TA_EMA(false, kBF16);
-        break;
-      default:
-        if (full) TA_EMA(true, kFP16);
-        else TA_EMA(false, kFP16);
-        break;
+      case kFP32: TA_EMA(kFP32); break;
+      case kBF16: TA_EMA(kBF16); break;
+      default: TA_EMA(kFP16); break;
     }
   }
 #undef TA_EMA
@@ -266,8 +257,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
       nf |= s_red[3][w];
     }
     // elements past the end of the tensor were counted as zero keys
-    const int64_t left = td.numel - base;
-    const uint32_t past = left < kChunk ? (uint32_t)(kChunk - left) : 0u;
+    // (the seventeenth elements are a wavefront's, of which left % 4 exist)
+    const uint32_t left = (uint32_t)chunk_left(base, td.numel), rest = left & 3u;
+    const uint32_t past = kChunk - (left - rest) + (rest ? kWave - rest : 0u);
     ema_partials[td.first_chunk + cr.index] = EmaPartial{az - (past << 16), mk, ln, nf};
   }
 }
@@ -350,8 +342,7 @@ __global__ __launch_bounds__(kThreads) void k_hist_pass(const TensorDesc* __rest
       }
     }
     const int64_t base = (int64_t)chunks[c].index * kChunk;
-    if (base + kChunk <= td.numel) hist_chunk<true>(td, base, w, s_hist, count_above, above);
-    else hist_chunk<false>(td, base, w, s_hist, count_above, above);
+    hist_chunk(td, base, w, s_hist, count_above, above);
     ++mine;
     ++c;
   }

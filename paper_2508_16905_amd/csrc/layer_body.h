@@ -64,8 +64,19 @@ __device__ __forceinline__ LayerAcc layer_accumulate(const TensorDesc& td, const
   return a;
 }
 
-// The same value in every lane, in a scalar register from here on.
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+// The curvature totals of the wavefronts' sums that layer_reduce left in shared memory (after its barrier).
+__device__ __forceinline__ EmaTotals layer_ema(const LayerShared& sh) {
+  EmaTotals e{0, 0, 0, 0, 0};
+#pragma unroll
+  for (int w = 0; w < kThreads / kWave; ++w) {
+    e.above += sh.red[0][w];
+    e.zeros += sh.red[1][w];
+    e.maxkey = max(e.maxkey, sh.red[2][w]);
+    e.listed += sh.red[3][w];
+    e.nonfin |= sh.red[4][w];
+  }
+  return EmaTotals{uniform(e.above), uniform(e.zeros), uniform(e.maxkey), uniform(e.listed), uniform(e.nonfin)};
+}
 
 template <bool PROBED>
 __device__ __forceinline__ LayerSums layer_reduce(const LayerAcc& a, int64_t numel, LayerShared& sh) {
@@ -93,20 +104,13 @@ __device__ __forceinline__ LayerSums layer_reduce(const LayerAcc& a, int64_t num
   }
   __syncthreads();
   s1 = s2 = 0.0;
-  e = EmaTotals{0, 0, 0, 0, 0};
 #pragma unroll
   for (int w = 0; w < kThreads / kWave; ++w) {
     s1 += sh.s1[w];
     s2 += sh.s2[w];
-    if constexpr (PROBED) {
-      e.above += sh.red[0][w];
-      e.zeros += sh.red[1][w];
-      e.maxkey = max(e.maxkey, sh.red[2][w]);
-      e.listed += sh.red[3][w];
-      e.nonfin |= sh.red[4][w];
-    }
   }
-  e = EmaTotals{uniform(e.above), uniform(e.zeros), uniform(e.maxkey), uniform(e.listed), uniform(e.nonfin)};
+  if constexpr (PROBED) e = layer_ema(sh);
+  else e = EmaTotals{0, 0, 0, 0, 0};
   const double n = (double)numel;
   const double m2 = s2 - s1 * s1 / n;
   // only a negative rounding error is cut off: an unscaled gradient that overflowed leaves NaN here, and the

@@ -32,30 +32,50 @@ __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, i
   // room for several wavefronts per SIMD to overlap their loads with the fp64 arithmetic
 #pragma unroll 1
   for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + (int64_t)r * kRowElems + (int64_t)threadIdx.x * kVec;
-    float u[K][4], w[K][4];
+    const int64_t at = base + (int64_t)r * kRowElems;
+    const int32_t left = FULL ? kRowElems : chunk_left(at, numel);
+    if (!FULL && left <= 0) break;
+    const float* const up = pd.u + at;
+    const float* const wp = pd.hu + at;
+    uint32_t u[K][4], w[K][4];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      if constexpr (FULL) {
-        load4<kFP32>(pd.u + (int64_t)j * pd.stride, idx, u[j]);
-        load4<kFP32, KEEP>(pd.hu + (int64_t)j * pd.stride, idx, w[j]);
-      } else {
-        load4_guard<kFP32>(pd.u + (int64_t)j * pd.stride, idx, numel, 0.0f, u[j]);
-        load4_guard<kFP32, KEEP>(pd.hu + (int64_t)j * pd.stride, idx, numel, 0.0f, w[j]);
-      }
+      load_words<4>(rows_of<4>(up + (int64_t)j * pd.stride, left), 0, threadIdx.x, u[j]);
+      load_words<4, KEEP>(rows_of<4>(wp + (int64_t)j * pd.stride, left), 0, threadIdx.x, w[j]);
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    const auto add = [&](const uint32_t (&ub)[K], const uint32_t (&wb)[K]) {
 #pragma unroll
       for (int j = 0; j < K; ++j) {
-        const double wj = (double)w[j][e], uj = (double)u[j][e];
+        const double wj = (double)u2f(wb[j]), uj = (double)u2f(ub[j]);
         c[j] = fma(uj, wj, c[j]);
         d[j] = fma(uj, uj, d[j]);
 #pragma unroll
-        for (int i = 0; i <= j; ++i) g[tri(i, j)] = fma((double)w[i][e], wj, g[tri(i, j)]);
+        for (int i = 0; i <= j; ++i) g[tri(i, j)] = fma((double)u2f(wb[i]), wj, g[tri(i, j)]);
       }
+    };
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint32_t ub[K], wb[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        ub[j] = u[j][e];
+        wb[j] = w[j][e];
+      }
+      add(ub, wb);
       // one element's conversions to double at a time: those of all four took 80 registers more
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!FULL) {
+      const Tail tail = tail_of(left, threadIdx.x);
+      if (tail.any && left < kRowElems) {
+        uint32_t ub[K], wb[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+          ub[j] = load_tail<4>(up + (int64_t)j * pd.stride, tail);
+          wb[j] = load_tail<4>(wp + (int64_t)j * pd.stride, tail);
+        }
+        add(ub, wb);
+      }
     }
   }
 }
@@ -197,26 +217,39 @@ __device__ __forceinline__ void apply_chunk(const PowerDesc& pd, int64_t numel, 
                                             const double (&t)[K * (K + 1) / 2]) {
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + (int64_t)r * kRowElems + (int64_t)threadIdx.x * kVec;
-    if (!FULL && idx >= numel) continue;
-    float w[K][4];
+    const int64_t at = base + (int64_t)r * kRowElems;
+    const int32_t left = FULL ? kRowElems : chunk_left(at, numel);
+    if (!FULL && left <= 0) break;
+    const float* const wp = pd.hu + at;
+    uint32_t w[K][4];
+#pragma unroll
+    for (int j = 0; j < K; ++j) load_words<4>(rows_of<4>(wp + (int64_t)j * pd.stride, left), 0, threadIdx.x, w[j]);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      if constexpr (FULL) load4<kFP32>(pd.hu + (int64_t)j * pd.stride, idx, w[j]);
-      else load4_guard<kFP32>(pd.hu + (int64_t)j * pd.stride, idx, numel, 0.0f, w[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      float q[4];
+      uint32_t q[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         double acc = 0.0;
 #pragma unroll
-        for (int i = 0; i <= j; ++i) acc = fma(t[tri(i, j)], (double)w[i][e], acc);
-        q[e] = (float)acc;
+        for (int i = 0; i <= j; ++i) acc = fma(t[tri(i, j)], (double)u2f(w[i][e]), acc);
+        q[e] = f2u((float)acc);
       }
-      if constexpr (FULL) store4<kFP32>(pd.u + (int64_t)j * pd.stride, idx, q);
-      else store4_guard<kFP32>(pd.u + (int64_t)j * pd.stride, idx, numel, q);
+      store_words<4>(rows_of<4>(pd.u + at + (int64_t)j * pd.stride, left), 0, threadIdx.x, q);
+    }
+    if constexpr (!FULL) {
+      const Tail tail = tail_of(left, threadIdx.x);
+      if (tail.any && left < kRowElems) {
+        double wt[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) wt[j] = (double)u2f(load_tail<4>(wp + (int64_t)j * pd.stride, tail));
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+          double acc = 0.0;
+#pragma unroll
+          for (int i = 0; i <= j; ++i) acc = fma(t[tri(i, j)], wt[i], acc);
+          store_tail<kFP32>(pd.u + at + (int64_t)j * pd.stride, tail, f2u((float)acc));
+        }
+      }
     }
   }
 }

@@ -42,22 +42,20 @@ template <bool ELEM, bool MOM, int GROUPS = 1>
 __device__ __forceinline__ void resize_item(const TensorDesc& td, int pd, int nd, const StepSize& ss, const ResizePlan& plan,
                                             char* scratch, uint32_t launch, uint32_t r, const StepScalars& sc, float wd,
                                             float mu) {
-  const int tid = (int)(threadIdx.x & (kThreads - 1));
-  const uint32_t group = threadIdx.x / kThreads;
+  const uint32_t tid = threadIdx.x & (kThreads - 1);
+  const uint32_t group = uniform(threadIdx.x / kThreads);
   const bool narrowing = elem_size(nd) < elem_size(pd);
   if (plan.n_stages == 1) {
     if (r != 0 || launch != 0) return;
     resize_walk_top(plan, td.n_chunks, narrowing, [&](uint32_t c) {
-      ChunkRegs regs;
-      update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
-      __syncthreads();  // chunk 0 overwrites itself; a later chunk overwrites what an earlier one loaded
-      update_store_any<MOM>(td, nd, (int64_t)c * kChunk, tid, regs);
+      // chunk 0 overwrites itself; a later chunk overwrites what an earlier one loaded
+      update_any<ELEM, MOM, true>(td, pd, nd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, [] { return true; });
     });
     return;
   }
   const uint32_t stage = resize_stage_of_launch(plan, launch, narrowing);
   // in place for the subtrees, into the scratch area for a chunk of stage 0
-  TensorDesc to = td;
+  void* to = td.param;
   uint32_t sub = r - plan.top;
   if (r < plan.top) {
     if (r >= td.n_chunks) return;
@@ -65,15 +63,13 @@ __device__ __forceinline__ void resize_item(const TensorDesc& td, int pd, int nd
       if (launch == resize_copy_launch(plan, narrowing)) resize_copy(td, resize_scratch(td, scratch, r), elem_size(nd), r);
       return;
     }
-    to.param = resize_scratch(td, scratch, r) - (int64_t)r * kChunk * elem_size(nd);
+    to = resize_scratch(td, scratch, r) - (int64_t)r * kChunk * elem_size(nd);
   } else {
     if (stage == 0 || sub >= resize_stage_roots(plan, stage) || plan.root[stage] + sub >= td.n_chunks) return;
   }
   const auto chunk = [&](uint32_t c) {
     if (GROUPS > 1 && c % GROUPS != group) return;
-    ChunkRegs regs;
-    update_load_any<ELEM, MOM>(td, pd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, regs);
-    update_store_any<MOM>(to, nd, (int64_t)c * kChunk, tid, regs);
+    update_any<ELEM, MOM>(td, pd, nd, (int64_t)c * kChunk, sc.inv_scale, wd, mu, ss, tid, [] { return true; }, to);
   };
   // a chunk of stage 0 is a walk of one level and one chunk
   if (r < plan.top) chunk(r);

@@ -36,28 +36,24 @@ __device__ __forceinline__ void flush_hist(uint32_t* s_hist, uint32_t bins, uint
   __syncthreads();
 }
 
-template <bool FULL>
 __device__ __forceinline__ void hist_chunk(const TensorDesc& td, int64_t base, const Window& w, uint32_t* s_hist,
                                            bool count_above, uint32_t& above) {
-  const int tid = threadIdx.x;
-  float h[kRows][4];
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t idx = base + r * kRowElems + tid * kVec;
-    if (FULL) load4<kFP32>(td.curv, idx, h[r]);
-    else load4_guard<kFP32>(td.curv, idx, td.numel, 0.0f, h[r]);
-  }
-#pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t key = f2u(h[r][i]) & 0x7fffffffu;  // guarded fill 0 is never counted
-      if (key != 0u && key >= w.lo) {
-        if (key < w.hi) atomicAdd(&s_hist[(key - w.lo) >> w.shift], 1u);
-        else if (count_above) ++above;
-      }
+  uint32_t h[kRows][4];
+  const int32_t left = chunk_left(base, td.numel);
+  const Tail tail = tail_of(left, threadIdx.x);
+  const uint32_t ht = load_chunk<4>(chunk_of<4>(td.curv, base), left, tail, h);
+  const auto count = [&](uint32_t bits) {
+    const uint32_t key = bits & 0x7fffffffu;  // what lies past the end reads as 0 and is never counted
+    if (key != 0u && key >= w.lo) {
+      if (key < w.hi) atomicAdd(&s_hist[(key - w.lo) >> w.shift], 1u);
+      else if (count_above) ++above;
     }
-  }
+  };
+#pragma unroll
+  for (int r = 0; r < kRows; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) count(h[r][i]);
+  if (tail.any) count(ht);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -319,8 +315,7 @@ __device__ __forceinline__ void select_serial(uint32_t l, const TensorDesc& td, 
     uint32_t unused = 0;
     for (uint32_t q = 0; q < td.n_chunks; ++q) {
       const int64_t b2 = (int64_t)q * kChunk;
-      if (b2 + kChunk <= td.numel) hist_chunk<true>(td, b2, w2, s_hist, false, unused);
-      else hist_chunk<false>(td, b2, w2, s_hist, false, unused);
+      hist_chunk(td, b2, w2, s_hist, false, unused);
     }
     __syncthreads();
     select_scan(l, td, ls, glob, hist, step_id, s_hist, s_part, s_out, false);

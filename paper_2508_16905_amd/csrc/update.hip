@@ -25,10 +25,7 @@ __global__ __launch_bounds__(kThreads) void k_mask_pass(const TensorDesc* __rest
     const uint32_t mode = ls.mode;
     if (!td.has_probe || ls.mask_done || mode == kSelHist) continue;
     const int64_t base = (int64_t)cr.index * kChunk;
-    if (base + kChunk <= td.numel)
-      mask_chunk<true>(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
-    else
-      mask_chunk<false>(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
+    mask_chunk(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
   }
 }
 
@@ -76,14 +73,11 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
   if (skip_epoch == sc.step_id) return;
   const int64_t base = (int64_t)cr.index * kChunk;
   const StepSize ss{-eta, sc.lr, alpha, theta_key};
-  if (elem_size(pd) == elem_size(nd)) update_any<ELEM, MOM>(td, pd, nd, base, sc.inv_scale, wd, mu, ss, (int)threadIdx.x);
+  if (elem_size(pd) == elem_size(nd)) update_any<ELEM, MOM>(td, pd, nd, base, sc.inv_scale, wd, mu, ss, threadIdx.x, [] { return true; });
   if constexpr (ELEM) return;
   // kSelHist cannot remain after the last scan; never write a mask from a stale range
   if (td.has_probe && !mask_done && mode != kSelHist) {
-    if (base + kChunk <= td.numel)
-      mask_chunk<true>(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
-    else
-      mask_chunk<false>(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
+    mask_chunk(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
   }
 }
 

@@ -61,27 +61,31 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   const bool probed = PROBED && td.has_probe != 0;
   const LayerAcc acc = layer_accumulate<PROBED>(td, partials, ema_partials, probed);
   // The chunk's own loads are under way while the sums are reduced and the decisions taken (2-3 % of a step from
-  // 11 M to 30 M parameters against loading after them, at 4 wavefronts per SIMD instead of 7).  They are of no use
+  // 11 M to 30 M parameters against loading after them, at 4 wavefronts per SIMD instead of 7; held
+  // down to 5 by the compiler nothing gains and a step in which 50 M parameters change size takes 1 % longer).  They are of no use
   // if the layer changes its storage size (50 M parameters all changing: 312 us a step with them, 238 without);
   // a layer that did so at its last step, or has its first, is taken to be about to do it.
   const bool early = in.applied_steps != 0 && elem_size(in.code) == elem_size(in.prev_code);
-  ChunkRegs regs;
-  CurvRegs unused;
-  if (early) update_fetch_any<false, MOM>(td, in.code, base, (int)threadIdx.x, regs, unused);
-  const LayerSums sums = layer_reduce<PROBED>(acc, td.numel, sh_layer);
-  const LayerOut o = layer_decide(in, sums, probed, sc.lr, hp);
-  if (threadIdx.x == 0) s_decision = o;  // for this thread alone, below
-  const int pd = in.code, nd = (int)uniform((uint32_t)o.code);
-  const StepSize ss{-u2f(uniform(f2u(o.eta))), sc.lr, hp.alpha, 0u};
-  if (elem_size(pd) == elem_size(nd)) {
-    if (!early) update_fetch_any<false, MOM>(td, pd, base, (int)threadIdx.x, regs, unused);
-    update_math<MOM, false>(sc.inv_scale, hp.weight_decay, hp.momentum, ss, regs, unused);
-    update_store_any<MOM>(td, nd, base, (int)threadIdx.x, regs);
-  } else {
-    // launch 0 of the in-place resize: slot r of the tensor is the workgroup of its chunk r
-    resize_item<false, MOM>(td, pd, nd, ss, plan, scratch, 0u, cr.index, sc, hp.weight_decay, hp.momentum);
-  }
-  const EmaTotals ema = sums.ema;
+  const int pd = in.code;
+  int nd;
+  StepSize ss;
+  const auto decide = [&]() {
+    const LayerSums sums = layer_reduce<PROBED>(acc, td.numel, sh_layer);
+    const LayerOut o = layer_decide(in, sums, probed, sc.lr, hp);
+    if (threadIdx.x == 0) s_decision = o;  // for this thread alone, below
+    nd = (int)uniform((uint32_t)o.code);
+    ss = StepSize{-u2f(uniform(f2u(o.eta))), sc.lr, hp.alpha, 0u};
+    return elem_size(pd) == elem_size(nd);
+  };
+  bool in_place = early || decide();
+  if (in_place)
+    in_place = update_any<false, MOM>(td, pd, nd, base, sc.inv_scale, hp.weight_decay, hp.momentum, ss, threadIdx.x,
+                                      [&]() { return early ? decide() : true; });
+  // launch 0 of the in-place resize: slot r of the tensor is the workgroup of its chunk r
+  if (!in_place) resize_item<false, MOM>(td, pd, nd, ss, plan, scratch, 0u, cr.index, sc, hp.weight_decay, hp.momentum);
+  // read again from shared memory: kept, they went to memory and back for want of registers
+  EmaTotals ema{0, 0, 0, 0, 0};
+  if constexpr (PROBED) ema = layer_ema(sh_layer);
   uint32_t k = 0;
   int outcome = kOutListed;
   if constexpr (PROBED) {
@@ -94,8 +98,7 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
         for (int b = threadIdx.x; b < kHistBins; b += kThreads) sh.hist[b] = 0;
         __syncthreads();
         uint32_t above = 0;
-        if (base + kChunk <= td.numel) hist_chunk<true>(td, base, w, sh.hist, now.predicted != 0, above);
-        else hist_chunk<false>(td, base, w, sh.hist, now.predicted != 0, above);
+        hist_chunk(td, base, w, sh.hist, now.predicted != 0, above);
         flush_hist(sh.hist, w.bins, hist + (size_t)cr.tensor * kHistBins);
         above = wave_sum(above);
         if ((threadIdx.x & (kWave - 1)) == 0 && above) atomicAdd(&ls.acc_above, above);
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
   const uint32_t part = blockIdx.x - n_tensors, parts = mask_wgs;
   const uint32_t per = (total_chunks + parts - 1) / parts;
   const uint32_t c1 = min((part + 1) * per, total_chunks);
-  const uint32_t group = threadIdx.x / kThreads;
+  const uint32_t group = uniform(threadIdx.x / kThreads);
   uint32_t c = min(part * per, total_chunks);
   while (c < c1) {
     const uint32_t l = chunks[c].tensor;
@@ -206,8 +209,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
     for (uint32_t q = c + group; q < end; q += kFinishThreads / kThreads) {
       const uint32_t index = q - td.first_chunk;
       const int64_t base = (int64_t)index * kChunk;
-      if (base + kChunk <= td.numel) mask_chunk<true, true>(td, base, mode, theta, rng_lo, rng_hi, index, l, cands, counters);
-      else mask_chunk<false, true>(td, base, mode, theta, rng_lo, rng_hi, index, l, cands, counters);
+      mask_chunk<true>(td, base, mode, theta, rng_lo, rng_hi, index, l, cands, counters);
     }
     c = end;
     published_before_here();  // mask words and listed keys are complete before the arrival is counted

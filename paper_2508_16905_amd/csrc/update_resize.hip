@@ -27,22 +27,19 @@ template <int ND>
 __global__ __launch_bounds__(kThreads) void k_cast(const float* __restrict__ src, void* dst, int64_t n) {
   // same shape as the step kernels: one workgroup per chunk, all loads of the chunk before its stores
   const int64_t base = (int64_t)blockIdx.x * kChunk;
-  float v[kRows][4];
-  if (base + kChunk <= n) {
+  const int32_t left = chunk_left(base, n);
+  constexpr int W = kWords<ND>;
+  uint32_t w[kRows][4];
+  const Tail tail = tail_of(left, threadIdx.x);
+  const uint32_t wt = load_chunk<4>(src + base, left, tail, w);
+  void* const to = chunk_of<W>(dst, base);
+  const Rows rows = rows_of<W>(to, left);
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) load4<kFP32>(src, base + r * kRowElems + (int64_t)threadIdx.x * kVec, v[r]);
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) store4<ND>(dst, base + r * kRowElems + (int64_t)threadIdx.x * kVec, v[r]);
-  } else {
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const int64_t idx = base + r * kRowElems + (int64_t)threadIdx.x * kVec;
-      if (idx < n) {
-        load4_guard<kFP32>(src, idx, n, 0.0f, v[r]);
-        store4_guard<ND>(dst, idx, n, v[r]);
-      }
-    }
+  for (int r = 0; r < kRows; ++r) {
+    narrow4<ND>(w[r]);
+    store_words<W>(rows, r, threadIdx.x, w[r]);
   }
+  if (tail.any) store_tail<ND>(to, tail, wt);
 }
 
 hipError_t launch_update_resize(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha,
