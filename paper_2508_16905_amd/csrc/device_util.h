@@ -32,6 +32,11 @@ __device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__b
 __device__ __forceinline__ uint32_t first_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 0); }
 // The same value in every lane, in a scalar register from here on.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+template <typename T>
+__device__ __forceinline__ T* uniform(T* p) {
+  const uint64_t a = (uint64_t)p;
+  return (T*)((uint64_t)uniform((uint32_t)(a >> 32)) << 32 | uniform((uint32_t)a));
+}
 // Sum over this lane and the lanes below it; all lanes of the wavefront must be active.
 __device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
   TA_DPP_TREE(v, TA_OP_ADD);

@@ -116,6 +116,25 @@ __device__ __forceinline__ Tail tail_of(int32_t left, uint32_t tid) {
   return Tail{any, any && lane < ((uint32_t)left & 3u), whole + lane, owner, whole / (kRowLanes * 4)};
 }
 // Its words: fp32, or a 16-bit element in the low half.  0 in the other lanes.
+// The same for fp32 rows at plain addresses, for kernels that read so many arrays that their descriptors would not fit
+// the scalar registers; `left`: elements from the row's first one to the end (a full row if FULL).
+template <bool FULL, bool KEEP = false>
+__device__ __forceinline__ void load_row4(const float* row, uint32_t tid, int32_t left, uint32_t (&out)[4]) {
+  v4u v{0, 0, 0, 0};
+  if (FULL || (int32_t)(tid * 4) + 4 <= left) {
+    const auto p = (const TA_GLOBAL v4u*)(as_global<char>(row) + tid * 16u);
+    v = KEEP ? *p : __builtin_nontemporal_load(p);
+  }
+  out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+}
+template <bool FULL>
+__device__ __forceinline__ void store_row4(float* row, uint32_t tid, int32_t left, const uint32_t (&w)[4]) {
+  if (!FULL && (int32_t)(tid * 4) + 4 > left) return;
+  v4u v;
+  v.x = w[0]; v.y = w[1]; v.z = w[2]; v.w = w[3];
+  __builtin_nontemporal_store(v, (TA_GLOBAL v4u*)(as_global<char>(row) + tid * 16u));
+}
+
 template <int W>
 __device__ __forceinline__ uint32_t load_tail(const void* chunk, const Tail& t) {
   uint32_t v = 0;

@@ -40,8 +40,8 @@ __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, i
     uint32_t u[K][4], w[K][4];
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      load_words<4>(rows_of<4>(up + (int64_t)j * pd.stride, left), 0, threadIdx.x, u[j]);
-      load_words<4, KEEP>(rows_of<4>(wp + (int64_t)j * pd.stride, left), 0, threadIdx.x, w[j]);
+      load_row4<FULL>(up + (int64_t)j * pd.stride, threadIdx.x, left, u[j]);
+      load_row4<FULL, KEEP>(wp + (int64_t)j * pd.stride, threadIdx.x, left, w[j]);
     }
     const auto add = [&](const uint32_t (&ub)[K], const uint32_t (&wb)[K]) {
 #pragma unroll
@@ -223,7 +223,7 @@ __device__ __forceinline__ void apply_chunk(const PowerDesc& pd, int64_t numel, 
     const float* const wp = pd.hu + at;
     uint32_t w[K][4];
 #pragma unroll
-    for (int j = 0; j < K; ++j) load_words<4>(rows_of<4>(wp + (int64_t)j * pd.stride, left), 0, threadIdx.x, w[j]);
+    for (int j = 0; j < K; ++j) load_row4<FULL>(wp + (int64_t)j * pd.stride, threadIdx.x, left, w[j]);
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       uint32_t q[4];
@@ -234,7 +234,7 @@ __device__ __forceinline__ void apply_chunk(const PowerDesc& pd, int64_t numel, 
         for (int i = 0; i <= j; ++i) acc = fma(t[tri(i, j)], (double)u2f(w[i][e]), acc);
         q[e] = f2u((float)acc);
       }
-      store_words<4>(rows_of<4>(pd.u + at + (int64_t)j * pd.stride, left), 0, threadIdx.x, q);
+      store_row4<FULL>(pd.u + at + (int64_t)j * pd.stride, threadIdx.x, left, q);
     }
     if constexpr (!FULL) {
       const Tail tail = tail_of(left, threadIdx.x);
