@@ -212,7 +212,7 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
   TA_HIP(launch_grad_stats(T, sa, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
-  if (any_probe) TA_HIP(launch_curv_ema(T, sa, beta_h, omb_h, fisher ? 1 : 0, s));
+  if (any_probe) TA_HIP(launch_curv_ema(T, sa, beta_h, omb_h, fisher ? 1 : 0, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[2], s));
   if (local) {
     // a set bound by its launches: the update takes the layers' decisions and settles the thresholds
@@ -376,7 +376,6 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   c->numel.resize(n);
   c->grad_dtype.resize(n);
   c->layer_host.resize(n);
-  uint64_t cand_total = 0;
   uint32_t max_chunks = 0;
   for (int32_t i = 0; i < n; ++i) {
     const triaccel_tensor& t = tensors[i];
@@ -387,12 +386,6 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     d.first_chunk = (uint32_t)chunks.size();
     d.n_chunks = nc;
     d.grad_dtype = t.grad_dtype;
-    d.cand_offset = cand_total;
-    const KeyLists lists = key_lists(t.numel);
-    d.cand_cap = lists.over_cap;
-    d.sub_cap = lists.sub_cap;
-    d.list_all = lists.list_all;
-    cand_total += lists.entries;
     for (uint32_t k = 0; k < nc; ++k) chunks.push_back(ChunkRef{(uint32_t)i, k});
     if (nc > max_chunks) max_chunks = nc;
     c->numel[i] = t.numel;
@@ -419,6 +412,15 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   T.n_tensors = (uint32_t)n;
   T.total_chunks = (uint32_t)chunks.size();
   T.max_chunks_per_tensor = max_chunks;
+  uint64_t cand_total = 0;
+  for (TensorDesc& d : c->desc) {
+    const KeyLists lists = key_lists(d.numel);
+    d.cand_offset = cand_total;
+    d.cand_cap = lists.over_cap;
+    d.sub_cap = lists.sub_cap;
+    d.list_all = lists.list_all;
+    if (!d.list_all || !local_form(*c)) cand_total += lists.entries;  // (select_local reads a small tensor's keys itself)
+  }
   uint64_t grad_bytes = 0;
   for (int32_t i = 0; i < n; ++i) grad_bytes += (uint64_t)tensors[i].numel * (tensors[i].grad_dtype == TRIACCEL_FP32 ? 4u : 2u);
   T.keep_grads = grad_bytes <= kKeepBytes;

@@ -216,20 +216,20 @@ struct EmaPartial {
   uint32_t nonfinite;    // a probe sample of the chunk was non-finite
 };
 
-// The layer's fields that the decisions of an applied step read.
+// The plan of a step's threshold selection, laid at the last probed step (a copy of LayerDev's fields).
+struct SelNow {
+  uint32_t use_band, band_lo, band_hi, predicted;
+  uint32_t win_lo, win_hi, win_shift, win_bins;
+};
+
+// The layer's fields that an applied step reads while its record is being rewritten: the workgroups of k_update_local
+// take the decisions and the selection's plan from this copy, which an earlier kernel made.
 struct LayerIn {
   float v, lambda, lambda_ctrl, lambda_power;
   int32_t code, prev_code;
   uint32_t applied_steps;
-};
-
-// The plan of a step's threshold selection, laid at the last probed step (a copy of LayerDev's fields).  The
-// workgroups of k_update_local read these fields of the live record while one of them writes others: of the
-// functions that run there only select_setup's kOutHist branch and what follows it may write them, in the workgroup
-// that arrives last, when all others have read them.
-struct SelNow {
-  uint32_t use_band, band_lo, band_hi, predicted;
-  uint32_t win_lo, win_hi, win_shift, win_bins;
+  uint32_t pad_;
+  SelNow plan;
 };
 
 struct StatPartial {

@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
                                                        const ChunkRef* __restrict__ chunks, const LayerDev* layers,
                                                        const GlobalDev* glob, EmaPartial* __restrict__ ema_partials,
                                                        Candidate* cands, uint32_t* counters, StepArg sa,
-                                                       float beta_h, float omb_h) {
+                                                       float beta_h, float omb_h, int list_small) {
   const StepScalars sc = step_scalars(sa);
   // the skip word travels together with the tables: its latency is not one more before the data's
   const uint64_t skip_epoch = glob->skip_epoch;
@@ -213,8 +213,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
             "s"(band_hi));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
   const bool first = probes_seen == 0;
-  const bool list_all = td.list_all != 0;
-  const bool listing = list_all || use_band != 0;
+  // a small tensor's keys are listed, all of them, or left to select_local, which reads them where they lie
+  const bool list_all = td.list_all != 0 && list_small != 0;
+  const bool listing = list_all || (td.list_all == 0 && use_band != 0);
   // band_lo >= 1 and band_hi <= 0x7f800000, so key 0 is never in a range; no key reaches 2^31
   const uint32_t list_lo = list_all ? 1u : listing ? band_lo : 0x80000000u;
   const uint32_t list_hi = list_all || !listing ? 0x80000000u : band_hi;
@@ -416,13 +417,10 @@ hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, bool loca
 }
 
 hipError_t launch_curv_ema(const DeviceTables& t, const StepArg& sa, float beta_h, float omb_h, int fisher,
-                           hipStream_t s) {
-  if (fisher)
-    hipLaunchKernelGGL(k_curv_ema<true>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.layers,
-                       t.glob, t.ema_partials, t.cands, t.cand_counters, sa, beta_h, omb_h);
-  else
-    hipLaunchKernelGGL(k_curv_ema<false>, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.layers,
-                       t.glob, t.ema_partials, t.cands, t.cand_counters, sa, beta_h, omb_h);
+                           bool local, hipStream_t s) {
+  const auto kernel = fisher ? k_curv_ema<true> : k_curv_ema<false>;
+  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.layers, t.glob,
+                     t.ema_partials, t.cands, t.cand_counters, sa, beta_h, omb_h, local ? 0 : 1);
   TA_LAUNCH_CHECK();
   return hipSuccess;
 }

@@ -119,7 +119,7 @@ __device__ __forceinline__ LayerSums layer_reduce(const LayerAcc& a, int64_t num
 }
 
 __device__ __forceinline__ LayerIn layer_in(const LayerDev& ls) {
-  return LayerIn{ls.v, ls.lambda, ls.lambda_ctrl, ls.lambda_power, ls.code, ls.prev_code, ls.applied_steps};
+  return LayerIn{ls.v, ls.lambda, ls.lambda_ctrl, ls.lambda_power, ls.code, ls.prev_code, ls.applied_steps, 0u, select_plan(ls)};
 }
 struct LayerOut {
   float mean, var, v, lambda, lambda_ctrl, eta;

@@ -157,8 +157,7 @@ __device__ __forceinline__ Window first_window(const SelNow& now, uint32_t maxke
   return Window{hi > span ? hi - span : 0u, kFirstShift, (uint32_t)kHistBins, hi};
 }
 
-// Lays down the selection state of tensor l for the outcome (one thread).  Only the kOutHist branch writes fields of
-// the plan (SelNow): in k_update_local the other two run while workgroups of the same tensor still read it.
+// Lays down the selection state of tensor l for the outcome (one thread).
 __device__ __forceinline__ void select_setup(const TensorDesc& td, LayerDev& ls, GlobalDev* glob, const SelNow& now,
                                              const EmaTotals& e, uint32_t k, int outcome, uint64_t step_id) {
   const uint32_t nonzero = (uint32_t)td.numel - e.zeros;
@@ -343,6 +342,99 @@ __device__ __forceinline__ FinishIn finish_in(const LayerDev& ls) {
                   ls.window_missed, ls.dens_count, ls.dens_width, ls.var_hold, ls.var_ext};
 }
 
+// Writes the result of a probed step's selection into the layer's record and plans the next one (one thread).
+__device__ __forceinline__ void select_publish(const TensorDesc& td, LayerDev& ls, const FinishIn& in, uint32_t theta, uint32_t nnz,
+                                               float beta_h) {
+  const uint32_t prev = in.theta_key_last;
+  const uint32_t have = in.n_theta;
+  ls.theta_key = theta;
+  ls.theta = u2f(theta);
+  ls.nnz = nnz;
+  ls.sel_passes = in.passes - 1 + (in.mask_done ? 0u : 1u);  // passes over h beyond the EMA pass
+  ls.probes_seen = in.probes_seen + 1;
+  // ---- plan the next probed step ----
+  // Two predictors of the next threshold are tracked by the error each made for this step:
+  // "hold" (the last threshold; best when the threshold only jitters) and a damped extrapolation
+  // in the value domain, theta + r (theta - prev), best while the curvature EMA still settles:
+  // the distance of the threshold from its limit then shrinks by a nearly constant factor per
+  // probe, so r is the ratio of the last two differences, kept within [0, 1] (between "hold" and
+  // a straight line), and beta_h, the factor by which the EMA forgets, while only two thresholds
+  // are known.  Each predictor keeps a running mean of its squared error in keys (an error three
+  // times the running deviation replaces the mean at once); the one with the smaller mean is
+  // used, and the band is a multiple of its deviation.
+  const uint32_t prev2 = in.theta_key_last2;
+  const float unknown2 = (float)kUnknownPredErr * (float)kUnknownPredErr;
+  auto track = [](float var, float err, bool first) {
+    const float e2 = err * err;
+    if (first || e2 > 9.0f * var) return e2;
+    return 0.75f * var + 0.25f * e2;
+  };
+  float v_hold = unknown2, v_ext = in.pred_ext_key ? in.var_ext : 3.0e38f;
+  if (have >= 1) v_hold = track(in.var_hold, (float)abs_diff(theta, prev), have < 2);
+  if (in.pred_ext_key) v_ext = track(v_ext, (float)abs_diff(theta, in.pred_ext_key), !(v_ext < 3.0e38f));
+  if (in.window_missed) {
+    v_hold = fmaxf(v_hold, unknown2);
+    if (v_ext < 3.0e38f) v_ext = fmaxf(v_ext, unknown2);
+  }
+  uint32_t ext = 0;
+  if (have >= 1) {
+    const double v0 = (double)u2f(theta), v1 = (double)u2f(prev);
+    const double d1 = v0 - v1;
+    double r = (double)beta_h;
+    if (have >= 2) {
+      const double d0 = v1 - (double)u2f(prev2);
+      r = d0 != 0.0 ? d1 / d0 : 1.0;
+    }
+    r = fmin(fmax(r, 0.0), 1.0);
+    const float p = (float)(v0 + r * d1);
+    ext = p > 0.0f ? min(max(f2u(p), 1u), 0x7f7fffffu) : 1u;
+  }
+  ls.var_hold = v_hold;
+  ls.var_ext = v_ext;
+  ls.pred_ext_key = ext;
+  ls.theta_key_last2 = prev;
+  ls.theta_key_last = theta;
+  ls.n_theta = have < 2 ? have + 1 : 2;
+  const bool extrapolate = ext != 0u && v_ext < v_hold;
+  // e: 1.5 deviations of the chosen predictor (band = 3 e = 4.5 deviations, window half = 32 e)
+  const float dev = 1.5f * sqrtf(extrapolate ? v_ext : v_hold);
+  const uint32_t e = dev < 16.0f ? 16u : (dev > 1.0e9f ? 1000000000u : (uint32_t)dev);
+  int64_t centre = extrapolate ? (int64_t)ext : (int64_t)theta;
+  if (centre < 1) centre = 1;
+  if (centre > 0x7f7fffff) centre = 0x7f7fffff;
+  // fallback window: 2048 bins whose half (1024 bins) spans 32 e
+  uint32_t s = kMinPredShift;
+  while (s < kFullShift && ((uint64_t)1024 << s) < (uint64_t)32 * e) ++s;
+  const uint32_t cbin = (uint32_t)centre >> s;
+  const uint32_t lo_bin = cbin > (uint32_t)(kHistBins / 2) ? cbin - kHistBins / 2 : 0u;
+  // band: 3 e on either side of the centre
+  const uint64_t half = (uint64_t)3 * e;
+  const uint32_t band_lo = (uint64_t)centre > half ? (uint32_t)((uint64_t)centre - half) : 1u;
+  const uint64_t hi64 = (uint64_t)centre + half + 1;
+  const uint32_t band_hi = hi64 < 0x7f800000ull ? (uint32_t)hi64 : 0x7f800000u;
+  // expected number of keys inside the band, from the key density around this step's threshold;
+  // listing them only pays when they fit the lists with room to spare
+  const uint64_t expect = in.dens_width ? ((uint64_t)(band_hi - band_lo) * in.dens_count) / in.dens_width : 0u;
+  ls.mode = kSelHist;
+  ls.win_lo = lo_bin << s;
+  ls.win_hi = ls.win_lo + ((uint32_t)kHistBins << s);
+  ls.win_shift = s;
+  ls.win_bins = kHistBins;
+  ls.band_lo = band_lo;
+  ls.band_hi = band_hi;
+  ls.use_band = expect <= (uint64_t)(td.cand_cap - td.cand_cap / 4) ? 1u : 0u;
+  ls.predicted = 1;
+  ls.window_missed = 0;
+  ls.mask_done = 0;
+  ls.passes = 0;
+  ls.above = 0;
+  ls.k_rem = 0;
+  ls.sel_count = 0;
+  ls.dens_count = 0;
+  ls.dens_width = 0;
+  ls.acc_above = 0;
+}
+
 // Shared memory of the histogram functions, for a workgroup of kThreads threads.
 struct HistShared {
   uint32_t hist[kHistBins];
@@ -464,97 +556,7 @@ __device__ __forceinline__ void select_finish(uint32_t l, const TensorDesc& td, 
   }
   __syncthreads();
   reset_cand_counters(counters, l);
-  if (threadIdx.x != 0) return;
-  // ---- publish ----
-  const uint32_t prev = in.theta_key_last;
-  const uint32_t have = in.n_theta;
-  ls.theta_key = theta;
-  ls.theta = u2f(theta);
-  ls.nnz = nnz;
-  ls.sel_passes = in.passes - 1 + (in.mask_done ? 0u : 1u);  // passes over h beyond the EMA pass
-  ls.probes_seen = in.probes_seen + 1;
-  // ---- plan the next probed step ----
-  // Two predictors of the next threshold are tracked by the error each made for this step:
-  // "hold" (the last threshold; best when the threshold only jitters) and a damped extrapolation
-  // in the value domain, theta + r (theta - prev), best while the curvature EMA still settles:
-  // the distance of the threshold from its limit then shrinks by a nearly constant factor per
-  // probe, so r is the ratio of the last two differences, kept within [0, 1] (between "hold" and
-  // a straight line), and beta_h, the factor by which the EMA forgets, while only two thresholds
-  // are known.  Each predictor keeps a running mean of its squared error in keys (an error three
-  // times the running deviation replaces the mean at once); the one with the smaller mean is
-  // used, and the band is a multiple of its deviation.
-  const uint32_t prev2 = in.theta_key_last2;
-  const float unknown2 = (float)kUnknownPredErr * (float)kUnknownPredErr;
-  auto track = [](float var, float err, bool first) {
-    const float e2 = err * err;
-    if (first || e2 > 9.0f * var) return e2;
-    return 0.75f * var + 0.25f * e2;
-  };
-  float v_hold = unknown2, v_ext = in.pred_ext_key ? in.var_ext : 3.0e38f;
-  if (have >= 1) v_hold = track(in.var_hold, (float)abs_diff(theta, prev), have < 2);
-  if (in.pred_ext_key) v_ext = track(v_ext, (float)abs_diff(theta, in.pred_ext_key), !(v_ext < 3.0e38f));
-  if (in.window_missed) {
-    v_hold = fmaxf(v_hold, unknown2);
-    if (v_ext < 3.0e38f) v_ext = fmaxf(v_ext, unknown2);
-  }
-  uint32_t ext = 0;
-  if (have >= 1) {
-    const double v0 = (double)u2f(theta), v1 = (double)u2f(prev);
-    const double d1 = v0 - v1;
-    double r = (double)beta_h;
-    if (have >= 2) {
-      const double d0 = v1 - (double)u2f(prev2);
-      r = d0 != 0.0 ? d1 / d0 : 1.0;
-    }
-    r = fmin(fmax(r, 0.0), 1.0);
-    const float p = (float)(v0 + r * d1);
-    ext = p > 0.0f ? min(max(f2u(p), 1u), 0x7f7fffffu) : 1u;
-  }
-  ls.var_hold = v_hold;
-  ls.var_ext = v_ext;
-  ls.pred_ext_key = ext;
-  ls.theta_key_last2 = prev;
-  ls.theta_key_last = theta;
-  ls.n_theta = have < 2 ? have + 1 : 2;
-  const bool extrapolate = ext != 0u && v_ext < v_hold;
-  // e: 1.5 deviations of the chosen predictor (band = 3 e = 4.5 deviations, window half = 32 e)
-  const float dev = 1.5f * sqrtf(extrapolate ? v_ext : v_hold);
-  const uint32_t e = dev < 16.0f ? 16u : (dev > 1.0e9f ? 1000000000u : (uint32_t)dev);
-  int64_t centre = extrapolate ? (int64_t)ext : (int64_t)theta;
-  if (centre < 1) centre = 1;
-  if (centre > 0x7f7fffff) centre = 0x7f7fffff;
-  // fallback window: 2048 bins whose half (1024 bins) spans 32 e
-  uint32_t s = kMinPredShift;
-  while (s < kFullShift && ((uint64_t)1024 << s) < (uint64_t)32 * e) ++s;
-  const uint32_t cbin = (uint32_t)centre >> s;
-  const uint32_t lo_bin = cbin > (uint32_t)(kHistBins / 2) ? cbin - kHistBins / 2 : 0u;
-  // band: 3 e on either side of the centre
-  const uint64_t half = (uint64_t)3 * e;
-  const uint32_t band_lo = (uint64_t)centre > half ? (uint32_t)((uint64_t)centre - half) : 1u;
-  const uint64_t hi64 = (uint64_t)centre + half + 1;
-  const uint32_t band_hi = hi64 < 0x7f800000ull ? (uint32_t)hi64 : 0x7f800000u;
-  // expected number of keys inside the band, from the key density around this step's threshold;
-  // listing them only pays when they fit the lists with room to spare
-  const uint64_t expect = in.dens_width ? ((uint64_t)(band_hi - band_lo) * in.dens_count) / in.dens_width : 0u;
-  ls.mode = kSelHist;
-  ls.win_lo = lo_bin << s;
-  ls.win_hi = ls.win_lo + ((uint32_t)kHistBins << s);
-  ls.win_shift = s;
-  ls.win_bins = kHistBins;
-  ls.band_lo = band_lo;
-  ls.band_hi = band_hi;
-  ls.use_band = expect <= (uint64_t)(td.cand_cap - td.cand_cap / 4) ? 1u : 0u;
-  ls.predicted = 1;
-  ls.window_missed = 0;
-  ls.mask_done = 0;
-  ls.passes = 0;
-  ls.above = 0;
-  ls.k_rem = 0;
-  ls.sel_count = 0;
-  ls.dens_count = 0;
-  ls.dens_width = 0;
-  ls.acc_above = 0;
+  if (threadIdx.x == 0) select_publish(td, ls, in, theta, nnz, beta_h);
 }
-
 
 }  // namespace triaccel

@@ -1,8 +1,8 @@
 // gfx950 kernels for sets bound by their launches: k_update_local does what the per-layer kernel, the fallback
 // histogram pass, the fused update + cast and the first launch of the in-place resize do one after the other on
 // larger sets, k_select_tail what the mask pass and the threshold resolution do.
-#include "layer_body.h"
 #include "resize_body.h"
+#include "select_local.h"
 
 namespace triaccel {
 
@@ -18,32 +18,45 @@ __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { re
 // tensor instead, with the last workgroup writing, cost one atomic per chunk: with the counters side by side
 // in a cache line 20 ns each, 205 us instead of 35 on the ResNet-18 set.)
 //
-// For a tensor whose listed keys do not settle the threshold the chunk workgroups also count |h| into its
-// histogram, and the last of the tensor scans it; k_select_tail does what is left of the selection.  (Settling
-// the listed keys in this launch, by workgroups beside the streaming ones, took 100-200 us: each of their
-// dependent accesses queues behind the streams of its compute unit.)
+// The first `select_wgs` workgroups settle the thresholds of the tensors whose listed keys suffice (select_local): they
+// need nothing of this launch, and they take as long as the streaming around them or less.  In a launch of their own
+// afterwards they cost 10 to 13 us of a probed step.  For the other tensors the chunk workgroups also count |h| into the
+// tensor's histogram, and the last of the tensor scans it; k_select_tail does what is left of their selection.
 //
-// Measured, per step, against the separate launches: two-layer perceptron (4 tensors, 0.1 M) 13.4 -> 8.8 us,
-// EfficientNet-B0 set 23.4 -> 19.5 (16-bit gradients, no probe) and 65.7 -> 57.1 (probed), ResNet-18 set
-// 54.6 -> 50.7 and 102.4 -> 94.5.
+// Measured, per step: the decisions in here against launches of their own, two-layer perceptron (4 tensors, 0.1 M)
+// 13.4 -> 8.8 us, EfficientNet-B0 set 23.4 -> 19.5 (16-bit gradients, no probe) and 65.7 -> 57.1 (probed), ResNet-18 set
+// 54.6 -> 50.7 and 102.4 -> 94.5; the selection in here against k_select_tail, with a probe: the perceptron with fp16
+// gradients and the result read each time 35.0 -> 29.0, EfficientNet-B0 49.2 -> 39.2, ResNet-18 84.5 -> 73.3, 41 ragged
+// tensors of 9.7 M with the Fisher source 59.5 -> 50.0, 4000 tensors of 10 to 300 elements 175 -> 75.
 template <bool MOM, bool PROBED>
 __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __restrict__ tds,
                                                            const ChunkRef* __restrict__ chunks,
                                                            const StatPartial* __restrict__ partials,
                                                            const EmaPartial* __restrict__ ema_partials,
                                                            const LayerIn* __restrict__ inputs, LayerDev* layers,
-                                                           GlobalDev* glob, GlobalDev* host_result, uint32_t* counters,
-                                                           uint32_t* hist, uint32_t* arrived, uint32_t* trans_list,
-                                                           uint32_t n_tensors, ResizePlan plan, char* scratch, StepArg sa,
-                                                           Hyper hp) {
+                                                           GlobalDev* glob, GlobalDev* host_result, const Candidate* cands,
+                                                           uint32_t* counters, uint32_t* hist, uint32_t* arrived,
+                                                           uint32_t* trans_list, uint32_t n_tensors, uint32_t select_wgs,
+                                                           ResizePlan plan, char* scratch, StepArg sa, Hyper hp) {
   __shared__ LayerShared sh_layer;
-  __shared__ HistShared sh;
+  __shared__ union {
+    HistShared hist;
+    LocalSelectShared select;
+  } shared;
+  HistShared& sh = shared.hist;
   __shared__ LayerOut s_decision;
   __shared__ uint32_t s_last;
   const StepScalars sc = step_scalars(sa);
+  if constexpr (PROBED) {
+    if (blockIdx.x < select_wgs) {
+      if (blockIdx.x < n_tensors)
+        select_local(blockIdx.x, tds, ema_partials, inputs, layers, glob, cands, counters, sc, hp, sh_layer, shared.select);
+      return;
+    }
+  }
   const uint64_t skip_epoch = glob->skip_epoch;
   const bool skip = skip_epoch == sc.step_id;
-  const ChunkRef cr = chunks[blockIdx.x];
+  const ChunkRef cr = chunks[blockIdx.x - (PROBED ? select_wgs : 0u)];
   const TensorDesc td = tds[cr.tensor];
   LayerDev& ls = layers[cr.tensor];
   const LayerIn in = inputs[cr.tensor];
@@ -61,10 +74,9 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   const bool probed = PROBED && td.has_probe != 0;
   const LayerAcc acc = layer_accumulate<PROBED>(td, partials, ema_partials, probed);
   // The chunk's own loads are under way while the sums are reduced and the decisions taken (2-3 % of a step from
-  // 11 M to 30 M parameters against loading after them, at 4 wavefronts per SIMD instead of 7; held
-  // down to 5 by the compiler nothing gains and a step in which 50 M parameters change size takes 1 % longer).  They are of no use
-  // if the layer changes its storage size (50 M parameters all changing: 312 us a step with them, 238 without);
-  // a layer that did so at its last step, or has its first, is taken to be about to do it.
+  // 11 M to 30 M parameters against loading after them).  They are of no use if the layer changes its storage size
+  // (50 M parameters all changing: 312 us a step with them, 238 without); a layer that did so at its last step, or has
+  // its first, is taken to be about to do it.
   const bool early = in.applied_steps != 0 && elem_size(in.code) == elem_size(in.prev_code);
   const int pd = in.code;
   int nd;
@@ -90,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   int outcome = kOutListed;
   if constexpr (PROBED) {
     if (probed) {
-      const SelNow now = select_plan(ls);
+      const SelNow now = in.plan;
       k = topk_count(td.numel, hp.sparsity_ppm, hp.topk_abs);
       outcome = select_outcome(td, now, ema, k);
       if (outcome == kOutHist) {
@@ -110,7 +122,8 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
     }
   }
   if (threadIdx.x == 0 && cr.index == 0) {
-    if (probed && outcome != kOutHist) select_setup(td, ls, glob, select_plan(ls), ema, k, outcome, sc.step_id);
+    // (kOutListed: select_local; kOutHist: below)
+    if (probed && outcome == kOutFewNonzero) select_setup(td, ls, glob, in.plan, ema, k, outcome, sc.step_id);
     layer_publish(cr.tensor, ls, s_decision, glob, trans_list, n_tensors, sc.step_id);
     if (cr.tensor == 0) step_record(glob, host_result, sc, hp, false);
   }
@@ -121,7 +134,7 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
       const bool last = atomicAdd(arrival(arrived, cr.tensor), 1u) + 1u == td.n_chunks;
       if (last) {
         *arrival(arrived, cr.tensor) = 0;
-        select_setup(td, ls, glob, select_plan(ls), ema, k, outcome, sc.step_id);
+        select_setup(td, ls, glob, in.plan, ema, k, outcome, sc.step_id);
       }
       s_last = last ? 1u : 0u;
     }
@@ -138,19 +151,22 @@ hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const H
   const bool mom = hp.momentum != 0.0f;
   const auto kernel = any_probe ? (mom ? k_update_local<true, true> : k_update_local<false, true>)
                                 : (mom ? k_update_local<true, false> : k_update_local<false, false>);
-  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.partials, t.ema_partials,
-                     t.inputs, t.layers, t.glob, t.host_result, t.cand_counters, t.hist, t.arrived, t.trans_list, t.n_tensors,
-                     plan, t.resize_scratch, sa, hp);
+  // a multiple of eight: a chunk's workgroup goes to the same die in every kernel
+  const uint32_t select_wgs = any_probe ? (t.n_tensors + 7u) & ~7u : 0u;
+  hipLaunchKernelGGL(kernel, dim3(select_wgs + t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.partials,
+                     t.ema_partials, t.inputs, t.layers, t.glob, t.host_result, t.cands, t.cand_counters, t.hist, t.arrived,
+                     t.trans_list, t.n_tensors, select_wgs, plan, t.resize_scratch, sa, hp);
   TA_LAUNCH_CHECK();
   return hipSuccess;
 }
 
 // What is left of the selection after k_update_local, and before the element-wise form of the update on sets
-// of that size (one launch for the mask pass and the threshold resolution).  Workgroup l < n_tensors settles tensor l if its listed
-// keys suffice.  The `mask_wgs` workgroups after those make the mask pass of the other tensors, four chunks at a
+// of that size (one launch for the mask pass and the threshold resolution).  Workgroup l < n_tensors settles tensor l if its
+// listed keys suffice (after k_update_local: if they were too many for select_local).  The `mask_wgs` workgroups after
+// those make the mask pass of the other tensors, four chunks at a
 // time, and the last workgroup to finish a part of such a tensor settles it among the keys the pass listed; the
-// rest take launch 1 of the in-place resize, four chunks of a level at a time.  The last two kinds leave at once
-// when no tensor needs them (the steady state); in a launch of its own the resize cost 4.5 us a step all the same.
+// rest take launch 1 of the in-place resize, four chunks of a level at a time.  After k_update_local all of them leave
+// at once in the steady state, which costs a step 1.5 us.
 template <bool MOM>
 __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc* __restrict__ tds,
                                                                 const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
@@ -158,12 +174,17 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
                                                                 Candidate* cands, uint32_t* counters, uint32_t* arrived,
                                                                 uint32_t mask_wgs, const uint32_t* trans_list,
                                                                 ResizePlan plan, char* scratch, uint32_t resize_slots,
-                                                                StepArg sa, float beta_h, float wd, float mu) {
+                                                                int local, StepArg sa, float beta_h, float wd, float mu) {
   __shared__ SelectShared<kFinishThreads> sh;
   __shared__ uint32_t s_last;
   const StepScalars sc = step_scalars(sa);
   const uint64_t skip_epoch = glob->skip_epoch;
+  const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
   if (blockIdx.x < n_tensors) {
+    if (local) {
+      TA_LOADED("s"(skip_epoch), "s"(pending));
+      if (pending == 0 || skip_epoch == sc.step_id) return;
+    }
     const uint32_t l = blockIdx.x;
     const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
     const TensorDesc td = tds[l];
@@ -173,7 +194,8 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
     const FinishIn in = finish_in(ls);
     TA_LOADED("s"(td.mask), "s"(td.has_probe), "s"(td.cand_cap), "s"(sel_outcome), "s"(in.mode), "s"(in.probes_seen),
               "s"(in.var_hold));
-    if (skip_epoch == sc.step_id || !td.has_probe || sel_outcome > 1u) return;
+    // (a tensor that select_local settled is no longer in this mode)
+    if (skip_epoch == sc.step_id || !td.has_probe || sel_outcome > 1u || in.mode != kSelCand) return;
     select_finish<kFinishThreads, kFinishRegs>(l, td, ls, in, listed, cands, counters, beta_h, sh);
     return;
   }
@@ -186,7 +208,6 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
                                                         gridDim.x - n_tensors - mask_wgs, sc, wd, mu, 0.0f);
     return;
   }
-  const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
   TA_LOADED("s"(skip_epoch), "s"(pending));
   if (pending == 0 || skip_epoch == sc.step_id) return;
   const uint32_t part = blockIdx.x - n_tensors, parts = mask_wgs;
@@ -236,20 +257,20 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
 
 static_assert((kResizeTopSmall << 6) >= kLocalMaxChunks && kLaunchBoundChunks <= kResizeBigSet,
               "one subtree stage: the resize of a set of the local form has two launches at most");
-hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool resize, hipStream_t s) {
+hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool local, hipStream_t s) {
   constexpr uint32_t kGroups = kFinishThreads / kThreads;
   const uint32_t all = (t.total_chunks + kGroups - 1) / kGroups, cap = t.persistent_grid / 8;  // one per CU
   const uint32_t mask_wgs = all < cap ? all : cap;
   const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
   ResizeGrid rg{1u, 0u};
-  if (resize && plan.n_stages > 1) {
+  if (local && plan.n_stages > 1) {
     rg = resize_grid(plan, 1u, t.n_tensors, true);
     if (rg.grid > cap) rg.grid = cap;
   }
   const auto kernel = hp.momentum != 0.0f ? k_select_tail<true> : k_select_tail<false>;
   hipLaunchKernelGGL(kernel, dim3(t.n_tensors + mask_wgs + rg.grid), dim3(kFinishThreads), 0, s, t.tensors, t.chunks,
                      t.total_chunks, t.n_tensors, t.layers, t.glob, t.cands, t.cand_counters, t.arrived, mask_wgs,
-                     t.trans_list, plan, t.resize_scratch, rg.slots, sa, hp.beta_curv, hp.weight_decay, hp.momentum);
+                     t.trans_list, plan, t.resize_scratch, rg.slots, local ? 1 : 0, sa, hp.beta_curv, hp.weight_decay, hp.momentum);
   TA_LAUNCH_CHECK();
   return hipSuccess;
 }
