@@ -131,16 +131,25 @@ __global__ __launch_bounds__(kThreads, K <= 5 ? 3 : 1) void k_power_gram(const T
   }
 }
 
-// Per-layer kernel: one workgroup per tensor adds the segment partials (fixed order) and thread 0
-// factorises the k x k Gram matrix.  A vector whose remainder after projecting out the earlier
+// Value of lane `src` (fp64), every lane its own `src`.
+__device__ __forceinline__ double from_lane(double v, int src) {
+  const int lo = __builtin_amdgcn_ds_bpermute(src * 4, __double2loint(v)), hi = __builtin_amdgcn_ds_bpermute(src * 4, __double2hiint(v));
+  return __hiloint2double(hi, lo);
+}
+
+// Per-layer kernel: one workgroup per tensor adds the segment partials (fixed order) and its first wavefront
+// factorises the k x k Gram matrix, one entry per lane.  A vector whose remainder after projecting out the earlier
 // directions is numerically nothing (pivot <= 1e-12 of its own squared norm) gets a zero column.
+// Bound by chains of fp64 divisions and square roots of some 200 cycles each: a column at a time by one thread there were
+// 55 of them one after the other at k = 5 and 110 at k = 8, here 4 and a few for each of the k steps.  ResNet-18 set,
+// k = 5: the call 147.2 -> 145.1 us; 3 M parameters, k = 8: 84.2 -> 78.8; 11 tensors of 60 elements, k = 8: 22.6 -> 16.9.
 template <int K>
 __global__ __launch_bounds__(kThreads) void k_power_layer(const TensorDesc* __restrict__ tds,
                                                           const uint32_t* __restrict__ seg_first,
                                                           uint32_t seg, const double* __restrict__ partials,
                                                           PowerLayer* state, LayerDev* layers, int latch) {
-  constexpr int NG = K * (K + 1) / 2, PP = NG + 2 * K;
-  static_assert(PP <= kWave, "one lane per partial entry");
+  constexpr int NG = K * (K + 1) / 2, PP = NG + 2 * K, N = kMaxPowerK;
+  static_assert(PP <= kWave && N * N == kWave, "one lane per partial entry, one per matrix entry");
   const uint32_t l = blockIdx.x;
   const uint32_t n_segs = (tds[l].n_chunks + seg - 1) / seg;
   const double* p = partials + (size_t)seg_first[l] * PP;
@@ -152,64 +161,62 @@ __global__ __launch_bounds__(kThreads) void k_power_layer(const TensorDesc* __re
   __shared__ double s_acc[kThreads / kWave][kWave];
   s_acc[part][e] = acc;
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  double G[K][K], c[K], d[K];
-  for (int j = 0; j < K; ++j) {
-    for (int i = 0; i <= j; ++i) {
-      const int t = tri(i, j);
-      G[i][j] = G[j][i] = ((s_acc[0][t] + s_acc[1][t]) + s_acc[2][t]) + s_acc[3][t];
-    }
-    c[j] = ((s_acc[0][NG + j] + s_acc[1][NG + j]) + s_acc[2][NG + j]) + s_acc[3][NG + j];
-    d[j] = ((s_acc[0][NG + K + j] + s_acc[1][NG + K + j]) + s_acc[2][NG + K + j]) + s_acc[3][NG + K + j];
-  }
+  if (part != 0) return;
+  const auto total = [&](int t) { return ((s_acc[0][t] + s_acc[1][t]) + s_acc[2][t]) + s_acc[3][t]; };
   PowerLayer& st = state[l];
-  double R[K][K], T[K][K];
-  uint32_t deficient = 0;
-  double lam_max = 0.0;
-  for (int j = 0; j < K; ++j) {
-    // Rayleigh quotient and residual ||w - lambda u|| / ||u|| from the sums (zero iterate: both 0)
+  // quotients, residuals ||w - lambda u|| / ||u|| and norms from the sums (zero iterate: both 0): lane j, vector j
+  {
+    const int j = e < K ? e : 0;
+    const double gjj = total(tri(j, j)), c = total(NG + j), d = total(NG + K + j);
     double lam = 0.0, res = 0.0;
-    if (d[j] > 0.0) {
-      lam = c[j] / d[j];
-      const double r2 = G[j][j] - 2.0 * lam * c[j] + lam * lam * d[j];
-      res = sqrt(r2 > 0.0 ? r2 : 0.0) / sqrt(d[j]);
+    if (d > 0.0) {
+      lam = c / d;
+      const double r2 = gjj - 2.0 * lam * c + lam * lam * d;
+      res = sqrt(r2 > 0.0 ? r2 : 0.0) / sqrt(d);
     }
-    st.rayleigh[j] = (float)lam;
-    st.resid[j] = (float)res;
-    st.hnorm[j] = (float)sqrt(G[j][j]);
-    lam_max = fmax(lam_max, fabs(lam));
-    // column j of the Cholesky factor R (G = R^T R) ...
-    for (int i = 0; i < j; ++i) {
-      double s = 0.0;
-      if (!((deficient >> i) & 1u)) {
-        s = G[i][j];
-        for (int q = 0; q < i; ++q) s -= R[q][i] * R[q][j];
-        s /= R[i][i];
-      }
-      R[i][j] = s;
+    if (e < N) {
+      st.rayleigh[e] = e < K ? (float)lam : 0.0f;
+      st.resid[e] = e < K ? (float)res : 0.0f;
+      st.hnorm[e] = e < K ? (float)sqrt(gjj) : 0.0f;
     }
-    double piv = G[j][j];
-    for (int q = 0; q < j; ++q) piv -= R[q][j] * R[q][j];
-    const bool def = piv <= 1e-12 * G[j][j];
-    R[j][j] = def ? 0.0 : sqrt(piv);
-    if (def) deficient |= 1u << j;
-    // ... and of its inverse: q_j = (w_j - sum_{p<j} R_pj q_p) / R_jj in terms of the w_i
-    for (int i = 0; i <= j; ++i) {
-      double s = 0.0;
-      if (!def) {
-        s = (i == j) ? 1.0 : 0.0;
-        for (int q = i; q < j; ++q) s -= T[i][q] * R[q][j];
-        s /= R[j][j];
-      }
-      T[i][j] = s;
+    double lam_max = 0.0;
+#pragma unroll
+    for (int q = 0; q < K; ++q) lam_max = fmax(lam_max, fabs(from_lane(lam, q)));
+    if (e == 0) {
+      st.lambda_max = (float)lam_max;
+      if (latch) layers[l].lambda_power = (float)lam_max;
     }
   }
-  for (int i = 0; i < kMaxPowerK; ++i)
-    for (int j = 0; j < kMaxPowerK; ++j) st.coef[i][j] = (i <= j && j < K) ? T[i][j] : 0.0;
-  for (int j = K; j < kMaxPowerK; ++j) st.rayleigh[j] = st.resid[j] = st.hnorm[j] = 0.0f;
-  st.deficient = deficient;
-  st.lambda_max = (float)lam_max;
-  if (latch) layers[l].lambda_power = (float)lam_max;
+  // lane N i + j, i <= j: entry (i, j) of the Gram matrix G, of its Cholesky factor R (G = R^T R) and of R^-1 = T; in the
+  // products the order of the subtractions is that of the left-looking forms
+  const int i = e / N, j = e % N;
+  const bool in = i <= j && j < K;
+  const double g = in ? total(tri(i, j)) : 0.0;
+  double s = g, r = 0.0;      // s: G_ij less the products of the rows above
+  double diag[K];             // R_pp, the same in all lanes
+  uint32_t deficient = 0;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const double piv = from_lane(s, q * N + q), full = from_lane(g, q * N + q);
+    const bool def = piv <= 1e-12 * full;
+    diag[q] = def ? 0.0 : sqrt(piv);
+    if (def) deficient |= 1u << q;
+    const double row = def ? 0.0 : s / diag[q];  // R_qj in the lanes of row q
+    if (i == q) r = j == q ? diag[q] : row;
+    const double a = from_lane(r, q * N + i), b = from_lane(r, q * N + j);
+    if (i > q) s -= a * b;
+  }
+  // q_j = (w_j - sum_{p<j} R_pj q_p) / R_jj in terms of the w_i
+  double t = i == j ? 1.0 : 0.0;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const double done = ((deficient >> q) & 1u) ? 0.0 : t / diag[q];
+    if (j == q) t = done;
+    const double a = from_lane(t, i * N + q), b = from_lane(r, q * N + j);
+    if (i <= q && q < j) t -= a * b;
+  }
+  st.coef[i][j] = in ? t : 0.0;
+  if (e == 0) st.deficient = deficient;
 }
 
 template <int K, bool FULL>
