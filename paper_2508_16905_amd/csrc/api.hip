@@ -466,7 +466,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     // workspace of the power iteration: segment table, per-segment sums, per-layer records
     std::vector<SegRef> segs;
     std::vector<uint32_t> seg_first((size_t)n);
-    const uint32_t seg = power_seg(T.total_chunks);
+    const uint32_t seg = power_seg(T.total_chunks, config->power_k);
     for (int32_t i = 0; i < n; ++i) {
       seg_first[i] = (uint32_t)segs.size();
       const uint32_t ns = (c->desc[i].n_chunks + seg - 1) / seg;

@@ -8,10 +8,16 @@
 namespace triaccel {
 
 constexpr int kMaxPowerK = 8;  // vectors per layer the workspace can be sized for
-// Chunks of one tensor that one workgroup of the Gram pass sums: 8, and 4 on sets below 16,384 chunks, where
-// segments of 8 leave the chip (768 workgroups at k = 5) short of work: 2768 chunks at k = 5, the three kernels of
-// an iteration together, 172 us with 8, 162 with 4, 165 with 2, 167 with 1 (more partial sums to add per tensor).
-constexpr uint32_t power_seg(uint32_t total_chunks) { return total_chunks < 16384 ? 4u : 8u; }
+// Chunks of one tensor that one workgroup of the Gram pass sums, for k vectors.  Sets that fit the chip with a workgroup
+// for every chunk (768 at k = 5) get one: the rows of a segment follow one after the other.  Above that segments of 4,
+// and of 8 from 16,384 chunks, where more partial sums to add per tensor cost more than the shorter segments gain.
+// An iteration, us, with segments of 1 and 4 chunks: 200 chunks, k = 1 12.6 and 18.6, k = 5 20.8 and 34.6, k = 8 30.4
+// and 49.1; 400: 13.8 and 19.9, 31.1 and 41.5, 50.9 and 60.5; 600: 15.3 and 22.0, 44.3 and 48.0, 72.3 and 70.8; 768:
+// 17.3 and 22.9, 51.9 and 53.9, 82.1 and 80.8; 1000: 19.8 and 24.5, 66.1 and 63.7, 101 and 96; 2700: 42.9 and 36.6,
+// 153 and 146, 246 and 244 (segments of 2 lie between the two).
+constexpr uint32_t power_seg(uint32_t total_chunks, int k) {
+  return total_chunks <= (k <= 5 ? 768u : 512u) ? 1u : total_chunks < 16384 ? 4u : 8u;
+}
 
 // Doubles one workgroup of the Gram pass leaves for k vectors: the upper triangle of W^T W
 // (W = [H u_0 .. H u_{k-1}]), then u_j . (H u_j), then u_j . u_j.
@@ -66,7 +72,7 @@ struct PowerTables {
   uint32_t n_tensors;
   uint32_t total_chunks;
   uint32_t total_segs;
-  uint32_t seg;  // power_seg(total_chunks)
+  uint32_t seg;  // power_seg
 };
 
 // One iteration on k vectors per tensor: Gram pass, per-layer factorisation, apply pass.  With

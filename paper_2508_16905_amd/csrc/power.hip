@@ -326,7 +326,8 @@ hipError_t launch_k(const PowerTables& t, const PowerDesc* descs, int latch, hip
 // ---------------------------------------------------------------------------------------------
 constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 constexpr size_t kStaticMaxSegs = kStaticMaxChunks / 8 + kStaticMaxTensors;
-static_assert(power_seg(16383) == 4 && power_seg(kStaticMaxChunks) == 8 && kStaticMaxChunks / 8 >= 16384 / 4,
+static_assert(power_seg(16383, 8) == 4 && power_seg(kStaticMaxChunks, 8) == 8 && kStaticMaxChunks / 8 >= 16384 / 4 &&
+                  power_seg(769, 1) == 4,
               "segments of any set fit the array");
 constexpr size_t kOffTensors = 0;
 constexpr size_t kOffDescs = kOffTensors + align256(sizeof(TensorDesc) * kStaticMaxTensors);
@@ -422,7 +423,7 @@ hipError_t launch_power_iter_static(const StaticTensor* tensors, int n, int k, P
   // tables: the prefix sums are formed here, the lists are written on the device
   uint32_t chunk_pos = 0, seg_pos = 0, total = 0;
   for (int i = 0; i < n; ++i) total += (uint32_t)((tensors[i].numel + kChunk - 1) / kChunk);
-  const uint32_t seg = power_seg(total);
+  const uint32_t seg = power_seg(total, k);
   for (int first = 0; first < n; first += kStaticBatch) {
     StaticBatchArg a{};
     a.first = (uint32_t)first;
