@@ -83,6 +83,7 @@ struct triaccel_ctx {
   int ev_level[TRIACCEL_PROFILE_RING] = {};      // profiling level that slot was recorded with
   std::vector<LayerDev> layer_host;
   std::vector<void*> device_allocs;
+  bool all_fp32 = false;  // every layer's precision was FP32 at init / set_state
   bool use_graph = false;
   // One captured step per (variant, device copy of the table): [0][s] steps without a curvature
   // refresh, [1][s] with; the kernels of a captured step hold the address of table copy s.
@@ -169,6 +170,15 @@ int validate_tensor(const triaccel_tensor& t, bool need_mom) {
   return TRIACCEL_OK;
 }
 
+void drop_graphs(triaccel_ctx* c) {
+  for (auto& variant : c->graphs)
+    for (auto& g : variant) {
+      if (g.exec) (void)hipGraphExecDestroy(g.exec);
+      if (g.graph) (void)hipGraphDestroy(g.graph);
+      g = StepGraph{};
+    }
+}
+
 void free_ctx(triaccel_ctx* c) {
   if (!c) return;
   for (void* p : c->device_allocs) (void)hipFree(p);
@@ -180,11 +190,7 @@ void free_ctx(triaccel_ctx* c) {
   }
   for (auto& e : c->power_prof)
     if (e) (void)hipEventDestroy(e);
-  for (auto& variant : c->graphs)
-    for (auto& g : variant) {
-      if (g.exec) (void)hipGraphExecDestroy(g.exec);
-      if (g.graph) (void)hipGraphDestroy(g.graph);
-    }
+  drop_graphs(c);
   if (c->pinned_res) (void)hipHostFree(c->pinned_res);
   for (auto& set : c->ev)
     for (auto& e : set)
@@ -196,6 +202,11 @@ void free_ctx(triaccel_ctx* c) {
 bool local_form(const triaccel_ctx& c) {
   return c.cfg.elementwise_scale != 1 && c.t.total_chunks < kLaunchBoundChunks && c.t.max_chunks_per_tensor <= kLocalMaxChunks;
 }
+
+// Whether a layer's storage size can change.  With tau_high <= 0 the precision rule chooses FP32 whatever the variance
+// (not negative, or NaN), so layers that are FP32 stay it, and the launches that rewrite a tensor at another size, idle on
+// every step, are left out: 1.5 us each.
+bool sizes_can_change(const triaccel_ctx& c) { return !(c.cfg.tau_high <= 0.0f && c.all_fp32); }
 
 // The kernels of one optimizer step, in order, on the handle's stream.  `ev` (eight events) records
 // the stage boundaries.  Order of the stages: the per-layer assignment needs only the gradient
@@ -209,6 +220,7 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   const bool fisher = h->cfg.curvature_source == 1;
   const bool elem = h->cfg.elementwise_scale == 1;
   const bool local = local_form(*h);
+  const bool resize = sizes_can_change(*h);
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
   TA_HIP(launch_grad_stats(T, sa, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
@@ -220,9 +232,10 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
     if (ev) TA_HIP(hipEventRecord(ev[4], s));
     TA_HIP(launch_update_local(T, sa, h->hp, any_probe, s));
     if (ev) TA_HIP(hipEventRecord(ev[5], s));
-    if (!any_probe) TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
+    if (!any_probe && resize)
+      TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
-    if (any_probe) TA_HIP(launch_select_tail(T, sa, h->hp, true, s));
+    if (any_probe) TA_HIP(launch_select_tail(T, sa, h->hp, true, resize, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
     return TRIACCEL_OK;
   }
@@ -240,16 +253,16 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   if (elem && any_probe) {
     // element-wise step sizes need the final threshold: finish the mask and the selection first
     if (T.total_chunks < kLaunchBoundChunks) {
-      TA_HIP(launch_select_tail(T, sa, h->hp, false, s));
+      TA_HIP(launch_select_tail(T, sa, h->hp, false, false, s));
     } else {
       TA_HIP(launch_mask_pass(T, sa, s));
       TA_HIP(launch_select_finish(T, sa, beta_h, s));
     }
   }
   if (ev) TA_HIP(hipEventRecord(ev[4], s));
-  TA_HIP(launch_update(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, s));
+  TA_HIP(launch_update(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, resize, s));
   if (ev) TA_HIP(hipEventRecord(ev[5], s));
-  TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, s));
+  if (resize) TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
   if (any_probe && !elem) TA_HIP(launch_select_finish(T, sa, h->hp.beta_curv, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
@@ -388,6 +401,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     d.grad_dtype = t.grad_dtype;
     for (uint32_t k = 0; k < nc; ++k) chunks.push_back(ChunkRef{(uint32_t)i, k});
     if (nc > max_chunks) max_chunks = nc;
+    c->all_fp32 = (i == 0 || c->all_fp32) && t.param_dtype == TRIACCEL_FP32;
     c->numel[i] = t.numel;
     c->grad_dtype[i] = t.grad_dtype;
     LayerDev& ls = c->layer_host[i];
@@ -727,6 +741,11 @@ int triaccel_set_state(triaccel_handle h, const void* buf, int64_t size) {
   TA_HIP(hipMemcpy(h->t.glob, &g, sizeof(g), hipMemcpyHostToDevice));
   TA_HIP(hipMemcpy(h->t.layers, static_cast<const char*>(buf) + sizeof(hd), (size_t)h->n * sizeof(LayerDev),
                    hipMemcpyHostToDevice));
+  std::memcpy(h->layer_host.data(), static_cast<const char*>(buf) + sizeof(hd), (size_t)h->n * sizeof(LayerDev));
+  const bool could = sizes_can_change(*h);
+  h->all_fp32 = true;
+  for (const LayerDev& ls : h->layer_host) h->all_fp32 = h->all_fp32 && ls.code == TRIACCEL_FP32 && ls.prev_code == TRIACCEL_FP32;
+  if (sizes_can_change(*h) != could) drop_graphs(h);  // captured with the launches of the other case
   h->step_index = hd.step_index;
   h->next_batch = hd.next_batch;
   std::memset(h->pinned_res, 0, sizeof(GlobalDev));

@@ -37,12 +37,13 @@ hipError_t launch_curv_ema(const DeviceTables& t, const StepArg& sa, float beta_
 hipError_t launch_hist_pass(const DeviceTables& t, const StepArg& sa, int serial_rounds, hipStream_t s);
 hipError_t launch_select_finish(const DeviceTables& t, const StepArg& sa, float beta_h, hipStream_t s);
 hipError_t launch_layer(const DeviceTables& t, const StepArg& sa, const Hyper& hp, hipStream_t s);
-hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem,
+// `resize`: with launch 0 of the in-place resize.
+hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem, bool resize,
                          hipStream_t s);
 hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool any_probe, hipStream_t s);
-// `local`: after k_update_local, which settled most tensors' thresholds, and with launch 1 of the in-place resize (sets of
-// the local form: its plans have two launches at most).
-hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool local, hipStream_t s);
+// `local`: after k_update_local, which settled most tensors' thresholds; `resize`: with launch 1 of the in-place resize (sets
+// of the local form: its plans have two launches at most).
+hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool local, bool resize, hipStream_t s);
 hipError_t launch_mask_pass(const DeviceTables& t, const StepArg& sa, hipStream_t s);
 hipError_t launch_update_resize(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha,
                                 bool elem, hipStream_t s);

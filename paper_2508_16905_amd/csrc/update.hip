@@ -81,10 +81,10 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
   }
 }
 
-hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem,
+hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem, bool resize,
                          hipStream_t s) {
   const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
-  const ResizeGrid rg = resize_grid(plan, 0u, t.n_tensors, t.total_chunks < kResizeBigSet);
+  const ResizeGrid rg = resize ? resize_grid(plan, 0u, t.n_tensors, t.total_chunks < kResizeBigSet) : ResizeGrid{1u, 0u};
   const dim3 grid(t.total_chunks + rg.grid);
   const auto kernel = elem ? (mu != 0.0f ? k_update<true, true> : k_update<true, false>)
                            : (mu != 0.0f ? k_update<false, true> : k_update<false, false>);

@@ -257,13 +257,13 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
 
 static_assert((kResizeTopSmall << 6) >= kLocalMaxChunks && kLaunchBoundChunks <= kResizeBigSet,
               "one subtree stage: the resize of a set of the local form has two launches at most");
-hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool local, hipStream_t s) {
+hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool local, bool resize, hipStream_t s) {
   constexpr uint32_t kGroups = kFinishThreads / kThreads;
   const uint32_t all = (t.total_chunks + kGroups - 1) / kGroups, cap = t.persistent_grid / 8;  // one per CU
   const uint32_t mask_wgs = all < cap ? all : cap;
   const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
   ResizeGrid rg{1u, 0u};
-  if (local && plan.n_stages > 1) {
+  if (resize && plan.n_stages > 1) {
     rg = resize_grid(plan, 1u, t.n_tensors, true);
     if (rg.grid > cap) rg.grid = cap;
   }
