@@ -235,13 +235,15 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
     if (!any_probe && resize)
       TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
-    if (any_probe) TA_HIP(launch_select_tail(T, sa, h->hp, true, resize, s));
+    // (with short tensors only, select_local leaves nothing over and no resize has a second launch: 12 tensors of 100
+    // elements 17.4 -> 14.8 us a step without it)
+    if (any_probe && !T.all_small) TA_HIP(launch_select_tail(T, sa, h->hp, true, resize, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
     return TRIACCEL_OK;
   }
   TA_HIP(launch_layer(T, sa, h->hp, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
-  if (any_probe) {
+  if (any_probe && !T.all_small) {
     // fallback radix select: two rounds at full width (a first window, then a refinement or the
     // other side of a window that missed); rarer further rounds are made inside the second launch.
     // Each launch leaves at once when no tensor is (still) in histogram mode.
@@ -427,8 +429,10 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   T.total_chunks = (uint32_t)chunks.size();
   T.max_chunks_per_tensor = max_chunks;
   uint64_t cand_total = 0;
+  T.all_small = true;
   for (TensorDesc& d : c->desc) {
     const KeyLists lists = key_lists(d.numel);
+    T.all_small = T.all_small && lists.list_all;
     d.cand_offset = cand_total;
     d.cand_cap = lists.over_cap;
     d.sub_cap = lists.sub_cap;

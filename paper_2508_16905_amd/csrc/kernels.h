@@ -27,6 +27,7 @@ struct DeviceTables {
   uint32_t n_tensors;
   uint32_t total_chunks;
   uint32_t max_chunks_per_tensor;
+  bool all_small;            // no tensor is longer than kListAllMax: their keys always settle the thresholds
   bool keep_grads;           // the gradients of the set have at most kKeepBytes
   uint32_t persistent_grid;  // workgroups of the persistent streaming kernels
 };
