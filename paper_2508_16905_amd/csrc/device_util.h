@@ -166,21 +166,34 @@ __device__ __forceinline__ void reset_cand_counters(uint32_t* counters, uint32_t
 // by (chunk, wavefront), so wavefronts running at the same time use different counters; a tensor that lists all
 // its keys (at most 8 wavefronts' worth) has a list of full size for each of them and needs no atomic.
 // EfficientNet-B0 set, curvature kernel: 19.4 us with both the other way, 16.0 now.
-template <bool SHARED = false>
-__device__ __forceinline__ void append_candidates(uint32_t flags, const uint32_t (&h)[kRows][4], uint32_t ht, const Tail& tail, int64_t base,
-                                                  uint32_t chunk_index, uint32_t tensor, const TensorDesc& td,
-                                                  Candidate* cands, uint32_t* counters) {
-  if (!__any(flags != 0u)) return;  // uniform over the wavefront
+// In two parts, so that something else can be done while the counter's answer is under way.
+struct Appending {
+  uint32_t total, list, start;
+};
+__device__ __forceinline__ Appending append_begin(uint32_t flags, uint32_t chunk_index, uint32_t tensor, const TensorDesc& td,
+                                                  uint32_t* counters) {
+  Appending a{0, 0, 0};
+  if (!__any(flags != 0u)) return a;  // uniform over the wavefront
   const int tid = threadIdx.x & (kThreads - 1);
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  const uint32_t total = wave_sum((uint32_t)__popc(flags));
-  const uint32_t list = (chunk_index * (kThreads / kWave) + wave) % kCandLists;
-  uint32_t start = 0, fit = total, ostart = 0;
-  if (td.list_all) {
-    if (lane == 0) *cand_counter(counters, tensor, list) = total;
-  } else {
+  a.total = wave_sum((uint32_t)__popc(flags));
+  a.list = (chunk_index * (kThreads / kWave) + tid / kWave) % kCandLists;
+  if ((tid & (kWave - 1)) == 0) {
+    if (td.list_all) *cand_counter(counters, tensor, a.list) = a.total;
+    else a.start = atomicAdd(cand_counter(counters, tensor, a.list), a.total);
+  }
+  return a;
+}
+template <bool SHARED = false>
+__device__ __forceinline__ void append_end(const Appending& a, uint32_t flags, const uint32_t (&h)[kRows][4], uint32_t ht,
+                                           const Tail& tail, int64_t base, uint32_t tensor, const TensorDesc& td,
+                                           Candidate* cands, uint32_t* counters) {
+  if (a.total == 0) return;  // uniform over the wavefront
+  const int tid = threadIdx.x & (kThreads - 1);
+  const int lane = tid & (kWave - 1);
+  const uint32_t total = a.total, list = a.list;
+  uint32_t start = a.start, fit = total, ostart = 0;
+  if (!td.list_all) {
     if (lane == 0) {
-      start = atomicAdd(cand_counter(counters, tensor, list), total);
       fit = start < td.sub_cap ? min(total, td.sub_cap - start) : 0u;
       if (fit < total) ostart = atomicAdd(cand_counter(counters, tensor, kCandLists), total - fit);
     }
@@ -256,7 +269,7 @@ __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, u
   if (tkey >= list_lo) cflags |= kTailFlag;
   cflags ^= kflags;  // the kept keys are above list_lo too
   store_mask_flags<SHARED>(td, base, kflags, tail);
-  append_candidates<SHARED>(cflags, h, ht, tail, base, chunk_index, tensor, td, cands, counters);
+  append_end<SHARED>(append_begin(cflags, chunk_index, tensor, td, counters), cflags, h, ht, tail, base, tensor, td, cands, counters);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -100,6 +100,41 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
   }
 }
 
+// A chunk's record: keys above the band and zero keys, largest key, keys listed, and whether a sample was not finite, of
+// every lane, in a fixed order.  All threads of the workgroup call it.
+__device__ __forceinline__ void ema_record(const TensorDesc& td, int64_t base, uint32_t chunk_index, uint32_t above_zeros,
+                                           uint32_t maxkey, uint32_t listed, uint32_t nonfin,
+                                           EmaPartial* __restrict__ ema_partials) {
+  above_zeros = wave_sum(above_zeros);  // at most 4096 in either half: no carry between the halves
+  maxkey = wave_max(maxkey);
+  listed = wave_sum(listed);
+  const uint32_t anynf = __any(nonfin != 0u) ? 1u : 0u;
+  __shared__ uint32_t s_red[4][kThreads / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (lane == 0) {
+    s_red[0][wave] = above_zeros;
+    s_red[1][wave] = maxkey;
+    s_red[2][wave] = listed;
+    s_red[3][wave] = anynf;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t az = 0, mk = 0, ln = 0, nf = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) {
+      az += s_red[0][w];
+      mk = max(mk, s_red[1][w]);
+      ln += s_red[2][w];
+      nf |= s_red[3][w];
+    }
+    // elements past the end of the tensor were counted as zero keys
+    // (the seventeenth elements are a wavefront's, of which left % 4 exist)
+    const uint32_t left = (uint32_t)chunk_left(base, td.numel), rest = left & 3u;
+    const uint32_t past = kChunk - (left - rest) + (rest ? kWave - rest : 0u);
+    ema_partials[td.first_chunk + chunk_index] = EmaPartial{az - (past << 16), mk, ln, nf};
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Stage 2: curvature EMA (diagonal Hutchinson signal of Sec. 3.2), one workgroup per chunk.
 // Per element, fp32:  u = (z * hz) * inv_scale;  h = u on the tensor's first probe, else
@@ -122,8 +157,8 @@ template <int SRC>
 __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, float inv_scale, float beta_h,
                                           float omb_h, bool first, bool listing, uint32_t list_lo, uint32_t list_hi,
                                           uint32_t chunk_index, uint32_t tensor, Candidate* cands,
-                                          uint32_t* counters, uint32_t& above_zeros, uint32_t& maxkey,
-                                          uint32_t& listed, uint32_t& nonfin) {
+                                          uint32_t* counters, EmaPartial* __restrict__ ema_partials) {
+  uint32_t maxkey = 0, nonfin = 0;
   const uint32_t tid = threadIdx.x;
   constexpr int ZW = SRC < 0 ? 4 : kWords<SRC>;
   const void* const zp = chunk_of<ZW>(SRC < 0 ? static_cast<const void*>(td.z) : td.grad, base);
@@ -185,13 +220,17 @@ __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, fl
     store_tail<kFP32>(hp, tail, ht);
   }
   // zero keys in the high half, keys above the band in the low half
-  above_zeros = (zeros << 16) | (uint32_t)__popc(hflags);
+  const uint32_t above_zeros = (zeros << 16) | (uint32_t)__popc(hflags);
   const uint32_t cflags = lflags ^ hflags;  // a key at or above list_hi is above list_lo too
-  listed = (uint32_t)__popc(cflags);
+  const uint32_t listed = (uint32_t)__popc(cflags);
+  // the chunk's record is made while the list's counter answers
+  Appending app{0, 0, 0};
   if (listing) {
+    app = append_begin(cflags, chunk_index, tensor, td, counters);
     store_mask_flags(td, base, hflags, tail);
-    append_candidates(cflags, h, ht, tail, base, chunk_index, tensor, td, cands, counters);
   }
+  ema_record(td, base, chunk_index, above_zeros, maxkey, listed, nonfin, ema_partials);
+  if (listing) append_end(app, cflags, h, ht, tail, base, tensor, td, cands, counters);
 }
 
 // At most 6 wavefronts per SIMD: room for the loads of all rows to be under way at once.
@@ -220,10 +259,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const uint32_t list_lo = list_all ? 1u : listing ? band_lo : 0x80000000u;
   const uint32_t list_hi = list_all || !listing ? 0x80000000u : band_hi;
   const int64_t base = (int64_t)cr.index * kChunk;
-  uint32_t above_zeros = 0, maxkey = 0, listed = 0, nonfin = 0;
-#define TA_EMA(SRC_)                                                                                   \
-  ema_chunk<SRC_>(td, base, sc.inv_scale, beta_h, omb_h, first, listing, list_lo, list_hi, cr.index,   \
-                         cr.tensor, cands, counters, above_zeros, maxkey, listed, nonfin)
+#define TA_EMA(SRC_)                                                                                                  \
+  ema_chunk<SRC_>(td, base, sc.inv_scale, beta_h, omb_h, first, listing, list_lo, list_hi, cr.index, cr.tensor, cands, \
+                  counters, ema_partials)
   if constexpr (!FISHER) {
     TA_EMA(-1);
   } else {
@@ -234,35 +272,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
     }
   }
 #undef TA_EMA
-  // per-chunk record: fixed-order reduction over lanes and wavefronts, one plain store
-  above_zeros = wave_sum(above_zeros);  // at most 4096 in either half: no carry between the halves
-  maxkey = wave_max(maxkey);
-  listed = wave_sum(listed);
-  const uint32_t anynf = __any(nonfin != 0u) ? 1u : 0u;
-  __shared__ uint32_t s_red[4][kThreads / kWave];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (lane == 0) {
-    s_red[0][wave] = above_zeros;
-    s_red[1][wave] = maxkey;
-    s_red[2][wave] = listed;
-    s_red[3][wave] = anynf;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t az = 0, mk = 0, ln = 0, nf = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) {
-      az += s_red[0][w];
-      mk = max(mk, s_red[1][w]);
-      ln += s_red[2][w];
-      nf |= s_red[3][w];
-    }
-    // elements past the end of the tensor were counted as zero keys
-    // (the seventeenth elements are a wavefront's, of which left % 4 exist)
-    const uint32_t left = (uint32_t)chunk_left(base, td.numel), rest = left & 3u;
-    const uint32_t past = kChunk - (left - rest) + (rest ? kWave - rest : 0u);
-    ema_partials[td.first_chunk + cr.index] = EmaPartial{az - (past << 16), mk, ln, nf};
-  }
 }
 
 // ---------------------------------------------------------------------------------------------

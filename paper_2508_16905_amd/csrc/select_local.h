@@ -53,18 +53,24 @@ __device__ __forceinline__ EmaTotals ema_totals(const TensorDesc& td, const EmaP
 // has at most 64 keys, they are collected and every wavefront compares each with all.  One histogram normally does
 // (2048 bins over a predicted band, or over the two octaves below the largest key).  Returns false, and nothing else
 // happens, if there are fewer than r such keys (`check`; r is at least 1).
+// Only the first `used` keys of every thread are looked at (uniform): one that no thread holds costs five instructions
+// and a branch all the same.
 template <int KEYS>
-__device__ __forceinline__ bool rank_select(const uint32_t (&key)[KEYS], uint32_t lo, uint32_t shift, uint32_t r, bool check,
-                                            LocalSelectShared& sh, uint32_t& theta) {
+__device__ __forceinline__ bool rank_select(const uint32_t (&key)[KEYS], uint32_t used, uint32_t lo, uint32_t shift, uint32_t r,
+                                            bool check, LocalSelectShared& sh, uint32_t& theta) {
+  const auto each_inside = [&](uint32_t from, uint32_t width_shift, auto f) {
+#pragma unroll
+    for (int i = 0; i < KEYS; ++i)
+      if ((uint32_t)(i & ~3) < used)
+        if (key[i] >= from && ((key[i] - from) >> width_shift) == 0u) f(key[i]);
+  };
   for (;;) {
     const uint32_t ns = shift > (uint32_t)kHistBits ? shift - kHistBits : 0u;
     const uint32_t bins = 1u << (shift - ns);
     for (uint32_t b = threadIdx.x * 4; b < kHistBins; b += kThreads * 4) *reinterpret_cast<v4u*>(&sh.hist[b]) = v4u{0, 0, 0, 0};
     if (threadIdx.x == 0) sh.n_few = 0;
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < KEYS; ++i)
-      if (key[i] >= lo && ((key[i] - lo) >> shift) == 0u) atomicAdd(&sh.hist[(key[i] - lo) >> ns], 1u);
+    each_inside(lo, shift, [&](uint32_t k) { atomicAdd(&sh.hist[(k - lo) >> ns], 1u); });
     __syncthreads();
     const BinHit hit = find_rank_from_top<kThreads>(sh.hist, bins, r, sh.part, sh.out);
     if (check) {
@@ -82,9 +88,7 @@ __device__ __forceinline__ bool rank_select(const uint32_t (&key)[KEYS], uint32_
       return true;
     }
     if (uniform(hit.count) > (uint32_t)kWave) continue;
-#pragma unroll
-    for (int i = 0; i < KEYS; ++i)
-      if (key[i] >= lo && ((key[i] - lo) >> shift) == 0u) sh.few[atomicAdd(&sh.n_few, 1u)] = key[i];
+    each_inside(lo, shift, [&](uint32_t k) { sh.few[atomicAdd(&sh.n_few, 1u)] = k; });
     __syncthreads();
     const uint32_t n = uniform(sh.n_few), lane = threadIdx.x & (kWave - 1);
     const uint32_t mine = lane < n ? sh.few[lane] : 0u;
@@ -127,33 +131,36 @@ __device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __res
   if (threadIdx.x == 0) sh.kept = 0;
   EmaTotals e;
   if (td.list_all) {
-    uint32_t key[kLocalKeys + 1];
-    uint32_t (&h0)[kRows][4] = *reinterpret_cast<uint32_t(*)[kRows][4]>(&key[0]);
-    uint32_t (&h1)[kRows][4] = *reinterpret_cast<uint32_t(*)[kRows][4]>(&key[kRows * 4]);
+    // the tail's key first, then the rows of the two chunks
+    uint32_t key[4 + kLocalKeys];
+    uint32_t (&h0)[kRows][4] = *reinterpret_cast<uint32_t(*)[kRows][4]>(&key[4]);
+    uint32_t (&h1)[kRows][4] = *reinterpret_cast<uint32_t(*)[kRows][4]>(&key[4 + kRows * 4]);
     const int32_t left0 = chunk_left(0, td.numel), left1 = td.numel > kChunk ? chunk_left(kChunk, td.numel) : 0;
     const Tail tail0 = tail_of(left0, threadIdx.x), tail1 = tail_of(left1, threadIdx.x);
     uint32_t tail = load_chunk<4>(td.curv, left0, tail0, h0);
     tail |= load_chunk<4>(chunk_of<4>(static_cast<const void*>(td.curv), kChunk), left1, tail1, h1);  // of one of the two
-    key[kLocalKeys] = tail;
+    key[0] = tail;
+    key[1] = key[2] = key[3] = 0;
+    const uint32_t used = 4u + 4u * (((uint32_t)td.numel + kRowElems - 1u) / kRowElems);
     e = ema_totals(td, ema_partials, shl);
 #pragma unroll
-    for (int i = 0; i <= kLocalKeys; ++i) key[i] &= 0x7fffffffu;
+    for (int i = 0; i < 4 + kLocalKeys; ++i) key[i] &= 0x7fffffffu;
     const uint32_t nonzero = (uint32_t)td.numel - e.zeros;
     if (k <= nonzero) {
       const uint32_t span = (uint32_t)kHistBins << kFirstShift;
       const bool low = e.maxkey < span;
       // keys are at least 1 here, and none exceeds the largest
-      if (!rank_select(key, low ? 1u : e.maxkey + 1u - span, kHistBits + kFirstShift, k, true, sh, theta))
-        rank_select(key, 1u, 31u, k, false, sh, theta);
+      if (!rank_select(key, used, low ? 1u : e.maxkey + 1u - span, kHistBits + kFirstShift, k, true, sh, theta))
+        rank_select(key, used, 1u, 31u, k, false, sh, theta);
     }
     const uint32_t from = max(theta, 1u);
     uint32_t f0 = 0, f1 = 0;
 #pragma unroll
     for (int i = 0; i < kRows * 4; ++i) {
-      f0 |= key[i] >= from ? 1u << i : 0u;
-      f1 |= key[kRows * 4 + i] >= from ? 1u << i : 0u;
+      f0 |= key[4 + i] >= from ? 1u << i : 0u;
+      f1 |= key[4 + kRows * 4 + i] >= from ? 1u << i : 0u;
     }
-    if (key[kLocalKeys] >= from) {
+    if (key[0] >= from) {
       if (tail0.mine) f0 |= kTailFlag;
       else f1 |= kTailFlag;
     }
@@ -203,7 +210,7 @@ __device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __res
     const uint32_t width = now.band_hi - now.band_lo;
     above = e.above;
     // band_lo is at least 1: a place without a key is in no range
-    rank_select(key, now.band_lo, width > 1u ? 32u - (uint32_t)__clz(width - 1u) : 0u, k - above, false, sh, theta);
+    rank_select(key, (inside + kThreads - 1) / kThreads, now.band_lo, width > 1u ? 32u - (uint32_t)__clz(width - 1u) : 0u, k - above, false, sh, theta);
     // listed keys had their bits left clear: set those at or above theta
     uint32_t kept = 0;
 #pragma unroll
