@@ -28,54 +28,63 @@ template <int K, bool FULL, bool KEEP>
 __device__ __forceinline__ void gram_chunk(const PowerDesc& pd, int64_t numel, int64_t base, double (&g)[K * (K + 1) / 2],
                                            double (&c)[K], double (&d)[K]) {
   // the products are read again by the apply pass: KEEP leaves them in the caches (figures at kKeepBytes)
-  // one row at a time: the 2k loads of a row are in flight together, and the accumulators leave
-  // room for several wavefronts per SIMD to overlap their loads with the fp64 arithmetic
-#pragma unroll 1
-  for (int r = 0; r < kRows; ++r) {
-    const int64_t at = base + (int64_t)r * kRowElems;
-    const int32_t left = FULL ? kRowElems : chunk_left(at, numel);
-    if (!FULL && left <= 0) break;
-    const float* const up = pd.u + at;
-    const float* const wp = pd.hu + at;
-    uint32_t u[K][4], w[K][4];
+  // the 2k loads of R rows are in flight together, and the accumulators leave room for several wavefronts per SIMD to
+  // overlap their loads with the fp64 arithmetic (one row, and R: 1000 chunks, k = 1 24.1 and 20.0 us an iteration, k = 2
+  // 32.5 and 30.4; 400 chunks, k = 1 12.5 and 11.7; 6000 chunks, k = 3 202 and 190, k = 4 the same)
+  const auto add = [&](const uint32_t (&ub)[K], const uint32_t (&wb)[K]) {
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      load_row4<FULL>(up + (int64_t)j * pd.stride, threadIdx.x, left, u[j]);
-      load_row4<FULL, KEEP>(wp + (int64_t)j * pd.stride, threadIdx.x, left, w[j]);
+      const double wj = (double)u2f(wb[j]), uj = (double)u2f(ub[j]);
+      c[j] = fma(uj, wj, c[j]);
+      d[j] = fma(uj, uj, d[j]);
+#pragma unroll
+      for (int i = 0; i <= j; ++i) g[tri(i, j)] = fma((double)u2f(wb[i]), wj, g[tri(i, j)]);
     }
-    const auto add = [&](const uint32_t (&ub)[K], const uint32_t (&wb)[K]) {
+  };
+  constexpr int R = K <= 2 ? 4 : K <= 4 ? 2 : 1;
+  static_assert(kRows % R == 0, "whole steps");
+#pragma unroll 1
+  for (int r0 = 0; r0 < kRows; r0 += R) {
+    if (!FULL && chunk_left(base + (int64_t)r0 * kRowElems, numel) <= 0) break;
+    uint32_t u[R][K][4], w[R][K][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int64_t at = base + (int64_t)(r0 + r) * kRowElems;
+      const int32_t left = FULL ? kRowElems : chunk_left(at, numel);
 #pragma unroll
       for (int j = 0; j < K; ++j) {
-        const double wj = (double)u2f(wb[j]), uj = (double)u2f(ub[j]);
-        c[j] = fma(uj, wj, c[j]);
-        d[j] = fma(uj, uj, d[j]);
-#pragma unroll
-        for (int i = 0; i <= j; ++i) g[tri(i, j)] = fma((double)u2f(wb[i]), wj, g[tri(i, j)]);
+        load_row4<FULL>(pd.u + at + (int64_t)j * pd.stride, threadIdx.x, left, u[r][j]);
+        load_row4<FULL, KEEP>(pd.hu + at + (int64_t)j * pd.stride, threadIdx.x, left, w[r][j]);
       }
-    };
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint32_t ub[K], wb[K];
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        ub[j] = u[j][e];
-        wb[j] = w[j][e];
-      }
-      add(ub, wb);
-      // one element's conversions to double at a time: those of all four took 80 registers more
-      __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (!FULL) {
-      const Tail tail = tail_of(left, threadIdx.x);
-      if (tail.any && left < kRowElems) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
         uint32_t ub[K], wb[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-          ub[j] = load_tail<4>(up + (int64_t)j * pd.stride, tail);
-          wb[j] = load_tail<4>(wp + (int64_t)j * pd.stride, tail);
+          ub[j] = u[r][j][e];
+          wb[j] = w[r][j][e];
         }
         add(ub, wb);
+        // one element's conversions to double at a time: those of all four took 80 registers more
+        __builtin_amdgcn_sched_barrier(0);
       }
+    }
+  }
+  if constexpr (!FULL) {
+    const float* const up = pd.u + base;
+    const float* const wp = pd.hu + base;
+    const Tail tail = tail_of(chunk_left(base, numel), threadIdx.x);
+    if (tail.any) {
+      uint32_t ub[K], wb[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        ub[j] = load_tail<4>(up + (int64_t)j * pd.stride, tail);
+        wb[j] = load_tail<4>(wp + (int64_t)j * pd.stride, tail);
+      }
+      add(ub, wb);
     }
   }
 }
@@ -143,8 +152,10 @@ __device__ __forceinline__ double from_lane(double v, int src) {
 // Bound by chains of fp64 divisions and square roots of some 200 cycles each: a column at a time by one thread there were
 // 55 of them one after the other at k = 5 and 110 at k = 8, here 4 and a few for each of the k steps.  ResNet-18 set,
 // k = 5: the call 147.2 -> 145.1 us; 3 M parameters, k = 8: 84.2 -> 78.8; 11 tensors of 60 elements, k = 8: 22.6 -> 16.9.
+// (Sixteen wavefronts for the sums: a tensor of 144 segments 9 of them each, in one or two batches of loads.)
+constexpr int kLayerThreads = 1024;
 template <int K>
-__global__ __launch_bounds__(kThreads) void k_power_layer(const TensorDesc* __restrict__ tds,
+__global__ __launch_bounds__(kLayerThreads) void k_power_layer(const TensorDesc* __restrict__ tds,
                                                           const uint32_t* __restrict__ seg_first,
                                                           uint32_t seg, const double* __restrict__ partials,
                                                           PowerLayer* state, LayerDev* layers, int latch) {
@@ -157,12 +168,15 @@ __global__ __launch_bounds__(kThreads) void k_power_layer(const TensorDesc* __re
   double acc = 0.0;
   if (e < PP)
 #pragma unroll 8
-    for (uint32_t s = part; s < n_segs; s += kThreads / kWave) acc += p[(size_t)s * PP + e];
-  __shared__ double s_acc[kThreads / kWave][kWave];
+    for (uint32_t s = part; s < n_segs; s += kLayerThreads / kWave) acc += p[(size_t)s * PP + e];
+  __shared__ double s_acc[kLayerThreads / kWave][kWave];
   s_acc[part][e] = acc;
   __syncthreads();
   if (part != 0) return;
-  const auto total = [&](int t) { return ((s_acc[0][t] + s_acc[1][t]) + s_acc[2][t]) + s_acc[3][t]; };
+  double sum = 0.0;
+#pragma unroll
+  for (int q = 0; q < kLayerThreads / kWave; ++q) sum += s_acc[q][e];
+  const auto total = [&](int t) { return from_lane(sum, t); };
   PowerLayer& st = state[l];
   // quotients, residuals ||w - lambda u|| / ||u|| and norms from the sums (zero iterate: both 0): lane j, vector j
   {
@@ -191,7 +205,8 @@ __global__ __launch_bounds__(kThreads) void k_power_layer(const TensorDesc* __re
   // products the order of the subtractions is that of the left-looking forms
   const int i = e / N, j = e % N;
   const bool in = i <= j && j < K;
-  const double g = in ? total(tri(i, j)) : 0.0;
+  const double gram = total(in ? tri(i, j) : 0);
+  const double g = in ? gram : 0.0;
   double s = g, r = 0.0;      // s: G_ij less the products of the rows above
   double diag[K];             // R_pp, the same in all lanes
   uint32_t deficient = 0;
@@ -308,7 +323,7 @@ hipError_t launch_k(const PowerTables& t, const PowerDesc* descs, int latch, hip
                      t.seg, t.partials);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_power_layer<K>, dim3(t.n_tensors), dim3(kThreads), 0, s, t.tensors, t.seg_first, t.seg,
+  hipLaunchKernelGGL(k_power_layer<K>, dim3(t.n_tensors), dim3(kLayerThreads), 0, s, t.tensors, t.seg_first, t.seg,
                      t.partials, t.state, t.layers, latch);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return e;
