@@ -36,7 +36,8 @@ constexpr uint32_t kFirstShift = 13;         // first window without a predictio
 constexpr uint32_t kMinPredShift = 6;        // finest predicted window: 2048 bins of 64 keys
 constexpr uint32_t kUnknownPredErr = 1u << 16;  // assumed prediction error (keys) before any is measured
 constexpr uint32_t kCandCap = 262144;        // keys a tensor may list in total (entries)
-constexpr uint32_t kListAllMax = 8192;       // tensors up to this size list every non-zero key (no prediction)
+constexpr uint32_t kListAllMax = 8192;       // tensors up to this size list every non-zero key (no prediction), or
+                                             // have their keys read by select_local
 constexpr int kFinishRegs = 8;               // listed keys per thread the finish kernel can hold in registers
 constexpr uint32_t kCandLists = 64;          // sub-lists per tensor (plus one overflow list)
 constexpr uint32_t kCandCounterStride = 32;  // words between list counters: one 128-byte line each

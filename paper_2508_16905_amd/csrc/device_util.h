@@ -160,7 +160,7 @@ __device__ __forceinline__ void reset_cand_counters(uint32_t* counters, uint32_t
   if (threadIdx.x <= kCandLists) *cand_counter(counters, tensor, threadIdx.x) = 0;
 }
 
-// Append a wavefront's candidates of one chunk (flag bit e of `flags` = element e of the lane's 16) with one
+// Append a wavefront's candidates of one chunk (`flags`: as for the mask words) with one
 // atomic per wavefront.  Slots go element by element and lane by lane inside an element, so that the lanes of
 // a store write side by side (lane by lane first, a store of 64 keys touched 64 lines).  The sub-list is chosen
 // by (chunk, wavefront), so wavefronts running at the same time use different counters; a tensor that lists all

@@ -16,7 +16,8 @@ namespace triaccel {
 //     the listed keys resolve theta exactly and only their mask bits are patched.
 //   * Otherwise (no prediction yet, prediction off, too many keys to list) the tensor falls
 //     back to a radix select by histogram passes over h and a separate mask pass.
-//   * Tensors with at most kListAllMax elements list all their non-zero keys and select from the list.
+//   * Tensors with at most kListAllMax elements list all their non-zero keys and select from the list; in sets bound by
+//     their launches the keys are not listed but read from h (select_local).
 // ---------------------------------------------------------------------------------------------
 struct Window {
   uint32_t lo, shift, bins;

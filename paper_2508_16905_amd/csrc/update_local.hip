@@ -11,10 +11,9 @@ __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { re
 
 // Every workgroup of a chunk adds up its tensor's chunk records (at most kLocalMaxChunks x 32 bytes, from
 // the caches) and takes the layer's decisions itself, each the same ones, while the chunk's own data is on
-// the way.  No workgroup waits for another: the fields of the layer's record that the decisions read were
-// copied aside by the statistics kernel, so that the workgroup of chunk 0 may write the record while the others
-// run; the selection's plan (SelNow) is read from the record, and nothing writes those fields before the last
-// workgroup of a tensor in histogram mode has arrived.  (An arrival counter per
+// the way.  No workgroup waits for another: what the decisions and the selection read of the layer's record was
+// copied aside by the statistics kernel (LayerIn), so that the record may be written while the others
+// run.  (An arrival counter per
 // tensor instead, with the last workgroup writing, cost one atomic per chunk: with the counters side by side
 // in a cache line 20 ns each, 205 us instead of 35 on the ResNet-18 set.)
 //
