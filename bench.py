@@ -38,12 +38,12 @@ STEP_SOURCES = ("update.hip", "update_body.h", "resize_body.h", "resize_schedule
 POWER_SOURCES = ("power.hip", "power.h", "numerics.h")
 MEASURED_TRAFFIC = {
     # k_update<false, true>, default run of the large_streaming workload
-    "step": {"sources_sha256": "1388fc8c625e3aeba5548ce1f988e03a3d88a1846e661d59ad1f1dc985bf156a", "workload": "large_streaming",
+    "step": {"sources_sha256": "61a3660aaf46bccf2c4647a13187ebaf5cf39362a1fbd8f557d9f7a7c3772096", "workload": "large_streaming",
              "alg_bytes": 18991808512, "fetch_bytes": 11.677e9, "write_bytes": 7.348e9,
              "from": "profiles/fused_step_large_streaming_hbm_counters.md"},
     # k_power_apply<5> / k_power_gram<5>, --mode power on the large_streaming workload
-    "power": {"sources_sha256": "a2f4e4745fa9f210c4040dcbc8748f270fd146fd11b1e4c5a25dcaa33c3b452b", "workload": "large_streaming",
-              "k_power_apply": {"fetch_bytes": 21.51e9, "write_bytes": 21.47e9},
+    "power": {"sources_sha256": "79aff79de7d571d2366d1509da079e678f167db552a6d4745d4945e9157fe826", "workload": "large_streaming",
+              "k_power_apply": {"fetch_bytes": 21.51e9, "write_bytes": 21.48e9},
               "k_power_gram": {"fetch_bytes": 42.95e9, "write_bytes": 0.01e9},
               "from": "profiles/power_iteration_large_streaming_k5.md"},
 }
