@@ -89,7 +89,7 @@ struct triaccel_ctx {
   // refresh, [1][s] with; the kernels of a captured step hold the address of table copy s.
   StepGraph graphs[2][kTableSlots];
   // power iteration (only with cfg.power_k > 0)
-  PowerTables pt{};
+  PowerTables pt[2];  // for calls with at most kPowerFewK vectors, and with more: only their segments differ
   std::vector<PowerDesc> power_descs;
   PowerDesc* power_staging[kRing] = {};  // pinned, for calls with more than kPowerArgMax tensors
   hipEvent_t power_ev[kRing] = {};
@@ -481,34 +481,54 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     if (e != hipSuccess) return fail(hip_fail(e, "hipEventCreate"));
   }
   if (config->power_k > 0) {
-    // workspace of the power iteration: segment table, per-segment sums, per-layer records
-    std::vector<SegRef> segs;
-    std::vector<uint32_t> seg_first((size_t)n);
-    const uint32_t seg = power_seg(T.total_chunks, config->power_k);
-    for (int32_t i = 0; i < n; ++i) {
-      seg_first[i] = (uint32_t)segs.size();
-      const uint32_t ns = (c->desc[i].n_chunks + seg - 1) / seg;
-      for (uint32_t k = 0; k < ns; ++k) segs.push_back(SegRef{(uint32_t)i, k});
-    }
-    PowerTables& P = c->pt;
-    P.tensors = T.tensors;
-    P.chunks = T.chunks;
-    P.layers = T.layers;
-    P.n_tensors = (uint32_t)n;
-    P.total_chunks = T.total_chunks;
-    P.total_segs = (uint32_t)segs.size();
-    P.seg = seg;
+    // workspace of the power iteration: segment tables, per-segment sums, per-layer records
+    struct Segments {
+      std::vector<SegRef> segs;
+      std::vector<uint32_t> first;
+    } lists[2];
+    const int few = config->power_k < kPowerFewK ? config->power_k : kPowerFewK;
+    const int kinds = power_seg(T.total_chunks, few) != power_seg(T.total_chunks, config->power_k) ? 2 : 1;
     Workspace pws;
+    size_t partials = 0;
+    for (int v = 0; v < kinds; ++v) {
+      Segments& list = lists[v];
+      PowerTables& P = c->pt[v];
+      P.tensors = T.tensors;
+      P.chunks = T.chunks;
+      P.layers = T.layers;
+      P.n_tensors = (uint32_t)n;
+      P.total_chunks = T.total_chunks;
+      const int most = v + 1 < kinds ? few : config->power_k;  // vectors of the calls that use these tables
+      P.seg = power_seg(T.total_chunks, most);
+      for (int32_t i = 0; i < n; ++i) {
+        list.first.push_back((uint32_t)list.segs.size());
+        const uint32_t ns = (c->desc[i].n_chunks + P.seg - 1) / P.seg;
+        for (uint32_t k = 0; k < ns; ++k) list.segs.push_back(SegRef{(uint32_t)i, k});
+      }
+      P.total_segs = (uint32_t)list.segs.size();
+      pws.add(&P.segs, list.segs.size());
+      pws.add(&P.seg_first, (size_t)n);
+      const size_t need = list.segs.size() * (size_t)power_partial_len(most);
+      if (need > partials) partials = need;
+    }
+    PowerTables& P = c->pt[0];
     pws.add(&P.descs, (size_t)n);
-    pws.add(&P.segs, segs.size());
-    pws.add(&P.seg_first, (size_t)n);
-    pws.add(&P.partials, segs.size() * (size_t)power_partial_len(config->power_k));
+    pws.add(&P.partials, partials);
     pws.add(&P.state, (size_t)n);
     if ((rc = pws.allocate(c))) return fail(rc);
-    e = hipMemcpy(P.segs, segs.data(), segs.size() * sizeof(SegRef), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segments)"));
-    e = hipMemcpy(P.seg_first, seg_first.data(), (size_t)n * sizeof(uint32_t), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segment index)"));
+    for (int v = 0; v < kinds; ++v) {
+      e = hipMemcpy(c->pt[v].segs, lists[v].segs.data(), lists[v].segs.size() * sizeof(SegRef), hipMemcpyHostToDevice);
+      if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segments)"));
+      e = hipMemcpy(c->pt[v].seg_first, lists[v].first.data(), (size_t)n * sizeof(uint32_t), hipMemcpyHostToDevice);
+      if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(segment index)"));
+    }
+    if (kinds == 1) {
+      c->pt[1] = P;
+    } else {
+      c->pt[1].descs = P.descs;
+      c->pt[1].partials = P.partials;
+      c->pt[1].state = P.state;
+    }
     for (int i = 0; i < kRing && (uint32_t)n > kPowerArgMax; ++i) {
       e = hipHostMalloc(reinterpret_cast<void**>(&c->power_staging[i]), (size_t)n * sizeof(PowerDesc), hipHostMallocDefault);
       if (e != hipSuccess) return fail(hip_fail(e, "hipHostMalloc(power staging)"));
@@ -781,7 +801,7 @@ int triaccel_power_iter(triaccel_handle h, const triaccel_power_tensor* vectors,
       const int slot = h->power_pos;
       if (h->power_used[slot]) TA_HIP(hipEventSynchronize(h->power_ev[slot]));
       std::memcpy(h->power_staging[slot], args, (size_t)n * sizeof(PowerDesc));
-      TA_HIP(hipMemcpyAsync(h->pt.descs, h->power_staging[slot], (size_t)n * sizeof(PowerDesc), hipMemcpyHostToDevice,
+      TA_HIP(hipMemcpyAsync(h->pt[0].descs, h->power_staging[slot], (size_t)n * sizeof(PowerDesc), hipMemcpyHostToDevice,
                             h->stream));
       TA_HIP(hipEventRecord(h->power_ev[slot], h->stream));
       h->power_used[slot] = true;
@@ -792,7 +812,7 @@ int triaccel_power_iter(triaccel_handle h, const triaccel_power_tensor* vectors,
   if (h->profiling)
     for (auto& e : h->power_prof)
       if (!e) TA_HIP(hipEventCreate(&e));
-  TA_HIP(launch_power_iter(h->pt, args, k, latch ? 1 : 0, h->stream, h->profiling ? h->power_prof : nullptr));
+  TA_HIP(launch_power_iter(h->pt[k <= kPowerFewK ? 0 : 1], args, k, latch ? 1 : 0, h->stream, h->profiling ? h->power_prof : nullptr));
   h->power_timed = h->profiling;
   h->power_called = true;
   return TRIACCEL_OK;
@@ -841,7 +861,7 @@ int triaccel_power_state(triaccel_handle h, triaccel_power_info* out, int32_t n)
   if ((uint32_t)n != h->n) return TRIACCEL_E_SHAPE_MISMATCH;
   if (h->cfg.power_k == 0 || !h->power_called) return TRIACCEL_E_NOT_INITIALISED;
   TA_HIP(hipStreamSynchronize(h->stream));
-  TA_HIP(hipMemcpy(h->power_host.data(), h->pt.state, (size_t)n * sizeof(PowerLayer), hipMemcpyDeviceToHost));
+  TA_HIP(hipMemcpy(h->power_host.data(), h->pt[0].state, (size_t)n * sizeof(PowerLayer), hipMemcpyDeviceToHost));
   TA_HIP(hipMemcpy(h->layer_host.data(), h->t.layers, (size_t)n * sizeof(LayerDev), hipMemcpyDeviceToHost));
   for (int32_t i = 0; i < n; ++i) {
     const PowerLayer& p = h->power_host[i];

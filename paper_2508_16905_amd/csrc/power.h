@@ -15,8 +15,11 @@ constexpr int kMaxPowerK = 8;  // vectors per layer the workspace can be sized f
 // and 49.1; 400: 13.8 and 19.9, 31.1 and 41.5, 50.9 and 60.5; 600: 15.3 and 22.0, 44.3 and 48.0, 72.3 and 70.8; 768:
 // 17.3 and 22.9, 51.9 and 53.9, 82.1 and 80.8; 1000: 19.8 and 24.5, 66.1 and 63.7, 101 and 96; 2700: 42.9 and 36.6,
 // 153 and 146, 246 and 244 (segments of 2 lie between the two).
+// k is the call's, in both entry points: the order of the sums, and with it the last bits of the result, is the same
+// with a handle of any size and without one.  A handle keeps the tables of both kinds of k if they differ.
+constexpr int kPowerFewK = 5;
 constexpr uint32_t power_seg(uint32_t total_chunks, int k) {
-  return total_chunks <= (k <= 5 ? 768u : 512u) ? 1u : total_chunks < 16384 ? 4u : 8u;
+  return total_chunks <= (k <= kPowerFewK ? 768u : 512u) ? 1u : total_chunks < 16384 ? 4u : 8u;
 }
 
 // Doubles one workgroup of the Gram pass leaves for k vectors: the upper triangle of W^T W
