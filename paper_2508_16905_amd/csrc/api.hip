@@ -437,7 +437,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     d.cand_cap = lists.over_cap;
     d.sub_cap = lists.sub_cap;
     d.list_all = lists.list_all;
-    if (!d.list_all || !local_form(*c)) cand_total += lists.entries;  // (select_local reads a small tensor's keys itself)
+    cand_total += lists.entries;
   }
   uint64_t grad_bytes = 0;
   for (int32_t i = 0; i < n; ++i) grad_bytes += (uint64_t)tensors[i].numel * (tensors[i].grad_dtype == TRIACCEL_FP32 ? 4u : 2u);

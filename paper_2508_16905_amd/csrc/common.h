@@ -85,6 +85,15 @@ inline KeyLists key_lists(int64_t numel) {
 // the call then pays and the traffic after it saves, all of it after a step, half of it after a power iteration.
 constexpr uint64_t kKeepBytes = 2ull << 30;
 
+// Sets of the local form with at most this many chunks (4.2 M elements): if a probed step had a tensor whose selection needs
+// k_select_tail (more listed keys than select_local holds, or histograms), the next probed step leaves all selections to
+// that launch, which takes its time anyway; small tensors list their keys for it.  select_local takes 11 to 15 us for a
+// tensor of some thousand elements: more than a short update, while a longer one covers it.  A step, us, without and with:
+// thresholds that move by up to 12 % (more listed keys), 41 tensors of 1.0 M 44.2 and 37.3, of 2.0 M 59.4 and 54.3, 213 of
+// 4.0 M 74.2 and 73.0, 20 of 5.0 M 126.3 and 127.5; curvature that jumps by a factor of 4000 (histograms), 10 tensors of
+// 0.5 M 122.7 and 115.2, 41 of 1.0 M 120.4 and 114.8, of 2.0 M 213.0 and 206.1, 60 of 12 M 298 and 303.
+constexpr uint32_t kLateChunks = 1024;
+
 enum SelMode : uint32_t {
   kSelHist = 0,   // a histogram over the window is (being) accumulated; the scan decides what next
   kSelCand = 1,   // theta lies in [rng_lo, rng_hi): few enough keys there to list them
@@ -193,6 +202,8 @@ struct GlobalDev {
   uint32_t trans_count[2]; // number of tensors whose storage size changes (double-buffered by step parity)
   uint32_t hist_pending[2];// tensors still in histogram mode this step (same double buffering)
   uint32_t mask_pending[2];// tensors whose mask the EMA kernel did not settle this step
+  uint32_t select_late;    // the last probed step had a selection that needs k_select_tail (written by that kernel)
+  uint64_t late_epoch;     // step_id at which select_local last found such a selection
   // result record
   int32_t res_skipped;
   float res_next_scale;

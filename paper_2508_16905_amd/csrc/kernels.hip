@@ -243,17 +243,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
   const StepScalars sc = step_scalars(sa);
   // the skip word travels together with the tables: its latency is not one more before the data's
   const uint64_t skip_epoch = glob->skip_epoch;
+  const uint32_t late = glob->select_late;
   const ChunkRef cr = chunks[blockIdx.x];
   const TensorDesc td = tds[cr.tensor];
   const LayerDev& ls = layers[cr.tensor];
   const uint32_t probes_seen = ls.probes_seen, use_band = ls.use_band, band_lo = ls.band_lo, band_hi = ls.band_hi;
   TA_LOADED("s"(td.grad), "s"(td.z), "s"(td.hz), "s"(td.curv), "s"(td.mask), "s"(td.numel), "s"(td.grad_dtype),
             "s"(td.has_probe), "s"(td.list_all), "s"(td.first_chunk), "s"(td.cand_offset), "s"(probes_seen), "s"(use_band), "s"(band_lo),
-            "s"(band_hi));
+            "s"(band_hi), "s"(late));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
   const bool first = probes_seen == 0;
-  // a small tensor's keys are listed, all of them, or left to select_local, which reads them where they lie
-  const bool list_all = td.list_all != 0 && list_small != 0;
+  // a small tensor's keys are listed, all of them, or left to select_local, which reads them where they lie (`late`: it
+  // leaves them to k_select_tail at this step)
+  const bool list_all = td.list_all != 0 && (list_small | (int)late) != 0;
   const bool listing = list_all || (td.list_all == 0 && use_band != 0);
   // band_lo >= 1 and band_hi <= 0x7f800000, so key 0 is never in a range; no key reaches 2^31
   const uint32_t list_lo = list_all ? 1u : listing ? band_lo : 0x80000000u;

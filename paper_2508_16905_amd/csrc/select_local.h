@@ -107,7 +107,8 @@ __device__ __forceinline__ bool rank_select(const uint32_t (&key)[KEYS], uint32_
 // One workgroup settles tensor l if its listed keys, or its own if it is small, settle the threshold.  A tensor of
 // up to kListAllMax elements is read whole, chunk by chunk as the curvature kernel wrote it (which lists nothing of it
 // and leaves its mask to this function); of a larger one the keys of the band are listed.  More of these than the
-// registers hold are left to k_select_tail, and so are tensors that need histograms over h.
+// registers hold are left to k_select_tail, and so are tensors that need histograms over h; both are noted for the next
+// probed step, which on short sets leaves everything to that launch (kLateChunks; `late`: this is such a step).
 //
 // Beside the streaming workgroups every dependent access takes about 3 us instead of 0.7, so there are few of them:
 // tables, records and list lengths; keys; then only stores.  (An earlier form with lists re-read in every pass took 100
@@ -117,6 +118,7 @@ __device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __res
                                              const Candidate* __restrict__ cands, uint32_t* counters, const StepScalars& sc,
                                              const Hyper& hp, LayerShared& shl, LocalSelectShared& sh) {
   const uint64_t skip_epoch = glob->skip_epoch;
+  const uint32_t late = glob->select_late;
   const TensorDesc td = tds[l];
   LayerDev& ls = layers[l];
   const SelNow now = inputs[l].plan;
@@ -124,13 +126,13 @@ __device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __res
   uint32_t listed_here = 0;
   if (threadIdx.x <= kCandLists) listed_here = *cand_counter(counters, l, threadIdx.x);
   TA_LOADED("s"(td.mask), "s"(td.curv), "s"(td.numel), "s"(td.has_probe), "s"(td.list_all), "s"(td.first_chunk), "s"(td.n_chunks),
-            "s"(now.use_band), "s"(now.band_lo), "s"(in.probes_seen), "s"(in.var_hold));
+            "s"(now.use_band), "s"(now.band_lo), "s"(in.probes_seen), "s"(in.var_hold), "s"(late));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
   const uint32_t k = topk_count(td.numel, hp.sparsity_ppm, hp.topk_abs);
   uint32_t theta = 0, nnz = 0, above = 0;
   if (threadIdx.x == 0) sh.kept = 0;
   EmaTotals e;
-  if (td.list_all) {
+  if (td.list_all && !late) {
     // the tail's key first, then the rows of the two chunks
     uint32_t key[4 + kLocalKeys];
     uint32_t (&h0)[kRows][4] = *reinterpret_cast<uint32_t(*)[kRows][4]>(&key[4]);
@@ -171,7 +173,18 @@ __device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __res
     if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&sh.kept, kept);
   } else {
     e = ema_totals(td, ema_partials, shl);
-    if (select_outcome(td, now, e, k) != kOutListed) return;
+    const bool listed = select_outcome(td, now, e, k) == kOutListed;
+    const bool fits = listed && e.listed <= (uint32_t)(kThreads * kLocalListed);  // (if so, no list has dropped a key)
+    if (!fits || late) {
+      if (threadIdx.x == 0) {
+        if (!fits && !td.list_all) glob->late_epoch = sc.step_id;
+        if (listed) {
+          select_setup(td, ls, glob, now, e, k, kOutListed, sc.step_id);
+          atomicAdd(&glob->mask_pending[sc.step_id & 1u], 1u);
+        }
+      }
+      return;
+    }
     // lengths and first places of the lists in a flat numbering of the listed keys
     if (threadIdx.x <= kCandLists) sh.counts[threadIdx.x] = min(listed_here, threadIdx.x < kCandLists ? td.sub_cap : td.cand_cap);
     if (threadIdx.x < kWave) {
@@ -180,14 +193,7 @@ __device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __res
       sh.prefix[threadIdx.x + 1] = incl;
     }
     __syncthreads();
-    const uint32_t inside = uniform(sh.prefix[kCandLists] + sh.counts[kCandLists]);
-    if (inside > (uint32_t)(kThreads * kLocalListed)) {
-      if (threadIdx.x == 0) {
-        select_setup(td, ls, glob, now, e, k, kOutListed, sc.step_id);
-        atomicAdd(&glob->mask_pending[sc.step_id & 1u], 1u);
-      }
-      return;
-    }
+    const uint32_t inside = e.listed;
     uint32_t key[kLocalListed], idx[kLocalListed];
 #pragma unroll
     for (int i = 0; i < kLocalListed; ++i) {

@@ -161,7 +161,7 @@ hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const H
 
 // What is left of the selection after k_update_local, and before the element-wise form of the update on sets
 // of that size (one launch for the mask pass and the threshold resolution).  Workgroup l < n_tensors settles tensor l if its
-// listed keys suffice (after k_update_local: if they were too many for select_local).  The `mask_wgs` workgroups after
+// listed keys suffice (after k_update_local: if select_local left them).  The `mask_wgs` workgroups after
 // those make the mask pass of the other tensors, four chunks at a
 // time, and the last workgroup to finish a part of such a tensor settles it among the keys the pass listed; the
 // rest take launch 1 of the in-place resize, four chunks of a level at a time.  After k_update_local all of them leave
@@ -169,7 +169,7 @@ hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const H
 template <bool MOM>
 __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc* __restrict__ tds,
                                                                 const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
-                                                                uint32_t n_tensors, LayerDev* layers, const GlobalDev* glob,
+                                                                uint32_t n_tensors, LayerDev* layers, GlobalDev* glob,
                                                                 Candidate* cands, uint32_t* counters, uint32_t* arrived,
                                                                 uint32_t mask_wgs, const uint32_t* trans_list,
                                                                 ResizePlan plan, char* scratch, uint32_t resize_slots,
@@ -179,10 +179,15 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
   const StepScalars sc = step_scalars(sa);
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
+  const uint64_t late_epoch = glob->late_epoch;
+  const uint32_t late = glob->select_late;
   if (blockIdx.x < n_tensors) {
     if (local) {
-      TA_LOADED("s"(skip_epoch), "s"(pending));
-      if (pending == 0 || skip_epoch == sc.step_id) return;
+      const uint32_t next = late_epoch == sc.step_id && total_chunks <= kLateChunks ? 1u : 0u;
+      TA_LOADED("s"(skip_epoch), "s"(pending), "s"(late_epoch), "s"(late));
+      if (skip_epoch == sc.step_id) return;
+      if (late != next && blockIdx.x == 0 && threadIdx.x == 0) glob->select_late = next;
+      if (pending == 0) return;
     }
     const uint32_t l = blockIdx.x;
     const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
