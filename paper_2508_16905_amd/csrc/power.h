@@ -8,18 +8,29 @@
 namespace triaccel {
 
 constexpr int kMaxPowerK = 8;  // vectors per layer the workspace can be sized for
-// Chunks of one tensor that one workgroup of the Gram pass sums, for k vectors.  Sets that fit the chip with a workgroup
-// for every chunk (768 at k = 5) get one: the rows of a segment follow one after the other.  Above that segments of 4,
-// and of 8 from 16,384 chunks, where more partial sums to add per tensor cost more than the shorter segments gain.
-// An iteration, us, with segments of 1 and 4 chunks: 200 chunks, k = 1 12.6 and 18.6, k = 5 20.8 and 34.6, k = 8 30.4
-// and 49.1; 400: 13.8 and 19.9, 31.1 and 41.5, 50.9 and 60.5; 600: 15.3 and 22.0, 44.3 and 48.0, 72.3 and 70.8; 768:
-// 17.3 and 22.9, 51.9 and 53.9, 82.1 and 80.8; 1000: 19.8 and 24.5, 66.1 and 63.7, 101 and 96; 2700: 42.9 and 36.6,
-// 153 and 146, 246 and 244 (segments of 2 lie between the two).
+// Chunks of one tensor that one workgroup of the Gram pass sums, for k vectors.  One, while segments of 4 would give a
+// compute unit hardly more than one workgroup: the rows of a segment follow one after the other.  Above that 4, and 8
+// from 16,384 chunks, as more partial sums to add per tensor cost more than the shorter segments gain.  The line is
+// where a set of one tensor, which has the most to add, gains nothing more.  With 7 and 8 vectors 512 workgroups fit
+// the chip (two wavefronts per SIMD; 768 and more with fewer vectors), and 700 to 900 of them leave a second round
+// nearly empty: 3 to 4 % lost, so the line is below that.
+// An iteration on 20 tensors, us, with segments of 4 and of 1 chunks:
+//   chunks   k = 1            k = 3            k = 5            k = 6            k = 8
+//   500      16.8 and 13.5    28.1 and 20.6    43.4 and 35.9    50.0 and 41.3    62.4 and 54.2
+//   640      17.1 and 14.3    32.3 and 26.2    48.3 and 43.5    56.1 and 52.4    71.9 and 71.7
+//   760      18.4 and 15.4    34.7 and 30.3    52.5 and 49.7    60.2 and 58.6    78.7 and 81.1
+//   900      19.7 and 16.2    39.4 and 36.6    60.7 and 58.0    68.8 and 68.1    91.1 and 93.4
+//   1200     22.8 and 17.6    51.6 and 45.7    80.2 and 72.1    95.3 and 88.8    126 and 115
+//   1500     25.1 and 22.1    57.7 and 55.1    91.0 and 87.0    108 and 103      142 and 140
+//   2800     39.0 and 36.1    94.4 and 95.8    150 and 151      181 and 181      257 and 248
+// One tensor of 1200 chunks: 23.0 and 22.3, 51.2 and 47.7, 75.9 and 73.8, 90.3 and 86.1, 120 and 112; of 1500: 26.1 and 25.9,
+// 55.9 and 58.8, 87.3 and 89.6, 103 and 105, 136 and 138; of 2800: 40.8 and 49.7, 93.8 and 105, 149 and 160, 178 and 188,
+// 239 and 248.  (Segments of 2 lie between the two.)
 // k is the call's, in both entry points: the order of the sums, and with it the last bits of the result, is the same
 // with a handle of any size and without one.  A handle keeps the tables of both kinds of k if they differ.
-constexpr int kPowerFewK = 5;
+constexpr int kPowerFewK = 6;
 constexpr uint32_t power_seg(uint32_t total_chunks, int k) {
-  return total_chunks <= (k <= kPowerFewK ? 768u : 512u) ? 1u : total_chunks < 16384 ? 4u : 8u;
+  return total_chunks <= (k <= kPowerFewK ? 1200u : 640u) ? 1u : total_chunks < 16384 ? 4u : 8u;
 }
 
 // Doubles one workgroup of the Gram pass leaves for k vectors: the upper triangle of W^T W

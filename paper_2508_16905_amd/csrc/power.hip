@@ -342,7 +342,7 @@ hipError_t launch_k(const PowerTables& t, const PowerDesc* descs, int latch, hip
 constexpr size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 constexpr size_t kStaticMaxSegs = kStaticMaxChunks / 8 + kStaticMaxTensors;
 static_assert(power_seg(16383, 8) == 4 && power_seg(kStaticMaxChunks, 8) == 8 && kStaticMaxChunks / 8 >= 16384 / 4 &&
-                  power_seg(769, 1) == 4,
+                  power_seg(1201, 1) == 4,
               "segments of any set fit the array");
 constexpr size_t kOffTensors = 0;
 constexpr size_t kOffDescs = kOffTensors + align256(sizeof(TensorDesc) * kStaticMaxTensors);

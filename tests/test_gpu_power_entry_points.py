@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.mark.parametrize("chunks", [3, 512, 513, 600, 768, 769, 1100])
-@pytest.mark.parametrize("sized,k", [(8, 2), (8, 5), (8, 8), (6, 3), (5, 2)])
+@pytest.mark.parametrize("chunks", [3, 512, 513, 640, 641, 768, 1200, 1201])
+@pytest.mark.parametrize("sized,k", [(8, 2), (8, 5), (8, 8), (7, 6), (6, 3), (5, 2)])
 def test_same_bits_from_both(sized, k, chunks):
     first = max(1, chunks // 2)
     numels = [first * 4096 - 5, (chunks - first - 2) * 4096 + 1, 100] if chunks > 8 else [4096, 4095, 777]

@@ -14,7 +14,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("entry", ["handle", "static"])
-@pytest.mark.parametrize("k,chunks", [(5, 768), (5, 769), (8, 512), (8, 513), (1, 768), (3, 3)])
+@pytest.mark.parametrize("k,chunks", [(5, 768), (5, 769), (8, 512), (8, 513), (1, 768), (3, 3), (6, 1200), (6, 1201), (7, 640), (8, 641)])
 def test_segments_of_one_chunk_and_of_four(k, chunks, entry):
     first = max(1, chunks // 2)
     numels = [first * 4096 - 5, (chunks - first - 3) * 4096 + 1, 4096, 100] if chunks > 8 else [4096, 4095, 777]
