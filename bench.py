@@ -38,11 +38,11 @@ STEP_SOURCES = ("update.hip", "update_body.h", "resize_body.h", "resize_schedule
 POWER_SOURCES = ("power.hip", "power.h", "numerics.h")
 MEASURED_TRAFFIC = {
     # k_update<false, true>, default run of the large_streaming workload
-    "step": {"sources_sha256": "61a3660aaf46bccf2c4647a13187ebaf5cf39362a1fbd8f557d9f7a7c3772096", "workload": "large_streaming",
+    "step": {"sources_sha256": "5d82fe733687afaf86ec774f0baba83ff73ab8939ee041f2645730c848130da8", "workload": "large_streaming",
              "alg_bytes": 18991808512, "fetch_bytes": 11.677e9, "write_bytes": 7.348e9,
              "from": "profiles/fused_step_large_streaming_hbm_counters.md"},
     # k_power_apply<5> / k_power_gram<5>, --mode power on the large_streaming workload
-    "power": {"sources_sha256": "79aff79de7d571d2366d1509da079e678f167db552a6d4745d4945e9157fe826", "workload": "large_streaming",
+    "power": {"sources_sha256": "0b2bf55622b432ebe7e80b620e38db5b39ea4c3d6e139d597e86aa3b0767fb8d", "workload": "large_streaming",
               "k_power_apply": {"fetch_bytes": 21.51e9, "write_bytes": 21.48e9},
               "k_power_gram": {"fetch_bytes": 42.95e9, "write_bytes": 0.01e9},
               "from": "profiles/power_iteration_large_streaming_k5.md"},

@@ -156,8 +156,9 @@ typedef struct {
   uint32_t curv_nonfinite; /* a probe sample was non-finite at the last probed step (element frozen) */
   uint32_t sel_passes;  /* diagnostic: passes over h, beyond the one that updates it, that the threshold
                            selection of the last probed step needed (0 when the prediction held)        */
-  uint32_t sel_listed;  /* diagnostic: keys listed by the curvature kernel at the last probed step          */
-  uint32_t sel_outcome; /* diagnostic: 0 small tensor (all keys listed), 1 predicted band held, 2 no band
+  uint32_t sel_listed;  /* diagnostic: keys listed by the curvature kernel at the last probed step; of a
+                           small tensor its non-zero keys, also where they are read and not listed          */
+  uint32_t sel_outcome; /* diagnostic: 0 small tensor (all its keys looked at), 1 predicted band held, 2 no band
                            this step, 3 threshold above the band, 4 below it, 5 too many keys listed,
                            6 fewer non-zero magnitudes than k                                              */
 } triaccel_layer_info;
@@ -172,9 +173,11 @@ typedef struct {
                                   unchanged (+ fallback mask pass), 5 in-place update of tensors whose
                                   size changes, 6 threshold resolution among listed keys + mask patch.
                                   Sets of fewer than 16,384 pieces of 4096 elements, none of whose tensors
-                                  has more than 1024: stages 2 and 3 are part of stage 4 and read 0; the
-                                  fallback mask pass and, on steps that refresh the curvature, the later
-                                  part of stage 5 are part of stage 6                                 */
+                                  has more than 1024, without element-wise step sizes: stages 2 and 3 are
+                                  part of stage 4 and read 0, and so is the threshold resolution of most
+                                  tensors; stage 6 is what is left of it, the fallback mask pass and, on
+                                  steps that refresh the curvature, the later part of stage 5 (no kernel
+                                  at all if no tensor has more than 8192 elements)                    */
 } triaccel_stage_times;
 
 /*

@@ -145,7 +145,7 @@ struct TensorDesc {
   uint64_t cand_offset;  // first entry of the tensor's candidate lists in the pool
   uint32_t cand_cap;     // min(numel, kCandCap): capacity of the overflow list (none if list_all)
   uint32_t sub_cap;      // capacity of each of the other lists (key_lists)
-  uint32_t list_all;     // numel <= kListAllMax: every non-zero key is listed, no prediction
+  uint32_t list_all;     // numel <= kListAllMax: every non-zero key is listed, or read by select_local; no prediction
   uint32_t resize_slot;  // the tensor's first chunk in the scratch area of the in-place resize
 };
 
@@ -159,7 +159,7 @@ struct LayerDev {
   int32_t code, prev_code;
   uint32_t found_inf, curv_nonfinite;
   uint32_t sel_passes;     // passes over h beyond the EMA pass that the last probed step needed
-  uint32_t sel_listed;     // keys the EMA kernel listed at the last probed step
+  uint32_t sel_listed;     // keys the EMA kernel listed at the last probed step (select_local: or read of a small tensor)
   uint32_t sel_outcome;    // how the band check of the last probed step ended (see select_setup)
   float lambda_power;      // max_j |Rayleigh quotient| latched by the power iteration (Sec. 3.2)
   // bookkeeping

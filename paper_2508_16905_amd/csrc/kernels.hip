@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __res
 __device__ __forceinline__ void ema_record(const TensorDesc& td, int64_t base, uint32_t chunk_index, uint32_t above_zeros,
                                            uint32_t maxkey, uint32_t listed, uint32_t nonfin,
                                            EmaPartial* __restrict__ ema_partials) {
-  above_zeros = wave_sum(above_zeros);  // at most 4096 in either half: no carry between the halves
+  above_zeros = wave_sum(above_zeros);  // at most 4096 + 64 (a wavefront's seventeenth elements) in either half: no carry
   maxkey = wave_max(maxkey);
   listed = wave_sum(listed);
   const uint32_t anynf = __any(nonfin != 0u) ? 1u : 0u;

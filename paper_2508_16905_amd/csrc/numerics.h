@@ -115,8 +115,8 @@ __device__ __forceinline__ Tail tail_of(int32_t left, uint32_t tid) {
   const bool any = (left & 3) != 0 && (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid / 64u)) == owner / 64u;
   return Tail{any, any && lane < ((uint32_t)left & 3u), whole + lane, owner, whole / (kRowLanes * 4)};
 }
-// Its words: fp32, or a 16-bit element in the low half.  0 in the other lanes.
-// The same for fp32 rows at plain addresses, for kernels that read so many arrays that their descriptors would not fit
+
+// Rows again, of fp32 elements at plain addresses, for kernels that read so many arrays that their descriptors would not fit
 // the scalar registers; `left`: elements from the row's first one to the end (a full row if FULL).
 template <bool FULL, bool KEEP = false>
 __device__ __forceinline__ void load_row4(const float* row, uint32_t tid, int32_t left, uint32_t (&out)[4]) {
@@ -135,6 +135,7 @@ __device__ __forceinline__ void store_row4(float* row, uint32_t tid, int32_t lef
   __builtin_nontemporal_store(v, (TA_GLOBAL v4u*)(as_global<char>(row) + tid * 16u));
 }
 
+// A lane's word of the tail: fp32, or a 16-bit element in the low half.  0 in the lanes without one.
 template <int W>
 __device__ __forceinline__ uint32_t load_tail(const void* chunk, const Tail& t) {
   uint32_t v = 0;

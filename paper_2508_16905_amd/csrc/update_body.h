@@ -10,9 +10,9 @@ namespace triaccel {
 //   theta = widen(param);  gt = widen(g) * inv_scale;  d = fma(wd, theta, gt);
 //   m = fma(mu, m, d) (m = d without a buffer);  theta' = fma(-eta, m, theta);
 //   store theta' in the layer's new precision, round to nearest even.
-// The body comes in two halves -- load + arithmetic into registers, then the stores -- so that a
-// kernel that rewrites a tensor in place at another element size can put its one workgroup barrier
-// between them, at a single place that every thread passes.
+// One function, update_as, loads, computes and stores a chunk; a kernel that rewrites a tensor in place at
+// another element size has it put one workgroup barrier between the loads and the stores, at a single place
+// that every thread passes (BARRIER).
 // ELEM: the step size is scaled per element instead of per layer (Sec. 3.2, "Step size scaling",
 // applied to each entry of the sparsified curvature): eta_i = lr / fma(alpha, a_i, 1) with
 // a_i = |h_i| if the entry is in the mask (|h_i| >= theta and |h_i| > 0), else 0; reads h once more.
@@ -51,9 +51,10 @@ __device__ __forceinline__ ChunkArrays chunk_arrays(const TensorDesc& td, int64_
 
 template <int GW, int PW, bool MOM, bool ELEM>
 __device__ __forceinline__ void update_fetch(const ChunkArrays& a, uint32_t tid, ChunkRegs& r, CurvRegs& c) {
-  // Row by row, the arrays interleaved.  (Measured over 48 placements of the arrays in memory each,
-  // with the accesses in the global address space: issuing the loads array by array instead is 2 %
-  // slower on average, rotating the row order between the arrays changes nothing.)
+  // Row by row, the arrays interleaved; the compiler pairs the rows of an array.  (Measured over 48 placements of the
+  // arrays in memory each, with accesses at plain addresses: issuing the loads array by array instead is 2 % slower
+  // on average, rotating the row order between the arrays changes nothing.  Holding the compiler to the written order
+  // through the descriptors: no difference that the placements let show.)
   const Rows grows = rows_of<GW>(a.g, a.left), trows = rows_of<PW>(a.th, a.left), mrows = rows_of<4>(a.m, a.left);
   const Rows hrows = rows_of<4>(a.h, a.left);
 #pragma unroll
