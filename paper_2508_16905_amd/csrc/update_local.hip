@@ -179,15 +179,13 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
   const StepScalars sc = step_scalars(sa);
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
-  const uint64_t late_epoch = glob->late_epoch;
-  const uint32_t late = glob->select_late;
   if (blockIdx.x < n_tensors) {
     if (local) {
-      const uint32_t next = late_epoch == sc.step_id && total_chunks <= kLateChunks ? 1u : 0u;
-      TA_LOADED("s"(skip_epoch), "s"(pending), "s"(late_epoch), "s"(late));
-      if (skip_epoch == sc.step_id) return;
-      if (late != next && blockIdx.x == 0 && threadIdx.x == 0) glob->select_late = next;
-      if (pending == 0) return;
+      TA_LOADED("s"(skip_epoch), "s"(pending));
+      if (pending == 0 || skip_epoch == sc.step_id) return;
+      // (a step with nothing pending was not a late one, so there is nothing to take back when all leave above)
+      if (blockIdx.x == 0 && threadIdx.x == 0)
+        glob->select_late = glob->late_epoch == sc.step_id && total_chunks <= kLateChunks ? 1u : 0u;
     }
     const uint32_t l = blockIdx.x;
     const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
