@@ -22,6 +22,10 @@ HIPCC_FLAGS = [
     "-fno-fast-math",
     "-fno-gpu-flush-denormals-to-zero",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's leading pointer arguments are in scalar registers when its wavefronts start, instead of one memory
+    # latency later (EfficientNet-B0 set, 16 bits, without a probe: 15.4 -> 14.8 us a step; 41 tensors of 1.0 M with a
+    # probe 22.9 -> 22.0)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall",
     "-Wno-unused-function",
 ]

@@ -52,7 +52,6 @@ struct triaccel_ctx {
   hipStream_t stream = nullptr;
   int device = 0;
   triaccel_config cfg{};
-  Hyper hp{};
   uint32_t n = 0;
   std::vector<int64_t> numel;
   std::vector<int32_t> grad_dtype;
@@ -107,6 +106,10 @@ namespace {
 // clear of its own for each of the twenty-odd tables were most of the time of triaccel_init on a small set).
 class Workspace {
  public:
+  template <typename T>
+  void add(DevPtr<T>* out, size_t count) {
+    add(reinterpret_cast<T**>(out), count);
+  }
   template <typename T>
   void add(T** out, size_t count) {
     requests_.push_back({reinterpret_cast<void**>(out), size_});
@@ -212,9 +215,7 @@ bool sizes_can_change(const triaccel_ctx& c) { return !(c.cfg.tau_high <= 0.0f &
 // the stage boundaries.  Order of the stages: the per-layer assignment needs only the gradient
 // moments and lambda_l = max |h_i| (known after the EMA pass), so it runs before the threshold is
 // final; the mask is an output that nothing in the per-layer update depends on.
-int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t* ev, int level) {
-  const float beta_h = h->cfg.beta_curv;
-  const float omb_h = 1.0f - beta_h;
+int enqueue_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, hipEvent_t* ev, int level) {
   const DeviceTables& T = h->t;
   hipStream_t s = h->stream;
   const bool fisher = h->cfg.curvature_source == 1;
@@ -222,26 +223,25 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
   const bool local = local_form(*h);
   const bool resize = sizes_can_change(*h);
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
-  TA_HIP(launch_grad_stats(T, sa, local, s));
+  TA_HIP(launch_grad_stats(T, sc, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
-  if (any_probe) TA_HIP(launch_curv_ema(T, sa, beta_h, omb_h, fisher ? 1 : 0, local, s));
+  if (any_probe) TA_HIP(launch_curv_ema(T, sc, fisher, local, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[2], s));
   if (local) {
     // a set bound by its launches: the update takes the layers' decisions and settles the thresholds
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
     if (ev) TA_HIP(hipEventRecord(ev[4], s));
-    TA_HIP(launch_update_local(T, sa, h->hp, any_probe, s));
+    TA_HIP(launch_update_local(T, sc, any_probe, s));
     if (ev) TA_HIP(hipEventRecord(ev[5], s));
-    if (!any_probe && resize)
-      TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, false, s));
+    if (!any_probe && resize) TA_HIP(launch_update_resize(T, sc, false, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
     // (with short tensors only, select_local leaves nothing over and no resize has a second launch: 12 tensors of 100
     // elements 17.4 -> 14.8 us a step without it)
-    if (any_probe && !T.all_small) TA_HIP(launch_select_tail(T, sa, h->hp, true, resize, s));
+    if (any_probe && !T.all_small) TA_HIP(launch_select_tail(T, sc, true, resize, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
     return TRIACCEL_OK;
   }
-  TA_HIP(launch_layer(T, sa, h->hp, s));
+  TA_HIP(launch_layer(T, sc, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
   if (any_probe && !T.all_small) {
     // fallback radix select: two rounds at full width (a first window, then a refinement or the
@@ -249,24 +249,24 @@ int enqueue_step(triaccel_ctx* h, const StepArg& sa, bool any_probe, hipEvent_t*
     // Each launch leaves at once when no tensor is (still) in histogram mode.
     // A set bound by its number of launches gets one: rounds beyond the first are then made by the
     // scanning workgroup alone.
-    if (T.total_chunks >= kLaunchBoundChunks) TA_HIP(launch_hist_pass(T, sa, 0, s));
-    TA_HIP(launch_hist_pass(T, sa, 8, s));
+    if (T.total_chunks >= kLaunchBoundChunks) TA_HIP(launch_hist_pass(T, sc, 0, s));
+    TA_HIP(launch_hist_pass(T, sc, 8, s));
   }
   if (elem && any_probe) {
     // element-wise step sizes need the final threshold: finish the mask and the selection first
     if (T.total_chunks < kLaunchBoundChunks) {
-      TA_HIP(launch_select_tail(T, sa, h->hp, false, false, s));
+      TA_HIP(launch_select_tail(T, sc, false, false, s));
     } else {
-      TA_HIP(launch_mask_pass(T, sa, s));
-      TA_HIP(launch_select_finish(T, sa, beta_h, s));
+      TA_HIP(launch_mask_pass(T, sc, s));
+      TA_HIP(launch_select_finish(T, sc, s));
     }
   }
   if (ev) TA_HIP(hipEventRecord(ev[4], s));
-  TA_HIP(launch_update(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, resize, s));
+  TA_HIP(launch_update(T, sc, elem, resize, s));
   if (ev) TA_HIP(hipEventRecord(ev[5], s));
-  if (resize) TA_HIP(launch_update_resize(T, sa, h->cfg.weight_decay, h->cfg.momentum, h->cfg.alpha, elem, s));
+  if (resize) TA_HIP(launch_update_resize(T, sc, elem, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
-  if (any_probe && !elem) TA_HIP(launch_select_finish(T, sa, h->hp.beta_curv, s));
+  if (any_probe && !elem) TA_HIP(launch_select_finish(T, sc, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
   return TRIACCEL_OK;
 }
@@ -284,7 +284,9 @@ int replay_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, int slot
     int rc = TRIACCEL_OK;
     hipError_t e = launch_set_scalars(h->t, sc, s);
     if (e != hipSuccess) rc = hip_fail(e, "launch_set_scalars");
-    if (!rc) rc = enqueue_step(h, StepArg{sc, h->t.scalars}, any_probe, nullptr, 0);
+    StepScalars captured = sc;
+    captured.captured = 1;
+    if (!rc) rc = enqueue_step(h, captured, any_probe, nullptr, 0);
     e = hipStreamEndCapture(s, &graph);  // always ends the capture, also after a failure above
     if (rc) {
       if (graph) (void)hipGraphDestroy(graph);
@@ -312,7 +314,7 @@ int replay_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, int slot
   }
   hipKernelNodeParams params{};
   void* args[2];
-  StepScalars* dst = h->t.scalars;
+  StepScalars* dst = &h->t.dev->scalars;
   set_scalars_node_params(&params, args, &sc, &dst);
   TA_HIP(hipGraphExecKernelNodeSetParams(g.exec, g.root, &params));
   TA_HIP(hipGraphLaunch(g.exec, s));
@@ -368,7 +370,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   c->stream = static_cast<hipStream_t>(hip_stream);
   c->cfg = *config;
   c->n = (uint32_t)n;
-  c->hp = Hyper{config->beta_var,     config->beta_curv,     config->tau_low,       config->tau_high,
+  c->t.hyper = Hyper{config->beta_var,     config->beta_curv,     config->tau_low,       config->tau_high,
                 config->tau_curv,     config->alpha,         config->sparsity_ppm,  config->momentum,
                 config->weight_decay, config->ctrl_interval, config->scale_backoff, config->scale_growth,
                 config->growth_interval, config->lambda_source, config->elementwise_scale,
@@ -417,7 +419,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     ls.var_ext = 3.0e38f;  // no extrapolation error measured yet
   }
   // scratch of the in-place resize: the first `top` chunks of every tensor, if the set needs subtree stages
-  const ResizePlan resize = make_resize_plan(max_chunks, (uint32_t)chunks.size());
+  const ResizePlan resize = c->t.plan = make_resize_plan(max_chunks, (uint32_t)chunks.size());
   uint64_t scratch_chunks = 0;
   if (resize.n_stages > 1)
     for (TensorDesc& d : c->desc) {
@@ -461,7 +463,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   ws.add(&T.resize_scratch, (size_t)scratch_chunks * kChunk * 4);
   ws.add(&T.inputs, (size_t)n);
   ws.add(&T.arrived, (size_t)n * kCandCounterStride);
-  ws.add(&T.scalars, 1);
+  ws.add(&T.dev, 1);
   if ((rc = ws.allocate(c))) return fail(rc);
   T.tensors = c->tables[0].dev;
   e = hipMemcpy(T.chunks, chunks.data(), chunks.size() * sizeof(ChunkRef), hipMemcpyHostToDevice);
@@ -543,6 +545,8 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   std::memset(c->pinned_res, 0, sizeof(GlobalDev));
   e = hipHostGetDevicePointer(reinterpret_cast<void**>(&T.host_result), c->pinned_res, 0);
   if (e != hipSuccess) return fail(hip_fail(e, "hipHostGetDevicePointer(result)"));
+  e = hipMemcpy(T.dev, static_cast<const StepTables*>(&T), sizeof(StepTables), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return fail(hip_fail(e, "hipMemcpy(step tables)"));
   e = hipDeviceSynchronize();
   if (e != hipSuccess) return fail(hip_fail(e, "hipDeviceSynchronize"));
   *out = c;
@@ -642,7 +646,7 @@ int triaccel_step(triaccel_handle h, const triaccel_tensor* tensors, int32_t n, 
     if (rc) return rc;
   } else {
     hipEvent_t* ev = prof ? h->ev[index % TRIACCEL_PROFILE_RING] : nullptr;
-    const int rc = enqueue_step(h, StepArg{sc, nullptr}, any_probe, ev, h->profiling);
+    const int rc = enqueue_step(h, sc, any_probe, ev, h->profiling);
     if (rc) return rc;
     if (prof) {
       h->ev_step[index % TRIACCEL_PROFILE_RING] = index;
@@ -741,7 +745,7 @@ int triaccel_get_state(triaccel_handle h, void* buf, int64_t size) {
   hd.next_batch = h->next_batch;
   hd.good_steps = g.good_steps;
   hd.shape_hash = shape_hash(h);
-  hd.config_hash = fnv1a(&h->hp, sizeof(h->hp));
+  hd.config_hash = fnv1a(&h->t.hyper, sizeof(h->t.hyper));
   std::memcpy(buf, &hd, sizeof(hd));
   TA_HIP(hipMemcpy(static_cast<char*>(buf) + sizeof(hd), h->t.layers, (size_t)h->n * sizeof(LayerDev),
                    hipMemcpyDeviceToHost));
@@ -756,7 +760,7 @@ int triaccel_set_state(triaccel_handle h, const void* buf, int64_t size) {
   std::memcpy(&hd, buf, sizeof(hd));
   if (hd.magic != kStateMagic || hd.layer_size != sizeof(LayerDev)) return TRIACCEL_E_INVALID_ARG;
   if (hd.n != h->n || hd.shape_hash != shape_hash(h)) return TRIACCEL_E_SHAPE_MISMATCH;
-  if (hd.config_hash != fnv1a(&h->hp, sizeof(h->hp))) return TRIACCEL_E_INVALID_ARG;
+  if (hd.config_hash != fnv1a(&h->t.hyper, sizeof(h->t.hyper))) return TRIACCEL_E_INVALID_ARG;
   TA_HIP(hipStreamSynchronize(h->stream));
   // the small global record starts clean (both parities of its per-step words are zero between steps)
   GlobalDev g;

@@ -112,20 +112,14 @@ struct Hyper {
   uint32_t topk_abs;      // > 0: entries kept per layer (instead of the fraction sparsity_ppm)
 };
 
-// Per-step scalars handed to the kernels.
+// Per-step scalars handed to the kernels by value; those of a captured step, whose kernel arguments are frozen at
+// capture, read them from device memory instead (StepTables::scalars).
 struct StepScalars {
   float lr;
   float loss_scale;
   float inv_scale;   // 1.0f / loss_scale, one fp32 division on the host
-  uint32_t pad_;
+  uint32_t captured; // the values are in device memory
   uint64_t step_id;  // 1-based count of triaccel_step calls; the epoch of the skip / overflow flags
-};
-
-// How a kernel receives them: by value (ordinary launch), or from device memory when `dev` is set
-// (a replayed graph, whose kernel arguments are frozen at capture).
-struct StepArg {
-  StepScalars value;
-  const StepScalars* dev;
 };
 
 // Device table, one entry per tensor; re-uploaded when a pointer changes.

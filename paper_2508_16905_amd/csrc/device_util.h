@@ -74,7 +74,14 @@ __device__ __forceinline__ bool step_skipped(const GlobalDev* glob, uint64_t ste
 // branch, where its latency comes on top of that of the load that the branch waits for.
 #define TA_LOADED(...) asm volatile("" ::__VA_ARGS__)
 
-__device__ __forceinline__ StepScalars step_scalars(const StepArg& sa) { return sa.dev ? *sa.dev : sa.value; }
+// The step's scalars: the launch's, or of a captured step the last ones that were written to device memory.  Both are
+// read, without a branch.
+__device__ __forceinline__ StepScalars step_scalars(const StepScalars& arg, const StepTables& tab) {
+  const StepScalars dev = tab.scalars;
+  const bool c = arg.captured != 0;
+  return StepScalars{c ? dev.lr : arg.lr, c ? dev.loss_scale : arg.loss_scale, c ? dev.inv_scale : arg.inv_scale, 0u,
+                     c ? dev.step_id : arg.step_id};
+}
 
 __device__ __forceinline__ uint32_t elem_size(int code) { return code == kFP32 ? 4u : 2u; }
 
@@ -271,14 +278,5 @@ __device__ __forceinline__ void mask_chunk(const TensorDesc& td, int64_t base, u
   store_mask_flags<SHARED>(td, base, kflags, tail);
   append_end<SHARED>(append_begin(cflags, chunk_index, tensor, td, counters), cflags, h, ht, tail, base, tensor, td, cands, counters);
 }
-
-// ---------------------------------------------------------------------------------------------
-// Host-side launchers
-// ---------------------------------------------------------------------------------------------
-#define TA_LAUNCH_CHECK()                      \
-  do {                                         \
-    hipError_t e_ = hipGetLastError();         \
-    if (e_ != hipSuccess) return e_;           \
-  } while (0)
 
 }  // namespace triaccel

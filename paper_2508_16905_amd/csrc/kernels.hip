@@ -52,15 +52,18 @@ __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, 
 }
 
 template <bool KEEP>
-__global__ __launch_bounds__(kThreads) void k_grad_stats(const TensorDesc* __restrict__ tds,
-                                                         const ChunkRef* __restrict__ chunks,
-                                                         StatPartial* __restrict__ partials, LayerDev* layers,
-                                                         GlobalDev* glob, LayerIn* inputs, StepArg sa) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) void k_grad_stats(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                         const ChunkRef* __restrict__ chunks, GlobalDev* glob, StepScalars arg,
+                                                         int local) {
   const ChunkRef cr = chunks[blockIdx.x];
+  const StepScalars sc = step_scalars(arg, *tab);
+  LayerDev* const layers = tab->layers;
+  StatPartial* const partials = tab->partials;
+  LayerIn* const inputs = tab->inputs;
   const TensorDesc td = tds[cr.tensor];
+  TA_LOADED("s"(td.grad), "s"(td.numel), "s"(td.grad_dtype), "s"(td.first_chunk), "s"(layers), "s"(partials), "s"(inputs));
   // k_update_local takes the step's decisions from this copy: it writes the layers' records while it runs
-  if (inputs && cr.index == 0 && threadIdx.x == 0) inputs[cr.tensor] = layer_in(layers[cr.tensor]);
+  if (local && cr.index == 0 && threadIdx.x == 0) inputs[cr.tensor] = layer_in(layers[cr.tensor]);
   const int64_t base = (int64_t)cr.index * kChunk;
   double s1 = 0.0, s2 = 0.0;
   uint32_t bad = 0;
@@ -235,22 +238,24 @@ __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, fl
 
 // At most 6 wavefronts per SIMD: room for the loads of all rows to be under way at once.
 template <bool FISHER>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void k_curv_ema(const TensorDesc* __restrict__ tds,
-                                                       const ChunkRef* __restrict__ chunks, const LayerDev* layers,
-                                                       const GlobalDev* glob, EmaPartial* __restrict__ ema_partials,
-                                                       Candidate* cands, uint32_t* counters, StepArg sa,
-                                                       float beta_h, float omb_h, int list_small) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void k_curv_ema(
+    const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds, const ChunkRef* __restrict__ chunks, const GlobalDev* glob,
+    StepScalars arg, int list_small) {
+  const ChunkRef cr = chunks[blockIdx.x];
+  const StepScalars sc = step_scalars(arg, *tab);
   // the skip word travels together with the tables: its latency is not one more before the data's
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t late = glob->select_late;
-  const ChunkRef cr = chunks[blockIdx.x];
+  const float beta_h = tab->hyper.beta_curv, omb_h = 1.0f - beta_h;
+  Candidate* const cands = tab->cands;
+  uint32_t* const counters = tab->cand_counters;
+  EmaPartial* const ema_partials = tab->ema_partials;
   const TensorDesc td = tds[cr.tensor];
-  const LayerDev& ls = layers[cr.tensor];
+  const LayerDev& ls = tab->layers[cr.tensor];
   const uint32_t probes_seen = ls.probes_seen, use_band = ls.use_band, band_lo = ls.band_lo, band_hi = ls.band_hi;
   TA_LOADED("s"(td.grad), "s"(td.z), "s"(td.hz), "s"(td.curv), "s"(td.mask), "s"(td.numel), "s"(td.grad_dtype),
             "s"(td.has_probe), "s"(td.list_all), "s"(td.first_chunk), "s"(td.cand_offset), "s"(probes_seen), "s"(use_band), "s"(band_lo),
-            "s"(band_hi), "s"(late));
+            "s"(band_hi), "s"(late), "s"(beta_h), "s"(cands), "s"(counters), "s"(ema_partials));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
   const bool first = probes_seen == 0;
   // a small tensor's keys are listed, all of them, or left to select_local, which reads them where they lie (`late`: it
@@ -289,11 +294,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
 // zero owns no chunk of a tensor still being counted, because a tensor's scan, which alone
 // lowers the count, needs every workgroup owning one of its chunks to have arrived.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_hist_pass(const TensorDesc* __restrict__ tds,
-                                                        const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
-                                                        LayerDev* layers, GlobalDev* glob, uint32_t* hist,
-                                                        StepArg sa, int serial_rounds) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) void k_hist_pass(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                        const ChunkRef* __restrict__ chunks, GlobalDev* glob, StepScalars arg,
+                                                        int serial_rounds, uint32_t n_wg) {
+  const StepScalars sc = step_scalars(arg, *tab);
+  LayerDev* const layers = tab->layers;
+  uint32_t* const hist = tab->hist;
+  const uint32_t total_chunks = tab->total_chunks;
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t pending = __hip_atomic_load(&glob->hist_pending[sc.step_id & 1u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (pending == 0 || skip_epoch == sc.step_id) return;
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void k_hist_pass(const TensorDesc* __rest
   __shared__ uint32_t s_last;
   for (int b = threadIdx.x; b < kHistBins; b += kThreads) s_hist[b] = 0;
   __syncthreads();
-  const uint32_t per = (total_chunks + gridDim.x - 1) / gridDim.x;
+  const uint32_t per = (total_chunks + n_wg - 1) / n_wg;
   const uint32_t c0 = min(blockIdx.x * per, total_chunks);
   const uint32_t c1 = min(c0 + per, total_chunks);
   int cur = -1;
@@ -363,12 +370,13 @@ __global__ __launch_bounds__(kThreads) void k_hist_pass(const TensorDesc* __rest
 // ---------------------------------------------------------------------------------------------
 // Finish (select_finish) as a kernel of its own, one workgroup per tensor.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kFinishThreads) void k_select_finish(const TensorDesc* __restrict__ tds,
-                                                                  LayerDev* layers, const GlobalDev* glob,
-                                                                  const Candidate* cands, uint32_t* counters,
-                                                                  StepArg sa, float beta_h) {
+__global__ __launch_bounds__(kFinishThreads) void k_select_finish(const StepTables* __restrict__ tab,
+                                                                  const TensorDesc* __restrict__ tds, const GlobalDev* glob,
+                                                                  StepScalars arg) {
   __shared__ SelectShared<kFinishThreads> sh;
-  const StepScalars sc = step_scalars(sa);
+  const StepScalars sc = step_scalars(arg, *tab);
+  LayerDev* const layers = tab->layers;
+  uint32_t* const counters = tab->cand_counters;
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t l = blockIdx.x;
   const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
@@ -376,7 +384,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_finish(const TensorDe
   const FinishIn in = finish_in(layers[l]);
   TA_LOADED("s"(td.mask), "s"(td.has_probe), "s"(td.cand_cap), "s"(in.mode), "s"(in.probes_seen), "s"(in.var_hold));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
-  select_finish<kFinishThreads, kFinishRegs>(l, td, layers[l], in, listed, cands, counters, beta_h, sh);
+  select_finish<kFinishThreads, kFinishRegs>(l, td, layers[l], in, listed, tab->cands, counters, tab->hyper.beta_curv, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -384,15 +392,13 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_finish(const TensorDe
 // threshold selection (select_outcome, select_setup), then the per-layer assignment (layer_body.h), overflow
 // decision and loss-scale schedule.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void k_layer(const TensorDesc* __restrict__ tds,
-                                                    const StatPartial* __restrict__ partials,
-                                                    const EmaPartial* __restrict__ ema_partials, uint32_t* counters,
-                                                    LayerDev* layers, GlobalDev* glob, GlobalDev* host_result,
-                                                    uint32_t* trans_list, uint32_t n_tensors, StepArg sa, Hyper hp) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) void k_layer(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                    GlobalDev* glob, StepScalars arg) {
+  const StepScalars sc = step_scalars(arg, *tab);
+  const Hyper hp = tab->hyper;
   const uint32_t l = blockIdx.x;
   const TensorDesc td = tds[l];
-  LayerDev& ls = layers[l];
+  LayerDev& ls = tab->layers[l];
   const bool skip = step_skipped(glob, sc.step_id);
   __shared__ LayerShared sh;
   LayerSums sums{};
@@ -401,61 +407,45 @@ __global__ __launch_bounds__(kThreads) void k_layer(const TensorDesc* __restrict
   const SelNow now = select_plan(ls);
   const LayerIn in = layer_in(ls);
   if (!skip) {
-    sums = layer_reduce<true>(layer_accumulate<true>(td, partials, ema_partials, td.has_probe != 0), td.numel, sh);
+    sums = layer_reduce<true>(layer_accumulate<true>(td, tab->partials, tab->ema_partials, td.has_probe != 0), td.numel, sh);
     if (td.has_probe) outcome = select_outcome(td, now, sums.ema, k);
-    if (outcome != kOutListed) reset_cand_counters(counters, l);  // drop whatever the EMA kernel listed
+    if (outcome != kOutListed) reset_cand_counters(tab->cand_counters, l);  // drop whatever the EMA kernel listed
   }
   if (threadIdx.x != 0) return;
   if (!skip) {
     if (td.has_probe) select_setup(td, ls, glob, now, sums.ema, k, outcome, sc.step_id);
-    layer_publish(l, ls, layer_decide(in, sums, td.has_probe != 0, sc.lr, hp), glob, trans_list, n_tensors,
+    layer_publish(l, ls, layer_decide(in, sums, td.has_probe != 0, sc.lr, hp), glob, tab->trans_list, tab->n_tensors,
                   sc.step_id);
   } else {
     ls.found_inf = (ls.found_epoch == sc.step_id) ? 1u : 0u;
   }
-  if (l == 0) step_record(glob, host_result, sc, hp, skip);
+  if (l == 0) step_record(glob, tab->host_result, sc, hp, skip);
 }
 
 // ---------------------------------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------------------------------
-hipError_t launch_grad_stats(const DeviceTables& t, const StepArg& sa, bool local, hipStream_t s) {
+hipError_t launch_grad_stats(const DeviceTables& t, const StepScalars& sc, bool local, hipStream_t s) {
   const auto kernel = t.keep_grads ? k_grad_stats<true> : k_grad_stats<false>;
-  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.partials,
-                     t.layers, t.glob, local ? t.inputs : nullptr, sa);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  return launch(kernel, t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc, local ? 1 : 0);
 }
 
-hipError_t launch_curv_ema(const DeviceTables& t, const StepArg& sa, float beta_h, float omb_h, int fisher,
-                           bool local, hipStream_t s) {
+hipError_t launch_curv_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, bool local, hipStream_t s) {
   const auto kernel = fisher ? k_curv_ema<true> : k_curv_ema<false>;
-  hipLaunchKernelGGL(kernel, dim3(t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.layers, t.glob,
-                     t.ema_partials, t.cands, t.cand_counters, sa, beta_h, omb_h, local ? 0 : 1);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  return launch(kernel, t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc, local ? 0 : 1);
 }
 
-hipError_t launch_hist_pass(const DeviceTables& t, const StepArg& sa, int serial_rounds, hipStream_t s) {
+hipError_t launch_hist_pass(const DeviceTables& t, const StepScalars& sc, int serial_rounds, hipStream_t s) {
   const uint32_t grid = t.total_chunks < t.persistent_grid ? t.total_chunks : t.persistent_grid;
-  hipLaunchKernelGGL(k_hist_pass, dim3(grid), dim3(kThreads), 0, s, t.tensors, t.chunks, t.total_chunks, t.layers,
-                     t.glob, t.hist, sa, serial_rounds);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  return launch(k_hist_pass, grid, kThreads, s, t.dev, t.tensors, t.chunks, t.glob, sc, serial_rounds, grid);
 }
 
-hipError_t launch_select_finish(const DeviceTables& t, const StepArg& sa, float beta_h, hipStream_t s) {
-  hipLaunchKernelGGL(k_select_finish, dim3(t.n_tensors), dim3(kFinishThreads), 0, s, t.tensors, t.layers, t.glob,
-                     t.cands, t.cand_counters, sa, beta_h);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+hipError_t launch_select_finish(const DeviceTables& t, const StepScalars& sc, hipStream_t s) {
+  return launch(k_select_finish, t.n_tensors, kFinishThreads, s, t.dev, t.tensors, t.glob, sc);
 }
 
-hipError_t launch_layer(const DeviceTables& t, const StepArg& sa, const Hyper& hp, hipStream_t s) {
-  hipLaunchKernelGGL(k_layer, dim3(t.n_tensors), dim3(kThreads), 0, s, t.tensors, t.partials, t.ema_partials,
-                     t.cand_counters, t.layers, t.glob, t.host_result, t.trans_list, t.n_tensors, sa, hp);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+hipError_t launch_layer(const DeviceTables& t, const StepScalars& sc, hipStream_t s) {
+  return launch(k_layer, t.n_tensors, kThreads, s, t.dev, t.tensors, t.glob, sc);
 }
 
 }  // namespace triaccel

@@ -23,11 +23,12 @@ __device__ __forceinline__ char* resize_scratch(const TensorDesc& td, char* scra
 }
 
 // Copies the new values of chunk c from the scratch area into place.
+template <int THREADS>
 __device__ __forceinline__ void resize_copy(const TensorDesc& td, const char* src, uint32_t esz, uint32_t c) {
   const int64_t base = (int64_t)c * kChunk, left = td.numel - base;
   const uint32_t bytes = (uint32_t)(left < kChunk ? left : kChunk) * esz;
   char* const dst = static_cast<char*>(td.param) + base * esz;
-  for (uint32_t off = threadIdx.x * 16; off < bytes; off += blockDim.x * 16) {
+  for (uint32_t off = threadIdx.x * 16; off < bytes; off += THREADS * 16) {
     if (off + 16 <= bytes) {
       *as_global<v4f>(dst + off) = *as_global<v4f>(src + off);
     } else {
@@ -40,8 +41,11 @@ __device__ __forceinline__ void resize_copy(const TensorDesc& td, const char* sr
 // consists of GROUPS times kThreads threads that take the chunks of a level in turn (launch 0: GROUPS = 1).
 template <bool ELEM, bool MOM, int GROUPS = 1>
 __device__ __forceinline__ void resize_item(const TensorDesc& desc, int old_code, int new_code, const StepSize& ss,
-                                            const ResizePlan& plan, char* scratch, uint32_t launch, uint32_t slot,
-                                            const StepScalars& sc, float wd, float mu) {
+                                            const StepTables& tab, uint32_t launch, uint32_t slot,
+                                            const StepScalars& sc) {
+  const ResizePlan& plan = tab.plan;
+  char* const scratch = tab.resize_scratch;
+  const float wd = tab.hyper.weight_decay, mu = tab.hyper.momentum;
   // The same in every lane, but the compiler does not see it here: without saying so every access through a buffer
   // descriptor becomes a loop over the descriptors that the lanes might hold (128 chunks one after the other: 211 us
   // with plain addresses, 248 with such loops).
@@ -74,7 +78,7 @@ __device__ __forceinline__ void resize_item(const TensorDesc& desc, int old_code
   if (r < plan.top) {
     if (r >= td.n_chunks) return;
     if (launch != 0) {
-      if (launch == resize_copy_launch(plan, narrowing)) resize_copy(td, resize_scratch(td, scratch, r), elem_size(nd), r);
+      if (launch == resize_copy_launch(plan, narrowing)) resize_copy<GROUPS * kThreads>(td, resize_scratch(td, scratch, r), elem_size(nd), r);
       return;
     }
     to = resize_scratch(td, scratch, r) - (int64_t)r * kChunk * elem_size(nd);
@@ -90,25 +94,22 @@ __device__ __forceinline__ void resize_item(const TensorDesc& desc, int old_code
   else resize_walk_subtree(plan, stage, sub, td.n_chunks, narrowing, chunk, [&]() { __syncthreads(); });
 }
 
-// Work items of a launch are (list entry, slot) pairs, `slots` per entry (enough for either direction);
+// Work items of a launch are (list entry, slot) pairs of the `count` tensors on the list, `slots` per entry (enough for either direction);
 // workgroup `wg` of `n_wg` takes the items wg,
 // wg + n_wg, ...  The list and its length are written on the device by the kernel that takes the layers'
 // decisions, so the work is offered on every step and nothing happens when the list is empty.
 template <bool ELEM, bool MOM, int GROUPS = 1>
-__device__ __forceinline__ void resize_items(const TensorDesc* __restrict__ tds, const LayerDev* layers,
-                                             const GlobalDev* glob, const uint32_t* trans_list, uint32_t n_tensors,
-                                             const ResizePlan& plan, char* scratch, uint32_t launch, uint32_t slots, uint32_t wg,
-                                             uint32_t n_wg, const StepScalars& sc, float wd, float mu, float alpha) {
-  const uint32_t count = glob->trans_count[sc.step_id & 1u];
-  const uint32_t* list = trans_list + (sc.step_id & 1u) * n_tensors;
+__device__ __forceinline__ void resize_items(const StepTables& tab, const TensorDesc* __restrict__ tds, uint32_t count,
+                                             uint32_t launch, uint32_t slots, uint32_t wg, uint32_t n_wg, const StepScalars& sc) {
+  const uint32_t* list = tab.trans_list + (sc.step_id & 1u) * tab.n_tensors;
   const uint64_t items = (uint64_t)count * slots;
   for (uint64_t item = wg; item < items; item += n_wg) {
     const uint32_t l = uniform(list[item / slots]);
     const uint32_t r = (uint32_t)(item % slots);
-    const LayerDev& ls = layers[l];
-    const StepSize ss{-ls.eta, sc.lr, alpha, ls.theta_key};
+    const LayerDev& ls = tab.layers[l];
+    const StepSize ss{-ls.eta, sc.lr, tab.hyper.alpha, ls.theta_key};
     const TensorDesc td = tds[l];
-    resize_item<ELEM, MOM, GROUPS>(td, ls.prev_code, ls.code, ss, plan, scratch, launch, r, sc, wd, mu);
+    resize_item<ELEM, MOM, GROUPS>(td, ls.prev_code, ls.code, ss, tab, launch, r, sc);
   }
 }
 

@@ -113,15 +113,16 @@ __device__ __forceinline__ bool rank_select(const uint32_t (&key)[KEYS], uint32_
 // Beside the streaming workgroups every dependent access takes about 3 us instead of 0.7, so there are few of them:
 // tables, records and list lengths; keys; then only stores.  (An earlier form with lists re-read in every pass took 100
 // to 200 us in this place.)
-__device__ __forceinline__ void select_local(uint32_t l, const TensorDesc* __restrict__ tds, const EmaPartial* __restrict__ ema_partials,
-                                             const LayerIn* __restrict__ inputs, LayerDev* layers, GlobalDev* glob,
-                                             const Candidate* __restrict__ cands, uint32_t* counters, const StepScalars& sc,
-                                             const Hyper& hp, LayerShared& shl, LocalSelectShared& sh) {
+__device__ __forceinline__ void select_local(uint32_t l, const StepTables& tab, const TensorDesc* __restrict__ tds, GlobalDev* glob,
+                                             const StepScalars& sc, const Hyper& hp, LayerShared& shl, LocalSelectShared& sh) {
+  const EmaPartial* const ema_partials = tab.ema_partials;
+  const Candidate* const cands = tab.cands;
+  uint32_t* const counters = tab.cand_counters;
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t late = glob->select_late;
   const TensorDesc td = tds[l];
-  LayerDev& ls = layers[l];
-  const SelNow now = inputs[l].plan;
+  LayerDev& ls = tab.layers[l];
+  const SelNow now = tab.inputs[l].plan;
   FinishIn in = finish_in(ls);
   uint32_t listed_here = 0;
   if (threadIdx.x <= kCandLists) listed_here = *cand_counter(counters, l, threadIdx.x);

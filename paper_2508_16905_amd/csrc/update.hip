@@ -9,23 +9,24 @@ namespace triaccel {
 // must be final before the update runs: the tensors whose mask the EMA kernel did not settle get
 // their mask written and their range keys listed here, before k_select_finish.  Leaves at once
 // when no tensor needs it (the steady state).
-__global__ __launch_bounds__(kThreads) void k_mask_pass(const TensorDesc* __restrict__ tds,
-                                                        const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
-                                                        const LayerDev* layers, const GlobalDev* glob, Candidate* cands,
-                                                        uint32_t* counters, StepArg sa) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) void k_mask_pass(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                        const ChunkRef* __restrict__ chunks, const GlobalDev* glob, StepScalars arg,
+                                                        uint32_t n_wg) {
+  const StepScalars sc = step_scalars(arg, *tab);
+  const LayerDev* const layers = tab->layers;
+  const uint32_t total_chunks = tab->total_chunks;
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
   TA_LOADED("s"(skip_epoch), "s"(pending));
   if (pending == 0 || skip_epoch == sc.step_id) return;
-  for (uint32_t c = blockIdx.x; c < total_chunks; c += gridDim.x) {
+  for (uint32_t c = blockIdx.x; c < total_chunks; c += n_wg) {
     const ChunkRef cr = chunks[c];
     const TensorDesc td = tds[cr.tensor];
     const LayerDev& ls = layers[cr.tensor];
     const uint32_t mode = ls.mode;
     if (!td.has_probe || ls.mask_done || mode == kSelHist) continue;
     const int64_t base = (int64_t)cr.index * kChunk;
-    mask_chunk(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
+    mask_chunk(td, base, mode, ls.theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, tab->cands, tab->cand_counters);
   }
 }
 
@@ -43,26 +44,24 @@ __global__ __launch_bounds__(kThreads) void k_mask_pass(const TensorDesc* __rest
 // In the element-wise form (ELEM) the threshold must be final before the update, so the mask and
 // the listed keys are completed by the kernels before this one and no mask pass runs here.
 template <bool ELEM, bool MOM>
-__global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restrict__ tds,
-                                                     const ChunkRef* __restrict__ chunks, LayerDev* layers,
-                                                     const GlobalDev* glob, Candidate* cands, uint32_t* counters,
-                                                     const uint32_t* trans_list, uint32_t n_tensors, ResizePlan plan,
-                                                     char* scratch, uint32_t resize_slots, uint32_t resize_wgs, StepArg sa, float wd,
-                                                     float mu, float alpha) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) void k_update(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                     const ChunkRef* __restrict__ chunks, const GlobalDev* glob, StepScalars arg,
+                                                     uint32_t resize_slots, uint32_t resize_wgs) {
+  const StepScalars sc = step_scalars(arg, *tab);
+  const LayerDev* const layers = tab->layers;
+  const float wd = tab->hyper.weight_decay, mu = tab->hyper.momentum, alpha = tab->hyper.alpha;
   if (blockIdx.x < resize_wgs) {
     const uint64_t skip_epoch = glob->skip_epoch;
     const uint32_t count = glob->trans_count[sc.step_id & 1u];
     TA_LOADED("s"(skip_epoch), "s"(count));
     if (count == 0 || skip_epoch == sc.step_id) return;
-    resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, scratch, 0u, resize_slots, blockIdx.x, resize_wgs, sc,
-                            wd, mu, alpha);
+    resize_items<ELEM, MOM>(*tab, tds, count, 0u, resize_slots, blockIdx.x, resize_wgs, sc);
     return;
   }
   // the skip word travels together with the tables: its latency is not one more before the data's
   const uint64_t skip_epoch = glob->skip_epoch;
   const ChunkRef cr = chunks[blockIdx.x - resize_wgs];
-  LayerDev& ls = layers[cr.tensor];
+  const LayerDev& ls = layers[cr.tensor];
   const int pd = ls.prev_code, nd = ls.code;
   const TensorDesc td = tds[cr.tensor];
   const float eta = ls.eta;
@@ -77,29 +76,20 @@ __global__ __launch_bounds__(kThreads) void k_update(const TensorDesc* __restric
   if constexpr (ELEM) return;
   // kSelHist cannot remain after the last scan; never write a mask from a stale range
   if (td.has_probe && !mask_done && mode != kSelHist) {
-    mask_chunk(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, cands, counters);
+    mask_chunk(td, base, mode, theta_key, ls.rng_lo, ls.rng_hi, cr.index, cr.tensor, tab->cands, tab->cand_counters);
   }
 }
 
-hipError_t launch_update(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha, bool elem, bool resize,
-                         hipStream_t s) {
-  const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
-  const ResizeGrid rg = resize ? resize_grid(plan, 0u, t.n_tensors, t.total_chunks < kResizeBigSet) : ResizeGrid{1u, 0u};
-  const dim3 grid(t.total_chunks + rg.grid);
-  const auto kernel = elem ? (mu != 0.0f ? k_update<true, true> : k_update<true, false>)
-                           : (mu != 0.0f ? k_update<false, true> : k_update<false, false>);
-  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, t.tensors, t.chunks, t.layers, t.glob, t.cands,
-                     t.cand_counters, t.trans_list, t.n_tensors, plan, t.resize_scratch, rg.slots, rg.grid, sa, wd, mu, alpha);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+hipError_t launch_update(const DeviceTables& t, const StepScalars& sc, bool elem, bool resize, hipStream_t s) {
+  const ResizeGrid rg = resize ? resize_grid(t.plan, 0u, t.n_tensors, t.total_chunks < kResizeBigSet) : ResizeGrid{1u, 0u};
+  const bool mom = t.hyper.momentum != 0.0f;
+  const auto kernel = elem ? (mom ? k_update<true, true> : k_update<true, false>) : (mom ? k_update<false, true> : k_update<false, false>);
+  return launch(kernel, t.total_chunks + rg.grid, kThreads, s, t.dev, t.tensors, t.chunks, t.glob, sc, rg.slots, rg.grid);
 }
 
-hipError_t launch_mask_pass(const DeviceTables& t, const StepArg& sa, hipStream_t s) {
+hipError_t launch_mask_pass(const DeviceTables& t, const StepScalars& sc, hipStream_t s) {
   const uint32_t grid = t.total_chunks < t.persistent_grid ? t.total_chunks : t.persistent_grid;
-  hipLaunchKernelGGL(k_mask_pass, dim3(grid), dim3(kThreads), 0, s, t.tensors, t.chunks, t.total_chunks, t.layers,
-                     t.glob, t.cands, t.cand_counters, sa);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  return launch(k_mask_pass, grid, kThreads, s, t.dev, t.tensors, t.chunks, t.glob, sc, grid);
 }
 
 }  // namespace triaccel

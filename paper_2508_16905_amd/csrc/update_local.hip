@@ -28,15 +28,9 @@ __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { re
 // gradients and the result read each time 35.0 -> 29.0, EfficientNet-B0 49.2 -> 39.2, ResNet-18 84.5 -> 73.3, 41 ragged
 // tensors of 9.7 M with the Fisher source 59.5 -> 50.0, 4000 tensors of 10 to 300 elements 175 -> 75.
 template <bool MOM, bool PROBED>
-__global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __restrict__ tds,
-                                                           const ChunkRef* __restrict__ chunks,
-                                                           const StatPartial* __restrict__ partials,
-                                                           const EmaPartial* __restrict__ ema_partials,
-                                                           const LayerIn* __restrict__ inputs, LayerDev* layers,
-                                                           GlobalDev* glob, GlobalDev* host_result, const Candidate* cands,
-                                                           uint32_t* counters, uint32_t* hist, uint32_t* arrived,
-                                                           uint32_t* trans_list, uint32_t n_tensors, uint32_t select_wgs,
-                                                           ResizePlan plan, char* scratch, StepArg sa, Hyper hp) {
+__global__ __launch_bounds__(kThreads) void k_update_local(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                           const ChunkRef* __restrict__ chunks, GlobalDev* glob, StepScalars arg,
+                                                           uint32_t select_wgs) {
   __shared__ LayerShared sh_layer;
   __shared__ union {
     HistShared hist;
@@ -45,27 +39,32 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   HistShared& sh = shared.hist;
   __shared__ LayerOut s_decision;
   __shared__ uint32_t s_last;
-  const StepScalars sc = step_scalars(sa);
   if constexpr (PROBED) {
     if (blockIdx.x < select_wgs) {
-      if (blockIdx.x < n_tensors)
-        select_local(blockIdx.x, tds, ema_partials, inputs, layers, glob, cands, counters, sc, hp, sh_layer, shared.select);
+      if (blockIdx.x < tab->n_tensors)
+        select_local(blockIdx.x, *tab, tds, glob, step_scalars(arg, *tab), tab->hyper, sh_layer, shared.select);
       return;
     }
   }
+  const ChunkRef cr = chunks[blockIdx.x - (PROBED ? select_wgs : 0u)];
+  const StepScalars sc = step_scalars(arg, *tab);
+  const Hyper hp = tab->hyper;
   const uint64_t skip_epoch = glob->skip_epoch;
   const bool skip = skip_epoch == sc.step_id;
-  const ChunkRef cr = chunks[blockIdx.x - (PROBED ? select_wgs : 0u)];
+  const StatPartial* const partials = tab->partials;
+  const EmaPartial* const ema_partials = tab->ema_partials;
   const TensorDesc td = tds[cr.tensor];
-  LayerDev& ls = layers[cr.tensor];
-  const LayerIn in = inputs[cr.tensor];
+  LayerDev& ls = tab->layers[cr.tensor];
+  const LayerIn in = tab->inputs[cr.tensor];
   TA_LOADED("s"(td.param), "s"(td.grad), "s"(td.mom), "s"(td.curv), "s"(td.numel), "s"(td.first_chunk), "s"(td.grad_dtype),
             "s"(td.has_probe), "s"(in.v), "s"(in.lambda), "s"(in.lambda_ctrl), "s"(in.code), "s"(in.prev_code), "s"(in.applied_steps),
-            "s"(in.lambda_power), "s"(td.n_chunks));
+            "s"(in.lambda_power), "s"(td.n_chunks), "s"(partials), "s"(ema_partials), "s"(hp.weight_decay), "s"(hp.momentum),
+            "s"(hp.beta_var), "s"(hp.tau_low), "s"(hp.tau_high), "s"(hp.tau_curv), "s"(hp.alpha), "s"(hp.ctrl_interval),
+            "s"(hp.lambda_source));
   if (skip) {
     if (threadIdx.x == 0 && cr.index == 0) {
       ls.found_inf = (ls.found_epoch == sc.step_id) ? 1u : 0u;
-      if (cr.tensor == 0) step_record(glob, host_result, sc, hp, true);
+      if (cr.tensor == 0) step_record(glob, tab->host_result, sc, hp, true);
     }
     return;
   }
@@ -93,7 +92,7 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
     in_place = update_any<false, MOM>(td, pd, nd, base, sc.inv_scale, hp.weight_decay, hp.momentum, ss, threadIdx.x,
                                       [&]() { return early ? decide() : true; });
   // launch 0 of the in-place resize: slot r of the tensor is the workgroup of its chunk r
-  if (!in_place) resize_item<false, MOM>(td, pd, nd, ss, plan, scratch, 0u, cr.index, sc, hp.weight_decay, hp.momentum);
+  if (!in_place) resize_item<false, MOM>(td, pd, nd, ss, *tab, 0u, cr.index, sc);
   // read again from shared memory: kept, they went to memory and back for want of registers
   EmaTotals ema{0, 0, 0, 0, 0};
   if constexpr (PROBED) ema = layer_ema(sh_layer);
@@ -110,7 +109,7 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
         __syncthreads();
         uint32_t above = 0;
         hist_chunk(td, base, w, sh.hist, now.predicted != 0, above);
-        flush_hist(sh.hist, w.bins, hist + (size_t)cr.tensor * kHistBins);
+        flush_hist(sh.hist, w.bins, tab->hist + (size_t)cr.tensor * kHistBins);
         above = wave_sum(above);
         if ((threadIdx.x & (kWave - 1)) == 0 && above) atomicAdd(&ls.acc_above, above);
         // This workgroup's counts (device-scope atomics) are complete before its arrival is counted.  With a
@@ -123,16 +122,16 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
   if (threadIdx.x == 0 && cr.index == 0) {
     // (kOutListed: select_local; kOutHist: below)
     if (probed && outcome == kOutFewNonzero) select_setup(td, ls, glob, in.plan, ema, k, outcome, sc.step_id);
-    layer_publish(cr.tensor, ls, s_decision, glob, trans_list, n_tensors, sc.step_id);
-    if (cr.tensor == 0) step_record(glob, host_result, sc, hp, false);
+    layer_publish(cr.tensor, ls, s_decision, glob, tab->trans_list, tab->n_tensors, sc.step_id);
+    if (cr.tensor == 0) step_record(glob, tab->host_result, sc, hp, false);
   }
   if constexpr (PROBED) {
-    if (cr.index == 0 && outcome != kOutListed) reset_cand_counters(counters, cr.tensor);  // drop what was listed
+    if (cr.index == 0 && outcome != kOutListed) reset_cand_counters(tab->cand_counters, cr.tensor);  // drop what was listed
     if (outcome != kOutHist) return;
     if (threadIdx.x == 0) {
-      const bool last = atomicAdd(arrival(arrived, cr.tensor), 1u) + 1u == td.n_chunks;
+      const bool last = atomicAdd(arrival(tab->arrived, cr.tensor), 1u) + 1u == td.n_chunks;
       if (last) {
-        *arrival(arrived, cr.tensor) = 0;
+        *arrival(tab->arrived, cr.tensor) = 0;
         select_setup(td, ls, glob, in.plan, ema, k, outcome, sc.step_id);
       }
       s_last = last ? 1u : 0u;
@@ -140,23 +139,18 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const TensorDesc* __r
     __syncthreads();
     if (!s_last) return;
     // the scan reads what the other workgroups added with device-scope loads
-    select_scan(cr.tensor, td, ls, glob, hist, sc.step_id, sh.hist, sh.part, sh.out, true);
-    select_serial(cr.tensor, td, ls, glob, hist, sc.step_id, sh.hist, sh.part, sh.out, 8);
+    select_scan(cr.tensor, td, ls, glob, tab->hist, sc.step_id, sh.hist, sh.part, sh.out, true);
+    select_serial(cr.tensor, td, ls, glob, tab->hist, sc.step_id, sh.hist, sh.part, sh.out, 8);
   }
 }
 
-hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool any_probe, hipStream_t s) {
-  const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
-  const bool mom = hp.momentum != 0.0f;
+hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, hipStream_t s) {
+  const bool mom = t.hyper.momentum != 0.0f;
   const auto kernel = any_probe ? (mom ? k_update_local<true, true> : k_update_local<false, true>)
                                 : (mom ? k_update_local<true, false> : k_update_local<false, false>);
   // a multiple of eight: a chunk's workgroup goes to the same die in every kernel
   const uint32_t select_wgs = any_probe ? (t.n_tensors + 7u) & ~7u : 0u;
-  hipLaunchKernelGGL(kernel, dim3(select_wgs + t.total_chunks), dim3(kThreads), 0, s, t.tensors, t.wg_chunks, t.partials,
-                     t.ema_partials, t.inputs, t.layers, t.glob, t.host_result, t.cands, t.cand_counters, t.hist, t.arrived,
-                     t.trans_list, t.n_tensors, select_wgs, plan, t.resize_scratch, sa, hp);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  return launch(kernel, select_wgs + t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc, select_wgs);
 }
 
 // What is left of the selection after k_update_local, and before the element-wise form of the update on sets
@@ -167,16 +161,16 @@ hipError_t launch_update_local(const DeviceTables& t, const StepArg& sa, const H
 // rest take launch 1 of the in-place resize, four chunks of a level at a time.  After k_update_local all of them leave
 // at once in the steady state, which costs a step 1.5 us.
 template <bool MOM>
-__global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc* __restrict__ tds,
-                                                                const ChunkRef* __restrict__ chunks, uint32_t total_chunks,
-                                                                uint32_t n_tensors, LayerDev* layers, GlobalDev* glob,
-                                                                Candidate* cands, uint32_t* counters, uint32_t* arrived,
-                                                                uint32_t mask_wgs, const uint32_t* trans_list,
-                                                                ResizePlan plan, char* scratch, uint32_t resize_slots,
-                                                                int local, StepArg sa, float beta_h, float wd, float mu) {
+__global__ __launch_bounds__(kFinishThreads) void k_select_tail(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                                GlobalDev* glob, StepScalars arg, uint32_t mask_wgs,
+                                                                uint32_t resize_wgs, uint32_t resize_slots, int local) {
   __shared__ SelectShared<kFinishThreads> sh;
   __shared__ uint32_t s_last;
-  const StepScalars sc = step_scalars(sa);
+  const StepScalars sc = step_scalars(arg, *tab);
+  const uint32_t n_tensors = tab->n_tensors, total_chunks = tab->total_chunks;
+  LayerDev* const layers = tab->layers;
+  uint32_t* const counters = tab->cand_counters;
+  const float beta_h = tab->hyper.beta_curv;
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t pending = glob->mask_pending[sc.step_id & 1u];
   if (blockIdx.x < n_tensors) {
@@ -198,16 +192,15 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
               "s"(in.var_hold));
     // (a tensor that select_local settled is no longer in this mode)
     if (skip_epoch == sc.step_id || !td.has_probe || sel_outcome > 1u || in.mode != kSelCand) return;
-    select_finish<kFinishThreads, kFinishRegs>(l, td, ls, in, listed, cands, counters, beta_h, sh);
+    select_finish<kFinishThreads, kFinishRegs>(l, td, ls, in, listed, tab->cands, counters, beta_h, sh);
     return;
   }
   if (blockIdx.x >= n_tensors + mask_wgs) {
     const uint32_t count = glob->trans_count[sc.step_id & 1u];
     TA_LOADED("s"(skip_epoch), "s"(count));
     if (count == 0 || skip_epoch == sc.step_id) return;
-    resize_items<false, MOM, kFinishThreads / kThreads>(tds, layers, glob, trans_list, n_tensors, plan, scratch, 1u,
-                                                        resize_slots, blockIdx.x - n_tensors - mask_wgs,
-                                                        gridDim.x - n_tensors - mask_wgs, sc, wd, mu, 0.0f);
+    resize_items<false, MOM, kFinishThreads / kThreads>(*tab, tds, count, 1u, resize_slots,
+                                                        blockIdx.x - n_tensors - mask_wgs, resize_wgs, sc);
     return;
   }
   TA_LOADED("s"(skip_epoch), "s"(pending));
@@ -218,7 +211,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
   const uint32_t group = uniform(threadIdx.x / kThreads);
   uint32_t c = min(part * per, total_chunks);
   while (c < c1) {
-    const uint32_t l = chunks[c].tensor;
+    const uint32_t l = tab->chunks[c].tensor;
     const TensorDesc td = tds[l];
     const uint32_t end = min(td.first_chunk + td.n_chunks, c1);
     const uint32_t mine = end - c;
@@ -232,14 +225,14 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
     for (uint32_t q = c + group; q < end; q += kFinishThreads / kThreads) {
       const uint32_t index = q - td.first_chunk;
       const int64_t base = (int64_t)index * kChunk;
-      mask_chunk<true>(td, base, mode, theta, rng_lo, rng_hi, index, l, cands, counters);
+      mask_chunk<true>(td, base, mode, theta, rng_lo, rng_hi, index, l, tab->cands, counters);
     }
     c = end;
     published_before_here();  // mask words and listed keys are complete before the arrival is counted
     __syncthreads();
     if (threadIdx.x == 0) {
-      const bool last = atomicAdd(arrival(arrived, l), mine) + mine == td.n_chunks;
-      if (last) *arrival(arrived, l) = 0;
+      const bool last = atomicAdd(arrival(tab->arrived, l), mine) + mine == td.n_chunks;
+      if (last) *arrival(tab->arrived, l) = 0;
       s_last = last ? 1u : 0u;
     }
     __syncthreads();
@@ -251,7 +244,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
       uint32_t listed = 0;
       if (threadIdx.x <= kCandLists)
         listed = __hip_atomic_load(cand_counter(counters, l, threadIdx.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      select_finish<kFinishThreads, kFinishRegs>(l, td, ls, finish_in(ls), listed, cands, counters, beta_h, sh);
+      select_finish<kFinishThreads, kFinishRegs>(l, td, ls, finish_in(ls), listed, tab->cands, counters, beta_h, sh);
       __syncthreads();
     }
   }
@@ -259,22 +252,18 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const TensorDesc
 
 static_assert((kResizeTopSmall << 6) >= kLocalMaxChunks && kLaunchBoundChunks <= kResizeBigSet,
               "one subtree stage: the resize of a set of the local form has two launches at most");
-hipError_t launch_select_tail(const DeviceTables& t, const StepArg& sa, const Hyper& hp, bool local, bool resize, hipStream_t s) {
+hipError_t launch_select_tail(const DeviceTables& t, const StepScalars& sc, bool local, bool resize, hipStream_t s) {
   constexpr uint32_t kGroups = kFinishThreads / kThreads;
   const uint32_t all = (t.total_chunks + kGroups - 1) / kGroups, cap = t.persistent_grid / 8;  // one per CU
   const uint32_t mask_wgs = all < cap ? all : cap;
-  const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
   ResizeGrid rg{1u, 0u};
-  if (resize && plan.n_stages > 1) {
-    rg = resize_grid(plan, 1u, t.n_tensors, true);
+  if (resize && t.plan.n_stages > 1) {
+    rg = resize_grid(t.plan, 1u, t.n_tensors, true);
     if (rg.grid > cap) rg.grid = cap;
   }
-  const auto kernel = hp.momentum != 0.0f ? k_select_tail<true> : k_select_tail<false>;
-  hipLaunchKernelGGL(kernel, dim3(t.n_tensors + mask_wgs + rg.grid), dim3(kFinishThreads), 0, s, t.tensors, t.chunks,
-                     t.total_chunks, t.n_tensors, t.layers, t.glob, t.cands, t.cand_counters, t.arrived, mask_wgs,
-                     t.trans_list, plan, t.resize_scratch, rg.slots, local ? 1 : 0, sa, hp.beta_curv, hp.weight_decay, hp.momentum);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  const auto kernel = t.hyper.momentum != 0.0f ? k_select_tail<true> : k_select_tail<false>;
+  return launch(kernel, t.n_tensors + mask_wgs + rg.grid, kFinishThreads, s, t.dev, t.tensors, t.glob, sc, mask_wgs, rg.grid,
+                rg.slots, local ? 1 : 0);
 }
 
 }  // namespace triaccel

@@ -6,18 +6,16 @@ namespace triaccel {
 
 // Launches 1 .. n_stages - 1 of the in-place resize (launch 0 is part of the update kernel's grid).
 template <bool ELEM, bool MOM>
-__global__ __launch_bounds__(kThreads) void k_update_resize(const TensorDesc* __restrict__ tds, const LayerDev* layers,
-                                                            const GlobalDev* glob, const uint32_t* trans_list,
-                                                            uint32_t n_tensors, ResizePlan plan, char* scratch, uint32_t launch,
-                                                            uint32_t slots, StepArg sa, float wd, float mu, float alpha) {
-  const StepScalars sc = step_scalars(sa);
+__global__ __launch_bounds__(kThreads) void k_update_resize(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                            const GlobalDev* glob, StepScalars arg, uint32_t launch, uint32_t slots,
+                                                            uint32_t n_wg) {
+  const StepScalars sc = step_scalars(arg, *tab);
   // nothing to do on most steps: the two words that say so are read together
   const uint64_t skip_epoch = glob->skip_epoch;
   const uint32_t count = glob->trans_count[sc.step_id & 1u];
   TA_LOADED("s"(skip_epoch), "s"(count));
   if (count == 0 || skip_epoch == sc.step_id) return;
-  resize_items<ELEM, MOM>(tds, layers, glob, trans_list, n_tensors, plan, scratch, launch, slots, blockIdx.x, gridDim.x, sc, wd, mu,
-                     alpha);
+  resize_items<ELEM, MOM>(*tab, tds, count, launch, slots, blockIdx.x, n_wg, sc);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -42,16 +40,14 @@ __global__ __launch_bounds__(kThreads) void k_cast(const float* __restrict__ src
   if (tail.any) store_tail<ND>(to, tail, wt);
 }
 
-hipError_t launch_update_resize(const DeviceTables& t, const StepArg& sa, float wd, float mu, float alpha,
-                                bool elem, hipStream_t s) {
-  const ResizePlan plan = make_resize_plan(t.max_chunks_per_tensor, t.total_chunks);
-  for (uint32_t launch = 1; launch < plan.n_stages; ++launch) {
-    const ResizeGrid rg = resize_grid(plan, launch, t.n_tensors, t.total_chunks < kResizeBigSet);
-    const auto kernel = elem ? (mu != 0.0f ? k_update_resize<true, true> : k_update_resize<true, false>)
-                             : (mu != 0.0f ? k_update_resize<false, true> : k_update_resize<false, false>);
-    hipLaunchKernelGGL(kernel, dim3(rg.grid), dim3(kThreads), 0, s, t.tensors, t.layers, t.glob, t.trans_list,
-                       t.n_tensors, plan, t.resize_scratch, launch, rg.slots, sa, wd, mu, alpha);
-    TA_LAUNCH_CHECK();
+hipError_t launch_update_resize(const DeviceTables& t, const StepScalars& sc, bool elem, hipStream_t s) {
+  const bool mom = t.hyper.momentum != 0.0f;
+  const auto kernel = elem ? (mom ? k_update_resize<true, true> : k_update_resize<true, false>)
+                           : (mom ? k_update_resize<false, true> : k_update_resize<false, false>);
+  for (uint32_t q = 1; q < t.plan.n_stages; ++q) {
+    const ResizeGrid rg = resize_grid(t.plan, q, t.n_tensors, t.total_chunks < kResizeBigSet);
+    const hipError_t e = launch(kernel, rg.grid, kThreads, s, t.dev, t.tensors, t.glob, sc, q, rg.slots, rg.grid);
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -61,9 +57,7 @@ __global__ void k_set_scalars(StepScalars v, StepScalars* dst) {
 }
 
 hipError_t launch_set_scalars(const DeviceTables& t, const StepScalars& sc, hipStream_t s) {
-  hipLaunchKernelGGL(k_set_scalars, dim3(1), dim3(kWave), 0, s, sc, t.scalars);
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  return launch(k_set_scalars, 1, kWave, s, sc, &t.dev->scalars);
 }
 
 void set_scalars_node_params(hipKernelNodeParams* p, void** args, const StepScalars* sc, StepScalars* const* dst) {
@@ -80,13 +74,8 @@ void set_scalars_node_params(hipKernelNodeParams* p, void** args, const StepScal
 hipError_t launch_cast(const float* src, void* dst, int64_t n, int dtype, hipStream_t s) {
   int64_t blocks = (n + kChunk - 1) / kChunk;
   if (blocks < 1) blocks = 1;
-  switch (dtype) {
-    case kFP32: hipLaunchKernelGGL(k_cast<kFP32>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, src, dst, n); break;
-    case kBF16: hipLaunchKernelGGL(k_cast<kBF16>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, src, dst, n); break;
-    default: hipLaunchKernelGGL(k_cast<kFP16>, dim3((uint32_t)blocks), dim3(kThreads), 0, s, src, dst, n); break;
-  }
-  TA_LAUNCH_CHECK();
-  return hipSuccess;
+  const auto kernel = dtype == kFP32 ? k_cast<kFP32> : dtype == kBF16 ? k_cast<kBF16> : k_cast<kFP16>;
+  return launch(kernel, (uint32_t)blocks, kThreads, s, src, dst, n);
 }
 
 }  // namespace triaccel
