@@ -223,15 +223,21 @@ int enqueue_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, hipEven
   const bool local = local_form(*h);
   const bool resize = sizes_can_change(*h);
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
-  TA_HIP(launch_grad_stats(T, sc, local, s));
-  if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
-  if (any_probe) TA_HIP(launch_curv_ema(T, sc, fisher, local, s));
+  // (with an event between the two they are launches of their own)
+  const bool fused = T.fused && any_probe && !(ev && level == 1);
+  if (fused) {
+    TA_HIP(launch_stats_ema(T, sc, fisher, s));
+  } else {
+    TA_HIP(launch_grad_stats(T, sc, local, s));
+    if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
+    if (any_probe) TA_HIP(launch_curv_ema(T, sc, fisher, local, s));
+  }
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[2], s));
   if (local) {
     // a set bound by its launches: the update takes the layers' decisions and settles the thresholds
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
     if (ev) TA_HIP(hipEventRecord(ev[4], s));
-    TA_HIP(launch_update_local(T, sc, any_probe, s));
+    TA_HIP(launch_update_local(T, sc, any_probe, fused, s));
     if (ev) TA_HIP(hipEventRecord(ev[5], s));
     if (!any_probe && resize) TA_HIP(launch_update_resize(T, sc, false, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[6], s));
@@ -463,6 +469,15 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   ws.add(&T.resize_scratch, (size_t)scratch_chunks * kChunk * 4);
   ws.add(&T.inputs, (size_t)n);
   ws.add(&T.arrived, (size_t)n * kCandCounterStride);
+  T.fused = local_form(*c) && T.total_chunks <= kFusedChunks;
+  uint64_t undo = 0;
+  if (T.fused)
+    for (TensorDesc& d : c->desc) {
+      d.undo_slot = (uint32_t)(undo / kUndoUnit);
+      undo += ((uint64_t)d.numel + kUndoUnit - 1) / kUndoUnit * kUndoUnit;
+    }
+  ws.add(&T.undo_h, (size_t)undo);
+  ws.add(&T.undo_mask, (size_t)undo / 32);
   ws.add(&T.dev, 1);
   if ((rc = ws.allocate(c))) return fail(rc);
   T.tensors = c->tables[0].dev;

@@ -94,6 +94,16 @@ constexpr uint64_t kKeepBytes = 2ull << 30;
 // 0.5 M 122.7 and 115.2, 41 of 1.0 M 120.4 and 114.8, of 2.0 M 213.0 and 206.1, 60 of 12 M 298 and 303.
 constexpr uint32_t kLateChunks = 1024;
 
+// Sets of the local form with at most this many chunks (2.1 M elements) take the statistics and the curvature average of a
+// probed step in one launch (k_stats_ema): 1.5 us less for the launch, against 4 bytes more written per element, as the
+// skip rule is only known after it.  A probed step, us, in two launches and in one: 12 tensors of 20,000 elements in all
+// 13.7 and 12.2, of 0.3 M 17.9 and 16.5, of 1.0 M 20.5 and 19.5 (bf16 20.2 and 18.6, Fisher 19.0 and 17.4), 60 of 0.7 M 20.8 and
+// 19.2, 40 of 1.7 M 24.0 and 23.2, 12 of 2.1 M 26.4 and 26.2, of 2.5 M 27.1 and 26.8 (bf16 26.0 and 26.1); 30 of 4 M 35.5
+// and 35.9, of 6 M 48.2 and 50.3.  With the hint for streaming data off on what is put aside: 12 of 2.1 M, Fisher, 22.4
+// instead of 21.5.
+constexpr uint32_t kFusedChunks = 512;
+constexpr uint32_t kUndoUnit = 128;  // elements whose mask is 16 bytes
+
 enum SelMode : uint32_t {
   kSelHist = 0,   // a histogram over the window is (being) accumulated; the scan decides what next
   kSelCand = 1,   // theta lies in [rng_lo, rng_hi): few enough keys there to list them
@@ -141,6 +151,7 @@ struct TensorDesc {
   uint32_t sub_cap;      // capacity of each of the other lists (key_lists)
   uint32_t list_all;     // numel <= kListAllMax: every non-zero key is listed, or read by select_local; no prediction
   uint32_t resize_slot;  // the tensor's first chunk in the scratch area of the in-place resize
+  uint32_t undo_slot;    // where its curvature and mask are kept while a step may have to be taken back, in kUndoUnit elements
 };
 
 // Per-layer device state.  The leading part mirrors triaccel_layer_info.

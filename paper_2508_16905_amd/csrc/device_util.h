@@ -134,7 +134,14 @@ __device__ __forceinline__ void published_before_here() { asm volatile("s_waitcn
 // Flags of a lane's elements: bit 4 r + i = element i of row r, kTailFlag = the seventeenth.
 constexpr uint32_t kTailFlag = 1u << 16;
 
-// Mask words of a chunk from every lane's flags: lane (8 j + r) of a wavefront writes row r's word j.
+// The word of a chunk's mask that this lane writes (`word` of the tensor), if any: lane (8 j + r) of a wavefront row r's word j.
+__device__ __forceinline__ bool mask_word_of(const TensorDesc& td, int64_t base, int64_t& word) {
+  const int tid = threadIdx.x & (kThreads - 1), sub = tid & 7;
+  word = ((base + (int64_t)sub * kRowElems) >> 5) + (tid >> 3);
+  return sub < kRows && word < ((td.numel + 31) >> 5);
+}
+
+// Mask words of a chunk from every lane's flags (mask_word_of).
 template <bool SHARED = false>
 __device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t base, uint32_t flags, const Tail& tail) {
   static_assert(kRows == 4, "one word per row, chosen by two bits of the lane");
@@ -148,10 +155,18 @@ __device__ __forceinline__ void store_mask_flags(const TensorDesc& td, int64_t b
   const uint32_t w0 = gather_mask_word(flags & 15u, lane), w1 = gather_mask_word((flags >> 4) & 15u, lane);
   const uint32_t w2 = gather_mask_word((flags >> 8) & 15u, lane), w3 = gather_mask_word((flags >> 12) & 15u, lane);
   const uint32_t lo = (sub & 1) ? w1 : w0, hi = (sub & 1) ? w3 : w2;
-  if (sub < kRows) {
-    const int64_t widx = ((base + (int64_t)sub * kRowElems) >> 5) + (tid >> 3);
-    if (widx < ((td.numel + 31) >> 5)) store_word<SHARED>(td.mask + widx, (sub & 2) ? hi : lo);
-  }
+  int64_t word;
+  if (mask_word_of(td, base, word)) store_word<SHARED>(td.mask + word, (sub & 2) ? hi : lo);
+}
+
+// What a launch that may have to be taken back overwrote of a chunk (k_stats_ema): curvature and mask words.
+struct EmaUndo {
+  float* h;
+  uint32_t* mask;
+};
+__device__ __forceinline__ EmaUndo ema_undo(float* undo_h, uint32_t* undo_mask, const TensorDesc& td, int64_t base) {
+  const int64_t at = (int64_t)td.undo_slot * kUndoUnit + base;
+  return EmaUndo{undo_h + at, undo_mask + (at >> 5)};
 }
 
 // Candidate storage.  Each tensor owns kCandLists sub-lists of sub_cap entries plus one overflow

@@ -43,6 +43,8 @@ struct StepTables {
   DevPtr<char> resize_scratch;  // new values of the first chunks of tensors that change size (resize_schedule.h)
   DevPtr<LayerIn> inputs;       // n_tensors: what the running step's decisions read of the layers' records (k_update_local)
   DevPtr<uint32_t> arrived;     // n_tensors counters, kCandCounterStride words apart: chunks done in a fallback pass; 0 between steps
+  DevPtr<float> undo_h;         // curvature and mask words that a step overwrites before it is known to be taken (kFusedChunks)
+  DevPtr<uint32_t> undo_mask;
   uint32_t n_tensors;
   uint32_t total_chunks;
   Hyper hyper;
@@ -57,18 +59,22 @@ struct DeviceTables : StepTables {
   GlobalDev* glob;
   uint32_t max_chunks_per_tensor;
   bool all_small;            // no tensor is longer than kListAllMax: their keys always settle the thresholds
+  bool fused;                // probed steps take statistics and curvature in one launch, and have the workspace for it
   bool keep_grads;           // the gradients of the set have at most kKeepBytes
   uint32_t persistent_grid;  // workgroups of the persistent streaming kernels
 };
 
 hipError_t launch_grad_stats(const DeviceTables& t, const StepScalars& sc, bool local, hipStream_t s);
 hipError_t launch_curv_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, bool local, hipStream_t s);
+// Both of these, on probed steps of sets of the local form that have the workspace for it.
+hipError_t launch_stats_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, hipStream_t s);
 hipError_t launch_hist_pass(const DeviceTables& t, const StepScalars& sc, int serial_rounds, hipStream_t s);
 hipError_t launch_select_finish(const DeviceTables& t, const StepScalars& sc, hipStream_t s);
 hipError_t launch_layer(const DeviceTables& t, const StepScalars& sc, hipStream_t s);
 // `resize`: with launch 0 of the in-place resize.
 hipError_t launch_update(const DeviceTables& t, const StepScalars& sc, bool elem, bool resize, hipStream_t s);
-hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, hipStream_t s);
+// `undo`: after k_stats_ema.
+hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, bool undo, hipStream_t s);
 // `local`: after k_update_local, which settled most tensors' thresholds; `resize`: with launch 1 of the in-place resize (sets
 // of the local form: its plans have two launches at most).
 hipError_t launch_select_tail(const DeviceTables& t, const StepScalars& sc, bool local, bool resize, hipStream_t s);

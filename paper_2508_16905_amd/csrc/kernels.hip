@@ -15,17 +15,18 @@ namespace triaccel {
 // (a sample of the data, so the sums stay small against their cancellation).  Lanes and
 // wavefronts are added in a fixed order; one (mean, M2) partial per chunk.
 // ---------------------------------------------------------------------------------------------
-template <int GD, bool KEEP>
-__device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, float inv_scale, double& shift,
-                                            double& s1, double& s2, uint32_t& bad) {
-  uint32_t g[kRows][4];
-  // the shift is read in the same batch of loads as the data: one memory latency per chunk, not two
-  const float first = load1<GD>(td.grad, base);
-  // the update reads the gradients again: KEEP leaves them in the caches (figures at kKeepBytes)
-  const int32_t left = chunk_left(base, td.numel);
-  const Tail tail = tail_of(left, threadIdx.x);
-  const uint32_t gt = load_chunk<kWords<GD>, KEEP>(chunk_of<kWords<GD>>(td.grad, base), left, tail, g);
-  shift = (double)(first * inv_scale);
+// A lane's sums over its elements.
+struct StatSums {
+  double shift, s1, s2;
+  uint32_t bad;
+};
+// `g`, `gt`: the chunk's gradients as loaded (widened in place); `first`: its first value.
+template <int GD>
+__device__ __forceinline__ StatSums stats_sums(uint32_t (&g)[kRows][4], uint32_t gt, float first, int32_t left, const Tail& tail,
+                                               float inv_scale) {
+  double s1 = 0.0, s2 = 0.0;
+  uint32_t bad = 0;
+  const double shift = (double)(first * inv_scale);
   const auto add = [&](uint32_t bits, bool inside) {
     bad |= ((bits & 0x7f800000u) == 0x7f800000u) ? 1u : 0u;
     double d = (double)(u2f(bits) * inv_scale) - shift;
@@ -49,6 +50,48 @@ __device__ __forceinline__ void stats_chunk(const TensorDesc& td, int64_t base, 
     }
     if (tail.any) add(widen1<GD>(gt), tail.mine);
   }
+  return StatSums{shift, s1, s2, bad};
+}
+
+template <int GD, bool KEEP>
+__device__ __forceinline__ StatSums stats_chunk(const TensorDesc& td, int64_t base, float inv_scale) {
+  uint32_t g[kRows][4];
+  // the shift is read in the same batch of loads as the data: one memory latency per chunk, not two
+  const float first = load1<GD>(td.grad, base);
+  // the update reads the gradients again: KEEP leaves them in the caches (figures at kKeepBytes)
+  const int32_t left = chunk_left(base, td.numel);
+  const Tail tail = tail_of(left, threadIdx.x);
+  const uint32_t gt = load_chunk<kWords<GD>, KEEP>(chunk_of<kWords<GD>>(td.grad, base), left, tail, g);
+  return stats_sums<GD>(g, gt, first, left, tail, inv_scale);
+}
+
+// The wavefronts' sums, and what a non-finite element sets; then, behind a barrier, the chunk's record (one thread).
+__device__ __forceinline__ void stats_reduce(const StatSums& s, double (&s_sum)[2][kThreads / kWave], LayerDev& ls, GlobalDev* glob,
+                                             uint64_t step_id) {
+  const double s1 = wave_sum_f64(s.s1), s2 = wave_sum_f64(s.s2);
+  const uint32_t bad = wave_or(s.bad);
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if (lane == 0) {
+    s_sum[0][wave] = s1;
+    s_sum[1][wave] = s2;
+    if (bad) {
+      atomicExch(reinterpret_cast<unsigned long long*>(&ls.found_epoch), (unsigned long long)step_id);
+      atomicExch(reinterpret_cast<unsigned long long*>(&glob->skip_epoch), (unsigned long long)step_id);
+    }
+  }
+}
+__device__ __forceinline__ void stats_record(double shift, const double (&s_sum)[2][kThreads / kWave], int64_t left,
+                                             StatPartial& p) {
+  double t1 = s_sum[0][0], t2 = s_sum[1][0];
+#pragma unroll
+  for (int w = 1; w < kThreads / kWave; ++w) {
+    t1 += s_sum[0][w];
+    t2 += s_sum[1][w];
+  }
+  const double n = (double)(left < kChunk ? left : kChunk);
+  const double m2 = t2 - t1 * t1 / n;
+  p.mean = shift + t1 / n;
+  p.m2 = m2 < 0.0 ? 0.0 : m2;  // inf and NaN (x overflowed) stay
 }
 
 template <bool KEEP>
@@ -65,54 +108,26 @@ __global__ __launch_bounds__(kThreads) void k_grad_stats(const StepTables* __res
   // k_update_local takes the step's decisions from this copy: it writes the layers' records while it runs
   if (local && cr.index == 0 && threadIdx.x == 0) inputs[cr.tensor] = layer_in(layers[cr.tensor]);
   const int64_t base = (int64_t)cr.index * kChunk;
-  double s1 = 0.0, s2 = 0.0;
-  uint32_t bad = 0;
-  double shift = 0.0;
+  StatSums sums;
   switch (td.grad_dtype) {
-    case kFP32: stats_chunk<kFP32, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-    case kBF16: stats_chunk<kBF16, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
-    default: stats_chunk<kFP16, KEEP>(td, base, sc.inv_scale, shift, s1, s2, bad); break;
+    case kFP32: sums = stats_chunk<kFP32, KEEP>(td, base, sc.inv_scale); break;
+    case kBF16: sums = stats_chunk<kBF16, KEEP>(td, base, sc.inv_scale); break;
+    default: sums = stats_chunk<kFP16, KEEP>(td, base, sc.inv_scale); break;
   }
-  s1 = wave_sum_f64(s1);
-  s2 = wave_sum_f64(s2);
-  bad = wave_or(bad);
   __shared__ double s_sum[2][kThreads / kWave];
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  if (lane == 0) {
-    s_sum[0][wave] = s1;
-    s_sum[1][wave] = s2;
-    if (bad) {
-      atomicExch(reinterpret_cast<unsigned long long*>(&layers[cr.tensor].found_epoch), (unsigned long long)sc.step_id);
-      atomicExch(reinterpret_cast<unsigned long long*>(&glob->skip_epoch), (unsigned long long)sc.step_id);
-    }
-  }
+  stats_reduce(sums, s_sum, layers[cr.tensor], glob, sc.step_id);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t1 = s_sum[0][0], t2 = s_sum[1][0];
-#pragma unroll
-    for (int w = 1; w < kThreads / kWave; ++w) {
-      t1 += s_sum[0][w];
-      t2 += s_sum[1][w];
-    }
-    const int64_t left = td.numel - base;
-    const double n = (double)(left < kChunk ? left : kChunk);
-    const double m2 = t2 - t1 * t1 / n;
-    StatPartial& p = partials[td.first_chunk + cr.index];
-    p.mean = shift + t1 / n;
-    p.m2 = m2 < 0.0 ? 0.0 : m2;  // inf and NaN (x overflowed) stay
-  }
+  if (threadIdx.x == 0) stats_record(sums.shift, s_sum, td.numel - base, partials[td.first_chunk + cr.index]);
 }
 
 // A chunk's record: keys above the band and zero keys, largest key, keys listed, and whether a sample was not finite, of
-// every lane, in a fixed order.  All threads of the workgroup call it.
-__device__ __forceinline__ void ema_record(const TensorDesc& td, int64_t base, uint32_t chunk_index, uint32_t above_zeros,
-                                           uint32_t maxkey, uint32_t listed, uint32_t nonfin,
-                                           EmaPartial* __restrict__ ema_partials) {
+// every lane, in a fixed order: the wavefronts' sums, then, behind a barrier, the record (one thread).
+__device__ __forceinline__ void ema_reduce(uint32_t above_zeros, uint32_t maxkey, uint32_t listed, uint32_t nonfin,
+                                           uint32_t (&s_red)[4][kThreads / kWave]) {
   above_zeros = wave_sum(above_zeros);  // at most 4096 + 64 (a wavefront's seventeenth elements) in either half: no carry
   maxkey = wave_max(maxkey);
   listed = wave_sum(listed);
   const uint32_t anynf = __any(nonfin != 0u) ? 1u : 0u;
-  __shared__ uint32_t s_red[4][kThreads / kWave];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   if (lane == 0) {
     s_red[0][wave] = above_zeros;
@@ -120,22 +135,21 @@ __device__ __forceinline__ void ema_record(const TensorDesc& td, int64_t base, u
     s_red[2][wave] = listed;
     s_red[3][wave] = anynf;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t az = 0, mk = 0, ln = 0, nf = 0;
+}
+__device__ __forceinline__ EmaPartial ema_record(int32_t chunk_left, const uint32_t (&s_red)[4][kThreads / kWave]) {
+  uint32_t az = 0, mk = 0, ln = 0, nf = 0;
 #pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) {
-      az += s_red[0][w];
-      mk = max(mk, s_red[1][w]);
-      ln += s_red[2][w];
-      nf |= s_red[3][w];
-    }
-    // elements past the end of the tensor were counted as zero keys
-    // (the seventeenth elements are a wavefront's, of which left % 4 exist)
-    const uint32_t left = (uint32_t)chunk_left(base, td.numel), rest = left & 3u;
-    const uint32_t past = kChunk - (left - rest) + (rest ? kWave - rest : 0u);
-    ema_partials[td.first_chunk + chunk_index] = EmaPartial{az - (past << 16), mk, ln, nf};
+  for (int w = 0; w < kThreads / kWave; ++w) {
+    az += s_red[0][w];
+    mk = max(mk, s_red[1][w]);
+    ln += s_red[2][w];
+    nf |= s_red[3][w];
   }
+  // elements past the end of the tensor were counted as zero keys
+  // (the seventeenth elements are a wavefront's, of which left % 4 exist)
+  const uint32_t left = (uint32_t)chunk_left, rest = left & 3u;
+  const uint32_t past = kChunk - (left - rest) + (rest ? kWave - rest : 0u);
+  return EmaPartial{az - (past << 16), mk, ln, nf};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -156,44 +170,87 @@ __device__ __forceinline__ void ema_record(const TensorDesc& td, int64_t base, u
 // instructions on sets that fit the chip at once (4.0 M parameters: 29.6 us with, 21.2 us
 // without; 11.2 M: 45.2, 35.6 us).  Elements past the tensor's end read as 0, whose sample is 0 and
 // whose key is 0: they only have to be taken off the count of zero keys.
-template <int SRC>
-__device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, float inv_scale, float beta_h,
-                                          float omb_h, bool first, bool listing, uint32_t list_lo, uint32_t list_hi,
-                                          uint32_t chunk_index, uint32_t tensor, Candidate* cands,
-                                          uint32_t* counters, EmaPartial* __restrict__ ema_partials) {
+//
+// SD: a precision code = the pass takes the gradients' moments as well (k_stats_ema; the same as SRC if SRC is one), and
+// leaves the old values of what it overwrites with `undo`.
+struct EmaRanges {
+  bool listing;
+  uint32_t list_lo, list_hi;
+};
+struct EmaShared {
+  uint32_t red[4][kThreads / kWave];
+};
+struct StatShared {
+  double sum[2][kThreads / kWave];
+};
+template <int SRC, int SD>
+__device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, const StepScalars& sc, float beta_h, float omb_h,
+                                          bool first, const EmaRanges& ranges, uint32_t chunk_index, uint32_t tensor,
+                                          Candidate* cands, uint32_t* counters, EmaPartial* __restrict__ ema_partials,
+                                          const EmaUndo& undo, StatPartial* __restrict__ partials, LayerDev* layers, GlobalDev* glob,
+                                          EmaShared& sh, StatShared& sh_stats) {
+  static_assert(SRC < 0 || SD < 0 || SRC == SD, "one gradient");
+  constexpr bool STATS = SD >= 0;
   uint32_t maxkey = 0, nonfin = 0;
   const uint32_t tid = threadIdx.x;
-  constexpr int ZW = SRC < 0 ? 4 : kWords<SRC>;
+  constexpr int ZW = SRC < 0 ? 4 : kWords<SRC>, GW = STATS ? kWords<SD> : 4;
   const void* const zp = chunk_of<ZW>(SRC < 0 ? static_cast<const void*>(td.z) : td.grad, base);
   const void* const hzp = chunk_of<4>(static_cast<const void*>(td.hz), base);
+  const void* const gp = chunk_of<GW>(td.grad, base);
   void* const hp = chunk_of<4>(static_cast<void*>(td.curv), base);
   const int32_t left = chunk_left(base, td.numel);
   const Rows zrows = rows_of<ZW>(zp, left), hzrows = rows_of<4>(hzp, left), hrows = rows_of<4>(hp, left);
-  uint32_t z[kRows][4], hz[SRC < 0 ? kRows : 1][4], h[kRows][4];
+  const Rows grows = rows_of<GW>(gp, left), urows = rows_of<4>(undo.h, left);
+  uint32_t z[kRows][4], hz[SRC < 0 ? kRows : 1][4], h[kRows][4], g[SRC < 0 && STATS ? kRows : 1][4];
+  float g0 = 0.0f;
+  if constexpr (STATS) g0 = load1<SD>(td.grad, base);
+  if constexpr (STATS && SRC < 0) {
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) load_words<GW, true>(grows, r, tid, g[r]);
+  }
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
-    load_words<ZW>(zrows, r, tid, z[r]);
+    load_words<ZW, STATS && SRC >= 0>(zrows, r, tid, z[r]);
     if constexpr (SRC < 0) load_words<4>(hzrows, r, tid, hz[r]);
     load_words<4>(hrows, r, tid, h[r]);
   }
   const Tail tail = tail_of(left, tid);
-  uint32_t zt = 0, hzt = 0, ht = 0;
+  uint32_t zt = 0, hzt = 0, ht = 0, gt = 0;
   if (tail.any) {
+    if constexpr (STATS && SRC < 0) gt = load_tail<GW>(gp, tail);
     zt = load_tail<ZW>(zp, tail);
     if constexpr (SRC < 0) hzt = load_tail<4>(hzp, tail);
     ht = load_tail<4>(hp, tail);
   }
+  uint32_t old_mask = 0;
+  if constexpr (STATS) {
+    // the lanes and words of store_mask_flags: each word is read and written by one lane
+    int64_t word;
+    if (mask_word_of(td, base, word)) old_mask = as_global<uint32_t>(td.mask)[word];
+  }
   __builtin_amdgcn_sched_barrier(0);  // all loads first
+  StatSums sums;
+  if constexpr (STATS) {
+    if constexpr (SRC < 0) sums = stats_sums<SD>(g, gt, g0, left, tail, sc.inv_scale);
+    else {
+      uint32_t x[kRows][4];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+#pragma unroll
+        for (int i = 0; i < GW; ++i) x[r][i] = z[r][i];
+      sums = stats_sums<SD>(x, zt, g0, left, tail, sc.inv_scale);
+    }
+  }
   uint32_t hflags = 0, lflags = 0, zeros = 0;  // keys >= list_hi / >= list_lo (bit 4 r + i), zero keys
   const uint32_t first_mask = first ? ~0u : 0u;
   const auto element = [&](uint32_t zbits, uint32_t hzbits, uint32_t& hbits, uint32_t flag) {
     float u;
     if constexpr (SRC < 0) {
       u = u2f(zbits) * u2f(hzbits);
-      u = u * inv_scale;
+      u = u * sc.inv_scale;
     } else {
       // x = g / S in both factors: u = x * x
-      const float x = u2f(zbits) * inv_scale;
+      const float x = u2f(zbits) * sc.inv_scale;
       u = x * x;
     }
     const uint32_t bad = (f2u(u) & 0x7f800000u) == 0x7f800000u ? ~0u : 0u;
@@ -207,17 +264,19 @@ __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, fl
     const uint32_t key = bits & 0x7fffffffu;
     maxkey = max(maxkey, key);
     zeros += key == 0u ? 1u : 0u;
-    hflags |= key >= list_hi ? flag : 0u;
-    lflags |= key >= list_lo ? flag : 0u;
+    hflags |= key >= ranges.list_hi ? flag : 0u;
+    lflags |= key >= ranges.list_lo ? flag : 0u;
   };
 #pragma unroll
   for (int r = 0; r < kRows; ++r) {
     if constexpr (SRC >= 0) widen4<SRC>(z[r]);
+    if constexpr (STATS) store_words<4>(urows, r, tid, h[r]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) element(z[r][i], SRC < 0 ? hz[r][i] : 0u, h[r][i], 1u << (r * 4 + i));
     store_words<4>(hrows, r, tid, h[r]);
   }
   if (tail.any) {
+    if constexpr (STATS) store_tail<kFP32>(undo.h, tail, ht);
     // lanes without a seventeenth element read 0 for it, like what lies past the end
     element(SRC < 0 ? zt : widen1<SRC < 0 ? kFP32 : SRC>(zt), hzt, ht, kTailFlag);
     store_tail<kFP32>(hp, tail, ht);
@@ -228,12 +287,31 @@ __device__ __forceinline__ void ema_chunk(const TensorDesc& td, int64_t base, fl
   const uint32_t listed = (uint32_t)__popc(cflags);
   // the chunk's record is made while the list's counter answers
   Appending app{0, 0, 0};
-  if (listing) {
+  if constexpr (STATS) {
+    int64_t word;
+    if (mask_word_of(td, base, word)) as_global<uint32_t>(undo.mask)[word - (base >> 5)] = old_mask;
+  }
+  if (ranges.listing) {
     app = append_begin(cflags, chunk_index, tensor, td, counters);
     store_mask_flags(td, base, hflags, tail);
   }
-  ema_record(td, base, chunk_index, above_zeros, maxkey, listed, nonfin, ema_partials);
-  if (listing) append_end(app, cflags, h, ht, tail, base, tensor, td, cands, counters);
+  ema_reduce(above_zeros, maxkey, listed, nonfin, sh.red);
+  if constexpr (STATS) stats_reduce(sums, sh_stats.sum, layers[tensor], glob, sc.step_id);
+  __syncthreads();
+  if (tid == 0) ema_partials[td.first_chunk + chunk_index] = ema_record(left, sh.red);
+  if constexpr (STATS) {
+    if (tid == kWave) stats_record(sums.shift, sh_stats.sum, td.numel - base, partials[td.first_chunk + chunk_index]);
+  }
+  if (ranges.listing) append_end(app, cflags, h, ht, tail, base, tensor, td, cands, counters);
+}
+
+// `small`: a small tensor's keys are listed, all of them, or left to select_local, which reads them where they lie.
+__device__ __forceinline__ EmaRanges ema_ranges(const TensorDesc& td, bool small, uint32_t use_band, uint32_t band_lo,
+                                                uint32_t band_hi) {
+  const bool list_all = td.list_all != 0 && small;
+  const bool listing = list_all || (td.list_all == 0 && use_band != 0);
+  // band_lo >= 1 and band_hi <= 0x7f800000, so key 0 is never in a range; no key reaches 2^31
+  return EmaRanges{listing, list_all ? 1u : listing ? band_lo : 0x80000000u, list_all || !listing ? 0x80000000u : band_hi};
 }
 
 // At most 6 wavefronts per SIMD: room for the loads of all rows to be under way at once.
@@ -241,6 +319,7 @@ template <bool FISHER>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void k_curv_ema(
     const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds, const ChunkRef* __restrict__ chunks, const GlobalDev* glob,
     StepScalars arg, int list_small) {
+  __shared__ EmaShared sh;
   const ChunkRef cr = chunks[blockIdx.x];
   const StepScalars sc = step_scalars(arg, *tab);
   // the skip word travels together with the tables: its latency is not one more before the data's
@@ -258,17 +337,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
             "s"(band_hi), "s"(late), "s"(beta_h), "s"(cands), "s"(counters), "s"(ema_partials));
   if (skip_epoch == sc.step_id || !td.has_probe) return;
   const bool first = probes_seen == 0;
-  // a small tensor's keys are listed, all of them, or left to select_local, which reads them where they lie (`late`: it
-  // leaves them to k_select_tail at this step)
-  const bool list_all = td.list_all != 0 && (list_small | (int)late) != 0;
-  const bool listing = list_all || (td.list_all == 0 && use_band != 0);
-  // band_lo >= 1 and band_hi <= 0x7f800000, so key 0 is never in a range; no key reaches 2^31
-  const uint32_t list_lo = list_all ? 1u : listing ? band_lo : 0x80000000u;
-  const uint32_t list_hi = list_all || !listing ? 0x80000000u : band_hi;
+  // (`late`: select_local leaves the small tensors to k_select_tail at this step, which takes them from lists)
+  const EmaRanges ranges = ema_ranges(td, (list_small | (int)late) != 0, use_band, band_lo, band_hi);
   const int64_t base = (int64_t)cr.index * kChunk;
-#define TA_EMA(SRC_)                                                                                                  \
-  ema_chunk<SRC_>(td, base, sc.inv_scale, beta_h, omb_h, first, listing, list_lo, list_hi, cr.index, cr.tensor, cands, \
-                  counters, ema_partials)
+  StatShared none;
+#define TA_EMA(SRC_)                                                                                                     \
+  ema_chunk<SRC_, -1>(td, base, sc, beta_h, omb_h, first, ranges, cr.index, cr.tensor, cands, counters, ema_partials,    \
+                      EmaUndo{nullptr, nullptr}, nullptr, nullptr, nullptr, sh, none)
   if constexpr (!FISHER) {
     TA_EMA(-1);
   } else {
@@ -279,6 +354,67 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))
     }
   }
 #undef TA_EMA
+}
+
+// ---------------------------------------------------------------------------------------------
+// Stages 1 and 2 in one launch, for probed steps of short sets (kFusedChunks).  Whether the step is skipped is only known
+// when the launch has ended, so every workgroup leaves the old values of the curvature and mask that it overwrites in the
+// workspace, and the update puts them back if the step turns out to be skipped (ema_undo).  Whether and what a workgroup
+// stores does not depend on the skip word, so what is put back is always this step's.
+// Bound by latency: 4.3 us for seven workgroups, 6.4 for 79 (the two kernels one after the other 3.1 + 5.2), 8.1 for 250, three
+// dependent accesses, the reductions and the end of a kernel among them; the gradients' loads go with the others'.
+// ---------------------------------------------------------------------------------------------
+template <bool FISHER>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 6))) void k_stats_ema(
+    const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds, const ChunkRef* __restrict__ chunks, GlobalDev* glob,
+    StepScalars arg) {
+  __shared__ EmaShared sh;
+  __shared__ StatShared sh_stats;
+  const ChunkRef cr = chunks[blockIdx.x];
+  const StepScalars sc = step_scalars(arg, *tab);
+  const uint32_t late = glob->select_late;
+  const float beta_h = tab->hyper.beta_curv, omb_h = 1.0f - beta_h;
+  Candidate* const cands = tab->cands;
+  uint32_t* const counters = tab->cand_counters;
+  EmaPartial* const ema_partials = tab->ema_partials;
+  LayerDev* const layers = tab->layers;
+  StatPartial* const partials = tab->partials;
+  LayerIn* const inputs = tab->inputs;
+  float* const undo_h = tab->undo_h;
+  uint32_t* const undo_mask = tab->undo_mask;
+  const TensorDesc td = tds[cr.tensor];
+  const LayerDev& ls = layers[cr.tensor];
+  const uint32_t probes_seen = ls.probes_seen, use_band = ls.use_band, band_lo = ls.band_lo, band_hi = ls.band_hi;
+  TA_LOADED("s"(td.grad), "s"(td.z), "s"(td.hz), "s"(td.curv), "s"(td.mask), "s"(td.numel), "s"(td.grad_dtype),
+            "s"(td.has_probe), "s"(td.list_all), "s"(td.first_chunk), "s"(td.cand_offset), "s"(td.undo_slot), "s"(probes_seen),
+            "s"(use_band), "s"(band_lo), "s"(band_hi), "s"(late), "s"(beta_h), "s"(cands), "s"(counters), "s"(ema_partials));
+  // k_update_local takes the step's decisions from this copy: it writes the layers' records while it runs
+  if (cr.index == 0 && threadIdx.x == 0) inputs[cr.tensor] = layer_in(ls);
+  const int64_t base = (int64_t)cr.index * kChunk;
+  if (td.has_probe) {
+    const bool first = probes_seen == 0;
+    const EmaRanges ranges = ema_ranges(td, late != 0, use_band, band_lo, band_hi);
+    const EmaUndo undo = ema_undo(undo_h, undo_mask, td, base);
+#define TA_EMA(SD_)                                                                                                   \
+  ema_chunk<FISHER ? SD_ : -1, SD_>(td, base, sc, beta_h, omb_h, first, ranges, cr.index, cr.tensor, cands, counters, \
+                                    ema_partials, undo, partials, layers, glob, sh, sh_stats)
+    switch (td.grad_dtype) {
+      case kFP32: TA_EMA(kFP32); break;
+      case kBF16: TA_EMA(kBF16); break;
+      default: TA_EMA(kFP16); break;
+    }
+#undef TA_EMA
+    return;
+  }
+  StatSums sums;
+  switch (td.grad_dtype) {
+    case kFP32: sums = stats_chunk<kFP32, true>(td, base, sc.inv_scale); break;
+    case kBF16: sums = stats_chunk<kBF16, true>(td, base, sc.inv_scale); break;
+    default: sums = stats_chunk<kFP16, true>(td, base, sc.inv_scale); break;
+  }
+  stats_reduce(sums, sh_stats.sum, layers[cr.tensor], glob, sc.step_id);
+  __syncthreads();
+  if (threadIdx.x == 0) stats_record(sums.shift, sh_stats.sum, td.numel - base, partials[td.first_chunk + cr.index]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -433,6 +569,11 @@ hipError_t launch_grad_stats(const DeviceTables& t, const StepScalars& sc, bool 
 hipError_t launch_curv_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, bool local, hipStream_t s) {
   const auto kernel = fisher ? k_curv_ema<true> : k_curv_ema<false>;
   return launch(kernel, t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc, local ? 0 : 1);
+}
+
+hipError_t launch_stats_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, hipStream_t s) {
+  const auto kernel = fisher ? k_stats_ema<true> : k_stats_ema<false>;
+  return launch(kernel, t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc);
 }
 
 hipError_t launch_hist_pass(const DeviceTables& t, const StepScalars& sc, int serial_rounds, hipStream_t s) {

@@ -9,6 +9,21 @@ namespace triaccel {
 // Arrival counter of a tensor, in a cache line of its own.
 __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { return arrived + (size_t)l * kCandCounterStride; }
 
+// Puts back the curvature and the mask words of a chunk.
+__device__ __forceinline__ void restore_chunk(const TensorDesc& td, int64_t base, const EmaUndo& undo) {
+  const int32_t left = chunk_left(base, td.numel);
+  const Tail tail = tail_of(left, threadIdx.x);
+  uint32_t h[kRows][4];
+  const uint32_t ht = load_chunk<4>(undo.h, left, tail, h);
+  void* const hp = chunk_of<4>(static_cast<void*>(td.curv), base);
+  const Rows rows = rows_of<4>(hp, left);
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) store_words<4>(rows, r, threadIdx.x, h[r]);
+  if (tail.any) store_tail<kFP32>(hp, tail, ht);
+  int64_t word;
+  if (mask_word_of(td, base, word)) as_global<uint32_t>(td.mask)[word] = as_global<uint32_t>(undo.mask)[word - (base >> 5)];
+}
+
 // Every workgroup of a chunk adds up its tensor's chunk records (at most kLocalMaxChunks x 32 bytes, from
 // the caches) and takes the layer's decisions itself, each the same ones, while the chunk's own data is on
 // the way.  No workgroup waits for another: what the decisions and the selection read of the layer's record was
@@ -27,7 +42,10 @@ __device__ __forceinline__ uint32_t* arrival(uint32_t* arrived, uint32_t l) { re
 // 54.6 -> 50.7 and 102.4 -> 94.5; the selection in here against k_select_tail, with a probe: the perceptron with fp16
 // gradients and the result read each time 35.0 -> 29.0, EfficientNet-B0 49.2 -> 39.2, ResNet-18 84.5 -> 73.3, 41 ragged
 // tensors of 9.7 M with the Fisher source 59.5 -> 50.0, 4000 tensors of 10 to 300 elements 175 -> 75.
-template <bool MOM, bool PROBED>
+// UNDO: after k_stats_ema, so a probed step that turns out to be skipped puts back what that kernel overwrote.  (As a
+// parameter of the launch it cost the probed form twice the scalar registers kept in vector registers, and the ResNet-18
+// set 0.4 us a step.)
+template <bool MOM, bool PROBED, bool UNDO>
 __global__ __launch_bounds__(kThreads) void k_update_local(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
                                                            const ChunkRef* __restrict__ chunks, GlobalDev* glob, StepScalars arg,
                                                            uint32_t select_wgs) {
@@ -62,6 +80,14 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const StepTables* __r
             "s"(hp.beta_var), "s"(hp.tau_low), "s"(hp.tau_high), "s"(hp.tau_curv), "s"(hp.alpha), "s"(hp.ctrl_interval),
             "s"(hp.lambda_source));
   if (skip) {
+    if constexpr (UNDO) {
+      if (td.has_probe) {
+        // the curvature kernel did not know it yet
+        const int64_t base = (int64_t)cr.index * kChunk;
+        restore_chunk(td, base, ema_undo(tab->undo_h, tab->undo_mask, td, base));
+        if (cr.index == 0) reset_cand_counters(tab->cand_counters, cr.tensor);
+      }
+    }
     if (threadIdx.x == 0 && cr.index == 0) {
       ls.found_inf = (ls.found_epoch == sc.step_id) ? 1u : 0u;
       if (cr.tensor == 0) step_record(glob, tab->host_result, sc, hp, true);
@@ -144,10 +170,11 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const StepTables* __r
   }
 }
 
-hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, hipStream_t s) {
+hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, bool undo, hipStream_t s) {
   const bool mom = t.hyper.momentum != 0.0f;
-  const auto kernel = any_probe ? (mom ? k_update_local<true, true> : k_update_local<false, true>)
-                                : (mom ? k_update_local<true, false> : k_update_local<false, false>);
+  const auto kernel = !any_probe ? (mom ? k_update_local<true, false, false> : k_update_local<false, false, false>)
+                      : undo     ? (mom ? k_update_local<true, true, true> : k_update_local<false, true, true>)
+                                 : (mom ? k_update_local<true, true, false> : k_update_local<false, true, false>);
   // a multiple of eight: a chunk's workgroup goes to the same die in every kernel
   const uint32_t select_wgs = any_probe ? (t.n_tensors + 7u) & ~7u : 0u;
   return launch(kernel, select_wgs + t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc, select_wgs);
