@@ -201,9 +201,13 @@ void free_ctx(triaccel_ctx* c) {
   delete c;
 }
 
-// Sets bound by their launches, whose update takes the layers' decisions itself (k_update_local).
+// Sets bound by their launches, whose update takes the layers' decisions itself (k_update_local); with step sizes per element a
+// kernel before it (k_decide_select, probed steps).
 bool local_form(const triaccel_ctx& c) {
   return c.cfg.elementwise_scale != 1 && c.t.total_chunks < kLaunchBoundChunks && c.t.max_chunks_per_tensor <= kLocalMaxChunks;
+}
+bool decide_form(const triaccel_ctx& c) {
+  return c.cfg.elementwise_scale == 1 && c.t.total_chunks <= kDecideTotalChunks && c.t.max_chunks_per_tensor <= kDecideMaxChunks;
 }
 
 // Whether a layer's storage size can change.  With tau_high <= 0 the precision rule chooses FP32 whatever the variance
@@ -225,12 +229,13 @@ int enqueue_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, hipEven
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[0], s));
   // (with an event between the two they are launches of their own)
   const bool fused = T.fused && any_probe && !(ev && level == 1);
+  const bool elem_local = any_probe && decide_form(*h);
   if (fused) {
     TA_HIP(launch_stats_ema(T, sc, fisher, s));
   } else {
-    TA_HIP(launch_grad_stats(T, sc, local, s));
+    TA_HIP(launch_grad_stats(T, sc, local || elem_local, s));
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[1], s));
-    if (any_probe) TA_HIP(launch_curv_ema(T, sc, fisher, local, s));
+    if (any_probe) TA_HIP(launch_curv_ema(T, sc, fisher, local || elem_local, s));
   }
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[2], s));
   if (local) {
@@ -247,9 +252,12 @@ int enqueue_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, hipEven
     if (ev && level == 1) TA_HIP(hipEventRecord(ev[7], s));
     return TRIACCEL_OK;
   }
-  TA_HIP(launch_layer(T, sc, s));
+  if (elem_local) TA_HIP(launch_decide_select(T, sc, fused, s));
+  else TA_HIP(launch_layer(T, sc, s));
   if (ev && level == 1) TA_HIP(hipEventRecord(ev[3], s));
-  if (any_probe && !T.all_small) {
+  if (elem_local) {
+    if (!T.all_small) TA_HIP(launch_select_tail(T, sc, true, false, s));
+  } else if (any_probe && !T.all_small) {
     // fallback radix select: two rounds at full width (a first window, then a refinement or the
     // other side of a window that missed); rarer further rounds are made inside the second launch.
     // Each launch leaves at once when no tensor is (still) in histogram mode.
@@ -258,7 +266,7 @@ int enqueue_step(triaccel_ctx* h, const StepScalars& sc, bool any_probe, hipEven
     if (T.total_chunks >= kLaunchBoundChunks) TA_HIP(launch_hist_pass(T, sc, 0, s));
     TA_HIP(launch_hist_pass(T, sc, 8, s));
   }
-  if (elem && any_probe) {
+  if (elem && any_probe && !elem_local) {
     // element-wise step sizes need the final threshold: finish the mask and the selection first
     if (T.total_chunks < kLaunchBoundChunks) {
       TA_HIP(launch_select_tail(T, sc, false, false, s));
@@ -469,7 +477,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   ws.add(&T.resize_scratch, (size_t)scratch_chunks * kChunk * 4);
   ws.add(&T.inputs, (size_t)n);
   ws.add(&T.arrived, (size_t)n * kCandCounterStride);
-  T.fused = local_form(*c) && T.total_chunks <= kFusedChunks;
+  T.fused = (local_form(*c) || decide_form(*c)) && T.total_chunks <= kFusedChunks;
   uint64_t undo = 0;
   if (T.fused)
     for (TensorDesc& d : c->desc) {

@@ -27,6 +27,15 @@ constexpr uint32_t kLaunchBoundChunks = 16384;
 // 16 bits without momentum 75 and 68, probed 236 and 220, Fisher 189 and 165.
 constexpr uint32_t kLocalMaxChunks = 1024;
 
+// With step sizes per element, the longest tensor (16.8 M elements) and the most chunks (42 M) of a set whose layers' decisions and
+// thresholds are taken in one launch (k_decide_select), in which up to 1024 workgroups add up their tensor's records.  A
+// probed step, us, with three launches and with it: 12 tensors of 0.1 M 27.2 and 18.8, 41 of 1.0 M 34.4 and 26.4, 12 of 2.1 M
+// 39.9 and 34.4, 30 of 6 M 66.1 and 60.6, 60 of 16 M 132.4 and 127.2; one tensor of 3 M 41.5 and 39.8, of 8.2 M 78.6 and
+// 76.9, of 16 M (3907 chunks) 131.9 and 130.2; 29 of 37 M, one of them 3460 chunks, the same (269.9), 12 of 60 M, one of them 4076
+// chunks, 427.8 and 434.6.  A step that needs histograms: 60 of 16 M 451 and 222, 29 of 37 M 662 and 399.
+constexpr uint32_t kDecideMaxChunks = 4096;
+constexpr uint32_t kDecideTotalChunks = 10240;
+
 // Radix-select parameters: magnitudes are 31-bit keys (sign bit cleared).
 constexpr int kHistBins = 2048;
 constexpr int kHistBits = 11;

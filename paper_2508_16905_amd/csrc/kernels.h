@@ -75,7 +75,9 @@ hipError_t launch_layer(const DeviceTables& t, const StepScalars& sc, hipStream_
 hipError_t launch_update(const DeviceTables& t, const StepScalars& sc, bool elem, bool resize, hipStream_t s);
 // `undo`: after k_stats_ema.
 hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, bool undo, hipStream_t s);
-// `local`: after k_update_local, which settled most tensors' thresholds; `resize`: with launch 1 of the in-place resize (sets
+// Probed steps with step sizes per element, on sets of the local form's sizes: the layers' decisions and most thresholds.
+hipError_t launch_decide_select(const DeviceTables& t, const StepScalars& sc, bool undo, hipStream_t s);
+// `local`: after k_update_local or k_decide_select, which settled most tensors' thresholds; `resize`: with launch 1 of the in-place resize (sets
 // of the local form: its plans have two launches at most).
 hipError_t launch_select_tail(const DeviceTables& t, const StepScalars& sc, bool local, bool resize, hipStream_t s);
 hipError_t launch_mask_pass(const DeviceTables& t, const StepScalars& sc, hipStream_t s);

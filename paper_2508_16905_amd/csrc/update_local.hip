@@ -170,6 +170,127 @@ __global__ __launch_bounds__(kThreads) void k_update_local(const StepTables* __r
   }
 }
 
+// Before the element-wise form of the update on sets of that size: what k_update_local does on probed steps, less the update,
+// which needs the thresholds.  Workgroups [0, select_wgs) settle the thresholds of the tensors whose keys suffice
+// (select_local), one each; [select_wgs, 2 select_wgs) take the layers' decisions; the others make the fallback histogram
+// pass, each over a run of chunks, and leave at once if no tensor of the run needs it.  They take the outcome of a
+// tensor from the chunks' records themselves, so that none waits for another.  With a kernel each for the decisions, for the
+// histograms and for the thresholds the steady state took two launches more; figures at kDecideMaxChunks.  Bound by latency: 6
+// to 10 us up to 16 M elements.
+// UNDO: after k_stats_ema; on a skipped step the last kind puts back what that kernel overwrote.
+template <bool UNDO>
+__global__ __launch_bounds__(kThreads) void k_decide_select(const StepTables* __restrict__ tab, const TensorDesc* __restrict__ tds,
+                                                            const ChunkRef* __restrict__ chunks, GlobalDev* glob, StepScalars arg,
+                                                            uint32_t select_wgs, uint32_t hist_wgs) {
+  __shared__ LayerShared sh_layer;
+  __shared__ union {
+    HistShared hist;
+    LocalSelectShared select;
+  } shared;
+  __shared__ uint32_t s_last;
+  const StepScalars sc = step_scalars(arg, *tab);
+  const uint32_t n_tensors = tab->n_tensors;
+  if (blockIdx.x < select_wgs) {
+    if (blockIdx.x < n_tensors) select_local(blockIdx.x, *tab, tds, glob, sc, tab->hyper, sh_layer, shared.select);
+    return;
+  }
+  const Hyper hp = tab->hyper;
+  const uint64_t skip_epoch = glob->skip_epoch;
+  const bool skip = skip_epoch == sc.step_id;
+  LayerDev* const layers = tab->layers;
+  const LayerIn* const inputs = tab->inputs;
+  const EmaPartial* const ema_partials = tab->ema_partials;
+  if (blockIdx.x < 2 * select_wgs) {
+    const uint32_t l = blockIdx.x - select_wgs;
+    if (l >= n_tensors) return;
+    const TensorDesc td = tds[l];
+    LayerDev& ls = layers[l];
+    const LayerIn in = inputs[l];
+    if (skip) {
+      if (UNDO && td.has_probe) reset_cand_counters(tab->cand_counters, l);
+      if (threadIdx.x == 0) {
+        ls.found_inf = (ls.found_epoch == sc.step_id) ? 1u : 0u;
+        if (l == 0) step_record(glob, tab->host_result, sc, hp, true);
+      }
+      return;
+    }
+    const bool probed = td.has_probe != 0;
+    const LayerSums sums = layer_reduce<true>(layer_accumulate<true>(td, tab->partials, ema_partials, probed), td.numel, sh_layer);
+    const uint32_t k = topk_count(td.numel, hp.sparsity_ppm, hp.topk_abs);
+    const int outcome = probed ? select_outcome(td, in.plan, sums.ema, k) : (int)kOutListed;
+    if (outcome != kOutListed) reset_cand_counters(tab->cand_counters, l);  // drop what was listed
+    if (threadIdx.x != 0) return;
+    // (kOutListed: select_local; kOutHist: below)
+    if (outcome == kOutFewNonzero) select_setup(td, ls, glob, in.plan, sums.ema, k, outcome, sc.step_id);
+    layer_publish(l, ls, layer_decide(in, sums, probed, sc.lr, hp), glob, tab->trans_list, n_tensors, sc.step_id);
+    if (l == 0) step_record(glob, tab->host_result, sc, hp, false);
+    return;
+  }
+  const uint32_t total_chunks = tab->total_chunks, part = blockIdx.x - 2 * select_wgs;
+  const uint32_t per = (total_chunks + hist_wgs - 1) / hist_wgs;
+  const uint32_t c1 = min((part + 1) * per, total_chunks);
+  uint32_t c = min(part * per, total_chunks);
+  HistShared& sh = shared.hist;
+  while (c < c1) {
+    const uint32_t l = uniform(chunks[c].tensor);
+    const TensorDesc td = tds[l];
+    const uint32_t end = min(td.first_chunk + td.n_chunks, c1);
+    const uint32_t first = c, mine = end - c;
+    c = end;
+    if (!td.has_probe) continue;
+    if (skip) {
+      if constexpr (UNDO)
+        for (uint32_t q = first; q < end; ++q) {
+          const int64_t base = (int64_t)(q - td.first_chunk) * kChunk;
+          restore_chunk(td, base, ema_undo(tab->undo_h, tab->undo_mask, td, base));
+        }
+      continue;
+    }
+    if (td.list_all) continue;
+    const SelNow now = inputs[l].plan;
+    const EmaTotals e = ema_totals(td, ema_partials, sh_layer);
+    const uint32_t k = topk_count(td.numel, hp.sparsity_ppm, hp.topk_abs);
+    const int outcome = select_outcome(td, now, e, k);
+    __syncthreads();  // the sums' shared memory may be written again
+    if (outcome != kOutHist) continue;
+    LayerDev& ls = layers[l];
+    const Window w = first_window(now, e.maxkey);
+    for (int b = threadIdx.x; b < kHistBins; b += kThreads) sh.hist[b] = 0;
+    __syncthreads();
+    uint32_t above = 0;
+    for (uint32_t q = first; q < end; ++q) hist_chunk(td, (int64_t)(q - td.first_chunk) * kChunk, w, sh.hist, now.predicted != 0, above);
+    flush_hist(sh.hist, w.bins, tab->hist + (size_t)l * kHistBins);
+    above = wave_sum(above);
+    if ((threadIdx.x & (kWave - 1)) == 0 && above) atomicAdd(&ls.acc_above, above);
+    published_before_here();  // as in k_update_local
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const bool last = atomicAdd(arrival(tab->arrived, l), mine) + mine == td.n_chunks;
+      if (last) {
+        *arrival(tab->arrived, l) = 0;
+        select_setup(td, ls, glob, now, e, k, outcome, sc.step_id);
+      }
+      s_last = last ? 1u : 0u;
+    }
+    __syncthreads();
+    if (s_last) {
+      select_scan(l, td, ls, glob, tab->hist, sc.step_id, sh.hist, sh.part, sh.out, true);
+      select_serial(l, td, ls, glob, tab->hist, sc.step_id, sh.hist, sh.part, sh.out, 8);
+    }
+    __syncthreads();
+  }
+}
+
+hipError_t launch_decide_select(const DeviceTables& t, const StepScalars& sc, bool undo, hipStream_t s) {
+  const uint32_t select_wgs = (t.n_tensors + 7u) & ~7u;
+  // four for a compute unit, which is as fast as eight (the pass is bound by the LDS's atomic adds), or a chunk each; none if
+  // there is nothing to count and nothing to put back
+  const uint32_t cap = t.persistent_grid / 2;
+  const uint32_t hist_wgs = t.all_small && !undo ? 0u : t.total_chunks < cap ? t.total_chunks : cap;
+  return launch(undo ? k_decide_select<true> : k_decide_select<false>, 2 * select_wgs + hist_wgs, kThreads, s, t.dev, t.tensors, t.chunks,
+                t.glob, sc, select_wgs, hist_wgs);
+}
+
 hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, bool undo, hipStream_t s) {
   const bool mom = t.hyper.momentum != 0.0f;
   const auto kernel = !any_probe ? (mom ? k_update_local<true, false, false> : k_update_local<false, false, false>)
@@ -180,9 +301,9 @@ hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, boo
   return launch(kernel, select_wgs + t.total_chunks, kThreads, s, t.dev, t.tensors, t.wg_chunks, t.glob, sc, select_wgs);
 }
 
-// What is left of the selection after k_update_local, and before the element-wise form of the update on sets
-// of that size (one launch for the mask pass and the threshold resolution).  Workgroup l < n_tensors settles tensor l if its
-// listed keys suffice (after k_update_local: if select_local left them).  The `mask_wgs` workgroups after
+// What is left of the selection after k_update_local or k_decide_select, and before the element-wise form of the update on
+// sets of fewer than kLaunchBoundChunks with longer tensors (one launch for the mask pass and the threshold resolution).
+// Workgroup l < n_tensors settles tensor l if its listed keys suffice (`local`: if select_local left them).  The `mask_wgs` workgroups after
 // those make the mask pass of the other tensors, four chunks at a
 // time, and the last workgroup to finish a part of such a tensor settles it among the keys the pass listed; the
 // rest take launch 1 of the in-place resize, four chunks of a level at a time.  After k_update_local all of them leave
