@@ -433,7 +433,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
     ls.var_ext = 3.0e38f;  // no extrapolation error measured yet
   }
   // scratch of the in-place resize: the first `top` chunks of every tensor, if the set needs subtree stages
-  const ResizePlan resize = c->t.plan = make_resize_plan(max_chunks, (uint32_t)chunks.size());
+  const ResizePlan resize = c->t.plan = make_resize_plan(max_chunks, (uint32_t)chunks.size(), (uint32_t)n);
   uint64_t scratch_chunks = 0;
   if (resize.n_stages > 1)
     for (TensorDesc& d : c->desc) {

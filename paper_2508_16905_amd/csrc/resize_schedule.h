@@ -41,6 +41,18 @@ constexpr uint32_t kResizeMaxStages = 8;     // stage 0 plus up to 7 subtree sta
 constexpr uint32_t kResizeTop = 16;          // chunks of stage 0 when subtree stages follow, large sets
 constexpr uint32_t kResizeTopSmall = 64;     // the same, sets below kResizeBigSet: fewer levels in all, so fewer
                                              // stages and shallower subtrees
+// Up to 256 of them where that pays.  More chunks side by side make the subtrees shallower and more, and give launch 0
+// of a narrowing tensor, which takes 27 us for the first 64 chunks of 12 tensors, more to do; they cost their copy, so they are at
+// most a quarter of the longest tensor, or all but one in short sets, whose launches have room.  Every tensor is offered as many work
+// items as the longest, so their number is limited too, by the chunks there are: a ragged set of 60 tensors (40 M) took
+// 354 us instead of 230 without that.  Longer tensors have two subtree stages and more roots from their first: one of some
+// 9000 chunks among 8 of 60 M 240 and 257.  A step in which every tensor is resized, us, with 64 and with this many: 12
+// of 1024 chunks 214 and 193 (256), 15 264 and 239, 4 89 and 72, one of 1000 39 and 25, 8 of 500 79 and 74, 4 of 160 22.8 and
+// 21.7 (128), 6 ragged of 6 M 44 and 36; with 128 all the same 30 of 200 118 and 125, 30 of 300 189 and 195.  512 of 1024: 75
+// instead of 72 for 4, 24.1 instead of 24.6 for one.
+constexpr uint32_t kResizeTopMax = 256;
+constexpr uint32_t kResizeShortSet = 4096;   // chunks in the whole set
+constexpr uint32_t kResizeOneSubtree = 1024; // longest tensor of the sets that the rule is for
 constexpr uint32_t kResizeTopOnly = 128;     // tensors up to this many chunks: stage 0 alone
 constexpr uint32_t kResizeBigSet = 16384;    // chunks in the whole set from which a launch more costs nothing
                                              // (= kLaunchBoundChunks of the step's other kernels)
@@ -52,10 +64,10 @@ struct ResizePlan {
   uint32_t depth[kResizeMaxStages];   // stage j >= 1: levels 0 .. depth[j] - 1
 };
 
-// Plan for a set whose largest tensor has `max_chunks` chunks.  Small sets are bound by the number of
+// Plan for a set of `n_tensors` whose largest tensor has `max_chunks` chunks.  Small sets are bound by the number of
 // launches, so they get deep subtrees (up to 6 levels, 63 chunks per workgroup) and as few stages as
 // possible; large sets get shallow ones (up to 4 levels, 15 chunks) for parallelism inside a tensor.
-TA_HD ResizePlan make_resize_plan(uint32_t max_chunks, uint32_t total_chunks) {
+TA_HD ResizePlan make_resize_plan(uint32_t max_chunks, uint32_t total_chunks, uint32_t n_tensors = 1) {
   ResizePlan p{};
   p.n_stages = 1;
   if (max_chunks <= kResizeTopOnly) {
@@ -63,6 +75,12 @@ TA_HD ResizePlan make_resize_plan(uint32_t max_chunks, uint32_t total_chunks) {
     return p;
   }
   p.top = total_chunks >= kResizeBigSet ? kResizeTop : kResizeTopSmall;
+  if (total_chunks < kResizeBigSet && max_chunks <= kResizeOneSubtree) {
+    const uint32_t most = total_chunks <= kResizeShortSet ? max_chunks - 1 : max_chunks / 4;
+    const uint32_t chunks = total_chunks + total_chunks / 8, items = chunks > kResizeShortSet ? chunks : kResizeShortSet;
+    // work items of a launch: as many roots as chunks of stage 0
+    while (2 * p.top <= most && 2 * p.top <= kResizeTopMax && (uint64_t)n_tensors * 2 * (2 * p.top) <= items) p.top *= 2;
+  }
   uint32_t levels = 0;  // smallest count with top << levels >= max_chunks
   while (((uint64_t)p.top << levels) < max_chunks) ++levels;
   const uint32_t dmax = total_chunks >= kResizeBigSet ? 4u : 6u;
