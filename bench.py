@@ -38,7 +38,7 @@ STEP_SOURCES = ("update.hip", "update_body.h", "resize_body.h", "resize_schedule
 POWER_SOURCES = ("power.hip", "power.h", "numerics.h")
 MEASURED_TRAFFIC = {
     # k_update<false, true>, default run of the large_streaming workload
-    "step": {"sources_sha256": "5d82fe733687afaf86ec774f0baba83ff73ab8939ee041f2645730c848130da8", "workload": "large_streaming",
+    "step": {"sources_sha256": "e9e4f5fc2c5916e5f0a8e49e83608a8034f63ef3296df4c24a68806926bddc9d", "workload": "large_streaming",
              "alg_bytes": 18991808512, "fetch_bytes": 11.677e9, "write_bytes": 7.348e9,
              "from": "profiles/fused_step_large_streaming_hbm_counters.md"},
     # k_power_apply<5> / k_power_gram<5>, --mode power on the large_streaming workload
