@@ -327,7 +327,8 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const StepTables
       if (pending == 0 || skip_epoch == sc.step_id) return;
       // (a step with nothing pending was not a late one, so there is nothing to take back when all leave above)
       if (blockIdx.x == 0 && threadIdx.x == 0)
-        glob->select_late = glob->late_epoch == sc.step_id && total_chunks <= kLateChunks ? 1u : 0u;
+        glob->select_late =
+            glob->late_epoch == sc.step_id && (total_chunks <= kLateChunks || tab->hyper.elementwise == 1) ? 1u : 0u;
     }
     const uint32_t l = blockIdx.x;
     const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;

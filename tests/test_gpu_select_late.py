@@ -49,3 +49,40 @@ def test_refreshes_of_both_kinds_in_turn(seed, source, graph):
         late = any(x.sel_outcome != 1 or x.sel_listed > HELD for x in state)
     assert min(steps.values()) >= 6, steps
     p.close()
+
+
+def test_step_sizes_per_element_do_not_select_in_the_first_launch_while_bands_are_wide():
+    """A refresh that leaves a long tensor's threshold to the second launch leaves the next one's all to it, also in sets of more
+    than 1024 pieces: the first launch is then shorter than that of refreshes that it settles itself (otherwise it takes
+    its time for the tensors that it can settle, and the second launch comes after it)."""
+    import torch
+
+    import paper_2508_16905_amd as ta
+    from workloads.configs import _DEFAULT_HYPER
+
+    sizes = [6_000_007] + [150_001] * 12 + [8192, 5000, 64]
+    params = [torch.zeros(n, device="cuda") for n in sizes]
+    opt = ta.TriAccel(dict(_DEFAULT_HYPER, beta_curv=0.0, tau_low=0.0, tau_high=0.0, elementwise_scale=1), params)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    grads = [torch.randn(n, device="cuda", generator=gen) for n in sizes]
+    z = [torch.ones(n, device="cuda") for n in sizes]
+    hz = [torch.randn(n, device="cuda", generator=gen) for n in sizes]
+    rng = random.Random(1)
+
+    def first_launch_us(width):
+        times = []
+        opt.set_profiling(1)
+        for t in range(40):
+            factor = 1.0 + width * rng.uniform(-1.0, 1.0)
+            opt.step(grads, z, [x * factor for x in hz], lr=1e-3, mem_used_bytes=1, mem_total_bytes=2)
+            state = opt.layer_state()  # waits for the step
+            if t >= 12 and all(x.sel_outcome == 1 for x, n in zip(state, sizes) if n > 8192):
+                if (state[0].sel_listed > HELD) == (width > 0.0):
+                    times.append(opt.stage_times()[2] * 1e3)
+        assert len(times) >= 8, times
+        return sorted(times)[len(times) // 2]
+
+    calm, wide = first_launch_us(0.0), first_launch_us(0.003)
+    opt.close()
+    # us here: 12.4 and 7.9; 12.5 and 12.6 where it still settled what it could in sets of more than 1024 pieces
+    assert wide < 0.85 * calm, (wide, calm)
