@@ -67,7 +67,7 @@ struct ResizePlan {
 // Plan for a set of `n_tensors` whose largest tensor has `max_chunks` chunks.  Small sets are bound by the number of
 // launches, so they get deep subtrees (up to 6 levels, 63 chunks per workgroup) and as few stages as
 // possible; large sets get shallow ones (up to 4 levels, 15 chunks) for parallelism inside a tensor.
-TA_HD ResizePlan make_resize_plan(uint32_t max_chunks, uint32_t total_chunks, uint32_t n_tensors = 1) {
+TA_HD ResizePlan make_resize_plan(uint32_t max_chunks, uint32_t total_chunks, uint32_t n_tensors) {
   ResizePlan p{};
   p.n_stages = 1;
   if (max_chunks <= kResizeTopOnly) {

@@ -9,9 +9,9 @@ using namespace triaccel;
 
 // Rows of five int32: launch, workgroup (of this tensor), kind (0 load, 1 barrier, 2 store), chunk, stage.
 // Returns the number of rows (also when it exceeds `cap`; only `cap` rows are written).
-extern "C" int64_t resize_replay(uint32_t max_chunks, uint32_t total_chunks, uint32_t n_chunks, int narrowing,
+extern "C" int64_t resize_replay(uint32_t max_chunks, uint32_t total_chunks, uint32_t n_tensors, uint32_t n_chunks, int narrowing,
                                  int32_t* out, int64_t cap) {
-  const ResizePlan p = make_resize_plan(max_chunks, total_chunks);
+  const ResizePlan p = make_resize_plan(max_chunks, total_chunks, n_tensors);
   int64_t n = 0;
   auto emit = [&](uint32_t launch, uint32_t wg, int kind, uint32_t chunk, uint32_t stage) {
     if (n < cap) {
@@ -42,8 +42,8 @@ extern "C" int64_t resize_replay(uint32_t max_chunks, uint32_t total_chunks, uin
   return n;
 }
 
-extern "C" void resize_plan(uint32_t max_chunks, uint32_t total_chunks, uint32_t* out /* 2 + 2 * 8 words */) {
-  const ResizePlan p = make_resize_plan(max_chunks, total_chunks);
+extern "C" void resize_plan(uint32_t max_chunks, uint32_t total_chunks, uint32_t n_tensors, uint32_t* out /* 2 + 2 * 8 words */) {
+  const ResizePlan p = make_resize_plan(max_chunks, total_chunks, n_tensors);
   out[0] = p.n_stages;
   out[1] = p.top;
   for (uint32_t j = 0; j < kResizeMaxStages; ++j) {
