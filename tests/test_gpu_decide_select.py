@@ -38,7 +38,14 @@ def test_steps_of_every_kind(which, source, graph):
             g[len(g) - 1][0] = float("nan")
         res = p.step(g, z, hz, label=f"{way} t={t}", update_curvature=way != "none")
         assert res["skipped"] == int(way == "skip")
-        outcomes |= {x.sel_outcome for x, n in zip(p.gpu.layer_state(), sizes) if n > 8192}
+        now = {x.sel_outcome for x, n in zip(p.gpu.layer_state(), sizes) if n > 8192}
+        if way == "few":
+            assert now == {6}, now
+        if way == "jump" and ways[t - 4:t - 1] == ["calm"] * 3:  # out of its band
+            assert now == {3}, now
+        if t > 1 and ways[t - 2] == "few":  # the band reaches down to the zeros of the step before: too many keys
+            assert 5 in now, now
+        outcomes |= now
     assert {1, 2} <= outcomes, outcomes
     p.close()
 
