@@ -94,21 +94,26 @@ inline KeyLists key_lists(int64_t numel) {
 // the call then pays and the traffic after it saves, all of it after a step, half of it after a power iteration.
 constexpr uint64_t kKeepBytes = 2ull << 30;
 
-// Sets of the local form with at most this many chunks (4.2 M elements), and all sets of the decide form: if a probed step had
-// a tensor whose selection needs k_select_tail (more listed keys than select_local holds, or histograms), the next probed
-// step leaves all selections to that launch, which takes its time anyway; small tensors list their keys for it.  In the
-// local form select_local takes 11 to 15 us for a tensor of some thousand elements: more than a short update, while a longer
-// one covers it.  A step, us, without and with:
+// Sets of the local form with at most this many chunks (4.2 M elements): if a probed step had a tensor whose selection needs
+// k_select_tail (more listed keys than select_local holds, or histograms), the next probed step leaves all selections to
+// that launch, which takes its time anyway; small tensors list their keys for it.  select_local takes 11 to 15 us for a
+// tensor of some thousand elements: more than a short update, while a longer one covers it.  A step, us, without and with:
 // thresholds that move by up to 12 % (more listed keys), 41 tensors of 1.0 M 44.2 and 37.3, of 2.0 M 59.4 and 54.3, 213 of
 // 4.0 M 74.2 and 73.0, 20 of 5.0 M 126.3 and 127.5; curvature that jumps by a factor of 4000 (histograms), 10 tensors of
 // 0.5 M 122.7 and 115.2, 41 of 1.0 M 120.4 and 114.8, of 2.0 M 213.0 and 206.1, 60 of 12 M 298 and 303.
+constexpr uint32_t kLateChunks = 1024;
 // In the decide form no update covers it, however long: k_decide_select takes 14 to 15 us with it and 5 without, before
-// k_select_tail's own time.  Beyond 1024 chunks, without and with (and with the three launches k_layer, k_hist_pass and
+// k_select_tail's own time.  There the rule is for sets of at most this many tensors, a workgroup of k_select_tail each, two
+// of which are resident on each of the 256 compute units; and only for too many listed keys: a few tensors that need
+// histograms take k_select_tail little time, and the histogram workgroups cover select_local.  Beyond 1024 chunks, without and with (and with the three launches k_layer, k_hist_pass and
 // k_select_tail): inputs that never repeat, 30 tensors of 6 M 71.1 and 70.5 (73.9), 60 of 16 M 138.0 and 136.7 (140.6), 29 of 37 M
 // 283.6 and 283.0 (286.3); curvature that moves by up to 1 % besides 88.2 and 82.3 (84.9), 163.9 and 154.5 (157.7), 354 and 343
 // (347); by up to 12 % 197.5 and 184.4 (189.3), 277.7 and 267.9 (282.5), 471 and 464 (536); by 5 % at every fourth step 124.0 and
-// 114.9 (118.1), 208.8 and 199.8 (206.2), 417 and 411 (430).
-constexpr uint32_t kLateChunks = 1024;
+// 114.9 (118.1), 208.8 and 199.8 (206.2), 417 and 411 (430).  By number of tensors, 20 M in all, up to 12 %: 100 tensors 340
+// and 327 (331), 200 307 and 295 (299), 300 235 and 225 (226), 400 214 and 205 (207), 600 265 and 266 (269), 1500 199 and 220
+// (216), 2500 196 and 258 (245); with inputs that never repeat 300 166.5 and 167.6 (173), 600 173 and 181 (185).  With histograms
+// as a reason too, and an atomic add for each tensor left over: 1500 of 9000 elements, inputs that never repeat, 143 and 186 (169).
+constexpr uint32_t kLateTensors = 512;
 
 // Sets of the local form with at most this many chunks (2.1 M elements) take the statistics and the curvature average of a
 // probed step in one launch (k_stats_ema): 1.5 us less for the launch, against 4 bytes more written per element, as the
@@ -225,7 +230,7 @@ struct GlobalDev {
   uint64_t late_epoch;     // step_id at which select_local last found such a selection
   uint32_t trans_count[2]; // number of tensors whose storage size changes (double-buffered by step parity)
   uint32_t hist_pending[2];// tensors still in histogram mode this step (same double buffering)
-  uint32_t mask_pending[2];// tensors whose mask the EMA kernel did not settle this step
+  uint32_t mask_pending[2];// not zero: there are tensors whose mask or threshold is left to later launches of this step
   // result record
   int32_t res_skipped;
   float res_next_scale;

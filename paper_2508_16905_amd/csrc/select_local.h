@@ -107,8 +107,9 @@ __device__ __forceinline__ bool rank_select(const uint32_t (&key)[KEYS], uint32_
 // One workgroup settles tensor l if its listed keys, or its own if it is small, settle the threshold.  A tensor of
 // up to kListAllMax elements is read whole, chunk by chunk as the curvature kernel wrote it (which lists nothing of it
 // and leaves its mask to this function); of a larger one the keys of the band are listed.  More of these than the
-// registers hold are left to k_select_tail, and so are tensors that need histograms over h; both are noted for the next
-// probed step, which on short sets leaves everything to that launch (kLateChunks; `late`: this is such a step).
+// registers hold are left to k_select_tail, and so are tensors that need histograms over h; both (in k_decide_select the
+// first) are noted for the next probed step, which leaves everything to that launch (`late`: this is such a step) if the
+// set is within kLateChunks or kLateTensors.
 //
 // Beside the streaming workgroups every dependent access takes about 3 us instead of 0.7, so there are few of them:
 // tables, records and list lengths; keys; then only stores.  (An earlier form with lists re-read in every pass took 100
@@ -178,10 +179,11 @@ __device__ __forceinline__ void select_local(uint32_t l, const StepTables& tab, 
     const bool fits = listed && e.listed <= (uint32_t)(kThreads * kLocalListed);  // (if so, no list has dropped a key)
     if (!fits || late) {
       if (threadIdx.x == 0) {
-        if (!fits && !td.list_all) glob->late_epoch = sc.step_id;
+        if (!fits && !td.list_all && (listed || hp.elementwise != 1)) glob->late_epoch = sc.step_id;
         if (listed) {
           select_setup(td, ls, glob, now, e, k, kOutListed, sc.step_id);
-          atomicAdd(&glob->mask_pending[sc.step_id & 1u], 1u);
+          // (only looked at for being zero; an atomic add takes 20 ns, one after the other for all tensors of a late step)
+          glob->mask_pending[sc.step_id & 1u] = 1;
         }
       }
       return;

@@ -1,6 +1,7 @@
 // gfx950 kernels for sets bound by their launches: k_update_local does what the per-layer kernel, the fallback
 // histogram pass, the fused update + cast and the first launch of the in-place resize do one after the other on
-// larger sets, k_select_tail what the mask pass and the threshold resolution do.
+// larger sets, k_select_tail what the mask pass and the threshold resolution do; with step sizes per element, where the
+// update comes last, k_decide_select takes the place of the per-layer kernel, the histogram pass and most of the resolution.
 #include "resize_body.h"
 #include "select_local.h"
 
@@ -327,8 +328,8 @@ __global__ __launch_bounds__(kFinishThreads) void k_select_tail(const StepTables
       if (pending == 0 || skip_epoch == sc.step_id) return;
       // (a step with nothing pending was not a late one, so there is nothing to take back when all leave above)
       if (blockIdx.x == 0 && threadIdx.x == 0)
-        glob->select_late =
-            glob->late_epoch == sc.step_id && (total_chunks <= kLateChunks || tab->hyper.elementwise == 1) ? 1u : 0u;
+        glob->select_late = glob->late_epoch == sc.step_id &&
+                            (tab->hyper.elementwise == 1 ? n_tensors <= kLateTensors : total_chunks <= kLateChunks);
     }
     const uint32_t l = blockIdx.x;
     const uint32_t listed = threadIdx.x <= kCandLists ? *cand_counter(counters, l, threadIdx.x) : 0u;
