@@ -190,9 +190,10 @@ typedef struct {
  * lists, per-layer state, eight device copies of the tensor table): a few MB, plus 20 KB per tensor, 48 bytes
  * per 4096 parameters of a tensor and its key lists, 16 bytes per element up to 4 MB a tensor.  In sets with a
  * tensor of more than 524,288 elements, further, scratch for storage sizes that change: 4 bytes for each of the
- * first 262,144 elements of every tensor (up to 1,048,576 in sets of few tensors, none longer than 4,194,304; 65,536 in
- * sets of 16,384 pieces of 4096 elements and more), rounded up to 4096 elements.  In sets of at most 512 pieces, further, 4.2 bytes per element (a probed step's old curvature
- * and mask, put back if the step is skipped).
+ * first 262,144 elements of every tensor (up to 1,048,576 in sets of few tensors, none longer than 4,194,304;
+ * 65,536 in sets of 16,384 pieces of 4096 elements and more), rounded up to 4096 elements.  In sets of at most 512
+ * pieces, no tensor more than 256, further, 4.125 bytes per element, each tensor rounded up to 128 elements (a probed
+ * step's old curvature and mask, put back if the step is skipped).
  */
 int triaccel_init(triaccel_handle *out, const triaccel_config *config, const triaccel_tensor *tensors,
                   int32_t n, void *hip_stream);

@@ -477,7 +477,7 @@ int triaccel_init(triaccel_handle* out, const triaccel_config* config, const tri
   ws.add(&T.resize_scratch, (size_t)scratch_chunks * kChunk * 4);
   ws.add(&T.inputs, (size_t)n);
   ws.add(&T.arrived, (size_t)n * kCandCounterStride);
-  T.fused = (local_form(*c) || decide_form(*c)) && T.total_chunks <= kFusedChunks;
+  T.fused = (local_form(*c) || decide_form(*c)) && T.total_chunks <= kFusedChunks && max_chunks <= kFusedTensorChunks;
   uint64_t undo = 0;
   if (T.fused)
     for (TensorDesc& d : c->desc) {

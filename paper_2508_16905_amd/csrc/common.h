@@ -115,14 +115,22 @@ constexpr uint32_t kLateChunks = 1024;
 // as a reason too, and an atomic add for each tensor left over: 1500 of 9000 elements, inputs that never repeat, 143 and 186 (169).
 constexpr uint32_t kLateTensors = 512;
 
-// Sets of the local form with at most this many chunks (2.1 M elements) take the statistics and the curvature average of a
-// probed step in one launch (k_stats_ema): 1.5 us less for the launch, against 4 bytes more written per element, as the
-// skip rule is only known after it.  A probed step, us, in two launches and in one: 12 tensors of 20,000 elements in all
+// Sets of the local or the decide form with at most this many chunks (2.1 M elements), none of whose tensors has more than
+// kFusedTensorChunks (1.0 M), take the statistics and the curvature average of a probed step in one launch (k_stats_ema):
+// 1.5 us less for the launch, against 4 bytes more written per element, as the skip rule is only known after it.  A probed step, us, in two launches and in one: 12 tensors of 20,000 elements in all
 // 13.7 and 12.2, of 0.3 M 17.9 and 16.5, of 1.0 M 20.5 and 19.5 (bf16 20.2 and 18.6, Fisher 19.0 and 17.4), 60 of 0.7 M 20.8 and
 // 19.2, 40 of 1.7 M 24.0 and 23.2, 12 of 2.1 M 26.4 and 26.2, of 2.5 M 27.1 and 26.8 (bf16 26.0 and 26.1); 30 of 4 M 35.5
 // and 35.9, of 6 M 48.2 and 50.3.  With the hint for streaming data off on what is put aside: 12 of 2.1 M, Fisher, 22.4
 // instead of 21.5.
+// Two kinds of step pay for it.  A skipped one: the launch does the curvature's work and the next one puts back what it
+// overwrote: 30 tensors of 0.3 M 7.7 and 8.4, 60 of 0.7 M 7.9 and 10.3, 41 of 1.0 M 7.9 and 12.6, 40 of 1.7 M 7.3 and 14.7, 500 of 4095
+// elements 7.4 and 15.9.  And one whose threshold k_select_tail settles: its atomics on mask words take 8 % longer if
+// k_stats_ema has read them (without that read they do not; read with the streaming hint they take 20 % longer).  In sets that one tensor makes
+// up that launch is most of the step: curvature that moves by up to 12 % at every refresh, one tensor of 1.0 M 46.6 and 45.9, of 1.2 M
+// 53.5 and 56.4, of 1.5 M 59.3 and 65.8, of 2.0 M 74.8 and 78.4, 4 of 2.0 M 63.5 and 67.1 (40 of 1.7 M 37.0 and 36.8), hence the
+// second bound; with inputs that never repeat 24.7 and 24.0, 27.0 and 26.4, 26.5 and 25.5.
 constexpr uint32_t kFusedChunks = 512;
+constexpr uint32_t kFusedTensorChunks = 256;
 constexpr uint32_t kUndoUnit = 128;  // elements whose mask is 16 bytes
 
 enum SelMode : uint32_t {
