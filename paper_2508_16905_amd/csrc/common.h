@@ -31,7 +31,7 @@ constexpr uint32_t kLocalMaxChunks = 1024;
 // thresholds are taken in one launch (k_decide_select), in which up to 1024 workgroups add up their tensor's records.  A
 // probed step, us, with three launches and with it: 12 tensors of 0.1 M 27.2 and 18.8, 41 of 1.0 M 34.4 and 26.4, 12 of 2.1 M
 // 39.9 and 34.4, 30 of 6 M 66.1 and 60.6, 60 of 16 M 132.4 and 127.2; one tensor of 3 M 41.5 and 39.8, of 8.2 M 78.6 and
-// 76.9, of 16 M (3907 chunks) 131.9 and 130.2; 29 of 37 M, one of them 3460 chunks, the same (269.9), 12 of 60 M, one of them 4076
+// 76.9, of 16 M (3907 chunks) 131.9 and 130.2; 29 of 37 M, one of them 3460 chunks, 272 and 269, 12 of 60 M, one of them 4076
 // chunks, 427.8 and 434.6.  A step that needs histograms: 60 of 16 M 451 and 222, 29 of 37 M 662 and 399.
 constexpr uint32_t kDecideMaxChunks = 4096;
 constexpr uint32_t kDecideTotalChunks = 10240;
@@ -105,8 +105,8 @@ constexpr uint32_t kLateChunks = 1024;
 // In the decide form no update covers it, however long: k_decide_select takes 14 to 15 us with it and 5 without, before
 // k_select_tail's own time.  There the rule is for sets of at most this many tensors, a workgroup of k_select_tail each, two
 // of which are resident on each of the 256 compute units; and only for too many listed keys: a few tensors that need
-// histograms take k_select_tail little time, and the histogram workgroups cover select_local.  Beyond 1024 chunks, without and with (and with the three launches k_layer, k_hist_pass and
-// k_select_tail): inputs that never repeat, 30 tensors of 6 M 71.1 and 70.5 (73.9), 60 of 16 M 138.0 and 136.7 (140.6), 29 of 37 M
+// histograms take k_select_tail little time, and the histogram workgroups cover select_local.  Beyond 1024 chunks, without
+// and with (and with the three launches k_layer, k_hist_pass and k_select_tail): inputs that never repeat, 30 tensors of 6 M 71.1 and 70.5 (73.9), 60 of 16 M 138.0 and 136.7 (140.6), 29 of 37 M
 // 283.6 and 283.0 (286.3); curvature that moves by up to 1 % besides 88.2 and 82.3 (84.9), 163.9 and 154.5 (157.7), 354 and 343
 // (347); by up to 12 % 197.5 and 184.4 (189.3), 277.7 and 267.9 (282.5), 471 and 464 (536); by 5 % at every fourth step 124.0 and
 // 114.9 (118.1), 208.8 and 199.8 (206.2), 417 and 411 (430).  By number of tensors, 20 M in all, up to 12 %: 100 tensors 340
@@ -125,8 +125,8 @@ constexpr uint32_t kLateTensors = 512;
 // Two kinds of step pay for it.  A skipped one: the launch does the curvature's work and the next one puts back what it
 // overwrote: 30 tensors of 0.3 M 7.7 and 8.4, 60 of 0.7 M 7.9 and 10.3, 41 of 1.0 M 7.9 and 12.6, 40 of 1.7 M 7.3 and 14.7, 500 of 4095
 // elements 7.4 and 15.9.  And one whose threshold k_select_tail settles: its atomics on mask words take 8 % longer if
-// k_stats_ema has read them (without that read they do not; read with the streaming hint they take 20 % longer).  In sets that one tensor makes
-// up that launch is most of the step: curvature that moves by up to 12 % at every refresh, one tensor of 1.0 M 46.6 and 45.9, of 1.2 M
+// k_stats_ema has read them (without that read they do not; read with the streaming hint they take 20 % longer).  In sets
+// that one tensor makes up that launch is most of the step: curvature that moves by up to 12 % at every refresh, one tensor of 1.0 M 46.6 and 45.9, of 1.2 M
 // 53.5 and 56.4, of 1.5 M 59.3 and 65.8, of 2.0 M 74.8 and 78.4, 4 of 2.0 M 63.5 and 67.1 (40 of 1.7 M 37.0 and 36.8), hence the
 // second bound; with inputs that never repeat 24.7 and 24.0, 27.0 and 26.4, 26.5 and 25.5.
 constexpr uint32_t kFusedChunks = 512;

@@ -23,7 +23,7 @@ struct DevPtr {
 // sizes, constant from triaccel_init on and kept in device memory.  A launch costs the host 2.6 us with up to 64 bytes of
 // arguments, 3.2 with 128, 3.5 with 330 and 4.1 if those are 20 separate ones and the hidden ones of a kernel that asks for
 // its grid's size, and that is what sets bound by their launches wait for.  So the kernels get the pointers that their
-// first loads need (this one, the tensor table, the chunk list, the global record), the step's scalars and up to two
+// first loads need (this one, the tensor table, the chunk list, the global record), the step's scalars and up to four
 // words more; the loads from here go beside those of the chunk's and the tensor's entries, so that no access to the
 // data comes later for them.  A step, us, with up to 20 arguments and now (the latter with the
 // pointers preloaded, build.py): two-layer perceptron 10.2 and 8.0, with a probe, fp16 gradients and the result read 28.2 and
@@ -66,7 +66,7 @@ struct DeviceTables : StepTables {
 
 hipError_t launch_grad_stats(const DeviceTables& t, const StepScalars& sc, bool local, hipStream_t s);
 hipError_t launch_curv_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, bool local, hipStream_t s);
-// Both of these, on probed steps of sets of the local form that have the workspace for it.
+// Both of these, on probed steps of sets that have the workspace for it (`fused`).
 hipError_t launch_stats_ema(const DeviceTables& t, const StepScalars& sc, bool fisher, hipStream_t s);
 hipError_t launch_hist_pass(const DeviceTables& t, const StepScalars& sc, int serial_rounds, hipStream_t s);
 hipError_t launch_select_finish(const DeviceTables& t, const StepScalars& sc, hipStream_t s);
@@ -75,10 +75,11 @@ hipError_t launch_layer(const DeviceTables& t, const StepScalars& sc, hipStream_
 hipError_t launch_update(const DeviceTables& t, const StepScalars& sc, bool elem, bool resize, hipStream_t s);
 // `undo`: after k_stats_ema.
 hipError_t launch_update_local(const DeviceTables& t, const StepScalars& sc, bool any_probe, bool undo, hipStream_t s);
-// Probed steps with step sizes per element, on sets of the local form's sizes: the layers' decisions and most thresholds.
+// Probed steps with step sizes per element, on sets within kDecideMaxChunks and kDecideTotalChunks: the layers' decisions and most
+// thresholds.
 hipError_t launch_decide_select(const DeviceTables& t, const StepScalars& sc, bool undo, hipStream_t s);
-// `local`: after k_update_local or k_decide_select, which settled most tensors' thresholds; `resize`: with launch 1 of the in-place resize (sets
-// of the local form: its plans have two launches at most).
+// `local`: after k_update_local or k_decide_select, which settled most tensors' thresholds; `resize`: with launch 1 of the
+// in-place resize (sets of the local form: its plans have two launches at most).
 hipError_t launch_select_tail(const DeviceTables& t, const StepScalars& sc, bool local, bool resize, hipStream_t s);
 hipError_t launch_mask_pass(const DeviceTables& t, const StepScalars& sc, hipStream_t s);
 hipError_t launch_update_resize(const DeviceTables& t, const StepScalars& sc, bool elem, hipStream_t s);

@@ -15,8 +15,8 @@ namespace triaccel {
 // subtrees.
 //
 // With one workgroup taking the 16 first chunks one after the other, as the form without subtree stages still
-// does, that stage is a chain of 2-6 us per chunk; side by side the 64 first chunks of 12 tensors take 26 us with
-// the rest of that launch.
+// does, that stage is a chain of 2-6 us per chunk; side by side the first 64 chunks of 12 tensors took 26 us with
+// the rest of that launch (they are up to 256 now, kResizeTopMax).
 // Scratch of the tensor for chunk c < top: kChunk elements of 4 bytes.
 __device__ __forceinline__ char* resize_scratch(const TensorDesc& td, char* scratch, uint32_t c) {
   return scratch + ((size_t)td.resize_slot + c) * (kChunk * 4);

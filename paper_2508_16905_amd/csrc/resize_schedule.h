@@ -45,11 +45,16 @@ constexpr uint32_t kResizeTopSmall = 64;     // the same, sets below kResizeBigS
 // of a narrowing tensor, which takes 27 us for the first 64 chunks of 12 tensors, more to do; they cost their copy, so they are at
 // most a quarter of the longest tensor, or all but one in short sets, whose launches have room.  Every tensor is offered as many work
 // items as the longest, so their number is limited too, by the chunks there are: a ragged set of 60 tensors (40 M) took
-// 354 us instead of 230 without that.  Longer tensors have two subtree stages and more roots from their first: one of some
-// 9000 chunks among 8 of 60 M 240 and 257.  A step in which every tensor is resized, us, with 64 and with this many: 12
+// 354 us instead of 230 without that.  Tensors of more than 4096 chunks have two subtree stages and more roots from their
+// first: one of some 9000 chunks among 8 of 60 M 240 and 257.  A step in which every tensor is resized, us, with 64 and with this many: 12
 // of 1024 chunks 214 and 193 (256), 15 264 and 239, 4 89 and 72, one of 1000 39 and 25, 8 of 500 79 and 74, 4 of 160 22.8 and
 // 21.7 (128), 6 ragged of 6 M 44 and 36; with 128 all the same 30 of 200 118 and 125, 30 of 300 189 and 195.  512 of 1024: 75
-// instead of 72 for 4, 24.1 instead of 24.6 for one.
+// instead of 72 for 4, 24.1 instead of 24.6 for one.  With step sizes per element 12 of 1024 254 and 220, one of 1000 50 and 30,
+// 6 ragged of 6 M 59 and 48, 60 ragged of 40 M (64 either way) 324 and 324.
+// The rule ends at 1024 chunks, the longest tensor of the local form, with which it was made; nothing in the scheme ends there.  From
+// 1025 to 4096 chunks, still one subtree stage, 256 would gain as well: 12 of 1025 220 and 200, one of 1025 40 and 26, 4 of 1500
+// 134 and 104, 8 of 2000 289 and 238, 3 of 4096 259 and 182, one of 4096 130 and 69, 12 ragged of 25 M 170 and 122; 30 ragged of 30 M
+// 160 and 162, steps without a change the same within 1 %.
 constexpr uint32_t kResizeTopMax = 256;
 constexpr uint32_t kResizeShortSet = 4096;   // chunks in the whole set
 constexpr uint32_t kResizeOneSubtree = 1024; // longest tensor of the sets that the rule is for
